@@ -146,9 +146,10 @@ __global__ void __launch_bounds__(256) k_col_stats(const unsigned short* __restr
   __shared__ double s_vsum[SMOOTH_V ? NRG : 1][D];
   __shared__ float s_max[SMOOTH_V ? 1 : NRG][D];
   const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
-  const HeadPos hp = head_pos(km, blockIdx.y);
+  const BlockPos bp = block_pos(km);
+  const HeadPos hp = head_pos(km, bp.y);
   const Seq sq = seq_of(sm, hp.b, Nq, N);
-  const int r0 = blockIdx.x * STAT_ROWS;
+  const int r0 = bp.x * STAT_ROWS;
   const int r1 = min(r0 + STAT_ROWS, sq.nk);
   const size_t hbase = hp.base + sq.k0 * (size_t)km.sn;
   double acc[8], vacc[8];
@@ -195,7 +196,7 @@ __global__ void __launch_bounds__(256) k_col_stats(const unsigned short* __restr
       s += s_sum[g][t];
       if constexpr (SMOOTH_V) sv += s_vsum[g][t]; else m = fmaxf(m, s_max[g][t]);
     }
-    const size_t slot = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * D + t;
+    const size_t slot = ((size_t)bp.y * bp.nx + bp.x) * D + t;
     k_sum[slot] = s;
     if constexpr (SMOOTH_V) v_sum[slot] = sv;
     else v_max[slot] = __float_as_uint(m);
@@ -211,14 +212,15 @@ __global__ void __launch_bounds__(256) k_v_absmax(const unsigned short* __restri
   constexpr int NCG = D / 8, NRG = 256 / NCG;
   __shared__ float s_max[NRG][D];
   const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
-  const HeadPos hp = head_pos(km, blockIdx.y);
+  const BlockPos bp = block_pos(km);
+  const HeadPos hp = head_pos(km, bp.y);
   const Seq sq = seq_of(sm, hp.b, Nq, N);
-  const int r0 = blockIdx.x * STAT_ROWS;
+  const int r0 = bp.x * STAT_ROWS;
   const int r1 = min(r0 + STAT_ROWS, sq.nk);
   const size_t hbase = hp.base + sq.k0 * (size_t)km.sn;
   float mean[8], mx[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) { mean[e] = v_mean[(size_t)blockIdx.y * D + cg * 8 + e]; mx[e] = 0.0f; }
+  for (int e = 0; e < 8; ++e) { mean[e] = v_mean[(size_t)bp.y * D + cg * 8 + e]; mx[e] = 0.0f; }
   for (int r = r0 + rg; r < r1; r += NRG) {
     float xv[8];
     load8<BF16>(V + row_offset(km, hbase, r) + cg * 8, xv);
@@ -231,7 +233,7 @@ __global__ void __launch_bounds__(256) k_v_absmax(const unsigned short* __restri
   if (t < D) {
     float m = 0.0f;
     for (int g = 0; g < NRG; ++g) m = fmaxf(m, s_max[g][t]);
-    v_max[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * D + t] = __float_as_uint(m);
+    v_max[((size_t)bp.y * bp.nx + bp.x) * D + t] = __float_as_uint(m);
   }
 }
 
@@ -415,10 +417,11 @@ __global__ void __launch_bounds__(256) k_quant_q8(const unsigned short* __restri
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BQ / NRG;  // RPT rows per thread (8 or 4)
   constexpr int QMAX = 127;
   const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
-  const int qb = blockIdx.x;
-  const size_t bh = blockIdx.y;
+  const BlockPos bp = block_pos(qm);
+  const int qb = bp.x;
+  const size_t bh = bp.y;
   const int n0 = qb * BQ;
-  const HeadPos hp = head_pos(qm, blockIdx.y);
+  const HeadPos hp = head_pos(qm, bp.y);
   const Seq sq = seq_of(sm, hp.b, N, Nk);
   const int valid = min(BQ, sq.n - n0);
   if (valid <= 0) return;                     // a block past the end of a shorter sequence
@@ -435,7 +438,7 @@ __global__ void __launch_bounds__(256) k_quant_q8(const unsigned short* __restri
     }
   }
   if (q_corr) row_constants<D, NCG, RPT>(x, q_corr + (bh * nQb + qb) * BQ + rg * RPT, valid - rg * RPT,
-                                         k_mean + kv_head(qm, blockIdx.y, G) * D + cg * 8, kappa, cg);
+                                         k_mean + kv_head(qm, bp.y, G) * D + cg * 8, kappa, cg);
   // codes go to LDS in the packed order of this 128-query slab (contiguous in the workspace) and
   // leave as coalesced 16-byte stores
   __shared__ uint4 s_codes[BQ * D / 16];
@@ -516,16 +519,21 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q4(const unsign
   static_assert(SLAB <= (int)sizeof(uint4) * BQ * NCG, "the code image fits where the raw rows were");
   __shared__ double s_sum[4][D];              // column sums, one row per wavefront
   __shared__ __align__(16) float s_mean[D];
+  __shared__ __align__(16) float s_kbar[D];   // mean(K) of the KV head (log-sum-exp output only)
   __shared__ float s_bmax[4];
   const int t = threadIdx.x;
-  const int qb = blockIdx.x;
-  const size_t bh = blockIdx.y;
+  const BlockPos bp = block_pos(qm);
+  const int qb = bp.x;
+  const size_t bh = bp.y;
   const int n0 = qb * BQ;
-  const HeadPos hp = head_pos(qm, blockIdx.y);
+  const HeadPos hp = head_pos(qm, bp.y);
   const Seq sq = seq_of(sm, hp.b, N, Nk);
   const int valid = min(BQ, sq.n - n0);
   if (valid <= 0) return;                     // a block past the end of a shorter sequence
   const size_t hbase = hp.base + sq.q0 * (size_t)qm.sn;
+  // (fetched now, under the loads of the rows: read from global memory where it is used, in front of every 8 channels of
+  // every row, it was a round trip each)
+  if (q_corr && t < D) s_kbar[t] = k_mean[kv_head(qm, bp.y, G) * D + t];
   auto swz = [](int r) { return (r >> 1) & (D >= 128 ? 3 : 1); };
   {
     const int cg = t % NCG, rg = t / NCG;
@@ -584,7 +592,9 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q4(const unsign
     for (int j = 0; j < CPC; ++j) {
       unpack8<BF16>(s_raw[r * NCG + ((c4 * CPC + j) ^ swz(r))], &x[i][8 * j]);
       if (q_corr) {
-        const float* kb = k_mean + kv_head(qm, blockIdx.y, G) * D + CPL * c4 + 8 * j;
+        const float4 b0 = *reinterpret_cast<const float4*>(&s_kbar[CPL * c4 + 8 * j]);
+        const float4 b1 = *reinterpret_cast<const float4*>(&s_kbar[CPL * c4 + 8 * j + 4]);
+        const float kb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
 #pragma unroll
         for (int e = 0; e < 8; ++e) dotk[i] += (double)x[i][8 * j + e] * (double)kb[e];
       }
@@ -718,13 +728,14 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS 
   __shared__ float s_qs[DS_QROWS];                 // 2^E of the staged rows
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int r16 = lane & 15, k4 = lane >> 4;
-  const int kb = blockIdx.x;
-  const size_t bhkv = blockIdx.y;
+  const BlockPos bp = block_pos(km);
+  const int kb = bp.x;
+  const size_t bhkv = bp.y;
   const int n0 = kb * BKV;
   const int r = 16 * w + r16, c0 = CPL * k4;
   // this sequence's key count N, query-block count nQs and causal offset (the slabs keep the
   // strides nQb, nKb of the longest sequence)
-  const HeadPos hp = head_pos(km, blockIdx.y);
+  const HeadPos hp = head_pos(km, bp.y);
   const Seq sq = seq_of(sm, hp.b, Nq, Nmax);
   const int N = sq.nk, coff = sq.coff;
   const int nQs = (sq.n + BQ - 1) / BQ;
@@ -1069,10 +1080,11 @@ __global__ void __launch_bounds__(256) k_quant_v(const unsigned short* __restric
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BKV / NRG;
   __shared__ uint8_t tile[BKV][D + 16];
   const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
-  const int kb = blockIdx.x;
-  const size_t bh = blockIdx.y;
+  const BlockPos bp = block_pos(km);
+  const int kb = bp.x;
+  const size_t bh = bp.y;
   const int n0 = kb * BKV;
-  const HeadPos hp = head_pos(km, blockIdx.y);
+  const HeadPos hp = head_pos(km, bp.y);
   const Seq sq = seq_of(sm, hp.b, Nq, Nmax);
   const int N = sq.nk;
   if (n0 >= N) return;                             // a block past the end of a shorter sequence
@@ -1195,10 +1207,10 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
   const unsigned short* k = (const unsigned short*)P.k;
   const unsigned short* v = (const unsigned short*)P.v;
   const int nstat = BHkv * Dm.d;
-  const dim3 gstat((Dm.Nk + STAT_ROWS - 1) / STAT_ROWS, BHkv);
   const TensorMap km = make_tensor_map(Dm.nhd, Dm.Hkv, Dm.Nk, Dm.d, Dm.seq.cu_q != nullptr);
   const SeqMap sm = Dm.seq;
-  const int nchunk = (int)gstat.x;
+  const int nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS;
+  const dim3 gstat = block_grid(km, nchunk, BHkv);
   const float code_max = Dm.pvf == PV_INT8 ? INT8_PV_MAX : (Dm.pvf == PV_E5M2 ? E5M2_MAX : E4M3_MAX);
   if (Dm.smooth_v) {
     k_col_stats<BF16, D, true><<<gstat, 256, 0, s>>>(k, v, P.k_sum, P.v_sum, P.v_max, Dm.N, Dm.Nk, km, sm);
@@ -1229,12 +1241,12 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   // the log-sum-exp output is wanted does Q wait for mean(K) (its row constants need it).
   auto quant_q_pass = [&](float* corr, const float* head_scale, int stats_only) {
     if constexpr (INT4)
-      k_quant_q4<BF16, D><<<dim3(Dm.nQb, BH), 256, 0, s>>>(q, P.q_mean, P.q_scale, P.q_codes, Dm.N, Dm.Nk, Dm.nQb,
+      k_quant_q4<BF16, D><<<block_grid(qm, Dm.nQb, BH), 256, 0, s>>>(q, P.q_mean, P.q_scale, P.q_codes, Dm.N, Dm.Nk, Dm.nQb,
                                                        Dm.block_groups, Dm.qg, qm, sm, corr, P.k_mean,
                                                        Dm.H / Dm.Hkv, Dm.kappa, head_scale, stats_only, Dm.smooth_q,
                                                        Dm.ds_mode == DS_DIGITS && Dm.smooth_q ? P.q_digits : nullptr, P.q_dscale);
     else
-      k_quant_q8<BF16, D><<<dim3(Dm.nQb, BH), 256, 0, s>>>(q, P.q_scale, P.q_codes, Dm.N, Dm.Nk, Dm.nQb,
+      k_quant_q8<BF16, D><<<block_grid(qm, Dm.nQb, BH), 256, 0, s>>>(q, P.q_scale, P.q_codes, Dm.N, Dm.Nk, Dm.nQb,
                                                        Dm.block_groups, Dm.qg, qm, sm, corr, P.k_mean,
                                                        Dm.H / Dm.Hkv, Dm.kappa, head_scale, stats_only);
   };
@@ -1251,7 +1263,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   };
   auto quant_k_pass = [&](const float* head_scale, int stats_only) {
 #define SAGE_QK(DSM_)                                                                                                  \
-  k_quant_k<BF16, INT4, D, DSM_><<<dim3(Dm.nKb, BHkv), 256, 0, s>>>(k, P.k_mean, P.k_scale, P.k_codes, P.q_mean, P.delta_s, \
+  k_quant_k<BF16, INT4, D, DSM_><<<block_grid(km, Dm.nKb, BHkv), 256, 0, s>>>(k, P.k_mean, P.k_scale, P.k_codes, P.q_mean, P.delta_s, \
                                                                     Dm.N, Dm.Nk, Dm.nKb, Dm.nQb, Dm.H / Dm.Hkv, Dm.kappa,  \
                                                                     Dm.block_groups, Dm.kg, Dm.causal, km, sm, head_scale, \
                                                                     stats_only, !Dm.smooth_q, P.q_digits, P.q_dscale)
@@ -1274,7 +1286,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   } else {
     quant_k_pass(nullptr, 0);
   }
-  const dim3 gv(Dm.nKb, BHkv);
+  const dim3 gv = block_grid(km, Dm.nKb, BHkv);
 #define SAGE_QV(SV, PF, VM) k_quant_v<BF16, D, SV, PF><<<gv, 256, 0, s>>>(v, P.v_scale, VM, P.v_codes, Dm.N, Dm.Nk, Dm.nKb, km, sm)
   if (Dm.smooth_v) {
     if (Dm.pvf == PV_INT8) SAGE_QV(true, PV_INT8, v_mean);
@@ -1315,13 +1327,14 @@ template <bool BF16, int D>
 static void launch_stats_update_t(const Dims& Dm, const Ptrs& P, double* state_sum, float* state_max, int fresh,
                                   long long n_total, hipStream_t s) {
   const int BHkv = Dm.B * Dm.Hkv, nstat = BHkv * Dm.d;
-  const dim3 gstat((Dm.Nk + STAT_ROWS - 1) / STAT_ROWS, BHkv);
   const TensorMap km = make_tensor_map(Dm.nhd, Dm.Hkv, Dm.Nk, Dm.d, false);
+  const int nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS;
+  const dim3 gstat = block_grid(km, nchunk, BHkv);
   const float code_max = Dm.pvf == PV_INT8 ? INT8_PV_MAX : (Dm.pvf == PV_E5M2 ? E5M2_MAX : E4M3_MAX);
   k_col_stats<BF16, D, false><<<gstat, 256, 0, s>>>((const unsigned short*)P.k, (const unsigned short*)P.v, P.k_sum, nullptr,
                                                     P.v_max, Dm.N, Dm.Nk, km, Dm.seq);
   k_accumulate_stats<<<(nstat + 255) / 256, 256, 0, s>>>(P.k_sum, P.v_max, state_sum, state_max, P.k_mean, P.v_scale, nstat,
-                                                         Dm.d, (int)gstat.x, fresh, n_total, code_max);
+                                                         Dm.d, nchunk, fresh, n_total, code_max);
 }
 
 hipError_t launch_kv_stats_update(const Dims& D, const Ptrs& P, double* state_sum, float* state_max, int fresh,
