@@ -77,6 +77,15 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
     D->pack = G >= 2 && G <= PACK_G && (long long)G * a->N <= BQ;     // (a->N: the longest sequence's queries)
     const long long tiles = D->pack ? (long long)a->B * a->H_kv : (long long)a->B * a->H * nQb;
     long long S = a->kv_splits > 1 ? a->kv_splits : (tiles < 256 ? (512 + tiles - 1) / tiles : 1);
+    if (a->kv_splits == 0 && !D->pack && tiles >= 256 && tiles < 512) {
+      // One or two workgroups per CU, of the three that fit: a lone wavefront issues far fewer vector instructions than
+      // two or three that share the SIMD.  Split for three per CU - where a chunk still has 48 key blocks: with fewer the
+      // partial results cost what the fuller chip gains.  Measured, us unsplit / split: 512 queries of 64 heads on 16384
+      // keys 319 / 270, 1024 of 32 heads of 64 channels on 9000 keys 146 / 119, causal 9000 on itself with 4 heads 167 /
+      // 140, 7000 with 6 heads 143 / 132; causal 4096 with 8 heads 98 / 89, but full 101 / 101 and with 10 heads 103 / 115.
+      S = (768 + tiles - 1) / tiles;
+      if (S > nKb / 48) S = nKb / 48;
+    }
     if (S > nKb / 8) S = nKb / 8;
     if (S > 64) S = 64;
     if (S >= 2) D->splits = (int)S;
@@ -85,6 +94,9 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
   D->kappa = sm * LOG2E;   // one FP32 rounding of the product of two FP32 values
   return SAGE_OK;
 }
+
+// A split that the library picked for a launch of 256 tiles or more (see validate).
+bool splits_by_choice(const Dims& D) { return !D.pack && D.splits > 1 && (long long)D.B * D.H * D.nQb >= 256; }
 
 int check_workspace(const sage_attn_args* a, const Workspace& w) {
   if (!a->workspace || a->workspace_bytes < w.total) return SAGE_ERR_WORKSPACE;
@@ -209,7 +221,11 @@ int sage_attn_fwd_static(const sage_attn_args* args) {
   Dims D;
   int st = validate(args, &D, true);
   if (st != SAGE_OK) return st;
-  const Workspace w = make_workspace(D);
+  Workspace w = make_workspace(D);
+  if (w.total > (size_t)SAGE_STATIC_WORKSPACE_BYTES && args->kv_splits == 0 && splits_by_choice(D)) {
+    D.splits = 1;                           // fits without the partial results of a split that is only there for speed
+    w = make_workspace(D);
+  }
   if (w.total > (size_t)SAGE_STATIC_WORKSPACE_BYTES) return SAGE_ERR_WORKSPACE;   // beyond the built-in workspace
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return hip_status(hipErrorUnknown);

@@ -940,9 +940,9 @@ __global__ void __launch_bounds__(256, (attn_occupancy<D, GM, PVF>())) k_attn_fw
 
 // Merge of the partial results of a tile's key chunks (Eq. 1 applied to disjoint key sets): under the largest of
 // the chunks' exponent offsets e* the sums add up with weights 2^(e_s - e*); then the epilogue of Algorithm 1.
-// One workgroup per tile; a thread owns four channels of a row, d / 4 threads a row, and the workgroup walks the
-// tile's rows 1024 / d at a time - so a tile with few valid rows (a decode step) still spreads over a whole row of
-// threads, and a row's chunks are read as contiguous 4 d bytes.
+// A thread owns four channels of a row, d / 4 threads a row, and a workgroup takes 1024 / d of its tile's rows (grid: tiles,
+// pieces of 1024 / d rows) - so a tile with few valid rows (a decode step) still spreads over a whole row of threads, and a
+// row's chunks are read as contiguous 4 d bytes.
 // PACK: the tiles of k_attn_fwd's packed form - row r of a tile is query r % n of head r / n of the KV head's group
 // (n: the sequence's query count).
 template <int D, bool BF16, bool PACK = false>
@@ -950,7 +950,7 @@ __global__ void __launch_bounds__(256) k_merge_splits(const AttnParams p) {
   constexpr int TPR = D / 4, RP = 256 / TPR;      // threads per row, rows per pass
   const int tile = blockIdx.x;
   const int t = threadIdx.x, c_lo = 4 * (t % TPR);
-  for (int r = t / TPR; r < BQ; r += RP) {
+  for (int r = blockIdx.y * RP + t / TPR; r < BQ; r += RP * gridDim.y) {
     int bh = tile / p.nQb, qb = tile % p.nQb, query = qb * BQ + r;
     if constexpr (PACK) bh = (tile / p.Hkv) * p.H + (tile % p.Hkv) * (p.H / p.Hkv);      // the group's first head
     const Seq sq = seq_of(p.seq, (unsigned)(bh / p.H), p.N, p.Nk);
@@ -1069,18 +1069,20 @@ static hipError_t launch_attention_g(const Dims& Dm, const Ptrs& P, hipStream_t 
   p.total_tiles = Dm.B * Dm.H * Dm.nQb;
   p.kappa = Dm.kappa;
   p.splits = Dm.splits; p.part_o = P.part_o; p.part_el = P.part_el;
+  constexpr int MERGE_ROWS = 1024 / D;              // rows a workgroup of k_merge_splits takes
   if constexpr (GM == 0 && PVF == PV_E4M3) {        // (the key split comes with the default groups and data type)
     if (Dm.pack) {                                  // packed tiles: one per (batch, KV head), any number of chunks
       p.total_tiles = Dm.B * Dm.Hkv;
       const int grid = 8 * ((p.total_tiles * Dm.splits + 7) / 8);
       k_attn_fwd<D, INT4, CAUSAL, BF16, GM, PVF, true, true><<<grid, 256, 0, s>>>(p);
-      k_merge_splits<D, BF16, true><<<p.total_tiles, 256, 0, s>>>(p);
+      const int rows = min(BQ, Dm.H / Dm.Hkv * Dm.N);
+      k_merge_splits<D, BF16, true><<<dim3(p.total_tiles, (rows + MERGE_ROWS - 1) / MERGE_ROWS), 256, 0, s>>>(p);
       return hipGetLastError();
     }
     if (Dm.splits > 1) {
       const int grid = 8 * ((p.total_tiles * Dm.splits + 7) / 8);
       k_attn_fwd<D, INT4, CAUSAL, BF16, GM, PVF, true><<<grid, 256, 0, s>>>(p);
-      k_merge_splits<D, BF16><<<p.total_tiles, 256, 0, s>>>(p);
+      k_merge_splits<D, BF16><<<dim3(p.total_tiles, BQ / MERGE_ROWS), 256, 0, s>>>(p);
       return hipGetLastError();
     }
   }

@@ -95,6 +95,20 @@ def test_key_split_policy():
     assert S(kv_splits=65) == 0 and S(kv_splits=-1) == 0              # invalid arguments
 
 
+def test_key_split_of_half_filled_launches():
+    """256 to 511 unpacked tiles leave a CU one or two of the three workgroups it holds: split for 768, in chunks of at
+    least 48 key blocks; 512 tiles and more, packed tiles and a caller's own number are not touched by that rule."""
+    pa, _ = _lib()
+    S = lambda **kw: pa.sage_attn_kv_splits(_args(pa, **kw))
+    assert S(B=2, H=32, H_kv=8, N=512, N_kv=16384, causal=1) == 3     # 256 tiles, 256 key blocks
+    assert S(B=3, H=32, H_kv=8, N=512, N_kv=16384, causal=1) == 2     # 384 tiles
+    assert S(B=2, H=32, H_kv=8, N=512, N_kv=64 * 96, causal=1) == 2   # 96 key blocks: two chunks of 48
+    assert S(B=2, H=32, H_kv=8, N=512, N_kv=64 * 95, causal=1) == 1
+    assert S(B=4, H=32, H_kv=8, N=512, N_kv=16384, causal=1) == 1     # 512 tiles
+    assert S(B=2, H=32, H_kv=8, N=512, N_kv=16384, causal=1, kv_splits=1) == 1
+    assert S(B=40, H=32, H_kv=8, N=1, N_kv=16384, causal=1) == 1      # 320 packed tiles
+
+
 def test_argument_errors_are_found_on_the_host():
     pa, lib = _lib()
     bad = [dict(d=96), dict(d=512), dict(mode=2), dict(dtype=3), dict(flags=64), dict(flags=-1), dict(N=(1 << 24) + 1), dict(N_kv=(1 << 24) + 1), dict(group_map=5), dict(group_map=-1), dict(layout=2), dict(pv_format=3),

@@ -50,6 +50,23 @@ def test_static_workspace_entry_point_equals_fwd_ex(mode):
     assert torch.equal(out2, want)
 
 
+@pytest.mark.parametrize("d,H,N,Nk,splits", [(64, 32, 1024, 6200, 2), (128, 16, 2048, 11000, 1)])
+def test_half_filled_launches(d, H, N, Nk, splits):
+    """256 tiles over many keys are split without being asked: the same bits as with the number given.  In the built-in
+    workspace the split is given up where only its partial results do not fit (d = 128: 49 MB of them beside 26)."""
+    pa = _pa()
+    print(f"half-filled launch: N={N} N_kv={Nk} d={d} H={H}", flush=True)
+    q, k, v = _inputs(N, d, H, 8, True, 5, Nk)
+    auto = pa.sage_attn_kv_splits(pa.make_args(q, k, v, causal=True, mode="int8_fp8"))
+    assert auto >= 2
+    out = pa.sage_attn_fwd_ex(q, k, v, causal=True, mode="int8_fp8")
+    asked = pa.sage_attn_fwd_ex(q, k, v, causal=True, mode="int8_fp8", kv_splits=auto)
+    static = pa.sage_attn_fwd_static(q, k, v, torch.empty_like(q), causal=True, mode="int8_fp8")
+    one = pa.sage_attn_fwd_ex(q, k, v, causal=True, mode="int8_fp8", kv_splits=splits if splits > 1 else 1)
+    torch.cuda.synchronize()
+    assert torch.equal(out, asked) and torch.equal(static, one)
+
+
 def test_static_workspace_limit_is_an_error_not_a_fault():
     pa = _pa()
     lib = pa.load_library()
