@@ -5,7 +5,7 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-SOURCES = ["sage_api.hip", "sage_prologue.hip", "sage_attn_kernel.hip"]
+SOURCES = ["sage_api.hip", "sage_prologue.hip", "sage_attn_kernel.hip", "sage_attn_raw.hip"]
 LIB = os.path.join(PKG, "libsageattn.so")
 
 HIPCC_FLAGS = [

@@ -121,6 +121,17 @@ int hip_status(hipError_t e) {
   return SAGE_ERR_HIP;
 }
 
+// Both halves of the forward pass on a workspace that has been checked.
+int run_forward(const Dims& D, const sage_attn_args* a, const Workspace& w) {
+  Ptrs P = ptrs_for(a, w);
+  const hipStream_t s = (hipStream_t)a->stream;
+  const bool raw = attention_raw_ok(D);
+  const int st = hip_status(launch_prologue(D, P, s, !raw));
+  if (st != SAGE_OK) return st;
+  P.lse = a->lse;
+  return hip_status(raw ? launch_attention_raw(D, P, s) : launch_attention(D, P, s));
+}
+
 // Workspace of sage_attn_fwd_static: device memory that exists from the moment the library is loaded on a GPU, so
 // the call itself allocates nothing.  Every GPU holds its own copy of the array at its own address; in host code the
 // array's name is only a handle for hipGetSymbolAddress, the address kernels can use is what that call returns, taken
@@ -184,9 +195,12 @@ int sage_attn_core(const sage_attn_args* args) {
 }
 
 int sage_attn_fwd_ex(const sage_attn_args* args) {
-  const int st = sage_attn_prologue(args);
+  Dims D;
+  int st = validate(args, &D, true);
   if (st != SAGE_OK) return st;
-  return sage_attn_core(args);
+  const Workspace w = make_workspace(D);
+  if ((st = check_workspace(args, w)) != SAGE_OK) return st;
+  return run_forward(D, args, w);
 }
 
 int sage_attn_fwd(const void* q, const void* k, const void* v, void* out, int B, int H, int N, int d,
@@ -240,10 +254,7 @@ int sage_attn_fwd_static(const sage_attn_args* args) {
   sage_attn_args a = *args;
   a.workspace = g_static_ws[dev];
   a.workspace_bytes = (size_t)SAGE_STATIC_WORKSPACE_BYTES;
-  Ptrs P = ptrs_for(&a, w);
-  if ((st = hip_status(launch_prologue(D, P, (hipStream_t)a.stream))) != SAGE_OK) return st;
-  P.lse = a.lse;
-  return hip_status(launch_attention(D, P, (hipStream_t)a.stream));
+  return run_forward(D, &a, w);
 }
 
 int sage_attn_kv_stats(const sage_attn_args* args, float* k_mean_out, float* v_scale_out) {

@@ -1,0 +1,444 @@
+// Attention straight from K and V, for calls in which every key block meets one tile of at most 32 query columns: decode
+// steps and very short query chunks.  There the general path reads K and V, writes their codes, reads the codes and the
+// Delta-S rows again and spends most of its time on that traffic; here a workgroup quantizes a 64-key block on its way
+// into LDS and uses it there, so K and V are read once after the statistics pass (or once in all, with the statistics
+// supplied) and nothing of their size is written.  Same groups, scales, codes, Delta-S and chunk rule as the general path.
+#include "sage_attn_core.h"
+#include "sage_quant.h"
+
+#include <type_traits>
+
+namespace sage {
+
+struct RawParams {
+  const unsigned short *k, *v;
+  const float *k_mean, *q_mean;   // mean(K) per KV head; block mean of Q per query head (one block: at most 32 queries)
+  TensorMap km;
+};
+
+// Keeps the accumulators' next vector read a wait state further away than the compiler does.  It puts 19 between a 16-pass
+// matrix instruction and the first vector read of its result; where that read took the result's LAST registers at exactly
+// that distance (a loop-carried copy of O, highest registers first), they were sometimes the old ones on gfx950.  It was
+// seen in this kernel only, when the P~V product sat in both branches of the masked / unmasked choice; the product now
+// has one place, nothing copies O, and this holds whatever the compiler makes of the loop.
+template <int N>
+__device__ __forceinline__ void settle(v16f (&o)[N]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("s_nop 3" : "+v"(o[i]));
+#endif
+}
+
+// One workgroup (8 wavefronts): one chunk of the key blocks of one (batch, KV head).  Column c of the tile is query c % n of
+// head c / n of the KV head's group (n: the sequence's query count).
+//
+// Wavefronts 0..3 quantize: a block's raw rows are in registers (requested a block ahead, as soon as the previous ones
+// are unpacked), are smoothed, quantized and written to LDS in the order the matrix operands are read in.  Wavefronts 4..7
+// attend: each forms the block's scores and P~ for all 32 columns - the same values in all four - and multiplies them
+// with its own quarter of the channels of V^.  That repeats the softmax piece four times, but in parallel; with one
+// wavefront doing all of it a block would take three times as long.  LDS holds two blocks, one barrier per block.
+//
+// Bound: the stream of K and V (32 KB per block at d = 128), with the vector work of a block just below it.  4 x 8 KV heads,
+// 32768 keys, d = 128, one query: 128 us in the 8-bit mode (537 MB: 4.2 TB/s; quantizers + attention kernel were 185), 160
+// in the 4-bit mode (255), whose Delta-S is FP64 matrix work that no vector work overlaps.  Four wavefronts doing both
+// parts in turn: 168 / 175.  More registers per thread (no spills in the 4-bit mode at d = 128) leave one workgroup per CU:
+// 153 / 170.  K by 64-byte pieces of four lanes and an exchange in registers pays at d = 256 only, where a lane's own
+// piece is a whole cache line (quad_exchange).
+template <int D, bool INT4, bool CAUSAL, bool BF16>
+__global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnParams p, const RawParams x) {
+  constexpr int CPL = D / 4;                                     // K: channels per lane
+  constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BKV / NRG;   // V: 8 channels of RPT consecutive keys per thread
+  constexpr int CT = D / 32, CTW = (CT + 3) / 4;                 // channel tiles of the output, per wavefront
+  constexpr int KCK = (int)(k_block_bytes(D, INT4) / 16), KC = D * BKV / 16;
+  constexpr int QMAX = INT4 ? 7 : 127;
+  constexpr int NP = qk_pieces<D, INT4>();
+  constexpr int QMS = CPL + 2;     // doubles per (head, channel quarter) in s_qm: 16 of them start in 16 different bank groups
+  __shared__ v4i s_k[2][KCK];
+  __shared__ v4i s_v[2][KC];
+  __shared__ __align__(16) float s_ds[INT4 ? 2 : 1][INT4 ? PACK_G : 1][BKV];
+  __shared__ __align__(16) double s_qm[INT4 ? PACK_G * 4 * QMS : 2];
+  __shared__ __align__(16) float s_km[D], s_vs[D], s_vi[D];      // mean(K); delta_V and its reciprocal (0: divide)
+  __shared__ float s_ks[2][4];
+
+  const int t = threadIdx.x, lane = t & 63;
+  const bool quantizer = __builtin_amdgcn_readfirstlane(t >> 8) == 0;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6) & 3;
+  const int n = lane & 31, half = lane >> 5;
+  const int split = blockIdx.x % p.splits, tile = blockIdx.x / p.splits;
+  const int G = p.H / p.Hkv;
+  const int b = tile / p.Hkv, h = (tile - b * p.Hkv) * G;        // the group's first query head
+  const size_t bh = (size_t)b * p.H + h, bhkv = tile;
+  const Seq sq = seq_of(p.seq, (unsigned)b, p.N, p.Nk);
+  if (sq.n <= 0) return;
+  const int col = n, cols = G * sq.n;                            // (cols <= 32: the launch rule)
+  const bool col_ok = col < cols;
+  const int hq = col_ok ? col / sq.n : 0, query = col_ok ? col - hq * sq.n : 0;
+  if (sq.nk == 0) {                                              // no keys at all: the rows are defined as zeros
+    if (split != 0) return;
+    for (int idx = t; idx < cols * (D / 8); idx += 512) {
+      const int c = idx / (D / 8), g = c / sq.n, r = c - g * sq.n;
+      unsigned short* o = reinterpret_cast<unsigned short*>(p.out) + row_offset(p.om, head_offset(p.om, (unsigned)(bh + g)), (int)sq.q0 + r);
+      *reinterpret_cast<uint4*>(o + (idx % (D / 8)) * 8) = make_uint4(0u, 0u, 0u, 0u);
+    }
+    if (p.lse && t < cols) p.lse[lse_index(p, sq, b, h + t / sq.n, t % sq.n)] = -INFINITY;
+    return;
+  }
+  int j0, j1;
+  {
+    int nblk = (sq.nk + BKV - 1) / BKV;
+    if (CAUSAL) nblk = min(nblk, (BQ - 1 + sq.coff) / BKV + 1);
+    const int n_vis = CAUSAL ? min(nblk, sq.coff / BKV + 1) : nblk;
+    const KeyChunk kc = key_chunk(split, p.splits, nblk, n_vis);
+    j0 = kc.j0;
+    j1 = kc.j1;
+  }
+  if (j0 >= j1) {                                                // an empty chunk: offset -inf, sum 0 (the merge skips it)
+    if (t < BQ) {
+      float* el = p.part_el + ((size_t)blockIdx.x * BQ + t) * 2;
+      el[0] = -INFINITY; el[1] = 0.0f;
+    }
+    return;
+  }
+
+  for (int c = t; c < D; c += 512) {
+    s_km[c] = x.k_mean[bhkv * D + c];
+    const float vs = p.v_scale[bhkv * D + c];
+    s_vs[c] = vs;
+    s_vi[c] = div_by_ok(vs) ? __fdiv_rn(1.0f, vs) : 0.0f;
+  }
+  if constexpr (INT4) {
+    for (int idx = t; idx < PACK_G * D; idx += 512) {
+      const int g = idx / D, c = idx % D;
+      s_qm[(g * 4 + c / CPL) * QMS + c % CPL] = g < G ? (double)x.q_mean[(bh + g) * D + c] : 0.0;
+    }
+  }
+  __syncthreads();
+
+  if (quantizer) {
+    // ---- this thread's share of a block: K as in k_quant_k - lane l of wavefront w holds key 16 w + l % 16, channels
+    // CPL (l / 16) .. - and V by rows
+    const int kk = lane >> 4, c0 = CPL * kk, kr = 16 * w + (lane & 15);
+    const int cg = t % NCG, vr = RPT * (t / NCG);
+    const size_t hbase = head_offset(x.km, (unsigned)bhkv) + sq.k0 * (size_t)x.km.sn;
+    uint4 rk[CPL / 8], rv[RPT];
+    auto fetch_k = [&](int j) {
+      const int key = j * BKV + kr;
+#pragma unroll
+      for (int i = 0; i < CPL / 8; ++i)
+        rk[i] = j < j1 && key < sq.nk ? *reinterpret_cast<const uint4*>(x.k + row_offset(x.km, hbase, key) +
+                                                                        (D == 256 ? 8 * quad_piece<D>(i, kk) : c0 + 8 * i))
+                                      : make_uint4(0u, 0u, 0u, 0u);
+    };
+    auto fetch_v = [&](int j) {
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+        const int kv = j * BKV + vr + i;
+        rv[i] = j < j1 && kv < sq.nk ? nt_load16(x.v + row_offset(x.km, hbase, kv) + 8 * cg) : make_uint4(0u, 0u, 0u, 0u);
+      }
+    };
+    fetch_k(j0);
+    fetch_v(j0);
+    bool v_fast = true;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v_fast = v_fast && (s_vi[8 * cg + e] != 0.0f || s_vs[8 * cg + e] == 0.0f);   // (an all-zero channel: 0 * 0 = 0 either way)
+    for (int j = j0, cur = 0; j < j1; ++j, cur ^= 1) {
+      // ---- K: smooth, group maximum over the wavefront's 16 keys, codes and scale (k_quant_k's arithmetic)
+      {
+        float xk[CPL];
+        float mx = 0.0f;
+        if constexpr (D == 256) quad_exchange<D>(rk);
+#pragma unroll
+        for (int i = 0; i < CPL / 8; ++i) {
+          unpack8<BF16>(rk[i], &xk[8 * i]);
+          const float4 m0 = *reinterpret_cast<const float4*>(&s_km[c0 + 8 * i]);
+          const float4 m1 = *reinterpret_cast<const float4*>(&s_km[c0 + 8 * i + 4]);
+          const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) xk[8 * i + e] = __fsub_rn(xk[8 * i + e], mean[e]);
+        }
+        fetch_k(j + 1);                    // (the registers are free; in flight under the rest of this block's work)
+        if (j * BKV + BKV > sq.nk && j * BKV + kr >= sq.nk) {        // padded keys: codes 0, Delta-S 0
+#pragma unroll
+          for (int e = 0; e < CPL; ++e) xk[e] = 0.0f;
+        }
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(xk[e]));
+        const float delta = __fdiv_rn(wave_max_dpp(mx), (float)QMAX);
+        if (lane == 0) s_ks[cur][w] = delta;
+        // codes: the wavefront is one group, so one reciprocal and one decision serve all of it
+        const bool fast = __builtin_amdgcn_readfirstlane(div_by_ok(delta));
+        const float rd = fast ? __fdiv_rn(1.0f, delta) : 0.0f;
+        uint8_t* img = reinterpret_cast<uint8_t*>(&s_k[cur][0]);
+        if constexpr (INT4) {
+          // Delta-S: q_bar_g . gamma(K)_t in float64, four heads at a time by v_mfma_f64_4x4x4_4b_f64: four independent
+          // 4 x 4 products per instruction, lane l supplies A[l % 4][l / 16] and B[l / 16][l % 4] of product (l / 4) % 4 and
+          // receives D[l / 16][l % 4].  Product i holds keys 16 w + 4 i + 0..3, contraction slot (step cs, l / 16) channel
+          // CPL (l / 16) + cs: the lane's own registers, in order.  (The 16-row form of the
+          // general path spends 2048 matrix cycles per block on rows that a few heads leave empty; this one 512 per 4 heads.)
+          const double kap = (double)p.kappa;
+          const double* qa = &s_qm[((lane & 3) * 4 + kk) * QMS];
+          auto delta_s = [&](int first) {
+            double acc[2] = {0.0, 0.0};                    // (two chains: each instruction waits for its accumulator)
+#pragma unroll
+            for (int cs = 0; cs < CPL; ++cs) {
+              float xs = xk[cs];
+              asm volatile("" : "+v"(xs) :: "memory");     // (operands are read and widened as they are used, not all at once)
+              acc[cs & 1] = __builtin_amdgcn_mfma_f64_4x4x4f64(qa[4 * first * QMS + cs], (double)xs, acc[cs & 1], 0, 0, 0);
+            }
+            s_ds[cur][first + kk][kr] = (float)(kap * (acc[0] + acc[1]));
+          };
+          delta_s(0);
+          if (G > 4) delta_s(4);
+          constexpr int NPL = CPL > 32 ? CPL / 32 : 1, CPP = CPL / NPL;
+#pragma unroll
+          for (int pl = 0; pl < NPL; ++pl) {
+            Codes32 cd;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) { cd.ev[e] = 0.0f; cd.od[e] = 0.0f; }
+            if (fast) {
+#pragma unroll
+              for (int e = 0; e < CPP; ++e) cd.set(e, rintf(div_by(xk[CPP * pl + e], delta, rd)));
+            } else {
+#pragma unroll
+              for (int e = 0; e < CPP; ++e) cd.set(e, (float)quant_code(xk[CPP * pl + e], delta, QMAX));
+            }
+            const v6u pw = cd.pack();
+            int lane_m, e0;
+            const size_t op = k_op6(kr, c0 + CPP * pl, D, &lane_m, &e0);
+            const int d0 = (6 * e0) >> 5;
+#pragma unroll
+            for (int i = 0; i < CPP * 6 / 32; ++i)
+              *reinterpret_cast<unsigned*>(img + op + op6_byte(lane_m, 4 * (d0 + i))) = pw[i];
+          }
+        } else {
+          // (adding 1.5 * 2^23 rounds to the nearest integer, ties to even, and leaves it in the low mantissa bits, so the
+          // low byte is the code)
+#pragma unroll
+          for (int i = 0; i < CPL / 16; ++i) {
+            unsigned c[16];
+            if (fast) {
+#pragma unroll
+              for (int e = 0; e < 16; ++e) c[e] = __float_as_uint(div_by(xk[16 * i + e], delta, rd) + 12582912.0f);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 16; ++e) c[e] = (unsigned)quant_code(xk[16 * i + e], delta, QMAX);
+            }
+            unsigned wd[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              wd[q] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(c[4 * q + 3], c[4 * q + 2], 0x0c0c0400u),
+                                            __builtin_amdgcn_perm(c[4 * q + 1], c[4 * q], 0x0c0c0400u), 0x05040100u);
+            *reinterpret_cast<uint4*>(img + k_code_off(kr, c0 + 16 * i, D)) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+          }
+        }
+      }
+      // ---- V: codes of RPT consecutive keys of a channel side by side.  Channel c's 16-byte chunks are XOR-ed in their
+      // place by (c / 16) % 8, so that the 16 channel groups of a store meet 16 different bank groups
+      {
+        uint8_t* img = reinterpret_cast<uint8_t*>(&s_v[cur][0]);
+        float xv[RPT][8], vs[8], vi[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { vs[e] = s_vs[8 * cg + e]; vi[e] = s_vi[8 * cg + e]; }
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) unpack8<BF16>(rv[i], xv[i]);
+        fetch_v(j + 1);
+        if (v_fast) {
+#pragma unroll
+          for (int i = 0; i < RPT; ++i) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xv[i][e] = div_by(xv[i][e], vs[e], vi[e]);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < RPT; ++i) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xv[i][e] = vs[e] > 0.0f ? __fdiv_rn(xv[i][e], vs[e]) : 0.0f;
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int c = 8 * cg + e;
+          const size_t off = v_code_off(vr, c, D) ^ (size_t)(((c >> 4) & 7) * 16);
+          int wd[(RPT + 3) / 4];
+#pragma unroll
+          for (int i = 0; i < RPT; i += 2) {
+            if ((i & 2) == 0) wd[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(xv[i][e], xv[i + 1][e], 0, false);
+            else wd[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(xv[i][e], xv[i + 1][e], wd[i / 4], true);
+          }
+          if constexpr (RPT == 2) *reinterpret_cast<unsigned short*>(img + off) = (unsigned short)wd[0];
+          else if constexpr (RPT == 4) *reinterpret_cast<int*>(img + off) = wd[0];
+          else *reinterpret_cast<int2*>(img + off) = make_int2(wd[0], wd[RPT / 4 - 1]);
+        }
+      }
+      __syncthreads();                     // block j is in LDS; the other wavefronts are done with block j - 1
+    }
+    return;
+  }
+
+  // ---- the wavefront's Q^ operands: all four hold the same 32 columns
+  typename QkOperand<INT4>::type qreg[NP];
+  {
+    const v4i* gq = reinterpret_cast<const v4i*>(p.q_codes + (bh + hq) * q_slab_bytes(D, INT4));
+#pragma unroll
+    for (int s = 0; s < NP; ++s) qreg[s] = load_qk_operand<INT4>(gq, s, query + 32 * half);
+  }
+  const float dq = p.q_scale[(bh + hq) * (BQ / QGROUP) + query / QGROUP];
+  const float lse_corr = p.lse ? p.q_corr[(bh + hq) * BQ + query] : 0.0f;
+  constexpr int DW = 32 * CTW;                                   // this wavefront's channels: DW w ..
+  RowState<DW> st;
+#pragma unroll
+  for (int ct = 0; ct < CTW; ++ct) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) st.O[ct][v] = 0.0f;
+  }
+  st.m_run = -INFINITY;
+  st.l_run = 0.0f;
+  float m_sub = -INFINITY;
+  const bool working = w * CTW < CT;                             // (d = 64: two wavefronts have no channels)
+  int n_plain = min(j1, sq.nk / BKV);                            // blocks that need no mask
+  if (CAUSAL) n_plain = min(n_plain, (sq.coff + 1) / BKV);
+  const int n_keys_end = min(sq.nk, j1 * BKV);
+  for (int j = j0, cur = 0; j < j1; ++j, cur ^= 1) {
+    __syncthreads();
+    if (!working) continue;
+    v8i pb;
+    float alpha;
+    auto attend = [&](auto masked_) {
+      constexpr bool MASKED = decltype(masked_)::value;
+      typename KBlockRegs<D, INT4>::type ka;
+      read_k_block<D, INT4>(&s_k[cur][0], lane, ka);
+      KeyScales<0> ks;
+      ks.s[0] = s_ks[cur][half];
+      ks.s[1] = s_ks[cur][2 + half];
+      v16i raw[2], sc[2];
+      qk_tile<D, INT4>(ka, qreg, raw);
+      asm volatile("" ::: "memory");     // Delta-S is read after the operands of the product, into registers they leave
+      if constexpr (INT4) {
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+          const v4f* dsv = reinterpret_cast<const v4f*>(&s_ds[cur][hq][32 * kt + 16 * half]);
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const v4f t4 = dsv[g];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sc[kt][4 * g + r] = __float_as_int(t4[r]);
+          }
+        }
+      }
+      Factors<0> fac;
+      fac.set(dq, p.kappa, ks);
+      const int key0 = j * BKV, last = query + sq.coff;
+      dequant_group<INT4, CAUSAL, MASKED, 0, 0, 0>(raw, sc, fac, half, key0, last, n_keys_end);
+      dequant_group<INT4, CAUSAL, MASKED, 0, 0, 1>(raw, sc, fac, half, key0, last, n_keys_end);
+      dequant_group<INT4, CAUSAL, MASKED, 0, 0, 2>(raw, sc, fac, half, key0, last, n_keys_end);
+      dequant_group<INT4, CAUSAL, MASKED, 0, 0, 3>(raw, sc, fac, half, key0, last, n_keys_end);
+      dequant_group<INT4, CAUSAL, MASKED, 0, 1, 0>(raw, sc, fac, half, key0, last, n_keys_end);
+      dequant_group<INT4, CAUSAL, MASKED, 0, 1, 1>(raw, sc, fac, half, key0, last, n_keys_end);
+      dequant_group<INT4, CAUSAL, MASKED, 0, 1, 2>(raw, sc, fac, half, key0, last, n_keys_end);
+      dequant_group<INT4, CAUSAL, MASKED, 0, 1, 3>(raw, sc, fac, half, key0, last, n_keys_end);
+      alpha = update_max<DW, INT4, 0, PV_E4M3>(st, sc, fac, m_sub);
+      float ls = 0.0f;
+      exp_group<INT4, MASKED, 0, PV_E4M3, 0, 0>(sc, fac, m_sub, pb, ls);
+      exp_group<INT4, MASKED, 0, PV_E4M3, 0, 1>(sc, fac, m_sub, pb, ls);
+      exp_group<INT4, MASKED, 0, PV_E4M3, 0, 2>(sc, fac, m_sub, pb, ls);
+      exp_group<INT4, MASKED, 0, PV_E4M3, 0, 3>(sc, fac, m_sub, pb, ls);
+      exp_group<INT4, MASKED, 0, PV_E4M3, 1, 0>(sc, fac, m_sub, pb, ls);
+      exp_group<INT4, MASKED, 0, PV_E4M3, 1, 1>(sc, fac, m_sub, pb, ls);
+      exp_group<INT4, MASKED, 0, PV_E4M3, 1, 2>(sc, fac, m_sub, pb, ls);
+      exp_group<INT4, MASKED, 0, PV_E4M3, 1, 3>(sc, fac, m_sub, pb, ls);
+      st.l_run = __fmaf_rn(alpha, st.l_run, ls);
+    };
+    if (j < n_plain) attend(std::false_type{}); else attend(std::true_type{});
+    block_rescale<DW>(st, alpha);
+    v4i va[2 * CTW];
+#pragma unroll
+    for (int i = 0; i < 2 * CTW; ++i) {
+      const int ct = w * CTW + i / 2;
+      va[i] = s_v[cur][(ct * 2 + (i & 1)) * 64 + (lane ^ ((2 * ct + (n >> 4)) & 7))];
+    }
+    pv_step<DW, 0, PV_E4M3>(st, va, pb);
+    if constexpr (CTW > 1) pv_step<DW, CTW - 1, PV_E4M3>(st, va, pb);
+    settle(st.O);
+  }
+  if (!working || !col_ok) return;
+
+  float l_tot = st.l_run;
+  {
+    const unsigned u = __float_as_uint(l_tot);
+    const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+  if (p.splits > 1) {
+    const size_t prow = (size_t)blockIdx.x * BQ + col;
+    if (w == 0 && half == 0) { p.part_el[prow * 2] = m_sub; p.part_el[prow * 2 + 1] = l_tot; }
+#pragma unroll
+    for (int ct = 0; ct < CTW; ++ct) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const v4f o4 = {st.O[ct][4 * g], st.O[ct][4 * g + 1], st.O[ct][4 * g + 2], st.O[ct][4 * g + 3]};
+        *reinterpret_cast<v4f*>(p.part_o + prow * D + DW * w + 32 * ct + 8 * g + 4 * half) = o4;
+      }
+    }
+    return;
+  }
+  if (p.lse && w == 0 && half == 0)
+    p.lse[lse_index(p, sq, b, h + hq, query)] = LN2 * ((m_sub + __builtin_amdgcn_logf(l_tot)) + lse_corr);
+  const float inv_l = __fdiv_rn(1.0f, l_tot);
+  unsigned short* orow = reinterpret_cast<unsigned short*>(p.out) +
+                         row_offset(p.om, head_offset(p.om, (unsigned)(bh + hq)), (int)sq.q0 + query);
+#pragma unroll
+  for (int ct = 0; ct < CTW; ++ct) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int oc = DW * w + 32 * ct + 8 * g + 4 * half;
+      const v4f sc = *reinterpret_cast<const v4f*>(p.v_scale + bhkv * D + oc);
+      float o4[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o4[r] = __fmul_rn(__fmul_rn(st.O[ct][4 * g + r], inv_l), sc[r]);
+      *reinterpret_cast<uint2*>(orow + oc) = make_uint2(pack16x2<BF16>(o4[0], o4[1]), pack16x2<BF16>(o4[2], o4[3]));
+    }
+  }
+}
+
+// Calls the kernel above serves: the 32 columns of a tile hold all queries that meet a KV head (beyond 32 the softmax piece
+// would be repeated for columns that another wavefront holds on the general path), with the default groups, data types
+// and smoothing; in the 4-bit mode Delta-S in float64 (the library's own choice for so few block means).  A workgroup works
+// through its chunk block by block, about 2 us each, where the general path spreads the quantizers over the chip: with
+// fewer than 96 workgroups that serial chain is longer than the launches it saves.  Whole calls, us, general path / this
+// one, d = 128 unless said: 8 KV heads, 4000 keys (56 workgroups) 37 / 42; 4 KV heads of 256 channels, 5000 keys (36) 54 /
+// 57; 8, 8192 keys (128) 46 / 41, 8-bit mode 42 / 34; 32 of 64 channels, 3000 keys (160) 41 / 34; 16 x 8, 5003 keys 142 /
+// 106; 4 x 8, 32768 keys 358 / 272; 16 of 256 channels, 60000 keys 600 / 391.
+bool attention_raw_ok(const Dims& D) {
+  const int G = D.H / D.Hkv;
+  return G <= PACK_G && (long long)G * D.N <= 32 && (long long)D.B * D.Hkv * D.splits >= 96 && D.kg == KGROUP && !D.block_groups && D.pvf == PV_E4M3 &&
+         D.smooth_k && D.smooth_q && !D.smooth_v && (!D.int4 || D.ds_mode == 2);
+}
+
+template <int DD, bool INT4, bool CAUSAL>
+static hipError_t launch_raw_t(const Dims& D, const Ptrs& P, hipStream_t s) {
+  AttnParams p = attn_params(D, P);
+  p.total_tiles = D.B * D.Hkv;
+  RawParams x;
+  x.k = (const unsigned short*)P.k; x.v = (const unsigned short*)P.v;
+  x.k_mean = P.k_mean; x.q_mean = P.q_mean;
+  x.km = make_tensor_map(D.nhd, D.Hkv, D.Nk, D.d, D.seq.cu_q != nullptr);
+  const int grid = p.total_tiles * D.splits;
+  if (D.bf16) k_attn_raw<DD, INT4, CAUSAL, true><<<grid, 512, 0, s>>>(p, x);
+  else        k_attn_raw<DD, INT4, CAUSAL, false><<<grid, 512, 0, s>>>(p, x);
+  if (D.splits > 1) return launch_merge_packed(D, p, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_attention_raw(const Dims& D, const Ptrs& P, hipStream_t s) {
+#define SAGE_RAW(DD) \
+  do { \
+    if (D.int4) return D.causal ? launch_raw_t<DD, true, true>(D, P, s) : launch_raw_t<DD, true, false>(D, P, s); \
+    return D.causal ? launch_raw_t<DD, false, true>(D, P, s) : launch_raw_t<DD, false, false>(D, P, s); \
+  } while (0)
+  if (D.d == 256) SAGE_RAW(256);
+  else if (D.d == 128) SAGE_RAW(128);
+  else SAGE_RAW(64);
+#undef SAGE_RAW
+}
+
+}  // namespace sage

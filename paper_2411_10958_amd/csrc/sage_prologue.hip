@@ -6,125 +6,10 @@
 // per-element divisions and per-element code packing.  Codes are written in the MFMA fragment
 // order described in sage_common.h so that the attention kernel can move them with plain 16-byte
 // copies.
-#include "sage_common.h"
+#include "sage_quant.h"
 #include "sage_attn.h"
 
 namespace sage {
-
-// ------------------------------------------------------------------------------------------
-// small helpers
-// 16-byte load marked non-temporal: Q, K and V are streamed once per pass, and keeping them out of the
-// way of the caches measured 25 % faster on the statistics pass
-__device__ inline uint4 nt_load16(const unsigned short* p) {
-  typedef unsigned v4u __attribute__((ext_vector_type(4)));
-  const v4u r = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p));
-  return make_uint4(r[0], r[1], r[2], r[3]);
-}
-
-template <bool BF16, bool NT = true>
-__device__ inline void load8(const unsigned short* p, float (&x)[8]) {
-  const uint4 raw = NT ? nt_load16(p) : *reinterpret_cast<const uint4*>(p);
-  const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    x[2 * i] = load16<BF16>((unsigned short)(w[i] & 0xffffu));
-    x[2 * i + 1] = load16<BF16>((unsigned short)(w[i] >> 16));
-  }
-}
-
-template <bool BF16>
-__device__ inline void unpack8(const uint4& raw, float* x) {
-  const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    x[2 * i] = load16<BF16>((unsigned short)(w[i] & 0xffffu));
-    x[2 * i + 1] = load16<BF16>((unsigned short)(w[i] >> 16));
-  }
-}
-
-__device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
-  return v;
-}
-
-// psi of Sec. 2.2: code = clip(round-half-even(x / delta)); delta == 0 gives code 0.
-__device__ inline int quant_code(float x, float delta, int qmax) {
-  if (!(delta > 0.0f)) return 0;
-  const float r = rintf(__fdiv_rn(x, delta));
-  const int c = (int)r;
-  return c > qmax ? qmax : (c < -qmax ? -qmax : c);
-}
-
-// The same psi without a division per element.  With r = 1/delta to within 1 ulp (the hardware
-// reciprocal), y = fl32(x * r) differs from the oracle's fl32(x / delta) by at most 2^-22 |y|, so
-// whenever y is further than tau = 2^-14 (|y| <= 127.5) or 2^-18 (|y| <= 7.5) from a half-integer the
-// two round to the same integer.  QuantScale holds r and the bound 0.5 - tau; the caller takes the
-// largest |y - rint(y)| of a group of elements and recomputes the group with quant_code when it
-// exceeds the bound (about one element in 2^13 resp. 2^17).  Scales outside [2^-100, 2^100]
-// always take the exact path (bound -1); delta == 0 gives r = 0 and codes 0.  No clamp is needed:
-// |x| <= the group maximum, and fl32(max / fl32(max / qmax)) rounds to qmax.
-struct QuantScale { float r, bound; };
-template <int QMAX>
-__device__ inline QuantScale quant_scale(float delta) {
-  QuantScale q;
-  const bool regular = delta >= 0x1p-100f && delta <= 0x1p100f;
-  q.r = regular ? __builtin_amdgcn_rcpf(delta) : 0.0f;
-  q.bound = (regular || delta == 0.0f) ? 0.5f - (QMAX > 7 ? 0x1p-14f : 0x1p-18f) : -1.0f;
-  return q;
-}
-// NE codes (as integer-valued floats) of x[0..NE) with one scale, handed to put(e, code)
-template <int NE, int QMAX, class Put>
-__device__ inline void quant_group(const float* x, float delta, const QuantScale& qs, Put&& put) {
-  float worst = 0.0f;
-#pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    const float y = x[e] * qs.r;
-    const float c = rintf(y);
-    worst = fmaxf(worst, fabsf(y - c));
-    put(e, c);
-  }
-  if (!(worst <= qs.bound)) {
-#pragma unroll
-    for (int e = 0; e < NE; ++e) put(e, (float)quant_code(x[e], delta, QMAX));
-  }
-}
-
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef unsigned v6u __attribute__((ext_vector_type(6)));
-// 32 INT4 codes held as integer-valued floats (every integer of [-7, 7] is an E2M3 value) become
-// consecutive 6-bit E2M3 fields, element e at bit 6e: the conversion instruction takes the even
-// elements in its first operand and the odd ones in its second (scale 1.0), so the codes are
-// collected in that shape from the start
-struct Codes32 {
-  v16f ev, od;
-  __device__ inline void set(int e, float c) { if (e & 1) od[e >> 1] = c; else ev[e >> 1] = c; }
-  // The instruction writes its first result registers before it has read all of its inputs, and
-  // the compiler does not know: a result allocated on top of part of an input corrupts the codes.
-  // The empty asm statements make both operands opaque 16-register values and then need them and
-  // the result at the same time, which keeps the three register ranges apart.  (Vector operands
-  // of asm statements do not parse in the host pass, which never calls this.)
-  __device__ inline v6u pack() const {
-    v6u r = {0u, 0u, 0u, 0u, 0u, 0u};
-#if defined(__HIP_DEVICE_COMPILE__)
-    v16f a = ev, b = od;
-    asm volatile("" : "+v"(a), "+v"(b));
-    r = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, 1.0f);
-    asm volatile("" ::"v"(r), "v"(a), "v"(b));
-#endif
-    return r;
-  }
-};
-
-// eight int8 codes as two's-complement bytes
-__device__ inline uint2 pack8(const int (&c)[8]) {
-  uint2 o;
-  o.x = (unsigned)(c[0] & 0xff) | ((unsigned)(c[1] & 0xff) << 8) | ((unsigned)(c[2] & 0xff) << 16) |
-        ((unsigned)(c[3] & 0xff) << 24);
-  o.y = (unsigned)(c[4] & 0xff) | ((unsigned)(c[5] & 0xff) << 8) | ((unsigned)(c[6] & 0xff) << 16) |
-        ((unsigned)(c[7] & 0xff) << 24);
-  return o;
-}
 
 // ------------------------------------------------------------------------------------------
 // Column statistics: exact token sums of K (float64 accumulation of 16-bit values) and
@@ -1226,7 +1111,7 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
 }
 
 template <bool BF16, bool INT4, int D>
-static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
+static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s, bool quant_kv) {
   const int BH = Dm.B * Dm.H, BHkv = Dm.B * Dm.Hkv;
   const unsigned short* q = (const unsigned short*)P.q;
   const unsigned short* k = (const unsigned short*)P.k;
@@ -1278,6 +1163,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   if (!Dm.want_lse) quant_q();
   if (!Dm.stats_given) launch_stats_t<BF16, D>(Dm, P, s);     // else P.k_mean and P.v_scale are the caller's arrays
   if (Dm.want_lse) quant_q();
+  if (!quant_kv) return hipGetLastError();
   if (Dm.tensor_groups) {
     quant_k_pass(nullptr, 1);
     k_head_scale<<<BHkv, 256, 0, s>>>(P.k_scale, P.k_head_scale, BKV / Dm.kg, Dm.nKb * (BKV / Dm.kg), BKV, Dm.Hkv, 1,
@@ -1301,8 +1187,8 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_prologue(const Dims& D, const Ptrs& P, hipStream_t s) {
-#define SAGE_PRO(BF, I4, DD) return launch_prologue_t<BF, I4, DD>(D, P, s)
+hipError_t launch_prologue(const Dims& D, const Ptrs& P, hipStream_t s, bool quant_kv) {
+#define SAGE_PRO(BF, I4, DD) return launch_prologue_t<BF, I4, DD>(D, P, s, quant_kv)
   if (D.d == 256) {
     if (D.bf16) { if (D.int4) SAGE_PRO(true, true, 256); else SAGE_PRO(true, false, 256); }
     else        { if (D.int4) SAGE_PRO(false, true, 256); else SAGE_PRO(false, false, 256); }

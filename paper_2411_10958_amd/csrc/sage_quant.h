@@ -1,0 +1,185 @@
+// Device code shared by the kernels that quantize Q, K and V (sage_prologue.hip, sage_attn_raw.hip): loads, the quantizer
+// psi of Sec. 2.2 and the packing of its codes.
+#pragma once
+#include "sage_common.h"
+
+namespace sage {
+
+// 16-byte load marked non-temporal: Q, K and V are streamed once per pass, and keeping them out of the
+// way of the caches measured 25 % faster on the statistics pass
+__device__ inline uint4 nt_load16(const unsigned short* p) {
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
+  const v4u r = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p));
+  return make_uint4(r[0], r[1], r[2], r[3]);
+}
+
+template <bool BF16, bool NT = true>
+__device__ inline void load8(const unsigned short* p, float (&x)[8]) {
+  const uint4 raw = NT ? nt_load16(p) : *reinterpret_cast<const uint4*>(p);
+  const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    x[2 * i] = load16<BF16>((unsigned short)(w[i] & 0xffffu));
+    x[2 * i + 1] = load16<BF16>((unsigned short)(w[i] >> 16));
+  }
+}
+
+template <bool BF16>
+__device__ inline void unpack8(const uint4& raw, float* x) {
+  const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    x[2 * i] = load16<BF16>((unsigned short)(w[i] & 0xffffu));
+    x[2 * i + 1] = load16<BF16>((unsigned short)(w[i] >> 16));
+  }
+}
+
+__device__ inline float wave_max(float v) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
+  return v;
+}
+
+// the same without LDS round trips: exchanges inside groups of 16 lanes, then between them
+__device__ __forceinline__ float wave_max_dpp(float v) {
+#define SAGE_DPP_MAX(CTRL_) \
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL_, 0xf, 0xf, true)))
+  SAGE_DPP_MAX(0xB1);      // quad_perm [1, 0, 3, 2]
+  SAGE_DPP_MAX(0x4E);      // quad_perm [2, 3, 0, 1]
+  SAGE_DPP_MAX(0x141);     // row_half_mirror
+  SAGE_DPP_MAX(0x140);     // row_mirror
+#undef SAGE_DPP_MAX
+  unsigned u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  u = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+  const auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// x / s rounded to nearest, given r = fl32(1 / s): the quotient corrected by its exact remainder (Markstein), three
+// instructions.  Correct for every s that div_by_ok accepts (the mantissa of all ones is the theorem's exception), except
+// where the remainder underflows: quotients below 2^-40, which every 8-bit and 4-bit code rounds to 0.
+__device__ __forceinline__ float div_by(float x, float s, float r) {
+  const float q = __fmul_rn(x, r);
+  return __fmaf_rn(__fmaf_rn(-q, s, x), r, q);
+}
+__device__ __forceinline__ bool div_by_ok(float s) {
+  return s >= 0x1p-60f && s <= 0x1p60f && (__float_as_uint(s) & 0x7fffffu) != 0x7fffffu;
+}
+
+// psi of Sec. 2.2: code = clip(round-half-even(x / delta)); delta == 0 gives code 0.
+__device__ inline int quant_code(float x, float delta, int qmax) {
+  if (!(delta > 0.0f)) return 0;
+  const float r = rintf(__fdiv_rn(x, delta));
+  const int c = (int)r;
+  return c > qmax ? qmax : (c < -qmax ? -qmax : c);
+}
+
+// The same psi without a division per element.  With r = 1/delta to within 1 ulp (the hardware
+// reciprocal), y = fl32(x * r) differs from the oracle's fl32(x / delta) by at most 2^-22 |y|, so
+// whenever y is further than tau = 2^-14 (|y| <= 127.5) or 2^-18 (|y| <= 7.5) from a half-integer the
+// two round to the same integer.  QuantScale holds r and the bound 0.5 - tau; the caller takes the
+// largest |y - rint(y)| of a group of elements and recomputes the group with quant_code when it
+// exceeds the bound (about one element in 2^13 resp. 2^17).  Scales outside [2^-100, 2^100]
+// always take the exact path (bound -1); delta == 0 gives r = 0 and codes 0.  No clamp is needed:
+// |x| <= the group maximum, and fl32(max / fl32(max / qmax)) rounds to qmax.
+struct QuantScale { float r, bound; };
+template <int QMAX>
+__device__ inline QuantScale quant_scale(float delta) {
+  QuantScale q;
+  const bool regular = delta >= 0x1p-100f && delta <= 0x1p100f;
+  q.r = regular ? __builtin_amdgcn_rcpf(delta) : 0.0f;
+  q.bound = (regular || delta == 0.0f) ? 0.5f - (QMAX > 7 ? 0x1p-14f : 0x1p-18f) : -1.0f;
+  return q;
+}
+// NE codes (as integer-valued floats) of x[0..NE) with one scale, handed to put(e, code)
+template <int NE, int QMAX, class Put>
+__device__ inline void quant_group(const float* x, float delta, const QuantScale& qs, Put&& put) {
+  float worst = 0.0f;
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const float y = x[e] * qs.r;
+    const float c = rintf(y);
+    worst = fmaxf(worst, fabsf(y - c));
+    put(e, c);
+  }
+  if (!(worst <= qs.bound)) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) put(e, (float)quant_code(x[e], delta, QMAX));
+  }
+}
+
+typedef unsigned v6u __attribute__((ext_vector_type(6)));
+// 32 INT4 codes held as integer-valued floats (every integer of [-7, 7] is an E2M3 value) become
+// consecutive 6-bit E2M3 fields, element e at bit 6e: the conversion instruction takes the even
+// elements in its first operand and the odd ones in its second (scale 1.0), so the codes are
+// collected in that shape from the start
+struct Codes32 {
+  v16f ev, od;
+  __device__ inline void set(int e, float c) { if (e & 1) od[e >> 1] = c; else ev[e >> 1] = c; }
+  // The instruction writes its first result registers before it has read all of its inputs, and
+  // the compiler does not know: a result allocated on top of part of an input corrupts the codes.
+  // The empty asm statements make both operands opaque 16-register values and then need them and
+  // the result at the same time, which keeps the three register ranges apart.  (Vector operands
+  // of asm statements do not parse in the host pass, which never calls this.)
+  __device__ inline v6u pack() const {
+    v6u r = {0u, 0u, 0u, 0u, 0u, 0u};
+#if defined(__HIP_DEVICE_COMPILE__)
+    v16f a = ev, b = od;
+    asm volatile("" : "+v"(a), "+v"(b));
+    r = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, 1.0f);
+    asm volatile("" ::"v"(r), "v"(a), "v"(b));
+#endif
+    return r;
+  }
+};
+
+// eight int8 codes as two's-complement bytes
+__device__ inline uint2 pack8(const int (&c)[8]) {
+  uint2 o;
+  o.x = (unsigned)(c[0] & 0xff) | ((unsigned)(c[1] & 0xff) << 8) | ((unsigned)(c[2] & 0xff) << 16) |
+        ((unsigned)(c[3] & 0xff) << 24);
+  o.y = (unsigned)(c[4] & 0xff) | ((unsigned)(c[5] & 0xff) << 8) | ((unsigned)(c[6] & 0xff) << 16) |
+        ((unsigned)(c[7] & 0xff) << 24);
+  return o;
+}
+
+// A row of D 16-bit values by four lanes l, l + 16, l + 32, l + 48 (kk = 0..3), each of which wants D / 4 consecutive values
+// (pieces (D / 32) kk .. of 8 values).  Loaded that way, a load instruction touches 16 bytes of every 64 (d = 128) and
+// the four instructions meet in the caches or not at all.  Instead instruction i loads piece quad_piece(i, kk) - the
+// four lanes side by side, 64 bytes - and quad_exchange moves the pieces to their lanes, in registers.
+// In bits: the pieces' number is (i, kk) with the low two bits in the lane; exchanging a register bit with a lane bit is
+// one v_permlane32_swap or v_permlane16_swap per pair of registers.
+template <int D>
+__device__ __forceinline__ int quad_piece(int i, int kk) {
+  return 4 * i + (D == 64 ? 2 * (kk & 1) + (kk >> 1) : kk);
+}
+__device__ __forceinline__ void quad_swap32(uint4& a, uint4& b) {
+  auto r = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false); a.x = r[0]; b.x = r[1];
+  r = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false); a.y = r[0]; b.y = r[1];
+  r = __builtin_amdgcn_permlane32_swap(a.z, b.z, false, false); a.z = r[0]; b.z = r[1];
+  r = __builtin_amdgcn_permlane32_swap(a.w, b.w, false, false); a.w = r[0]; b.w = r[1];
+}
+__device__ __forceinline__ void quad_swap16(uint4& a, uint4& b) {
+  auto r = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false); a.x = r[0]; b.x = r[1];
+  r = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false); a.y = r[0]; b.y = r[1];
+  r = __builtin_amdgcn_permlane16_swap(a.z, b.z, false, false); a.z = r[0]; b.z = r[1];
+  r = __builtin_amdgcn_permlane16_swap(a.w, b.w, false, false); a.w = r[0]; b.w = r[1];
+}
+template <int D>
+__device__ __forceinline__ void quad_exchange(uint4 (&x)[D / 32]) {
+  if constexpr (D == 64) {             // bits (register; lane) = (p2; p0 p1) -> (p0; p2 p1)
+    quad_swap32(x[0], x[1]);
+  } else if constexpr (D == 128) {     // (p3 p2; p1 p0) -> (p1 p0; p3 p2)
+    quad_swap32(x[0], x[2]); quad_swap32(x[1], x[3]);
+    quad_swap16(x[0], x[1]); quad_swap16(x[2], x[3]);
+  } else {                             // (p4 p3 p2; p1 p0) -> (p1 p0 p2; p4 p3), then the registers in order
+    quad_swap32(x[0], x[4]); quad_swap32(x[1], x[5]); quad_swap32(x[2], x[6]); quad_swap32(x[3], x[7]);
+    quad_swap16(x[0], x[2]); quad_swap16(x[1], x[3]); quad_swap16(x[4], x[6]); quad_swap16(x[5], x[7]);
+    const uint4 y[8] = {x[0], x[2], x[4], x[6], x[1], x[3], x[5], x[7]};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = y[i];
+  }
+}
+
+}  // namespace sage

@@ -1,0 +1,115 @@
+"""Calls whose queries of a KV head fit 32 columns, with 96 workgroups or more (B x H_kv x key chunks), are served by a kernel
+that quantizes K and V itself (csrc/sage_attn_raw.hip).  sage_attn_prologue + sage_attn_core always take the general path, so the two can be compared on
+the same arguments: same codes, scales, chunks and order of blocks.  They differ where Delta-S, summed in float64 in another
+order, rounds to the other FP32 neighbour: that moves a code of P~ by one step now and then.  One step of the largest
+code (2^-4 of its value, on a key that carries all of a row) bounds any element: 2^-4 of the row's largest output, plus
+half a unit of the 16-bit type; all but a few elements are the same bits."""
+import ctypes
+
+import pytest
+import torch
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _pa():
+    import paper_2411_10958_amd as pa
+    pa.load_library()
+    return pa
+
+
+def _inputs(B, N, Nk, d, H, Hkv, dtype, layout, seed=0):
+    spec = wl.WorkloadSpec("raw", B, H, Hkv, N, d, dtype, True, 3.0, 1.5, 2, 10.0, 1.0, 77, 0.0, Nk)
+    data = wl.make_inputs(spec, seed)
+    q, k, v = (wl.to_torch(data[n], dtype, torch.device("cuda:0")) for n in "qkv")
+    if layout == "NHD":
+        q, k, v = (x.transpose(1, 2).contiguous() for x in (q, k, v))
+    return q, k, v
+
+
+def _both(pa, q, k, v, args):
+    """(out, lse) of the call as a whole and of its two halves (the general path)."""
+    lib, res = pa.load_library(), []
+    ws = torch.empty(pa.sage_attn_workspace_bytes(args), dtype=torch.uint8, device="cuda")
+    for whole in (True, False):
+        out = torch.full_like(q, 3.0)
+        lse = torch.full((args.B * args.H * args.N,), 5.0, dtype=torch.float32, device="cuda")
+        args.out, args.lse, args.workspace, args.workspace_bytes = out.data_ptr(), lse.data_ptr(), ws.data_ptr(), ws.numel()
+        if whole:
+            assert lib.sage_attn_fwd_ex(ctypes.byref(args)) == 0
+        else:
+            assert lib.sage_attn_prologue(ctypes.byref(args)) == 0 and lib.sage_attn_core(ctypes.byref(args)) == 0
+        torch.cuda.synchronize()
+        res.append((out, lse))
+    return res
+
+
+def _compare(res, dtype):
+    (a, la), (b, lb) = res
+    x, y = a.float(), b.float()
+    assert torch.isfinite(x).all()
+    bar = (2.0 ** -4 + (2.0 ** -8 if dtype == "bf16" else 2.0 ** -11)) * y.abs().amax(-1, keepdim=True)
+    assert ((x - y).abs() <= bar).all()
+    assert (x != y).float().mean() < 0.02
+    # (of the log-sum-exp only the unquantized sum and the rounding of the scores remain)
+    both = torch.isfinite(lb)
+    assert torch.equal(la[~both], lb[~both])
+    assert ((la - lb).abs()[both] <= 2.0 ** -20 * lb.abs()[both].clamp(min=1.0)).all()
+
+
+# B, N, N_kv, d, dtype, H, Hkv, causal, layout, kv_splits: the fewest keys; block and group edges (63, 64, 65, 16 n + 1); one
+# to eight heads in a group (four at a time in the Delta-S product); all 32 columns; split and unsplit, asked for and not
+CASES = [
+    (96, 1, 1, 128, "bf16", 1, 1, True, "HND", 0),
+    (48, 1, 63, 64, "fp16", 4, 2, True, "NHD", 0),
+    (100, 2, 64, 128, "bf16", 5, 1, True, "HND", 0),
+    (96, 4, 65, 256, "bf16", 8, 1, True, "NHD", 0),
+    (48, 32, 145, 128, "fp16", 2, 2, True, "NHD", 0),
+    (96, 32, 300, 64, "bf16", 1, 1, False, "HND", 1),
+    (24, 1, 1041, 128, "bf16", 8, 2, True, "HND", 0),
+    (16, 3, 2000, 256, "fp16", 6, 2, False, "NHD", 3),
+    (48, 5, 1500, 64, "bf16", 6, 1, True, "NHD", 2),
+    (11, 1, 1999, 128, "fp16", 3, 3, True, "NHD", 0),
+]
+
+
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+@pytest.mark.parametrize("B,N,Nk,d,dtype,H,Hkv,causal,layout,splits", CASES)
+def test_equals_the_general_path(B, N, Nk, d, dtype, H, Hkv, causal, layout, splits, mode):
+    pa = _pa()
+    q, k, v = _inputs(B, N, Nk, d, H, Hkv, dtype, layout)
+    if Nk > 300:
+        v[..., 3] = 0.0                       # an all-zero channel: scale 0
+        k.view(-1)[: 16 * d * (Hkv if layout == "NHD" else 1)] *= 64.0      # one loud group of keys
+    a = pa.make_args(q, k, v, None, causal=causal, mode=mode, layout=layout, kv_splits=splits)
+    print(f"raw K, V: B={B} N={N} N_kv={Nk} d={d} {dtype} H={H}/{Hkv} causal={causal} {layout} {mode} "
+          f"splits={pa.sage_attn_kv_splits(a)}", flush=True)
+    assert B * Hkv * pa.sage_attn_kv_splits(a) >= 96
+    _compare(_both(pa, q, k, v, a), dtype)
+
+
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+def test_packed_batch_equals_the_general_path(mode):
+    """Sequences without queries, without keys, with fewer keys than queries, and of very different lengths."""
+    pa = _pa()
+    lens_q, lens_k, d, H, Hkv = [1, 0, 8, 3, 2] * 10, [700, 90, 5, 0, 1300] * 10, 128, 8, 2
+    cu = [torch.tensor([0] + list(torch.tensor(x).cumsum(0)), dtype=torch.int32, device="cuda") for x in (lens_q, lens_k)]
+    q, _, _ = _inputs(1, sum(lens_q), sum(lens_q), d, H, Hkv, "bf16", "NHD")
+    _, k, v = _inputs(1, 1, sum(lens_k), d, H, Hkv, "bf16", "NHD", 1)
+    q, k, v = q[0], k[0], v[0]
+    a = pa.make_varlen_args(q, k, v, None, *cu, max(lens_q), max(lens_k), causal=True, mode=mode)
+    print(f"raw K, V: packed batch {lens_q[:5]} / {lens_k[:5]}, ten times, {mode}", flush=True)
+    _compare(_both(pa, q, k, v, a), "bf16")
+
+
+def test_scales_at_the_ends_of_the_range():
+    """delta_V outside the range of the quick division (and a subnormal one): the exact division takes over."""
+    pa = _pa()
+    q, k, v = _inputs(96, 1, 200, 128, 2, 1, "bf16", "HND")
+    v[..., 0:8] *= 2.0 ** -70
+    v[..., 8] *= 2.0 ** 60
+    v[..., 9] *= 2.0 ** 100
+    for mode in ("int4_fp8", "int8_fp8"):
+        _compare(_both(pa, q, k, v, pa.make_args(q, k, v, None, causal=True, mode=mode)), "bf16")
