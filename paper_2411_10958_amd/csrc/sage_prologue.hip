@@ -21,17 +21,15 @@ constexpr int STAT_UNROLL = 4; // rows per thread in flight
 // With the smooth-V option the first pass takes the exact token sums of V instead of max|V| (the
 // maximum must be taken of the centred values, which needs the mean first: k_v_absmax below).
 template <bool BF16, int D, bool SMOOTH_V>
-__global__ void __launch_bounds__(256) k_col_stats(const unsigned short* __restrict__ K,
-                                                   const unsigned short* __restrict__ V,
-                                                   double* __restrict__ k_sum, double* __restrict__ v_sum,
-                                                   unsigned* __restrict__ v_max, int Nq, int N, TensorMap km,
-                                                   SeqMap sm) {
+__device__ __forceinline__ void col_stats_block(const BlockPos bp, const unsigned short* __restrict__ K,
+                                                const unsigned short* __restrict__ V, double* __restrict__ k_sum,
+                                                double* __restrict__ v_sum, unsigned* __restrict__ v_max, int Nq, int N,
+                                                const TensorMap& km, const SeqMap& sm) {
   constexpr int NCG = D / 8, NRG = 256 / NCG;
   __shared__ double s_sum[NRG][D];
   __shared__ double s_vsum[SMOOTH_V ? NRG : 1][D];
   __shared__ float s_max[SMOOTH_V ? 1 : NRG][D];
   const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
-  const BlockPos bp = block_pos(km);
   const HeadPos hp = head_pos(km, bp.y);
   const Seq sq = seq_of(sm, hp.b, Nq, N);
   const int r0 = bp.x * STAT_ROWS;
@@ -88,6 +86,15 @@ __global__ void __launch_bounds__(256) k_col_stats(const unsigned short* __restr
   }
 }
 
+template <bool BF16, int D, bool SMOOTH_V>
+__global__ void __launch_bounds__(256) k_col_stats(const unsigned short* __restrict__ K,
+                                                   const unsigned short* __restrict__ V,
+                                                   double* __restrict__ k_sum, double* __restrict__ v_sum,
+                                                   unsigned* __restrict__ v_max, int Nq, int N, TensorMap km,
+                                                   SeqMap sm) {
+  col_stats_block<BF16, D, SMOOTH_V>(block_pos(km), K, V, k_sum, v_sum, v_max, Nq, N, km, sm);
+}
+
 // Smooth-V option, second pass over V: per-channel max |fl32(V - mean(V))|.
 template <bool BF16, int D>
 __global__ void __launch_bounds__(256) k_v_absmax(const unsigned short* __restrict__ V,
@@ -120,6 +127,13 @@ __global__ void __launch_bounds__(256) k_v_absmax(const unsigned short* __restri
     for (int g = 0; g < NRG; ++g) m = fmaxf(m, s_max[g][t]);
     v_max[((size_t)bp.y * bp.nx + bp.x) * D + t] = __float_as_uint(m);
   }
+}
+
+// the sum over a head's chunks of one channel (exact, whatever the order)
+__device__ __forceinline__ double sum_partials(const double* __restrict__ part, size_t head, int nchunk, int d, int c) {
+  double s = 0.0;
+  for (int ch = 0; ch < nchunk; ++ch) s += part[(head * nchunk + ch) * d + c];
+  return s;
 }
 
 // k_mean = fl32(sum / N) (Eq. 2), delta_V = fl32(max|V| / 448) (Sec. 3.3); with the smooth-V option
@@ -289,20 +303,39 @@ __device__ inline void row_constants(const float (&x)[RPT][8], float* out, int n
   }
 }
 
+// Arguments of the Q quantizers (the 8-bit one leaves the last five alone).
+struct QuantQ {
+  const unsigned short* q;
+  float *q_mean, *q_scale;
+  int8_t* q_codes;
+  int N, Nk, nQb, block_groups, qg;
+  TensorMap qm;
+  SeqMap sm;
+  float* q_corr;             // null, or where the row constants of the log-sum-exp go (needs mean(K))
+  const float* k_mean;
+  int G;
+  float kappa;
+  const float* head_scale;
+  int stats_only, smooth_q;
+  unsigned char* q_digits;
+  float* q_dscale;
+};
+#define SAGE_QUANT_Q_ARGS                                                                                              \
+  const unsigned short* __restrict__ Q = a.q; float* __restrict__ q_scale = a.q_scale;                                 \
+  int8_t* __restrict__ q_codes = a.q_codes;                                                                            \
+  const int N = a.N, Nk = a.Nk, nQb = a.nQb, block_groups = a.block_groups, qg = a.qg, G = a.G, stats_only = a.stats_only; \
+  const TensorMap& qm = a.qm; const SeqMap& sm = a.sm; float* __restrict__ q_corr = a.q_corr;                          \
+  const float* __restrict__ k_mean = a.k_mean; const float* __restrict__ head_scale = a.head_scale; const float kappa = a.kappa
+
 // Q, 8-bit variant: pair-group quantization psi_Q(Q_i), no smoothing (the 8-bit kernel of the
 // paper's "two kernel implementations" leaves Q as it is).  One workgroup per 128 queries of one
 // (batch, head).
 template <bool BF16, int D>
-__global__ void __launch_bounds__(256) k_quant_q8(const unsigned short* __restrict__ Q,
-                                                  float* __restrict__ q_scale, int8_t* __restrict__ q_codes,
-                                                  int N, int Nk, int nQb, int block_groups, int qg,
-                                                  TensorMap qm, SeqMap sm, float* __restrict__ q_corr,
-                                                  const float* __restrict__ k_mean, int G, float kappa,
-                                                  const float* __restrict__ head_scale, int stats_only) {
+__device__ __forceinline__ void quant_q8_block(const BlockPos bp, const QuantQ& a) {
+  SAGE_QUANT_Q_ARGS;
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BQ / NRG;  // RPT rows per thread (8 or 4)
   constexpr int QMAX = 127;
   const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
-  const BlockPos bp = block_pos(qm);
   const int qb = bp.x;
   const size_t bh = bp.y;
   const int n0 = qb * BQ;
@@ -388,14 +421,11 @@ __global__ void __launch_bounds__(256) k_quant_q8(const unsigned short* __restri
 // registers, and one row of column sums per wavefront (the row groups of a wavefront are summed by lane exchanges
 // first) - 37 KB, so that four workgroups share a CU and their loads, arithmetic and stores overlap.
 template <bool BF16, int D>
-__global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q4(const unsigned short* __restrict__ Q,
-                                                  float* __restrict__ q_mean, float* __restrict__ q_scale,
-                                                  int8_t* __restrict__ q_codes, int N, int Nk, int nQb,
-                                                  int block_groups, int qg, TensorMap qm, SeqMap sm,
-                                                  float* __restrict__ q_corr, const float* __restrict__ k_mean,
-                                                  int G, float kappa, const float* __restrict__ head_scale,
-                                                  int stats_only, int smooth_q, unsigned char* __restrict__ q_digits,
-                                                  float* __restrict__ q_dscale) {
+__device__ __forceinline__ void quant_q4_block(const BlockPos bp, const QuantQ& a) {
+  SAGE_QUANT_Q_ARGS;
+  float *__restrict__ q_mean = a.q_mean, *__restrict__ q_dscale = a.q_dscale;
+  unsigned char* __restrict__ q_digits = a.q_digits;
+  const int smooth_q = a.smooth_q;
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BQ / NRG;   // load map: RPT rows x 8 channels
   constexpr int CPL = D / 4, CPC = CPL / 8;                      // quantization map: 2 rows x CPL channels
   constexpr int QMAX = 7;
@@ -407,7 +437,6 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q4(const unsign
   __shared__ __align__(16) float s_kbar[D];   // mean(K) of the KV head (log-sum-exp output only)
   __shared__ float s_bmax[4];
   const int t = threadIdx.x;
-  const BlockPos bp = block_pos(qm);
   const int qb = bp.x;
   const size_t bh = bp.y;
   const int n0 = qb * BQ;
@@ -546,6 +575,17 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q4(const unsign
   for (int i = t; i < SLAB / 16; i += 256) dst[i] = src[i];
 }
 
+template <bool BF16, bool INT4, int D>
+__device__ __forceinline__ void quant_q_block(const BlockPos bp, const QuantQ& a) {
+  if constexpr (INT4) quant_q4_block<BF16, D>(bp, a); else quant_q8_block<BF16, D>(bp, a);
+}
+template <bool BF16, int D>
+__global__ void __launch_bounds__(256) k_quant_q8(const QuantQ a) { quant_q8_block<BF16, D>(block_pos(a.qm), a); }
+template <bool BF16, int D>
+__global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q4(const QuantQ a) {
+  quant_q4_block<BF16, D>(block_pos(a.qm), a);
+}
+
 // ------------------------------------------------------------------------------------------
 // K: smoothing by the token mean, group quantization (runs of 16 keys by default) and, in the int4
 // mode, Delta-S.
@@ -586,17 +626,42 @@ constexpr int DS_QROWS = 32;    // query-block means staged in LDS per pass: two
 // the FP64 instruction's time, and - being INT8 matrix work - it runs alongside the vector work of the quantizers.
 enum { DS_DIGITS = 0, DS_FP32 = 1, DS_FP64 = 2 };
 
-template <bool BF16, bool INT4, int D, int DSM = DS_DIGITS>
-__global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS ? 3 : 4)) k_quant_k(const unsigned short* __restrict__ K,
-                                                 const float* __restrict__ k_mean,
-                                                 float* __restrict__ k_scale, int8_t* __restrict__ k_codes,
-                                                 const float* __restrict__ q_mean,
-                                                 float* __restrict__ delta_s, int Nq, int Nmax, int nKb,
-                                                 int nQb, int G, float kappa, int block_groups, int kg,
-                                                 int causal, TensorMap km, SeqMap sm,
-                                                 const float* __restrict__ head_scale, int stats_only,
-                                                 int zero_ds, const unsigned char* __restrict__ q_digits,
-                                                 const float* __restrict__ q_dscale) {
+// Arguments of the K and V quantizers.  Where the statistics pass left partial results that nobody has reduced (k_sum, v_max
+// not null: the launch that covers both, k_quant_kv), every workgroup reduces its head's and the first one writes
+// mean(K) and delta_V for the attention kernel.
+struct QuantKV {
+  const unsigned short *k, *v;
+  float *k_mean, *v_scale;
+  const float* v_mean;
+  float* k_scale;
+  int8_t* k_codes;
+  uint8_t* v_codes;
+  const float* q_mean;
+  float* delta_s;
+  int Nq, Nk, nKb, nQb, G;
+  float kappa;
+  int block_groups, kg, causal;
+  TensorMap km;
+  SeqMap sm;
+  const float* head_scale;
+  int stats_only, zero_ds;
+  const unsigned char* q_digits;
+  const float* q_dscale;
+  const double* k_sum;
+  const unsigned* v_max;
+  int nchunk, smooth_k;
+  float code_max;
+};
+
+template <bool BF16, bool INT4, int D, int DSM = DS_DIGITS, bool REDUCE = false>
+__device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& a) {
+  const unsigned short* __restrict__ K = a.k;
+  float* __restrict__ k_scale = a.k_scale; int8_t* __restrict__ k_codes = a.k_codes;
+  const float* __restrict__ q_mean = a.q_mean; float* __restrict__ delta_s = a.delta_s;
+  const int Nq = a.Nq, Nmax = a.Nk, nKb = a.nKb, nQb = a.nQb, G = a.G, block_groups = a.block_groups, kg = a.kg, causal = a.causal;
+  const float kappa = a.kappa; const TensorMap& km = a.km; const SeqMap& sm = a.sm;
+  const float* __restrict__ head_scale = a.head_scale; const int stats_only = a.stats_only, zero_ds = a.zero_ds;
+  const unsigned char* __restrict__ q_digits = a.q_digits; const float* __restrict__ q_dscale = a.q_dscale;
   constexpr bool DS32 = DSM == DS_FP32, DSD = INT4 && DSM == DS_DIGITS;
   constexpr int CPL = D / 4;                       // channels per lane (32 or 16)
   constexpr int QMAX = INT4 ? 7 : 127;
@@ -613,7 +678,6 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS 
   __shared__ float s_qs[DS_QROWS];                 // 2^E of the staged rows
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int r16 = lane & 15, k4 = lane >> 4;
-  const BlockPos bp = block_pos(km);
   const int kb = bp.x;
   const size_t bhkv = bp.y;
   const int n0 = kb * BKV;
@@ -723,6 +787,20 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS 
   };
   if constexpr (INT4) load_q(pass_first);
 
+  // mean(K) of this head: reduced by the statistics pass, or here
+  __shared__ __align__(16) float s_kmean[REDUCE ? D : 4];
+  if constexpr (REDUCE) {
+    if (t < D) {
+      const float m = a.smooth_k ? (float)(sum_partials(a.k_sum, (size_t)bhkv, a.nchunk, D, t) / (double)N) : 0.0f;
+      s_kmean[t] = m;
+      if (kb == 0) a.k_mean[bhkv * D + t] = m;
+    }
+    __syncthreads();
+  }
+  auto mean4 = [&](int c) {
+    return REDUCE ? *reinterpret_cast<const float4*>(&s_kmean[c]) : *reinterpret_cast<const float4*>(a.k_mean + bhkv * D + c);
+  };
+
   float x[CPL];
   float mx = 0.0f;
   const size_t hbase = hp.base + sq.k0 * (size_t)km.sn;
@@ -731,8 +809,7 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS 
     for (int p = 0; p < CPL / 8; ++p) {
       float x8[8];
       load8<BF16, false>(K + row_offset(km, hbase, n0 + r) + c0 + 8 * p, x8);
-      const float4 m0 = *reinterpret_cast<const float4*>(k_mean + bhkv * D + c0 + 8 * p);
-      const float4 m1 = *reinterpret_cast<const float4*>(k_mean + bhkv * D + c0 + 8 * p + 4);
+      const float4 m0 = mean4(c0 + 8 * p), m1 = mean4(c0 + 8 * p + 4);
       const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -956,16 +1033,15 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS 
 // order of the P~V product
 // (Sec. 3.3; Algorithm 1 "Preprocessing": (delta_V, V^) = psi_V(V)).  v_mean is null, or the token
 // mean to subtract first (smooth-V option, SMOOTH_V).
-template <bool BF16, int D, bool SMOOTH_V, int PVF>
-__global__ void __launch_bounds__(256) k_quant_v(const unsigned short* __restrict__ V,
-                                                 const float* __restrict__ v_scale,
-                                                 const float* __restrict__ v_mean,
-                                                 uint8_t* __restrict__ v_codes, int Nq, int Nmax, int nKb,
-                                                 TensorMap km, SeqMap sm) {
+template <bool BF16, int D, bool SMOOTH_V, int PVF, bool REDUCE = false>
+__device__ __forceinline__ void quant_v_block(const BlockPos bp, const QuantKV& a) {
+  const unsigned short* __restrict__ V = a.v;
+  const float* __restrict__ v_mean = a.v_mean; uint8_t* __restrict__ v_codes = a.v_codes;
+  const int Nq = a.Nq, Nmax = a.Nk, nKb = a.nKb;
+  const TensorMap& km = a.km; const SeqMap& sm = a.sm;
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BKV / NRG;
   __shared__ uint8_t tile[BKV][D + 16];
   const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
-  const BlockPos bp = block_pos(km);
   const int kb = bp.x;
   const size_t bh = bp.y;
   const int n0 = kb * BKV;
@@ -974,10 +1050,21 @@ __global__ void __launch_bounds__(256) k_quant_v(const unsigned short* __restric
   const int N = sq.nk;
   if (n0 >= N) return;                             // a block past the end of a shorter sequence
   const size_t hbase = hp.base + sq.k0 * (size_t)km.sn;
+  __shared__ float s_vscale[REDUCE ? D : 1];       // delta_V of this head, reduced here
+  if constexpr (REDUCE) {
+    if (t < D) {
+      float vm = 0.0f;
+      for (int ch = 0; ch < a.nchunk; ++ch) vm = fmaxf(vm, __uint_as_float(a.v_max[(bh * a.nchunk + ch) * D + t]));
+      const float v = __fdiv_rn(vm, a.code_max);
+      s_vscale[t] = v;
+      if (kb == 0) a.v_scale[bh * D + t] = v;
+    }
+    __syncthreads();
+  }
   float sc[8], mean[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    sc[e] = v_scale[bh * D + cg * 8 + e];
+    sc[e] = REDUCE ? s_vscale[cg * 8 + e] : a.v_scale[bh * D + cg * 8 + e];
     mean[e] = SMOOTH_V ? v_mean[bh * D + cg * 8 + e] : 0.0f;
   }
 #pragma unroll
@@ -1029,6 +1116,44 @@ __global__ void __launch_bounds__(256) k_quant_v(const unsigned short* __restric
              ((unsigned)tile[key0 + 4 * q + 2][c] << 16) | ((unsigned)tile[key0 + 4 * q + 3][c] << 24);
     *reinterpret_cast<uint4*>(dst + (size_t)ch * 16) = make_uint4(w[0], w[1], w[2], w[3]);
   }
+}
+
+template <bool BF16, bool INT4, int D, int DSM = DS_DIGITS>
+__global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS ? 3 : 4)) k_quant_k(const QuantKV a) {
+  quant_k_block<BF16, INT4, D, DSM>(block_pos(a.km), a);
+}
+template <bool BF16, int D, bool SMOOTH_V, int PVF>
+__global__ void __launch_bounds__(256) k_quant_v(const QuantKV a) {
+  quant_v_block<BF16, D, SMOOTH_V, PVF>(block_pos(a.km), a);
+}
+
+// ------------------------------------------------------------------------------------------
+// Small calls: a launch that fills a fraction of the chip costs its latency (3 to 7 us) whatever it does, so the six
+// launches of the general sequence become three: Q and the statistics side by side, then K and V side by side with
+// the reduction of the statistics in front (each workgroup for its own head), then the attention kernel.
+// Where a kernel of the sequence fills the chip by itself the pair is slower than the two (the workgroups of one
+// take the slots and registers of the other): see the rule in launch_prologue_t.
+struct SmallStats {
+  const unsigned short *k, *v;
+  double* k_sum;
+  unsigned* v_max;
+  int nchunk;
+  TensorMap km;
+};
+template <bool BF16, bool INT4, int D>
+__global__ void __launch_bounds__(256) k_quant_q_and_stats(const QuantQ q, const SmallStats st) {
+  // grid: (query blocks, then chunks of keys; query heads) - the chunks of the first B H_kv rows count as KV heads
+  if ((int)blockIdx.x < q.nQb) {
+    quant_q_block<BF16, INT4, D>(BlockPos{blockIdx.x, blockIdx.y, (unsigned)q.nQb}, q);
+  } else if ((int)blockIdx.y < (int)gridDim.y / q.G) {
+    col_stats_block<BF16, D, false>(BlockPos{blockIdx.x - q.nQb, blockIdx.y, (unsigned)st.nchunk}, st.k, st.v, st.k_sum, nullptr,
+                                    st.v_max, q.N, q.Nk, st.km, q.sm);
+  }
+}
+template <bool BF16, bool INT4, int D, int DSM, bool REDUCE>
+__global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS ? 3 : 4)) k_quant_kv(const QuantKV a) {
+  if ((int)blockIdx.x < a.nKb) quant_k_block<BF16, INT4, D, DSM, REDUCE>(BlockPos{blockIdx.x, blockIdx.y, (unsigned)a.nKb}, a);
+  else quant_v_block<BF16, D, false, PV_E4M3, REDUCE>(BlockPos{blockIdx.x - a.nKb, blockIdx.y, (unsigned)a.nKb}, a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1110,6 +1235,19 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
   }
 }
 
+// Calls that the three-launch sequence serves (k_quant_q_and_stats, k_quant_kv): E4M3, exact Delta-S, no row constants (they
+// need mean(K) before Q), at most 8 chunks of keys to be reduced in every workgroup, and at most two workgroups per CU in
+// any of the kernels it replaces.  Whole calls, us, six launches / three: 2 heads of 64 channels, 256 tokens 26.5 / 18.7;
+// 32 heads on 8, 300 tokens 34.5 / 23.6; 8 heads, 2000 tokens 58 / 47; 32 of 256 channels on 16, 700 tokens 73 / 59; 64,
+// 500 tokens, 8-bit mode (512 workgroups) 51 / 39.  Beyond: 128 heads, 1024 tokens (2048 workgroups) 99 / 109, 64 of 64
+// channels, 2000 tokens (2048) 84 / 86.
+constexpr int SMALL_CALL_WG = 512;
+static bool small_call(const Dims& Dm) {
+  return !Dm.want_lse && !Dm.smooth_v && !Dm.tensor_groups && Dm.pvf == PV_E4M3 && !Dm.ds32 && !Dm.seq.cu_q &&
+         Dm.Nk <= 8 * STAT_ROWS && (long long)Dm.B * Dm.Hkv * Dm.nKb <= SMALL_CALL_WG &&
+         (long long)Dm.B * Dm.H * Dm.nQb <= SMALL_CALL_WG;
+}
+
 template <bool BF16, bool INT4, int D>
 static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s, bool quant_kv) {
   const int BH = Dm.B * Dm.H, BHkv = Dm.B * Dm.Hkv;
@@ -1124,16 +1262,43 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   // Q goes first: it depends on nothing, and with the statistics pass next to the K and V quantizers
   // those re-read K and V while the chip's memory-side cache still holds most of them.  Only when
   // the log-sum-exp output is wanted does Q wait for mean(K) (its row constants need it).
+  QuantQ qa;
+  qa.q = q; qa.q_mean = P.q_mean; qa.q_scale = P.q_scale; qa.q_codes = P.q_codes;
+  qa.N = Dm.N; qa.Nk = Dm.Nk; qa.nQb = Dm.nQb; qa.block_groups = Dm.block_groups; qa.qg = Dm.qg;
+  qa.qm = qm; qa.sm = sm; qa.q_corr = nullptr; qa.k_mean = P.k_mean; qa.G = Dm.H / Dm.Hkv; qa.kappa = Dm.kappa;
+  qa.head_scale = nullptr; qa.stats_only = 0; qa.smooth_q = Dm.smooth_q;
+  qa.q_digits = Dm.ds_mode == DS_DIGITS && Dm.smooth_q ? P.q_digits : nullptr; qa.q_dscale = P.q_dscale;
+  QuantKV ka;
+  ka.k = k; ka.v = v; ka.k_mean = P.k_mean; ka.v_scale = P.v_scale; ka.v_mean = v_mean;
+  ka.k_scale = P.k_scale; ka.k_codes = P.k_codes; ka.v_codes = P.v_codes; ka.q_mean = P.q_mean; ka.delta_s = P.delta_s;
+  ka.Nq = Dm.N; ka.Nk = Dm.Nk; ka.nKb = Dm.nKb; ka.nQb = Dm.nQb; ka.G = qa.G; ka.kappa = Dm.kappa;
+  ka.block_groups = Dm.block_groups; ka.kg = Dm.kg; ka.causal = Dm.causal; ka.km = km; ka.sm = sm;
+  ka.head_scale = nullptr; ka.stats_only = 0; ka.zero_ds = !Dm.smooth_q; ka.q_digits = P.q_digits; ka.q_dscale = P.q_dscale;
+  ka.k_sum = P.k_sum; ka.v_max = P.v_max; ka.nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS; ka.smooth_k = Dm.smooth_k;
+  ka.code_max = E4M3_MAX;
+  if (quant_kv && small_call(Dm)) {
+    if (Dm.stats_given) {
+      k_quant_q_and_stats<BF16, INT4, D><<<dim3(Dm.nQb, BH), 256, 0, s>>>(qa, SmallStats{});
+    } else {
+      const SmallStats st = {k, v, P.k_sum, P.v_max, ka.nchunk, km};
+      k_quant_q_and_stats<BF16, INT4, D><<<dim3(Dm.nQb + ka.nchunk, BH), 256, 0, s>>>(qa, st);
+    }
+    const dim3 gkv(2 * Dm.nKb, BHkv);
+#define SAGE_QKV(DSM_)                                                                                      \
+  do {                                                                                                      \
+    if (Dm.stats_given) k_quant_kv<BF16, INT4, D, DSM_, false><<<gkv, 256, 0, s>>>(ka);                      \
+    else k_quant_kv<BF16, INT4, D, DSM_, true><<<gkv, 256, 0, s>>>(ka);                                      \
+  } while (0)
+    if (INT4 && Dm.ds_mode == DS_FP64) SAGE_QKV(INT4 ? DS_FP64 : DS_DIGITS);
+    else SAGE_QKV(DS_DIGITS);
+#undef SAGE_QKV
+    return hipGetLastError();
+  }
   auto quant_q_pass = [&](float* corr, const float* head_scale, int stats_only) {
-    if constexpr (INT4)
-      k_quant_q4<BF16, D><<<block_grid(qm, Dm.nQb, BH), 256, 0, s>>>(q, P.q_mean, P.q_scale, P.q_codes, Dm.N, Dm.Nk, Dm.nQb,
-                                                       Dm.block_groups, Dm.qg, qm, sm, corr, P.k_mean,
-                                                       Dm.H / Dm.Hkv, Dm.kappa, head_scale, stats_only, Dm.smooth_q,
-                                                       Dm.ds_mode == DS_DIGITS && Dm.smooth_q ? P.q_digits : nullptr, P.q_dscale);
-    else
-      k_quant_q8<BF16, D><<<block_grid(qm, Dm.nQb, BH), 256, 0, s>>>(q, P.q_scale, P.q_codes, Dm.N, Dm.Nk, Dm.nQb,
-                                                       Dm.block_groups, Dm.qg, qm, sm, corr, P.k_mean,
-                                                       Dm.H / Dm.Hkv, Dm.kappa, head_scale, stats_only);
+    QuantQ x = qa;
+    x.q_corr = corr; x.head_scale = head_scale; x.stats_only = stats_only;
+    if constexpr (INT4) k_quant_q4<BF16, D><<<block_grid(qm, Dm.nQb, BH), 256, 0, s>>>(x);
+    else                k_quant_q8<BF16, D><<<block_grid(qm, Dm.nQb, BH), 256, 0, s>>>(x);
   };
   auto quant_q = [&]() {
     float* corr = Dm.want_lse ? P.q_corr : nullptr;
@@ -1147,11 +1312,9 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
     }
   };
   auto quant_k_pass = [&](const float* head_scale, int stats_only) {
-#define SAGE_QK(DSM_)                                                                                                  \
-  k_quant_k<BF16, INT4, D, DSM_><<<block_grid(km, Dm.nKb, BHkv), 256, 0, s>>>(k, P.k_mean, P.k_scale, P.k_codes, P.q_mean, P.delta_s, \
-                                                                    Dm.N, Dm.Nk, Dm.nKb, Dm.nQb, Dm.H / Dm.Hkv, Dm.kappa,  \
-                                                                    Dm.block_groups, Dm.kg, Dm.causal, km, sm, head_scale, \
-                                                                    stats_only, !Dm.smooth_q, P.q_digits, P.q_dscale)
+    QuantKV x = ka;
+    x.head_scale = head_scale; x.stats_only = stats_only;
+#define SAGE_QK(DSM_) k_quant_k<BF16, INT4, D, DSM_><<<block_grid(km, Dm.nKb, BHkv), 256, 0, s>>>(x)
     // (the 8-bit build has no Delta-S: one instantiation, named by the default mode)
     if (INT4 && Dm.ds_mode == DS_FP32) SAGE_QK(INT4 ? DS_FP32 : DS_DIGITS);
     else if (INT4 && Dm.ds_mode == DS_FP64) SAGE_QK(INT4 ? DS_FP64 : DS_DIGITS);
@@ -1173,15 +1336,15 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
     quant_k_pass(nullptr, 0);
   }
   const dim3 gv = block_grid(km, Dm.nKb, BHkv);
-#define SAGE_QV(SV, PF, VM) k_quant_v<BF16, D, SV, PF><<<gv, 256, 0, s>>>(v, P.v_scale, VM, P.v_codes, Dm.N, Dm.Nk, Dm.nKb, km, sm)
+#define SAGE_QV(SV, PF) k_quant_v<BF16, D, SV, PF><<<gv, 256, 0, s>>>(ka)
   if (Dm.smooth_v) {
-    if (Dm.pvf == PV_INT8) SAGE_QV(true, PV_INT8, v_mean);
-    else if (Dm.pvf == PV_E5M2) SAGE_QV(true, PV_E5M2, v_mean);
-    else SAGE_QV(true, PV_E4M3, v_mean);
+    if (Dm.pvf == PV_INT8) SAGE_QV(true, PV_INT8);
+    else if (Dm.pvf == PV_E5M2) SAGE_QV(true, PV_E5M2);
+    else SAGE_QV(true, PV_E4M3);
   } else {
-    if (Dm.pvf == PV_INT8) SAGE_QV(false, PV_INT8, nullptr);
-    else if (Dm.pvf == PV_E5M2) SAGE_QV(false, PV_E5M2, nullptr);
-    else SAGE_QV(false, PV_E4M3, nullptr);
+    if (Dm.pvf == PV_INT8) SAGE_QV(false, PV_INT8);
+    else if (Dm.pvf == PV_E5M2) SAGE_QV(false, PV_E5M2);
+    else SAGE_QV(false, PV_E4M3);
   }
 #undef SAGE_QV
   return hipGetLastError();
