@@ -163,7 +163,7 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
         }
 #pragma unroll
         for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(xk[e]));
-        const float delta = __fdiv_rn(wave_max_dpp(mx), (float)QMAX);
+        const float delta = __fdiv_rn(wave_max(mx), (float)QMAX);
         if (lane == 0) s_ks[cur][w] = delta;
         // codes: the wavefront is one group, so one reciprocal and one decision serve all of it
         const bool fast = __builtin_amdgcn_readfirstlane(div_by_ok(delta));

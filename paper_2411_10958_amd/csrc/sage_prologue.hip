@@ -183,20 +183,36 @@ __global__ void k_finalize_stats(const double* __restrict__ k_sum, const double*
 // maxima of |V| are kept as state, a new chunk's partial results are added to them, and mean(K), delta_V of the whole
 // are written.  Float64 sums of 16-bit values are exact, so the state after any sequence of chunks equals the one
 // pass over everything, bit for bit.  fresh != 0: the state is initialised from this chunk.
-__global__ void k_accumulate_stats(const double* __restrict__ k_sum, const unsigned* __restrict__ v_max,
+// Workgroups of FIN_ENT entries with FIN_PARTS threads each, as in k_finalize_stats: a thread per entry took one round trip
+// per eight chunks (k_finalize_vscale, 70 chunks of 96 heads of 64 channels: 21 us, now 5).
+__global__ void __launch_bounds__(256) k_accumulate_stats(const double* __restrict__ k_sum, const unsigned* __restrict__ v_max,
                                    double* __restrict__ state_sum, float* __restrict__ state_max,
                                    float* __restrict__ k_mean, float* __restrict__ v_scale, int n, int d, int nchunk,
                                    int fresh, long long n_total, float code_max) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ double s_k[FIN_PARTS][FIN_ENT];
+  __shared__ float s_m[FIN_PARTS][FIN_ENT];
+  const int e = threadIdx.x % FIN_ENT, part = threadIdx.x / FIN_ENT;
+  const int i = blockIdx.x * FIN_ENT + e;
+  double ks = 0.0;
+  float vm = 0.0f;
   if (i < n) {
     const int head = i / d, c = i - head * d;
     const size_t p0 = (size_t)head * nchunk * d + c;
-    double ks = fresh ? 0.0 : state_sum[i];
-    float vm = fresh ? 0.0f : state_max[i];
-#pragma unroll 8
-    for (int ch = 0; ch < nchunk; ++ch) {
+#pragma unroll 4
+    for (int ch = part; ch < nchunk; ch += FIN_PARTS) {
       ks += k_sum[p0 + (size_t)ch * d];
       vm = fmaxf(vm, __uint_as_float(v_max[p0 + (size_t)ch * d]));
+    }
+  }
+  s_k[part][e] = ks; s_m[part][e] = vm;
+  __syncthreads();
+  if (part == 0 && i < n) {
+    ks = fresh ? 0.0 : state_sum[i];
+    vm = fresh ? 0.0f : state_max[i];
+#pragma unroll
+    for (int q = 0; q < FIN_PARTS; ++q) {
+      ks += s_k[q][e];
+      vm = fmaxf(vm, s_m[q][e]);
     }
     state_sum[i] = ks;
     state_max[i] = vm;
@@ -205,13 +221,23 @@ __global__ void k_accumulate_stats(const double* __restrict__ k_sum, const unsig
   }
 }
 
-__global__ void k_finalize_vscale(const unsigned* __restrict__ v_max, float* __restrict__ v_scale, int n, int d,
-                                  int nchunk, float code_max) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) k_finalize_vscale(const unsigned* __restrict__ v_max, float* __restrict__ v_scale, int n,
+                                                         int d, int nchunk, float code_max) {
+  __shared__ float s_m[FIN_PARTS][FIN_ENT];
+  const int e = threadIdx.x % FIN_ENT, part = threadIdx.x / FIN_ENT;
+  const int i = blockIdx.x * FIN_ENT + e;
+  float vm = 0.0f;
   if (i < n) {
     const int head = i / d, c = i - head * d;
-    float vm = 0.0f;
-    for (int ch = 0; ch < nchunk; ++ch) vm = fmaxf(vm, __uint_as_float(v_max[((size_t)head * nchunk + ch) * d + c]));
+    const size_t p0 = (size_t)head * nchunk * d + c;
+#pragma unroll 4
+    for (int ch = part; ch < nchunk; ch += FIN_PARTS) vm = fmaxf(vm, __uint_as_float(v_max[p0 + (size_t)ch * d]));
+  }
+  s_m[part][e] = vm;
+  __syncthreads();
+  if (part == 0 && i < n) {
+#pragma unroll
+    for (int q = 0; q < FIN_PARTS; ++q) vm = fmaxf(vm, s_m[q][e]);
     v_scale[i] = __fdiv_rn(vm, code_max);
   }
 }
@@ -261,8 +287,7 @@ __device__ __forceinline__ void ds_slice_row(const float* row, unsigned char* __
     x[e] = row[PER * lane + e];
     mx = fmaxf(mx, fabsf(x[e]));
   }
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  mx = wave_max(mx);
   float down, up;
   ds_row_scale(mx, &down, &up);
   if (lane == 0) *scale = up;
@@ -297,8 +322,9 @@ __device__ inline void row_constants(const float (&x)[RPT][8], float* out, int n
     double dot = 0.0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) dot += (double)x[i][e] * (double)kbar8[e];
-#pragma unroll
-    for (int m = NCG / 2; m >= 1; m >>= 1) dot += __shfl_xor(dot, m, 64);
+    dot = butterfly_sum<4>(butterfly_sum<2>(butterfly_sum<1>(dot)));
+    if constexpr (NCG > 8) dot = butterfly_sum<8>(dot);
+    if constexpr (NCG > 16) dot = butterfly_sum<16>(dot);
     if (cg == 0 && i < n_valid) out[i] = (float)((double)kappa * dot);
   }
 }
@@ -382,8 +408,7 @@ __device__ __forceinline__ void quant_q8_block(const BlockPos bp, const QuantQ& 
       mxr[i] = 0.0f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) mxr[i] = fmaxf(mxr[i], fabsf(x[2 * p + i][e]));
-#pragma unroll
-      for (int m = NCG / 2; m >= 1; m >>= 1) mxr[i] = fmaxf(mxr[i], __shfl_xor(mxr[i], m, 64));
+      mxr[i] = group_max<NCG>(mxr[i]);
     }
     if (qg == 2) mxr[0] = mxr[1] = fmaxf(mxr[0], mxr[1]);
     if (block_groups) mxr[0] = mxr[1] = block_max;
@@ -474,8 +499,9 @@ __device__ __forceinline__ void quant_q4_block(const BlockPos bp, const QuantQ& 
     // (float64 sums of 16-bit values are exact: the order of the additions does not matter)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-#pragma unroll
-      for (int o = NCG; o < 64; o <<= 1) cs[e] += __shfl_xor(cs[e], o, 64);
+      if constexpr (NCG == 8) cs[e] = butterfly_sum<8>(cs[e]);
+      if constexpr (NCG <= 16) cs[e] = butterfly_sum<16>(cs[e]);
+      cs[e] = butterfly_sum<32>(cs[e]);
     }
     if ((t & 63) < NCG) {
 #pragma unroll
@@ -491,10 +517,6 @@ __device__ __forceinline__ void quant_q4_block(const BlockPos bp, const QuantQ& 
     q_mean[(bh * nQb + qb) * D + t] = m;
   }
   __syncthreads();
-  // the block mean cut into digits for the Delta-S product (first wavefront; the others go on)
-  if (q_digits && t < 64)
-    ds_slice_row<D>(s_mean, q_digits + (bh * nQb + qb) * (size_t)(DS_ND * D), q_dscale + (bh * nQb + qb), t);
-
   const int pair = t >> 2, c4 = t & 3;
   float x[2][CPL];
   float mxr[2] = {0.0f, 0.0f};          // per query; the pair shares the larger one unless qg == 1
@@ -523,11 +545,9 @@ __device__ __forceinline__ void quant_q4_block(const BlockPos bp, const QuantQ& 
         }
       }
     }
-    mxr[i] = fmaxf(mxr[i], __shfl_xor(mxr[i], 1, 64));
-    mxr[i] = fmaxf(mxr[i], __shfl_xor(mxr[i], 2, 64));
+    mxr[i] = group_max<4>(mxr[i]);
     if (q_corr) {
-      dotk[i] += __shfl_xor(dotk[i], 1, 64);
-      dotk[i] += __shfl_xor(dotk[i], 2, 64);
+      dotk[i] = butterfly_sum<2>(butterfly_sum<1>(dotk[i]));
       if (c4 == 0 && r < valid) q_corr[(bh * nQb + qb) * BQ + r] = (float)((double)kappa * dotk[i]);
     }
   }
@@ -573,6 +593,10 @@ __device__ __forceinline__ void quant_q4_block(const BlockPos bp, const QuantQ& 
   const uint4* src = reinterpret_cast<const uint4*>(img);
 #pragma unroll
   for (int i = t; i < SLAB / 16; i += 256) dst[i] = src[i];
+  // the block mean cut into digits for the Delta-S product: by one wavefront, where nobody waits for it any more (done in
+  // front of the quantization it held up the other three: 4096 blocks of d = 128 48 us, now 45)
+  if (q_digits && t >= 192)
+    ds_slice_row<D>(s_mean, q_digits + (bh * nQb + qb) * (size_t)(DS_ND * D), q_dscale + (bh * nQb + qb), t - 192);
 }
 
 template <bool BF16, bool INT4, int D>
@@ -823,17 +847,10 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   }
   // lanes l, l^16, l^32, l^48 hold one key: its maximum first, then (unless every key has its own
   // scale) the run of 4 keys, then (default) the wavefront's run of 16
-  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  mx = butterfly_max<32>(butterfly_max<16>(mx));
   const float mx_key = mx;                         // this key's largest magnitude (DS_DIGITS: its fixed-point exponent)
-  if (kg >= 4) {
-    mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
-  }
-  if (kg == 16) {
-    mx = fmaxf(mx, __shfl_xor(mx, 4, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 8, 64));
-  }
+  if (kg >= 4) mx = group_max<4>(mx);
+  if (kg == 16) mx = butterfly_max<8>(butterfly_max<4>(mx));
   __shared__ float s_bmax[4];
   if (block_groups) {       // per-block granularity: one scale for the whole 64-key block
     if (lane == 0) s_bmax[w] = mx;
@@ -1227,7 +1244,7 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
     k_finalize_stats<<<(nstat + FIN_ENT - 1) / FIN_ENT, FIN_ENT * FIN_PARTS, 0, s>>>(P.k_sum, P.v_sum, P.v_max, P.k_mean, P.v_mean, P.v_scale,
                                                         nstat, Dm.N, Dm.Nk, Dm.d, Dm.Hkv, nchunk, sm, code_max, Dm.smooth_k);
     k_v_absmax<BF16, D><<<gstat, 256, 0, s>>>(v, P.v_mean, P.v_max, Dm.N, Dm.Nk, km, sm);
-    k_finalize_vscale<<<(nstat + 255) / 256, 256, 0, s>>>(P.v_max, P.v_scale, nstat, Dm.d, nchunk, code_max);
+    k_finalize_vscale<<<(nstat + FIN_ENT - 1) / FIN_ENT, FIN_ENT * FIN_PARTS, 0, s>>>(P.v_max, P.v_scale, nstat, Dm.d, nchunk, code_max);
   } else {
     k_col_stats<BF16, D, false><<<gstat, 256, 0, s>>>(k, v, P.k_sum, nullptr, P.v_max, Dm.N, Dm.Nk, km, sm);
     k_finalize_stats<<<(nstat + FIN_ENT - 1) / FIN_ENT, FIN_ENT * FIN_PARTS, 0, s>>>(P.k_sum, nullptr, P.v_max, P.k_mean, nullptr, P.v_scale,
@@ -1382,7 +1399,7 @@ static void launch_stats_update_t(const Dims& Dm, const Ptrs& P, double* state_s
   const float code_max = Dm.pvf == PV_INT8 ? INT8_PV_MAX : (Dm.pvf == PV_E5M2 ? E5M2_MAX : E4M3_MAX);
   k_col_stats<BF16, D, false><<<gstat, 256, 0, s>>>((const unsigned short*)P.k, (const unsigned short*)P.v, P.k_sum, nullptr,
                                                     P.v_max, Dm.N, Dm.Nk, km, Dm.seq);
-  k_accumulate_stats<<<(nstat + 255) / 256, 256, 0, s>>>(P.k_sum, P.v_max, state_sum, state_max, P.k_mean, P.v_scale, nstat,
+  k_accumulate_stats<<<(nstat + FIN_ENT - 1) / FIN_ENT, FIN_ENT * FIN_PARTS, 0, s>>>(P.k_sum, P.v_max, state_sum, state_max, P.k_mean, P.v_scale, nstat,
                                                          Dm.d, nchunk, fresh, n_total, code_max);
 }
 

@@ -34,27 +34,52 @@ __device__ inline void unpack8(const uint4& raw, float* x) {
   }
 }
 
-__device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
+// The value of lane l ^ O - one step of a butterfly - without an LDS round trip: data-parallel moves inside 16 lanes, exchanges
+// of register halves beyond.  For O = 4 the move mirrors half a row, which is lane l ^ 4 where the lanes of a quad agree:
+// that step comes after 1 and 2.
+template <int O>
+__device__ __forceinline__ unsigned butterfly(unsigned u) {
+  static_assert(O == 1 || O == 2 || O == 4 || O == 8 || O == 16 || O == 32, "a power of two below 64");
+  if constexpr (O == 16 || O == 32) {
+    const auto r = O == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false) : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return (__lane_id() & O) ? r[0] : r[1];
+  } else {
+    constexpr int CTRL = O == 1 ? 0xB1 : (O == 2 ? 0x4E : (O == 4 ? 0x141 : 0x128));   // quad_perm, row_half_mirror, row_ror:8
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xf, 0xf, true);
+  }
+}
+template <int O> __device__ __forceinline__ float butterfly_max(float v) {
+  if constexpr (O == 16 || O == 32) {
+    const unsigned u = __float_as_uint(v);
+    const auto r = O == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false) : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  } else {
+    return fmaxf(v, __uint_as_float(butterfly<O>(__float_as_uint(v))));
+  }
+}
+template <int O> __device__ __forceinline__ double butterfly_sum(double v) {
+  const unsigned long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  auto join = [](unsigned l, unsigned h) { return __longlong_as_double((long long)(((unsigned long long)h << 32) | l)); };
+  if constexpr (O == 16 || O == 32) {
+    const auto rl = O == 16 ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false) : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto rh = O == 16 ? __builtin_amdgcn_permlane16_swap(hi, hi, false, false) : __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return join(rl[0], rh[0]) + join(rl[1], rh[1]);
+  } else {
+    return v + join(butterfly<O>(lo), butterfly<O>(hi));
+  }
+}
+// over groups of N consecutive lanes
+template <int N> __device__ __forceinline__ float group_max(float v) {
+  v = butterfly_max<1>(v);
+  if constexpr (N > 2) v = butterfly_max<2>(v);
+  if constexpr (N > 4) v = butterfly_max<4>(v);
+  if constexpr (N > 8) v = butterfly_max<8>(v);
+  if constexpr (N > 16) v = butterfly_max<16>(v);
+  if constexpr (N > 32) v = butterfly_max<32>(v);
   return v;
 }
-
-// the same without LDS round trips: exchanges inside groups of 16 lanes, then between them
-__device__ __forceinline__ float wave_max_dpp(float v) {
-#define SAGE_DPP_MAX(CTRL_) \
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL_, 0xf, 0xf, true)))
-  SAGE_DPP_MAX(0xB1);      // quad_perm [1, 0, 3, 2]
-  SAGE_DPP_MAX(0x4E);      // quad_perm [2, 3, 0, 1]
-  SAGE_DPP_MAX(0x141);     // row_half_mirror
-  SAGE_DPP_MAX(0x140);     // row_mirror
-#undef SAGE_DPP_MAX
-  unsigned u = __float_as_uint(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  u = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
-  const auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
+__device__ __forceinline__ float wave_max(float v) { return group_max<64>(v); }
 
 // x / s rounded to nearest, given r = fl32(1 / s): the quotient corrected by its exact remainder (Markstein), three
 // instructions.  Correct for every s that div_by_ok accepts (the mantissa of all ones is the theorem's exception), except
