@@ -126,7 +126,9 @@ int run_forward(const Dims& D, const sage_attn_args* a, const Workspace& w) {
   Ptrs P = ptrs_for(a, w);
   const hipStream_t s = (hipStream_t)a->stream;
   const bool raw = attention_raw_ok(D);
-  const int st = hip_status(launch_prologue(D, P, s, !raw));
+  int st = SAGE_OK;
+  if (!raw) st = hip_status(launch_prologue(D, P, s));
+  else if (!D.stats_given) st = hip_status(launch_kv_stats(D, P, s));
   if (st != SAGE_OK) return st;
   P.lse = a->lse;
   return hip_status(raw ? launch_attention_raw(D, P, s) : launch_attention(D, P, s));

@@ -2,7 +2,7 @@
 // steps and very short query chunks.  There the general path reads K and V, writes their codes, reads the codes and the
 // Delta-S rows again and spends most of its time on that traffic; here a workgroup quantizes a 64-key block on its way
 // into LDS and uses it there, so K and V are read once after the statistics pass (or once in all, with the statistics
-// supplied) and nothing of their size is written.  Same groups, scales, codes, Delta-S and chunk rule as the general path.
+// supplied) and nothing of their size is written.  The few query rows are quantized by the workgroups themselves too.  Same groups, scales, codes, Delta-S and chunk rule as the general path.
 #include "sage_attn_core.h"
 #include "sage_quant.h"
 
@@ -11,8 +11,9 @@
 namespace sage {
 
 struct RawParams {
-  const unsigned short *k, *v;
-  const float *k_mean, *q_mean;   // mean(K) per KV head; block mean of Q per query head (one block: at most 32 queries)
+  const unsigned short *q, *k, *v;   // (q is laid out like the output)
+  const float* k_mean;               // mean(K) per KV head
+  float* q_corr;                     // where the row constants of the log-sum-exp go for the merge
   TensorMap km;
 };
 
@@ -109,7 +110,13 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
   if constexpr (INT4) {
     for (int idx = t; idx < PACK_G * D; idx += 512) {
       const int g = idx / D, c = idx % D;
-      s_qm[(g * 4 + c / CPL) * QMS + c % CPL] = g < G ? (double)x.q_mean[(bh + g) * D + c] : 0.0;
+      double mean = 0.0;                     // block mean of the head's queries (one block: at most 32), as k_quant_q4 forms it
+      if (g < G) {
+        const unsigned short* qh = x.q + row_offset(p.om, head_offset(p.om, (unsigned)(bh + g)), (int)sq.q0) + c;
+        for (int r = 0; r < sq.n; ++r) mean += (double)load16<BF16>(qh[(size_t)r * (size_t)p.om.sn]);
+        mean = (double)(float)(mean / (double)sq.n);
+      }
+      s_qm[(g * 4 + c / CPL) * QMS + c % CPL] = mean;
     }
   }
   __syncthreads();
@@ -275,15 +282,92 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
     return;
   }
 
-  // ---- the wavefront's Q^ operands: all four hold the same 32 columns
+  // ---- the wavefront's Q^ operands: all four hold the same 32 columns and quantize them themselves (a separate launch for so
+  // few rows costs 7 us: 16 x 8 KV heads, 5003 keys 106 / 95 us, 4 x 8, 32768 keys 272 / 259).  Lane (n, half) supplies, of its column's query, PC consecutive channels per operand: smoothed
+  // (4-bit mode), scale from the pair of queries, codes as k_quant_q4 / k_quant_q8 give them.
+  constexpr int PC = INT4 ? 32 : 16;
   typename QkOperand<INT4>::type qreg[NP];
+  float dq, lse_corr = 0.0f;
   {
-    const v4i* gq = reinterpret_cast<const v4i*>(p.q_codes + (bh + hq) * q_slab_bytes(D, INT4));
+    const unsigned short* qrow = x.q + row_offset(p.om, head_offset(p.om, (unsigned)(bh + hq)), (int)sq.q0 + query);
+    float mx = 0.0f;
+    double dot = 0.0;
+    // one operand's channels at a time, fetched once for the maximum and again for the codes: kept, the row would cost a
+    // wide head its registers for the whole kernel
+    auto fetch = [&](int s, float (&xq)[PC]) {
+      const int cq = (2 * s + half) * PC;
 #pragma unroll
-    for (int s = 0; s < NP; ++s) qreg[s] = load_qk_operand<INT4>(gq, s, query + 32 * half);
+      for (int i = 0; i < PC / 8; ++i) unpack8<BF16>(*reinterpret_cast<const uint4*>(qrow + cq + 8 * i), &xq[8 * i]);
+    };
+    auto smooth = [&](int s, float (&xq)[PC]) {
+      const int cq = (2 * s + half) * PC;
+      if constexpr (INT4) {
+#pragma unroll
+        for (int e = 0; e < PC; ++e) {
+          xq[e] = __fsub_rn(xq[e], (float)s_qm[(hq * 4 + (cq + e) / CPL) * QMS + (cq + e) % CPL]);
+          if (e % 8 == 7) asm volatile("" ::: "memory");     // (not all of the means out of LDS at once)
+        }
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < NP; ++s) {
+      float xq[PC];
+      fetch(s, xq);
+      if (p.lse) {
+#pragma unroll
+        for (int e = 0; e < PC; ++e) dot += (double)xq[e] * (double)s_km[(2 * s + half) * PC + e];
+      }
+      smooth(s, xq);
+#pragma unroll
+      for (int e = 0; e < PC; ++e) mx = fmaxf(mx, fabsf(xq[e]));
+      asm volatile("" ::: "memory");
+    }
+    mx = butterfly_max<32>(mx);
+    const int other = (query ^ 1) < sq.n ? hq * sq.n + (query ^ 1) : hq * sq.n + query;      // column of the pair's other query
+    dq = __fdiv_rn(fmaxf(mx, __shfl(mx, other, 64)), (float)QMAX);
+    if (p.lse) {
+      lse_corr = (float)((double)p.kappa * butterfly_sum<32>(dot));
+      if (p.splits > 1 && split == 0 && w == 0 && half == 0 && col_ok) x.q_corr[(bh + hq) * BQ + query] = lse_corr;
+    }
+    const bool fast = __builtin_amdgcn_ballot_w64(!(div_by_ok(dq) || dq == 0.0f)) == 0;      // (scale 0: all values are 0)
+    const float rq = fast && dq > 0.0f ? __fdiv_rn(1.0f, dq) : 0.0f;
+    auto codes = [&](float (&v)[PC]) {                     // v: values, then their codes
+      if (fast) {
+#pragma unroll
+        for (int e = 0; e < PC; ++e) v[e] = rintf(div_by(v[e], dq, rq));
+      } else {
+#pragma unroll
+        for (int e = 0; e < PC; ++e) {
+          v[e] = (float)quant_code(v[e], dq, QMAX);
+          asm volatile("" : "+v"(v[e]) :: "memory");       // (one division at a time)
+        }
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < NP; ++s) {
+      float xq[PC];
+      fetch(s, xq);
+      smooth(s, xq);
+      codes(xq);
+      if constexpr (INT4) {
+        Codes32 cd;
+#pragma unroll
+        for (int e = 0; e < PC; ++e) cd.set(e, xq[e]);
+        const v6u pw = cd.pack();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) qreg[s][i] = i < 6 ? (int)pw[i < 6 ? i : 0] : 0;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          unsigned wd = 0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) wd |= ((unsigned)(int)xq[4 * i + e] & 0xffu) << (8 * e);
+          qreg[s][i] = (int)wd;
+        }
+      }
+      asm volatile("" ::: "memory");
+    }
   }
-  const float dq = p.q_scale[(bh + hq) * (BQ / QGROUP) + query / QGROUP];
-  const float lse_corr = p.lse ? p.q_corr[(bh + hq) * BQ + query] : 0.0f;
   constexpr int DW = 32 * CTW;                                   // this wavefront's channels: DW w ..
   RowState<DW> st;
 #pragma unroll
@@ -406,8 +490,8 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
 // through its chunk block by block, about 2 us each, where the general path spreads the quantizers over the chip: with
 // fewer than 96 workgroups that serial chain is longer than the launches it saves.  Whole calls, us, general path / this
 // one, d = 128 unless said: 8 KV heads, 4000 keys (56 workgroups) 37 / 42; 4 KV heads of 256 channels, 5000 keys (36) 54 /
-// 57; 8, 8192 keys (128) 46 / 41, 8-bit mode 42 / 34; 32 of 64 channels, 3000 keys (160) 41 / 34; 16 x 8, 5003 keys 142 /
-// 106; 4 x 8, 32768 keys 358 / 272; 16 of 256 channels, 60000 keys 600 / 391.
+// 57; 8, 8192 keys (128) 46 / 37, 8-bit mode 42 / 31; 32 of 64 channels, 3000 keys (160) 41 / 29; 16 x 8, 5003 keys 142 /
+// 95; 4 x 8, 32768 keys 358 / 259; 16 of 256 channels, 60000 keys 600 / 388.
 bool attention_raw_ok(const Dims& D) {
   const int G = D.H / D.Hkv;
   return G <= PACK_G && (long long)G * D.N <= 32 && (long long)D.B * D.Hkv * D.splits >= 96 && D.kg == KGROUP && !D.block_groups && D.pvf == PV_E4M3 &&
@@ -419,8 +503,8 @@ static hipError_t launch_raw_t(const Dims& D, const Ptrs& P, hipStream_t s) {
   AttnParams p = attn_params(D, P);
   p.total_tiles = D.B * D.Hkv;
   RawParams x;
-  x.k = (const unsigned short*)P.k; x.v = (const unsigned short*)P.v;
-  x.k_mean = P.k_mean; x.q_mean = P.q_mean;
+  x.q = (const unsigned short*)P.q; x.k = (const unsigned short*)P.k; x.v = (const unsigned short*)P.v;
+  x.k_mean = P.k_mean; x.q_corr = P.q_corr;
   x.km = make_tensor_map(D.nhd, D.Hkv, D.Nk, D.d, D.seq.cu_q != nullptr);
   const int grid = p.total_tiles * D.splits;
   if (D.bf16) k_attn_raw<DD, INT4, CAUSAL, true><<<grid, 512, 0, s>>>(p, x);

@@ -317,9 +317,9 @@ template <bool BF16> __device__ inline unsigned pack16x2(float a, float b) {
 }
 
 // launchers (defined in the .hip files)
-hipError_t launch_prologue(const Dims& D, const Ptrs& P, hipStream_t s, bool quant_kv = true);
-bool attention_raw_ok(const Dims& D);      // the attention kernel that quantizes K and V itself serves this call ...
-hipError_t launch_attention_raw(const Dims& D, const Ptrs& P, hipStream_t s);   // ... after launch_prologue without quant_kv
+hipError_t launch_prologue(const Dims& D, const Ptrs& P, hipStream_t s);
+bool attention_raw_ok(const Dims& D);      // the attention kernel that quantizes Q, K and V itself serves this call ...
+hipError_t launch_attention_raw(const Dims& D, const Ptrs& P, hipStream_t s);   // ... with P.k_mean, P.v_scale in place
 hipError_t launch_kv_stats(const Dims& D, const Ptrs& P, hipStream_t s);   // writes P.k_mean, P.v_scale
 hipError_t launch_kv_stats_update(const Dims& D, const Ptrs& P, double* state_sum, float* state_max, int fresh,
                                   long long n_total, hipStream_t s);

@@ -1266,7 +1266,7 @@ static bool small_call(const Dims& Dm) {
 }
 
 template <bool BF16, bool INT4, int D>
-static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s, bool quant_kv) {
+static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
   const int BH = Dm.B * Dm.H, BHkv = Dm.B * Dm.Hkv;
   const unsigned short* q = (const unsigned short*)P.q;
   const unsigned short* k = (const unsigned short*)P.k;
@@ -1293,7 +1293,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   ka.head_scale = nullptr; ka.stats_only = 0; ka.zero_ds = !Dm.smooth_q; ka.q_digits = P.q_digits; ka.q_dscale = P.q_dscale;
   ka.k_sum = P.k_sum; ka.v_max = P.v_max; ka.nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS; ka.smooth_k = Dm.smooth_k;
   ka.code_max = E4M3_MAX;
-  if (quant_kv && small_call(Dm)) {
+  if (small_call(Dm)) {
     if (Dm.stats_given) {
       k_quant_q_and_stats<BF16, INT4, D><<<dim3(Dm.nQb, BH), 256, 0, s>>>(qa, SmallStats{});
     } else {
@@ -1343,7 +1343,6 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   if (!Dm.want_lse) quant_q();
   if (!Dm.stats_given) launch_stats_t<BF16, D>(Dm, P, s);     // else P.k_mean and P.v_scale are the caller's arrays
   if (Dm.want_lse) quant_q();
-  if (!quant_kv) return hipGetLastError();
   if (Dm.tensor_groups) {
     quant_k_pass(nullptr, 1);
     k_head_scale<<<BHkv, 256, 0, s>>>(P.k_scale, P.k_head_scale, BKV / Dm.kg, Dm.nKb * (BKV / Dm.kg), BKV, Dm.Hkv, 1,
@@ -1367,8 +1366,8 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_prologue(const Dims& D, const Ptrs& P, hipStream_t s, bool quant_kv) {
-#define SAGE_PRO(BF, I4, DD) return launch_prologue_t<BF, I4, DD>(D, P, s, quant_kv)
+hipError_t launch_prologue(const Dims& D, const Ptrs& P, hipStream_t s) {
+#define SAGE_PRO(BF, I4, DD) return launch_prologue_t<BF, I4, DD>(D, P, s)
   if (D.d == 256) {
     if (D.bf16) { if (D.int4) SAGE_PRO(true, true, 256); else SAGE_PRO(true, false, 256); }
     else        { if (D.int4) SAGE_PRO(false, true, 256); else SAGE_PRO(false, false, 256); }
