@@ -2,7 +2,8 @@
 // steps and very short query chunks.  There the general path reads K and V, writes their codes, reads the codes and the
 // Delta-S rows again and spends most of its time on that traffic; here a workgroup quantizes a 64-key block on its way
 // into LDS and uses it there, so K and V are read once after the statistics pass (or once in all, with the statistics
-// supplied) and nothing of their size is written.  The few query rows are quantized by the workgroups themselves too.  Same groups, scales, codes, Delta-S and chunk rule as the general path.
+// supplied) and nothing of their size is written.  The few query rows are quantized by the workgroups themselves too.
+// Same groups, scales, codes, Delta-S and chunk rule as the general path.
 #include "sage_attn_core.h"
 #include "sage_quant.h"
 
@@ -40,7 +41,7 @@ __device__ __forceinline__ void settle(v16f (&o)[N]) {
 // wavefront doing all of it a block would take three times as long.  LDS holds two blocks, one barrier per block.
 //
 // Bound: the stream of K and V (32 KB per block at d = 128), with the vector work of a block just below it.  4 x 8 KV heads,
-// 32768 keys, d = 128, one query: 128 us in the 8-bit mode (537 MB: 4.2 TB/s; quantizers + attention kernel were 185), 160
+// 32768 keys, d = 128, one query: 128 us in the 8-bit mode (537 MB: 4.2 TB/s; quantizers + attention kernel 185), 160
 // in the 4-bit mode (255), whose Delta-S is FP64 matrix work that no vector work overlaps.  Four wavefronts doing both
 // parts in turn: 168 / 175.  More registers per thread (no spills in the 4-bit mode at d = 128) leave one workgroup per CU:
 // 153 / 170.  K by 64-byte pieces of four lanes and an exchange in registers pays at d = 256 only, where a lane's own
@@ -283,7 +284,8 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
   }
 
   // ---- the wavefront's Q^ operands: all four hold the same 32 columns and quantize them themselves (a separate launch for so
-  // few rows costs 7 us: 16 x 8 KV heads, 5003 keys 106 / 95 us, 4 x 8, 32768 keys 272 / 259).  Lane (n, half) supplies, of its column's query, PC consecutive channels per operand: smoothed
+  // few rows costs 7 us: 16 x 8 KV heads, 5003 keys 106 / 95 us, 4 x 8, 32768 keys 272 / 259).  Lane (n, half)
+  // supplies, of its column's query, PC consecutive channels per operand: smoothed
   // (4-bit mode), scale from the pair of queries, codes as k_quant_q4 / k_quant_q8 give them.
   constexpr int PC = INT4 ? 32 : 16;
   typename QkOperand<INT4>::type qreg[NP];
