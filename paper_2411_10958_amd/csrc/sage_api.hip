@@ -81,8 +81,8 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
       // One or two workgroups per CU, of the three that fit: a lone wavefront issues far fewer vector instructions than
       // two or three that share the SIMD.  Split for three per CU - where a chunk still has 48 key blocks: with fewer the
       // partial results cost what the fuller chip gains.  Measured, us unsplit / split: 512 queries of 64 heads on 16384
-      // keys 319 / 270, 1024 of 32 heads of 64 channels on 9000 keys 146 / 119, causal 9000 on itself with 4 heads 167 /
-      // 140, 7000 with 6 heads 143 / 132; causal 4096 with 8 heads 98 / 89, but full 101 / 101 and with 10 heads 103 / 115.
+      // keys 319 / 270, 1024 of 32 heads of 64 channels on 9000 keys 146 / 127, causal 9000 on itself with 4 heads 167 /
+      // 149, 7000 with 6 heads 143 / 135; chunks of 32 blocks, causal 4096: 8 heads 98 / 89, but 10 heads 103 / 115.
       S = (768 + tiles - 1) / tiles;
       if (S > nKb / 48) S = nKb / 48;
     }
