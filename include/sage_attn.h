@@ -21,7 +21,8 @@
  *     key tokens cu_seqlens_k[b] .. cu_seqlens_k[b+1]-1, and N / N_kv are the LONGEST query / key
  *     length (they size the launch and the workspace; a longer sequence is cut to them).  Every
  *     sequence is smoothed, quantized and attended on its own, exactly as a batch of one (bit for bit when
- *     kv_splits is the same in both calls: left to the library it depends on the call's tile count).  The
+ *     kv_splits and the form of the Delta-S product are the same in both calls: left to the library the one depends on the
+ *     call's tile count, the other on the longest query length, see SAGE_FLAG_DIGIT_DELTA_S).  The
  *     prefix sums live on the device and are not checked on the host: under a causal mask a
  *     sequence with fewer keys than queries is masked as if aligned to the first query and key,
  *     and a sequence without keys gets zeros.
@@ -183,10 +184,12 @@ int sage_attn_kv_splits(const sage_attn_args* args);
    Sec. 3.1-3.3) followed by the fused attention kernel (inner loop and epilogue). */
 int sage_attn_fwd_ex(const sage_attn_args* args);
 
-/* The two halves of sage_attn_fwd_ex, for timing them apart the way the paper's kernel
+/* The two halves of the general path of sage_attn_fwd_ex, for timing them apart the way the paper's kernel
    benchmark does (Appendix "Kernel Benchmark Setup" times the attention kernel on already
    quantized operands).  sage_attn_core reads what sage_attn_prologue left in the workspace
-   for the same args; q, k, v are not touched by it. */
+   for the same args; q, k, v are not touched by it.  Calls whose query heads of a KV head have at most 32 queries together
+   can be served by sage_attn_fwd_ex / _static from k and v directly, with one kernel that quantizes as it attends; the
+   two halves then give the same results bit for bit, but their times are not that call's. */
 int sage_attn_prologue(const sage_attn_args* args);
 int sage_attn_core(const sage_attn_args* args);
 

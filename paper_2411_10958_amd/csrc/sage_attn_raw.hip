@@ -3,7 +3,8 @@
 // Delta-S rows again and spends most of its time on that traffic; here a workgroup quantizes a 64-key block on its way
 // into LDS and uses it there, so K and V are read once after the statistics pass (or once in all, with the statistics
 // supplied) and nothing of their size is written.  The few query rows are quantized by the workgroups themselves too.
-// Same groups, scales, codes, Delta-S and chunk rule as the general path.
+// Same groups, scales, codes, Delta-S and chunk rule as the general path, and the same order of every float64 sum: which of the
+// two serves a call depends on how many workgroups it makes, its results must not.
 #include "sage_attn_core.h"
 #include "sage_quant.h"
 
@@ -17,6 +18,17 @@ struct RawParams {
   float* q_corr;                     // where the row constants of the log-sum-exp go for the merge
   TensorMap km;
 };
+
+// x[0] + ... + x[N - 1], neighbours first.
+template <int N>
+__device__ __forceinline__ double pair_sum(double (&x)[N]) {
+#pragma unroll
+  for (int m = 1; m < N; m *= 2) {
+#pragma unroll
+    for (int i = 0; i + m < N; i += 2 * m) x[i] += x[i + m];
+  }
+  return x[0];
+}
 
 // Keeps the accumulators' next vector read a wait state further away than the compiler does.  It puts 19 between a 16-pass
 // matrix instruction and the first vector read of its result; where that read took the result's LAST registers at exactly
@@ -111,11 +123,18 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
   if constexpr (INT4) {
     for (int idx = t; idx < PACK_G * D; idx += 512) {
       const int g = idx / D, c = idx % D;
-      double mean = 0.0;                     // block mean of the head's queries (one block: at most 32), as k_quant_q4 forms it
+      // block mean of the head's queries (one block: at most 32), added in k_quant_q4's order
+      double mean = 0.0;
       if (g < G) {
+        constexpr int RG = D / 16, NG = 32 / RG;             // rows are summed in runs of RG, the runs in pairs
         const unsigned short* qh = x.q + row_offset(p.om, head_offset(p.om, (unsigned)(bh + g)), (int)sq.q0) + c;
-        for (int r = 0; r < sq.n; ++r) mean += (double)load16<BF16>(qh[(size_t)r * (size_t)p.om.sn]);
-        mean = (double)(float)(mean / (double)sq.n);
+        double run[NG];
+#pragma unroll
+        for (int k = 0; k < NG; ++k) {
+          run[k] = 0.0;
+          for (int r = RG * k; r < min(sq.n, RG * (k + 1)); ++r) run[k] += (double)load16<BF16>(qh[(size_t)r * (size_t)p.om.sn]);
+        }
+        mean = (double)(float)(pair_sum(run) / (double)sq.n);
       }
       s_qm[(g * 4 + c / CPL) * QMS + c % CPL] = mean;
     }
@@ -183,17 +202,19 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
           // receives D[l / 16][l % 4].  Product i holds keys 16 w + 4 i + 0..3, contraction slot (step cs, l / 16) channel
           // CPL (l / 16) + cs: the lane's own registers, in order.  (The 16-row form of the
           // general path spends 2048 matrix cycles per block on rows that a few heads leave empty; this one 512 per 4 heads.)
+          // One chain of accumulations, in the general path's order: with two, which are a little shorter, a Delta-S that
+          // lies next to the middle of two FP32 values could round to the other one (decode of 32768 keys: 249 us either way).
           const double kap = (double)p.kappa;
           const double* qa = &s_qm[((lane & 3) * 4 + kk) * QMS];
           auto delta_s = [&](int first) {
-            double acc[2] = {0.0, 0.0};                    // (two chains: each instruction waits for its accumulator)
+            double acc = 0.0;
 #pragma unroll
             for (int cs = 0; cs < CPL; ++cs) {
               float xs = xk[cs];
               asm volatile("" : "+v"(xs) :: "memory");     // (operands are read and widened as they are used, not all at once)
-              acc[cs & 1] = __builtin_amdgcn_mfma_f64_4x4x4f64(qa[4 * first * QMS + cs], (double)xs, acc[cs & 1], 0, 0, 0);
+              acc = __builtin_amdgcn_mfma_f64_4x4x4f64(qa[4 * first * QMS + cs], (double)xs, acc, 0, 0, 0);
             }
-            s_ds[cur][first + kk][kr] = (float)(kap * (acc[0] + acc[1]));
+            s_ds[cur][first + kk][kr] = (float)(kap * acc);
           };
           delta_s(0);
           if (G > 4) delta_s(4);
@@ -289,11 +310,10 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
   // (4-bit mode), scale from the pair of queries, codes as k_quant_q4 / k_quant_q8 give them.
   constexpr int PC = INT4 ? 32 : 16;
   typename QkOperand<INT4>::type qreg[NP];
-  float dq, lse_corr = 0.0f;
+  float dq;
   {
     const unsigned short* qrow = x.q + row_offset(p.om, head_offset(p.om, (unsigned)(bh + hq)), (int)sq.q0 + query);
     float mx = 0.0f;
-    double dot = 0.0;
     // one operand's channels at a time, fetched once for the maximum and again for the codes: kept, the row would cost a
     // wide head its registers for the whole kernel
     auto fetch = [&](int s, float (&xq)[PC]) {
@@ -315,10 +335,6 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
     for (int s = 0; s < NP; ++s) {
       float xq[PC];
       fetch(s, xq);
-      if (p.lse) {
-#pragma unroll
-        for (int e = 0; e < PC; ++e) dot += (double)xq[e] * (double)s_km[(2 * s + half) * PC + e];
-      }
       smooth(s, xq);
 #pragma unroll
       for (int e = 0; e < PC; ++e) mx = fmaxf(mx, fabsf(xq[e]));
@@ -327,10 +343,6 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
     mx = butterfly_max<32>(mx);
     const int other = (query ^ 1) < sq.n ? hq * sq.n + (query ^ 1) : hq * sq.n + query;      // column of the pair's other query
     dq = __fdiv_rn(fmaxf(mx, __shfl(mx, other, 64)), (float)QMAX);
-    if (p.lse) {
-      lse_corr = (float)((double)p.kappa * butterfly_sum<32>(dot));
-      if (p.splits > 1 && split == 0 && w == 0 && half == 0 && col_ok) x.q_corr[(bh + hq) * BQ + query] = lse_corr;
-    }
     const bool fast = __builtin_amdgcn_ballot_w64(!(div_by_ok(dq) || dq == 0.0f)) == 0;      // (scale 0: all values are 0)
     const float rq = fast && dq > 0.0f ? __fdiv_rn(1.0f, dq) : 0.0f;
     auto codes = [&](float (&v)[PC]) {                     // v: values, then their codes
@@ -454,7 +466,31 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
     const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
   }
+  // Row constant of the log-sum-exp, kappa <q, mean(K)>, for whoever finishes the row.  Added in the order of the quantizers'
+  // lanes: runs of CR consecutive channels, then neighbours in pairs, so that the two halves of the wavefront, which take
+  // half of the channels each, meet last.  (Here and not beside Q^: the d = 256 4-bit form, which has no register to spare in
+  // the loop, then keeps everything in registers: 16 heads, 30000 keys, 249 -> 229 us.)
+  float lse_corr = 0.0f;
+  if (p.lse && w == 0 && split == 0) {
+    constexpr int CR = INT4 ? D / 4 : 8;
+    const unsigned short* qrow = x.q + row_offset(p.om, head_offset(p.om, (unsigned)(bh + hq)), (int)sq.q0 + query);
+    double runs[D / 2 / CR];
+#pragma unroll
+    for (int i = 0; i < D / 2 / CR; ++i) {
+      runs[i] = 0.0;
+#pragma unroll
+      for (int e = 0; e < CR; e += 8) {
+        const int c = half * (D / 2) + i * CR + e;
+        float x8[8];
+        unpack8<BF16>(*reinterpret_cast<const uint4*>(qrow + c), x8);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) runs[i] += (double)x8[k] * (double)s_km[c + k];
+      }
+    }
+    lse_corr = (float)((double)p.kappa * butterfly_sum<32>(pair_sum(runs)));
+  }
   if (p.splits > 1) {
+    if (p.lse && w == 0 && split == 0 && half == 0) x.q_corr[(bh + hq) * BQ + query] = lse_corr;
     const size_t prow = (size_t)blockIdx.x * BQ + col;
     if (w == 0 && half == 0) { p.part_el[prow * 2] = m_sub; p.part_el[prow * 2 + 1] = l_tot; }
 #pragma unroll

@@ -113,3 +113,37 @@ def test_scales_at_the_ends_of_the_range():
     v[..., 9] *= 2.0 ** 100
     for mode in ("int4_fp8", "int8_fp8"):
         _compare(_both(pa, q, k, v, pa.make_args(q, k, v, None, causal=True, mode=mode)), "bf16")
+
+
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+@pytest.mark.parametrize("d,H,Hkv", [(64, 2, 2), (128, 2, 1), (128, 8, 1), (256, 2, 1)])
+def test_sequence_of_a_packed_batch_equals_the_sequence_alone(d, H, Hkv, mode):
+    """Bit for bit at the same kv_splits, whichever kernel the number of sequences leads to: 100 decode steps together are
+    served from raw K and V, one of them alone is not.  The inputs make the order of float64 sums visible: <q, k> is 2^14,
+    plus half a unit of its last FP32 place, plus terms that a float64 sum of 2^14 keeps only if they meet each other first, at
+    random channels.  Even sequences carry them in Delta-S (keys 1 and -1, so mean(K) = 0), odd ones in the row constant of
+    the log-sum-exp (all keys 1, so mean(K) = 1).  sm_scale = ln 2 makes kappa 1."""
+    pa = _pa()
+    B, nk = 100, 8
+    gen = torch.Generator().manual_seed(d + H)
+    q = torch.zeros(B, H, d, dtype=torch.float64)
+    for b in range(B):
+        for h in range(H):
+            c = torch.randperm(d, generator=gen)
+            q[b, h, c[0]], q[b, h, c[1]] = 2.0 ** 14, 2.0 ** -10
+            n_tiny = int(torch.randint(d // 8, d - 1, (1,), generator=gen))
+            q[b, h, c[2: 2 + n_tiny]] = 2.0 ** -torch.randint(41, 46, (n_tiny,), generator=gen).double()
+    k = torch.ones(B, nk, Hkv, d)
+    k[::2, 1::2] = -1.0
+    v = torch.randn(B, nk, Hkv, d, generator=gen)
+    q, k, v = (x.to(torch.bfloat16).cuda() for x in (q, k, v))
+    cu_q = torch.arange(B + 1, dtype=torch.int32, device="cuda")
+    kw = dict(causal=True, mode=mode, sm_scale=0.69314718, kv_splits=1, return_lse=True)
+    print(f"packed batch and its sequences: d={d} H={H}/{Hkv} {mode}", flush=True)
+    out, lse = pa.sage_attn_fwd_ex(q, k.reshape(-1, Hkv, d), v.reshape(-1, Hkv, d), cu_seqlens_q=cu_q, cu_seqlens_k=cu_q * nk,
+                                   max_seqlen_q=1, max_seqlen_k=nk, **kw)
+    for b in range(B):
+        one, one_lse = pa.sage_attn_fwd_ex(q[b][None, None], k[b][None], v[b][None], layout="NHD", **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], out[b:b + 1]), f"sequence {b}"
+        assert torch.equal(one_lse[0, :, 0], lse[:, b]), f"sequence {b}: {(one_lse[0, :, 0] - lse[:, b]).tolist()}"
