@@ -155,7 +155,7 @@ typedef struct sage_attn_args {
                               chunks by the rule that combines consecutive blocks in Eq. 1 (Sec. 2.1).  For calls with
                               few query tiles and many keys - a decode step, a short chunk of queries against a long
                               cache - where one workgroup per tile would leave most of the chip idle.  0: the library
-                              decides (it splits when there are fewer than 256 tiles, and 256 to 511 tiles over keys
+                              decides (it splits when there are fewer than 256 tiles, and 256 to 384 tiles over keys
                               long enough for chunks of 48 key blocks; sage_attn_kv_splits tells; sage_attn_fwd_static
                               leaves the latter unsplit where only their partial results would not fit);
                               1: never; 2..64: this many (cut to one chunk per 8 key blocks at most).  Default groups

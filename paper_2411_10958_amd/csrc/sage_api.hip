@@ -77,14 +77,19 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
     D->pack = G >= 2 && G <= PACK_G && (long long)G * a->N <= BQ;     // (a->N: the longest sequence's queries)
     const long long tiles = D->pack ? (long long)a->B * a->H_kv : (long long)a->B * a->H * nQb;
     long long S = a->kv_splits > 1 ? a->kv_splits : (tiles < 256 ? (512 + tiles - 1) / tiles : 1);
-    if (a->kv_splits == 0 && !D->pack && tiles >= 256 && tiles < 512) {
+    if (a->kv_splits == 0 && !D->pack && tiles >= 256) {
       // One or two workgroups per CU, of the three that fit: a lone wavefront issues far fewer vector instructions than
-      // two or three that share the SIMD.  Split for three per CU - where a chunk still has 48 key blocks: with fewer the
-      // partial results cost what the fuller chip gains.  Measured, us unsplit / split: 512 queries of 64 heads on 16384
-      // keys 319 / 270, 1024 of 32 heads of 64 channels on 9000 keys 146 / 127, causal 9000 on itself with 4 heads 167 /
-      // 149, 7000 with 6 heads 143 / 135; chunks of 32 blocks, causal 4096: 8 heads 98 / 89, but 10 heads 103 / 115.
-      S = (768 + tiles - 1) / tiles;
+      // two or three that share the SIMD.  Three chunks per tile while they make four workgroups per CU at most, two while they
+      // make three - with more, what does not fit the chip at once runs on after the rest, and the partial results are paid
+      // for nothing - and a chunk keeps 48 key blocks: with fewer the partial results cost what the fuller chip gains.
+      // 256-wide heads, of which two workgroups fit a CU, take two chunks only where those fit.
+      // Measured over 256 to 504 tiles, three head widths, causal or not, both modes (time with the chunks / without): three
+      // chunks up to 341 tiles 0.67 - 0.98, two up to 384 0.74 - 1.01; past the lines three at 352 - 384 tiles up to 1.06
+      // (256-wide 1.16), two at 392 - 504 tiles up to 1.25 (10 heads of 6400 tokens, causal: 145 us, 183), two of 256-wide
+      // heads at 264 - 384 tiles up to 1.17.
+      S = tiles <= 341 ? 3 : (tiles <= 384 ? 2 : 1);
       if (S > nKb / 48) S = nKb / 48;
+      if (a->d == 256 && S == 2 && tiles > 256) S = 1;
     }
     if (S > nKb / 8) S = nKb / 8;
     if (S > 64) S = 64;

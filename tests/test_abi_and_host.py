@@ -96,8 +96,8 @@ def test_key_split_policy():
 
 
 def test_key_split_of_half_filled_launches():
-    """256 to 511 unpacked tiles leave a CU one or two of the three workgroups it holds: split for 768, in chunks of at
-    least 48 key blocks; 512 tiles and more, packed tiles and a caller's own number are not touched by that rule."""
+    """256 to 384 unpacked tiles leave a CU one or two of the three workgroups it holds: three chunks up to 341 tiles, two up
+    to 384, of at least 48 key blocks each; more tiles, packed tiles and a caller's own number are not touched by that rule."""
     pa, _ = _lib()
     S = lambda **kw: pa.sage_attn_kv_splits(_args(pa, **kw))
     assert S(B=2, H=32, H_kv=8, N=512, N_kv=16384, causal=1) == 3     # 256 tiles, 256 key blocks
@@ -105,6 +105,11 @@ def test_key_split_of_half_filled_launches():
     assert S(B=2, H=32, H_kv=8, N=512, N_kv=64 * 96, causal=1) == 2   # 96 key blocks: two chunks of 48
     assert S(B=2, H=32, H_kv=8, N=512, N_kv=64 * 95, causal=1) == 1
     assert S(B=4, H=32, H_kv=8, N=512, N_kv=16384, causal=1) == 1     # 512 tiles
+    # the lines: more chunks than fit the chip at once would run after the rest
+    assert [S(B=1, H=t, H_kv=t, N=128, N_kv=16384) for t in (341, 342, 384, 385, 511)] == [3, 2, 2, 1, 1]
+    assert S(B=1, H=10, H_kv=10, N=6400, causal=1) == 1                    # 500 tiles
+    assert [S(B=1, H=t, H_kv=t, N=128, N_kv=16384, d=256) for t in (256, 257, 341, 342)] == [3, 3, 3, 1]
+    assert [S(B=1, H=t, H_kv=t, N=128, N_kv=64 * 143, d=256) for t in (256, 257)] == [2, 1]
     assert S(B=2, H=32, H_kv=8, N=512, N_kv=16384, causal=1, kv_splits=1) == 1
     assert S(B=40, H=32, H_kv=8, N=1, N_kv=16384, causal=1) == 1      # 320 packed tiles
 
