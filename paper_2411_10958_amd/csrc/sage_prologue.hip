@@ -1258,11 +1258,19 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
 // 32 heads on 8, 300 tokens 34.5 / 23.6; 8 heads, 2000 tokens 58 / 47; 32 of 256 channels on 16, 700 tokens 73 / 59; 64,
 // 500 tokens, 8-bit mode (512 workgroups) 51 / 39.  Beyond: 128 heads, 1024 tokens (2048 workgroups) 99 / 109, 64 of 64
 // channels, 2000 tokens (2048) 84 / 86.
+// A pair holds the LDS of both its bodies, so in the 4-bit mode fewer of its workgroups fit a CU than of the Q quantizer alone
+// (d = 128: two instead of four; d = 256: one instead of two): the Q blocks and statistics chunks together are held to
+// what still gained.  32 sequences' heads of 60 tokens, d = 128: 768 workgroups 38.3 / 33.2, 896 39.0 / 39.0, 1024 41.0 / 41.9;
+// d = 256: 576 72.9 / 64.7, 640 55.6 / 60.1, 896 64.6 / 72.8.  And the K quantizer's digits at d = 256 leave one
+// K / V pair per CU: 128 key blocks 85.6 / 78.1, 256 127.7 / 134.2, 512 126.1 / 145.0.
 constexpr int SMALL_CALL_WG = 512;
 static bool small_call(const Dims& Dm) {
+  const long long nk = (long long)Dm.B * Dm.Hkv * Dm.nKb, nq = (long long)Dm.B * Dm.H * Dm.nQb;
+  const long long stats = Dm.stats_given ? 0 : (long long)Dm.B * Dm.Hkv * ((Dm.Nk + STAT_ROWS - 1) / STAT_ROWS);
+  if (Dm.int4 && Dm.d >= 128 && nq + stats > (Dm.d == 256 ? 576 : 768)) return false;
+  if (Dm.int4 && Dm.d == 256 && Dm.ds_mode == DS_DIGITS && nk > 128) return false;
   return !Dm.want_lse && !Dm.smooth_v && !Dm.tensor_groups && Dm.pvf == PV_E4M3 && !Dm.ds32 && !Dm.seq.cu_q &&
-         Dm.Nk <= 8 * STAT_ROWS && (long long)Dm.B * Dm.Hkv * Dm.nKb <= SMALL_CALL_WG &&
-         (long long)Dm.B * Dm.H * Dm.nQb <= SMALL_CALL_WG;
+         Dm.Nk <= 8 * STAT_ROWS && nk <= SMALL_CALL_WG && nq <= SMALL_CALL_WG;
 }
 
 template <bool BF16, bool INT4, int D>
