@@ -473,7 +473,9 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
   float lse_corr = 0.0f;
   if (p.lse && w == 0 && split == 0) {
     constexpr int CR = INT4 ? D / 4 : 8;
-    const unsigned short* qrow = x.q + row_offset(p.om, head_offset(p.om, (unsigned)(bh + hq)), (int)sq.q0 + query);
+    int row = (int)sq.q0 + query;
+    asm volatile("" : "+v"(row));          // (the address is formed anew: kept from the start, it would cost the loop registers)
+    const unsigned short* qrow = x.q + row_offset(p.om, head_offset(p.om, (unsigned)(bh + hq)), row);
     double runs[D / 2 / CR];
 #pragma unroll
     for (int i = 0; i < D / 2 / CR; ++i) {
