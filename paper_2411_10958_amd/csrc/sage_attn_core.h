@@ -380,6 +380,13 @@ __device__ __forceinline__ void pv_step(RowState<D>& st, const v4i (&va)[2 * (D 
   // operand formats: 0 = E4M3, 1 = E5M2, for both V^ (A) and P^ (B)
   constexpr int FMT = PVF == PV_E5M2 ? 1 : 0;
   st.O[CT] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, pb, st.O[CT], FMT, FMT, 0, 0, 0, 0);
+  // The product is a 16-pass instruction, and a vector read of its result needs 20 wait states behind it.  The compiler fills
+  // them in, but looks for the instruction only 19 back: a read that comes exactly 19 behind by itself gets nothing, and
+  // returned old values of the registers written last (seen at a copy of O at the end of a loop body).  It counts an
+  // asm statement as nothing, so this one makes every distance it leaves one longer than it thinks.  No measurable cost.
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 0" : "+v"(st.O[CT]));
+#endif
 }
 
 // Wavefronts per SIMD the attention kernel is built for, by variant.  d = 128 with the default key groups: 3 (168

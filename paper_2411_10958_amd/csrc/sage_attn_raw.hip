@@ -30,19 +30,6 @@ __device__ __forceinline__ double pair_sum(double (&x)[N]) {
   return x[0];
 }
 
-// Keeps the accumulators' next vector read a wait state further away than the compiler does.  It puts 19 between a 16-pass
-// matrix instruction and the first vector read of its result; where that read took the result's LAST registers at exactly
-// that distance (a loop-carried copy of O, highest registers first), they were sometimes the old ones on gfx950.  It was
-// seen in this kernel only, when the P~V product sat in both branches of the masked / unmasked choice; the product now
-// has one place, nothing copies O, and this holds whatever the compiler makes of the loop.
-template <int N>
-__device__ __forceinline__ void settle(v16f (&o)[N]) {
-#if defined(__HIP_DEVICE_COMPILE__)
-#pragma unroll
-  for (int i = 0; i < N; ++i) asm volatile("s_nop 3" : "+v"(o[i]));
-#endif
-}
-
 // One workgroup (8 wavefronts): one chunk of the key blocks of one (batch, KV head).  Column c of the tile is query c % n of
 // head c / n of the KV head's group (n: the sequence's query count).
 //
@@ -456,7 +443,6 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
     }
     pv_step<DW, 0, PV_E4M3>(st, va, pb);
     if constexpr (CTW > 1) pv_step<DW, CTW - 1, PV_E4M3>(st, va, pb);
-    settle(st.O);
   }
   if (!working || !col_ok) return;
 
