@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
 #pragma unroll
       for (int i = 0; i < CPL / 8; ++i)
         rk[i] = j < j1 && key < sq.nk ? *reinterpret_cast<const uint4*>(x.k + row_offset(x.km, hbase, key) +
-                                                                        (D == 256 ? 8 * quad_piece<D>(i, kk) : c0 + 8 * i))
+                                                                        (D == 256 ? 8 * quad_piece(i, kk) : c0 + 8 * i))
                                       : make_uint4(0u, 0u, 0u, 0u);
     };
     auto fetch_v = [&](int j) {
@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
       {
         float xk[CPL];
         float mx = 0.0f;
-        if constexpr (D == 256) quad_exchange<D>(rk);
+        if constexpr (D == 256) quad_exchange(rk);
 #pragma unroll
         for (int i = 0; i < CPL / 8; ++i) {
           unpack8<BF16>(rk[i], &xk[8 * i]);
@@ -254,7 +254,7 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
         uint8_t* img = reinterpret_cast<uint8_t*>(&s_v[cur][0]);
         float xv[RPT][8], vs[8], vi[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) { vs[e] = s_vs[8 * cg + e]; vi[e] = s_vi[8 * cg + e]; }
+        for (int e = 0; e < 8; ++e) { vs[e] = s_vs[8 * cg + e]; vi[e] = s_vi[8 * cg + e]; }
 #pragma unroll
         for (int i = 0; i < RPT; ++i) unpack8<BF16>(rv[i], xv[i]);
         fetch_v(j + 1);

@@ -34,19 +34,14 @@ __device__ inline void unpack8(const uint4& raw, float* x) {
   }
 }
 
-// The value of lane l ^ O - one step of a butterfly - without an LDS round trip: data-parallel moves inside 16 lanes, exchanges
-// of register halves beyond.  For O = 4 the move mirrors half a row, which is lane l ^ 4 where the lanes of a quad agree:
-// that step comes after 1 and 2.
+// The value of lane l ^ O - one step of a butterfly - without an LDS round trip: data-parallel moves inside 16 lanes (steps
+// of 16 and 32 exchange register halves instead, below).  For O = 4 the move mirrors half a row, which is lane l ^ 4 where the
+// lanes of a quad agree: that step comes after 1 and 2.
 template <int O>
 __device__ __forceinline__ unsigned butterfly(unsigned u) {
-  static_assert(O == 1 || O == 2 || O == 4 || O == 8 || O == 16 || O == 32, "a power of two below 64");
-  if constexpr (O == 16 || O == 32) {
-    const auto r = O == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false) : __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return (__lane_id() & O) ? r[0] : r[1];
-  } else {
-    constexpr int CTRL = O == 1 ? 0xB1 : (O == 2 ? 0x4E : (O == 4 ? 0x141 : 0x128));   // quad_perm, row_half_mirror, row_ror:8
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xf, 0xf, true);
-  }
+  static_assert(O == 1 || O == 2 || O == 4 || O == 8, "a step inside 16 lanes");
+  constexpr int CTRL = O == 1 ? 0xB1 : (O == 2 ? 0x4E : (O == 4 ? 0x141 : 0x128));   // quad_perm, row_half_mirror, row_ror:8
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xf, 0xf, true);
 }
 template <int O> __device__ __forceinline__ float butterfly_max(float v) {
   if constexpr (O == 16 || O == 32) {
@@ -169,16 +164,14 @@ __device__ inline uint2 pack8(const int (&c)[8]) {
   return o;
 }
 
-// A row of D 16-bit values by four lanes l, l + 16, l + 32, l + 48 (kk = 0..3), each of which wants D / 4 consecutive values
-// (pieces (D / 32) kk .. of 8 values).  Loaded that way, a load instruction touches 16 bytes of every 64 (d = 128) and
-// the four instructions meet in the caches or not at all.  Instead instruction i loads piece quad_piece(i, kk) - the
+// A row of 256 16-bit values by four lanes l, l + 16, l + 32, l + 48 (kk = 0..3), each of which wants 64 consecutive values
+// (pieces 8 kk .. of 8 values).  Loaded that way, a load instruction touches 16 bytes of a lane's 128, and the eight
+// instructions meet in the caches or not at all.  Instead instruction i loads piece quad_piece(i, kk) - the
 // four lanes side by side, 64 bytes - and quad_exchange moves the pieces to their lanes, in registers.
 // In bits: the pieces' number is (i, kk) with the low two bits in the lane; exchanging a register bit with a lane bit is
-// one v_permlane32_swap or v_permlane16_swap per pair of registers.
-template <int D>
-__device__ __forceinline__ int quad_piece(int i, int kk) {
-  return 4 * i + (D == 64 ? 2 * (kk & 1) + (kk >> 1) : kk);
-}
+// one v_permlane32_swap or v_permlane16_swap per pair of registers.  (Rows of 64 and 128 values, where a lane's piece is a part
+// of one cache line, are faster without.)
+__device__ __forceinline__ int quad_piece(int i, int kk) { return 4 * i + kk; }
 __device__ __forceinline__ void quad_swap32(uint4& a, uint4& b) {
   auto r = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false); a.x = r[0]; b.x = r[1];
   r = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false); a.y = r[0]; b.y = r[1];
@@ -191,20 +184,12 @@ __device__ __forceinline__ void quad_swap16(uint4& a, uint4& b) {
   r = __builtin_amdgcn_permlane16_swap(a.z, b.z, false, false); a.z = r[0]; b.z = r[1];
   r = __builtin_amdgcn_permlane16_swap(a.w, b.w, false, false); a.w = r[0]; b.w = r[1];
 }
-template <int D>
-__device__ __forceinline__ void quad_exchange(uint4 (&x)[D / 32]) {
-  if constexpr (D == 64) {             // bits (register; lane) = (p2; p0 p1) -> (p0; p2 p1)
-    quad_swap32(x[0], x[1]);
-  } else if constexpr (D == 128) {     // (p3 p2; p1 p0) -> (p1 p0; p3 p2)
-    quad_swap32(x[0], x[2]); quad_swap32(x[1], x[3]);
-    quad_swap16(x[0], x[1]); quad_swap16(x[2], x[3]);
-  } else {                             // (p4 p3 p2; p1 p0) -> (p1 p0 p2; p4 p3), then the registers in order
-    quad_swap32(x[0], x[4]); quad_swap32(x[1], x[5]); quad_swap32(x[2], x[6]); quad_swap32(x[3], x[7]);
-    quad_swap16(x[0], x[2]); quad_swap16(x[1], x[3]); quad_swap16(x[4], x[6]); quad_swap16(x[5], x[7]);
-    const uint4 y[8] = {x[0], x[2], x[4], x[6], x[1], x[3], x[5], x[7]};
+__device__ __forceinline__ void quad_exchange(uint4 (&x)[8]) {     // (p4 p3 p2; p1 p0) -> (p1 p0 p2; p4 p3), then the registers in order
+  quad_swap32(x[0], x[4]); quad_swap32(x[1], x[5]); quad_swap32(x[2], x[6]); quad_swap32(x[3], x[7]);
+  quad_swap16(x[0], x[2]); quad_swap16(x[1], x[3]); quad_swap16(x[4], x[6]); quad_swap16(x[5], x[7]);
+  const uint4 y[8] = {x[0], x[2], x[4], x[6], x[1], x[3], x[5], x[7]};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = y[i];
-  }
+  for (int i = 0; i < 8; ++i) x[i] = y[i];
 }
 
 }  // namespace sage
