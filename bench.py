@@ -7,6 +7,7 @@ causal mask) on the headline workload, the attention kernel's own roofline figur
 workloads at N >= 8192 in both modes (kernel alone and whole path), and the CPU oracle timed on a bounded sample.
 """
 import argparse
+import ctypes
 import json
 import os
 import sys
@@ -218,6 +219,20 @@ def main():
     for _ in range(args.warmup):
         step(a)
     ms_step, ms_pro, ms_core = timed(a, args.steps, 1 if args.steps < 20 else 5)
+    # A decode-shaped call (a few queries per sequence against a long cache) is not the sum of its two halves: it can be
+    # served from K and V directly, by one kernel that quantizes as it attends.  Its step is therefore the call itself;
+    # the breakdown stays that of the general path.
+    decode_shaped = spec.N <= 128 and spec.kv_len >= 64 * spec.N
+    if decode_shaped:
+        whole = pa.load_library().sage_attn_fwd_ex
+        for _ in range(max(args.warmup, 1)):
+            assert whole(ctypes.byref(a)) == 0
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(args.steps):
+            whole(ctypes.byref(a))
+        torch.cuda.synchronize()
+        ms_step = (time.perf_counter() - t0) * 1e3 / args.steps
     ops = wl.flops(spec)
     tops = ops / (ms_step * 1e-3) / 1e12
     core_tops = ops / (ms_core * 1e-3) / 1e12
@@ -262,7 +277,8 @@ def main():
                    "fp32_delta_s": bool(args.fp32_delta_s), "given_kv_stats": bool(args.given_kv_stats),
                    "group_map": args.group_map, "pv_format": args.pv_format, "kv_splits": splits,
                    "ops_formula": "4*B*H*N^2*d" + ("/2" if spec.causal else "")},
-        "breakdown_ms": {"prologue": round(ms_pro, 4), "attention_kernel": round(ms_core, 4)},
+        "breakdown_ms": {"prologue": round(ms_pro, 4), "attention_kernel": round(ms_core, 4),
+                         **({"of": "the general path in two halves, not the call timed as the step"} if decode_shaped else {})},
         # The attention kernel is a dense contraction whose vector work (the softmax between its two products) takes
         # longer than its matrix work: the counters show the vector ALU as the busy unit, so that is the bound named.
         # `peak` is the matrix peak of the instructions the kernel issues (score product in the FP6 operand format at
@@ -278,10 +294,10 @@ def main():
                      "algorithmic_bytes": alg_bytes, "ops_per_launch": ops},
     }
 
-    if spec.N <= 128 and spec.kv_len >= 64 * spec.N:
-        # decode-shaped: a few queries per sequence against a long cache.  The attention kernel then reads every code of
-        # K and V once per KV head (query heads of a group find them in the caches) and does next to no arithmetic per
-        # byte: its bound is HBM bandwidth, and its figure is bytes per second.
+    if decode_shaped:
+        # The attention kernel of the general path (the half timed in the breakdown) then reads every code of K and V once
+        # per KV head (query heads of a group find them in the caches) and does next to no arithmetic per byte: its bound is
+        # HBM bandwidth, and its figure is bytes per second.
         kv_bytes = int(BHkv * spec.kv_len * spec.d * (qk_code_bytes + 1.0)) + ds_bytes + 4 * BHkv * spec.kv_len // kg
         res["roofline"] = {"bound": "hbm", "kernel": "k_attn_fwd (key range split) + k_merge_splits",
                            "achieved": round(kv_bytes / (ms_core * 1e-3) / 1e9, 1), "peak": 8000.0, "unit": "GB/s",
