@@ -39,10 +39,13 @@ __device__ __forceinline__ double pair_sum(double (&x)[N]) {
 // with its own quarter of the channels of V^.  That repeats the softmax piece four times, but in parallel; with one
 // wavefront doing all of it a block would take three times as long.  LDS holds two blocks, one barrier per block.
 //
-// Bound: the stream of K and V (32 KB per block at d = 128), with the vector work of a block just below it.  4 x 8 KV heads,
-// 32768 keys, d = 128, one query: 128 us in the 8-bit mode (537 MB: 4.2 TB/s; quantizers + attention kernel 185), 160
-// in the 4-bit mode (255), whose Delta-S is FP64 matrix work that no vector work overlaps.  Four wavefronts doing both
-// parts in turn: 168 / 175.  More registers per thread (no spills in the 4-bit mode at d = 128) leave one workgroup per CU:
+// Bound: neither the stream of K and V (32 KB per block at d = 128) nor the vector ALU alone; each block is a chain of both
+// halves' work behind one barrier.  4 x 8 KV heads, 32768 keys, d = 128, one query, statistics supplied: 117 us in the 8-bit mode
+// (537 MB: 4.6 TB/s; quantizers + attention kernel 185), 148 in the 4-bit mode (3.6 TB/s; 255), whose Delta-S is FP64 matrix
+// work that no vector work overlaps.  The vector ALU issues in 75 / 71 % of the cycles: 795 / 873 instructions per SIMD and
+// block.  At d = 128 the 128 registers do not hold everything: the 4-bit form spills 16 to 19 (8 to 12 reloads in the two block
+// loops, of values that stay the same), the 8-bit one 11 to 13 (4 reloads); d = 64 and 256 none.  Tried: four wavefronts doing
+// both parts in turn, 168 / 175 us when the two-part form took 128 / 160; more registers per thread, so one workgroup per CU,
 // 153 / 170.  K by 64-byte pieces of four lanes and an exchange in registers pays at d = 256 only, where a lane's own
 // piece is a whole cache line (quad_exchange).
 template <int D, bool INT4, bool CAUSAL, bool BF16>
@@ -292,7 +295,8 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
   }
 
   // ---- the wavefront's Q^ operands: all four hold the same 32 columns and quantize them themselves (a separate launch for so
-  // few rows costs 7 us: 16 x 8 KV heads, 5003 keys 106 / 95 us, 4 x 8, 32768 keys 272 / 259).  Lane (n, half)
+  // few rows costs 7 us: 16 x 8 KV heads, 5003 keys, 8-bit mode 85 / 79 us, 4 x 8, 32768 keys, 4-bit 263 / 243; 16 of 256 channels,
+  // 30000 keys, 4-bit 238 / 231).  Lane (n, half)
   // supplies, of its column's query, PC consecutive channels per operand: smoothed
   // (4-bit mode), scale from the pair of queries, codes as k_quant_q4 / k_quant_q8 give them.
   constexpr int PC = INT4 ? 32 : 16;
@@ -513,11 +517,11 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
 // Calls the kernel above serves: the 32 columns of a tile hold all queries that meet a KV head (beyond 32 the softmax piece
 // would be repeated for columns that another wavefront holds on the general path), with the default groups, data types
 // and smoothing; in the 4-bit mode Delta-S in float64 (the library's own choice for so few block means).  A workgroup works
-// through its chunk block by block, about 2 us each, where the general path spreads the quantizers over the chip: with
-// fewer than 96 workgroups that serial chain is longer than the launches it saves.  Whole calls, us, general path / this
-// one, d = 128 unless said: 8 KV heads, 4000 keys (56 workgroups) 37 / 42; 4 KV heads of 256 channels, 5000 keys (36) 54 /
-// 57; 8, 8192 keys (128) 46 / 37, 8-bit mode 42 / 31; 32 of 64 channels, 3000 keys (160) 41 / 29; 16 x 8, 5003 keys 142 /
-// 95; 4 x 8, 32768 keys 358 / 259; 16 of 256 channels, 60000 keys 600 / 388.
+// through its chunk block by block, about 2 us each, where the general path spreads the quantizers over the chip: with few
+// workgroups that serial chain is longer than the launches it saves.  Whole calls of 96 to 104 workgroups, 1 to 8 heads per KV
+// head, both modes, general path / this one: 64 channels 1.06 to 1.64, 128 1.09 to 1.71, 256 1.12 to 1.91 (one block per chunk
+// gains most).  64 workgroups: 1.02 to 1.36, so the line is on the safe side.  Larger: 16 x 8 KV heads, 5003 keys, statistics
+// supplied, 8-bit 131 us / 79; 4 x 8, 32768 keys 357 / 243; 16 of 256 channels, 30000 keys 383 / 231.
 bool attention_raw_ok(const Dims& D) {
   const int G = D.H / D.Hkv;
   return G <= PACK_G && (long long)G * D.N <= 32 && (long long)D.B * D.Hkv * D.splits >= 96 && D.kg == KGROUP && !D.block_groups && D.pvf == PV_E4M3 &&

@@ -81,7 +81,11 @@ __host__ __device__ inline size_t row_offset(const TensorMap& m, size_t head_bas
 // which addresses are read at the same time.  Head by head that is one contiguous stretch of a head-major tensor - but of
 // a token-major one the same d channels of every row, a stride of H d elements that falls on a few of the memory channels
 // once it is long: 8 KB rows (32 heads of 128) run heads first (Q of a packed batch of 12300 tokens: 72 us -> 49 with the
-// log-sum-exp constants, of the 95 before those changed too), 2 KB rows (8 heads) measured 4 us of 142 slower that way.
+// log-sum-exp constants, of the 95 before those changed too).  Whole calls, K and V head by head / heads first: 32 KV heads of
+// 128, 4096 tokens 162 us / 158, 512 queries on 16384 keys 271 / 258, a packed batch 335 / 316, decode on 16384 keys 508 / 487;
+// 64 of 64 channels, 5000 tokens 297 / 296; 16 of 256, 6000 tokens 287 / 282.  Shorter rows keep their order: 2 KB rows
+// (8 heads) measured 4 us of 142 slower heads first, 4 KB rows (16 heads, 8000 tokens) 232 / 228 (so the line may lie
+// lower; only this point was measured).
 struct BlockPos { unsigned x, y, nx; };
 __device__ inline BlockPos block_pos(const TensorMap& m) {
   BlockPos p = {blockIdx.x, blockIdx.y, gridDim.x};
