@@ -51,12 +51,14 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
   D->smooth_k = (a->flags & SAGE_FLAG_NO_SMOOTH_K) == 0;
   D->smooth_q = (a->flags & SAGE_FLAG_NO_SMOOTH_Q) == 0;
   D->ds32 = (a->flags & SAGE_FLAG_FP32_DELTA_S) != 0;
-  // Delta-S: digit products on the INT8 matrix unit, unless a key block meets at most 16 rows of block means (a decode
-  // step, a short chunk): one chain of FP64 matrix instructions is then cheaper than cutting the keys into digits
+  // Delta-S: digit products on the INT8 matrix unit, unless a key block meets at most 8 rows of block means (a decode
+  // step, a short chunk): two chains of the 4-row FP64 matrix instruction are then cheaper than cutting the keys into digits
+  // (K quantizer, 4 x 32 heads of 1024 tokens, 8 rows: 20.1 us FP64, 21.4 digits; 16 rows of 512 queries of 4 heads on 16384
+  // keys: 41.3 and 40.7)
   D->ds_mode = D->ds32 ? 1
              : (a->flags & SAGE_FLAG_FP64_DELTA_S) != 0 ? 2
              : (a->flags & SAGE_FLAG_DIGIT_DELTA_S) != 0 ? 0
-             : ((long long)(D->H / D->Hkv) * D->nQb <= 16 ? 2 : 0);
+             : ((long long)(D->H / D->Hkv) * D->nQb <= 8 ? 2 : 0);
 
   D->stats_given = a->k_mean_in != nullptr;
   D->tensor_groups = a->group_map == SAGE_GROUPS_TENSOR;
@@ -312,6 +314,7 @@ int sage_attn_quant(const sage_attn_args* args, const sage_quant_out* out) {
   const Workspace w = make_workspace(D);
   if ((st = check_workspace(args, w)) != SAGE_OK) return st;
   const Ptrs P = ptrs_for(args, w);
+  D.causal = 0;      // (every value of Delta-S is handed out, also those no query under a causal mask would ask for)
   if ((st = hip_status(launch_prologue(D, P, (hipStream_t)args->stream))) != SAGE_OK) return st;
   return hip_status(launch_unpack(D, P, out, (hipStream_t)args->stream));
 }

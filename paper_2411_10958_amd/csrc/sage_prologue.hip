@@ -245,33 +245,42 @@ __global__ void __launch_bounds__(256) k_finalize_vscale(const unsigned* __restr
 // ------------------------------------------------------------------------------------------
 // Fixed-point digits for the Delta-S product (the scheme is described at k_quant_k).
 constexpr int DS_ND = 6;                         // digits per number
-constexpr int DS_MAXPAIR = 7;                    // digit pairs (a, b) with a + b up to this are multiplied: 30 of 36
-constexpr float DS_MAGIC = 12582912.0f;          // 1.5 * 2^23: adding it leaves rint() of a small number in the low mantissa bits
+constexpr int DS_MAXPAIR = 6;                    // digit pairs (a, b) with a + b up to this are multiplied: 26 of 36
 
-// The DS_ND digit bytes of y (|y| < 0.5: a value already divided by its row's 2^E) into byte `pos` of out[0..DS_ND).
-// y 2^42 is taken as two integers of 21 bits and a sign, N1 = rint(y 2^21) and N2 = rint((y 2^21 - N1) 2^21) (both
-// steps exact in FP32: adding 1.5 * 2^23 leaves the integer in the low mantissa bits), and each is cut into a signed
-// top digit (bits 14..21, -64..64) and two digits of 7 bits (0..127): y = sum_a n_a 2^(-7(a+1)) up to 2^-43.
-static_assert(DS_ND == 6, "two halves of three digits");
-__device__ __forceinline__ void ds_digits(float y, unsigned (&out)[DS_ND], int pos) {
-  const float s1 = __fmaf_rn(y, 0x1p21f, DS_MAGIC);           // MAGIC + N1
-  const float r = __fmaf_rn(y, 0x1p21f, -(s1 - DS_MAGIC));    // y 2^21 - N1, exact, |r| <= 1/2
-  const float s2 = __fmaf_rn(r, 0x1p21f, DS_MAGIC);           // MAGIC + N2
-  const unsigned b1 = __float_as_uint(s1), b2 = __float_as_uint(s2);   // low 22 bits: N in two's complement
-  out[0] |= ((b1 >> 14) & 0xffu) << (8 * pos);
-  out[1] |= ((b1 >> 7) & 0x7fu) << (8 * pos);
-  out[2] |= (b1 & 0x7fu) << (8 * pos);
-  out[3] |= ((b2 >> 14) & 0xffu) << (8 * pos);
-  out[4] |= ((b2 >> 7) & 0x7fu) << (8 * pos);
-  out[5] |= (b2 & 0x7fu) << (8 * pos);
-}
-// 2^-E and 2^E for a row whose largest magnitude is mx: E = exponent(mx) + 2, so that |x| 2^-E < 0.5.  A row of
-// zeros, or magnitudes of 2^125 and beyond (whose products overflow FP32 anyway), get 0 and 0: Delta-S = 0.
-__device__ __forceinline__ void ds_row_scale(float mx, float* down, float* up) {
+// A row's fixed point: up = 2^E with E = exponent(mx) + 3 of the row's largest magnitude mx, so that |x| < 2^(E-2), and the
+// FP64 number whose addition leaves N = rint(x 2^(48-E)), plus 128 in each of its six bytes, in the low 48 mantissa bits.
+// A row of zeros, or magnitudes of 2^125 and beyond (whose products overflow FP32 anyway), get up = 0: Delta-S = 0.
+struct DsScale { double magic; float up; };
+__device__ __forceinline__ DsScale ds_row_scale(float mx) {
   const unsigned eb = __float_as_uint(mx) >> 23;              // biased exponent (mx >= 0)
   const bool ok = mx > 0.0f && eb <= 251u;
-  *down = ok ? __uint_as_float((252u - eb) << 23) : 0.0f;
-  *up = ok ? __uint_as_float((eb + 2u) << 23) : 0.0f;
+  DsScale s;
+  s.magic = __longlong_as_double((long long)(((unsigned long long)(((eb + 903u) << 20) | 0x88080u) << 32) | 0x80808080u));
+  s.up = ok ? __uint_as_float((eb + 3u) << 23) : 0.0f;
+  return s;
+}
+// The DS_ND digits of four numbers of a row, digit a of the four in the bytes of out[a]: x = 2^E sum_a n_a 2^(-8(a+1)) up to
+// 2^(E-49), n_a in -128..127 (n_0 in -64..64).  The 128 added to every byte turns the bytes of a two's-complement number
+// into signed digits - a byte of 128 and more carries into the next one - and comes off again by flipping its top bit.
+// Two instructions cut a number, one addition and the widening in front of it, and 18 lay four numbers out; bit-field
+// extracts of two rounded halves (six digits of 7 bits) took 16 per number.
+__device__ __forceinline__ void ds_digits4(const float (&x)[4], double magic, unsigned (&out)[DS_ND]) {
+  static_assert(DS_ND == 6, "48 bits");
+  unsigned lo[4], hi[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong((double)x[j] + magic);
+    lo[j] = (unsigned)b; hi[j] = (unsigned)(b >> 32);
+  }
+  auto bytes01 = [](unsigned x1, unsigned x0) { return __builtin_amdgcn_perm(x1, x0, 0x05010400u); };   // byte 0 of both, byte 1 of both
+  auto bytes23 = [](unsigned x1, unsigned x0) { return __builtin_amdgcn_perm(x1, x0, 0x07030602u); };
+  auto low = [](unsigned x1, unsigned x0) { return __builtin_amdgcn_perm(x1, x0, 0x05040100u); };
+  auto high = [](unsigned x1, unsigned x0) { return __builtin_amdgcn_perm(x1, x0, 0x07060302u); };
+  const unsigned l01 = bytes01(lo[1], lo[0]), l23 = bytes01(lo[3], lo[2]), m01 = bytes23(lo[1], lo[0]), m23 = bytes23(lo[3], lo[2]),
+                 h01 = bytes01(hi[1], hi[0]), h23 = bytes01(hi[3], hi[2]);
+  out[5] = low(l23, l01) ^ 0x80808080u; out[4] = high(l23, l01) ^ 0x80808080u;
+  out[3] = low(m23, m01) ^ 0x80808080u; out[2] = high(m23, m01) ^ 0x80808080u;
+  out[1] = low(h23, h01) ^ 0x80808080u; out[0] = high(h23, h01) ^ 0x80808080u;
 }
 
 // Digits of one row of block means (DS_DIGITS), by one wavefront: `row` holds the D means (LDS or global), `digits`
@@ -288,14 +297,13 @@ __device__ __forceinline__ void ds_slice_row(const float* row, unsigned char* __
     mx = fmaxf(mx, fabsf(x[e]));
   }
   mx = wave_max(mx);
-  float down, up;
-  ds_row_scale(mx, &down, &up);
-  if (lane == 0) *scale = up;
+  const DsScale sc = ds_row_scale(mx);
+  if (lane == 0) *scale = sc.up;
+  float y[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) y[e] = x[e < PER ? e : 0];
   unsigned dg[DS_ND];
-#pragma unroll
-  for (int a = 0; a < DS_ND; ++a) dg[a] = 0u;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) ds_digits(x[e] * down, dg, e);
+  ds_digits4(y, sc.magic, dg);
 #pragma unroll
   for (int a = 0; a < DS_ND; ++a) {
     unsigned char* dst = digits + a * D + PER * lane;
@@ -625,13 +633,14 @@ __global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q4(const QuantQ
 //
 // Delta-S: D[i, t] = fl32(kappa * <q_bar_i, gamma(K)_t>), the inner product formed exactly (or in float64) so that
 // the value does not depend on summation order: a small GEMM [nQb x d] . [d x 64] per query head of the KV group,
-// walked 32 query blocks ("a pass") at a time; three forms, template parameter DSM below.  The FP64 form:
+// walked 16 query blocks (a step) at a time, their rows in one half of an LDS buffer while the next step's arrive for the other;
+// three forms, template parameter DSM below.  The FP64 form:
 // v_mfma_f64_16x16x4_f64 sustains about 70 TFLOP/s on the whole chip and, unlike the low-precision matrix
 // instructions, does not run concurrently with other vector work of the SIMD, so it costs its own matrix time
 // (2*nQb*N*d flops per head) on top of the quantization.
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int DS_QROWS = 32;    // query-block means staged in LDS per pass: two 16-row MFMA tiles
+constexpr int DS_ROWS = 16;     // block means per step of the Delta-S product: one tile of the 16-row matrix instructions
 
 // How the Delta-S product is formed (template parameter DSM of k_quant_k):
 //   DS_DIGITS  both factors cut into 7-bit digits of a fixed-point number and multiplied digit by digit on the INT8
@@ -639,15 +648,16 @@ constexpr int DS_QROWS = 32;    // query-block means staged in LDS per pass: two
 //   DS_FP32    v_mfma_f32_16x16x4_f32: faster still, approximate (an option of the boundary),
 //   DS_FP64    v_mfma_f64_16x16x4_f64: the reference form (an option of the boundary).
 //
-// DS_DIGITS.  A row x of d numbers (a block mean q_bar_i, or a smoothed key) with largest magnitude below 2^(E-1) is
-// written x_c = 2^E sum_a n_a[c] 2^(-7(a+1)) + rest, a = 0..5, with digits that fit a signed byte (ds_digits: n_0 and
-// n_3 in -64..64, the others in 0..127); the rest is zero for every x_c whose exponent is within 17 of the row's
-// largest (smaller ones lose what lies below 2^(E-42)).  Then
-//   <x, y> = 2^(Ex+Ey) sum_{a,b} 2^(-7(a+b+2)) sum_c n_a[c] m_b[c],
-// the inner sums are integers below 2^23 that v_mfma_i32_16x16x64_i8 forms exactly, pairs with the same a + b share
-// an accumulator (below 2^25), and the pairs with a + b > 7 are left out: together less than 2^-45 of
+// DS_DIGITS.  A row x of d numbers (a block mean q_bar_i, or a smoothed key) with largest magnitude below 2^(E-2) is
+// written x_c = 2^E sum_a n_a[c] 2^(-8(a+1)) + rest, a = 0..5, with digits that fit a signed byte (ds_digits4); the rest is
+// zero for every x_c whose exponent is within 21 of the row's largest (smaller ones lose what lies below 2^(E-48)).  Then
+//   <x, y> = 2^(Ex+Ey) sum_{a,b} 2^(-8(a+b+2)) sum_c n_a[c] m_b[c],
+// the inner sums are integers below 2^21 (d = 128) that v_mfma_i32_16x16x64_i8 forms exactly, pairs with the same a + b share
+// an accumulator (below 2^24), and the pairs with a + b > 6 are left out: together less than 2^-49 of
 // |x|_max |y|_max d.  The result agrees with the float64 inner product far below its FP32 rounding, at a quarter of
 // the FP64 instruction's time, and - being INT8 matrix work - it runs alongside the vector work of the quantizers.
+// Bound: vector issue (four cycles an instruction, whatever its class, once the wavefronts of a SIMD are out of step), which
+// the cutting of the keys and the joining of the accumulators set for a few rows, and the matrix pipe together for many.
 enum { DS_DIGITS = 0, DS_FP32 = 1, DS_FP64 = 2 };
 
 // Arguments of the K and V quantizers.  Where the statistics pass left partial results that nobody has reduced (k_sum, v_max
@@ -693,13 +703,13 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   // 32 lanes of a half-wavefront (16 rows x 2 channel groups) hit 32 different banks (odd stride)
   constexpr int SQW = D + (D >= 128 ? 48 : 0) + 1;
   constexpr int PADSH = D == 256 ? 6 : 5;          // 16 columns of padding after every 32 (d = 128) / 64 (d = 256) channels
-  __shared__ uint4 s_codes[BKV * D / 16];          // the block's packed image
-  __shared__ float s_q[INT4 && !DSD ? DS_QROWS : 1][SQW];
+  __shared__ uint4 s_codes[k_block_bytes(D, INT4) / 16];   // the block's packed image
+  __shared__ float s_q[INT4 && !DSD ? 2 * DS_ROWS : 1][SQW];
   // DS_DIGITS: a staged row is its DS_ND digit planes of D bytes; 16 bytes of padding make the 16 rows of an operand read
   // start in 16 different bank groups
   constexpr int ROWB = DS_ND * D + 16;
-  __shared__ __align__(16) unsigned char s_qd[DSD ? DS_QROWS : 1][DSD ? ROWB : 16];
-  __shared__ float s_qs[DS_QROWS];                 // 2^E of the staged rows
+  __shared__ __align__(16) unsigned char s_qd[DSD ? 2 * DS_ROWS : 1][DSD ? ROWB : 16];
+  __shared__ double s_qs[DSD ? 2 * DS_ROWS : 1];   // 2^E of the staged rows
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int r16 = lane & 15, k4 = lane >> 4;
   const int kb = bp.x;
@@ -714,102 +724,90 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   const int nQs = (sq.n + BQ - 1) / BQ;
   if (n0 >= N) return;                             // a block past the end of a shorter sequence
 
-  // Delta-S passes: (query head of the group, 32 query blocks); the first pass's block means are
-  // requested before the K rows so that both round trips overlap
-  constexpr int QPT = DS_QROWS * (D / 4) / 256;    // float4 pieces per thread per pass
-  // A sequence with fewer than 32 query blocks (a decode step, a short chunk against a long cache) would leave most
-  // rows of a pass empty: there the rows of all the query heads of the group are numbered through, head-major,
-  // and share passes ("flat").  Which pass a row sits in changes nothing in its value.
-  const bool flat = nQs < DS_QROWS;
-  const int npass_h = flat ? 1 : (nQs + DS_QROWS - 1) / DS_QROWS;
-  const int nrow = flat ? G * max(nQs, 0) : 0;
-  const int npass = INT4 ? (flat ? (nrow + DS_QROWS - 1) / DS_QROWS : G * npass_h) : 0;
-  // under a causal mask (query r sees keys t <= r + coff) query block i sees this key block only
-  // if 128 i + 127 + coff >= its first key: the passes of a head start with the one that holds
-  // block (first key - coff) / 128
-  const int p_first = causal && !flat ? (max(kb * BKV - coff, 0) / BQ) / DS_QROWS : 0;
-  // A pass is named by (head of the group, pass within the head), or by (0, pass) when flat; carried as a pair so
-  // that nothing in the pass loop divides.
-  struct PassId { int g, ph; };
-  const PassId pass_first = {0, p_first};
-  auto pass_ok = [&](PassId q) { return INT4 && (flat ? q.ph < npass : q.g < G); };
-  auto pass_next = [&](PassId q) {
-    PassId n = q;
-    if (flat || q.ph + 1 < npass_h) n.ph = q.ph + 1;
-    else { n.g = q.g + 1; n.ph = p_first; }
-    return n;
-  };
-  const float inv_nqs = 1.0f / (float)max(nQs, 1);
-  // row rr of a pass: its index (head, query block) in the [B H][nQb] arrays, or -1 for an empty row
+  // The rows of the Delta-S product - the block means of the G query heads that share this KV head, from the first query block
+  // that sees a key of this block on (under a causal mask block i does if 128 i + 127 + coff >= its first key) - are numbered
+  // through all the heads and taken 16 at a time.  Which step a row sits in changes nothing in its value.
+  const int i0 = causal ? min(max(n0 - coff, 0) / BQ, nQs) : 0;
+  const int nr = nQs - i0, nrow = INT4 ? G * nr : 0;
   const int bh0 = (int)bhkv * G;
-  auto pass_row = [&](PassId q, int rr) {
-    if (flat) {
-      // (R + 1/2) / nQs never comes within rounding distance of an integer for the few thousand rows there can be
-      const int R = q.ph * DS_QROWS + rr, g = (int)(((float)R + 0.5f) * inv_nqs);
-      return R < nrow ? (bh0 + g) * nQb + (R - g * nQs) : -1;
+  const float inv_nr = 1.0f / (float)max(nr, 1);
+  // A step's rows: nr >= 16 leaves room for one change of head, `cut` rows of the current one and then the next one's;
+  // shorter heads are told apart by a division per row.
+  struct Step { int R, base, next, cut; };         // first row, its place in the [B H][nQb] arrays, that of the next head's first row, cut
+  auto step_at = [&](int R, int g, int i) { return Step{R, (bh0 + g) * nQb + i, (bh0 + g + 1) * nQb + i0, nQs - i}; };
+  const bool few = nr < DS_ROWS;
+  auto step_row = [&](const Step& q, int rr) {     // place of row rr of the step, or -1 for an empty row
+    if (q.R + rr >= nrow) return -1;
+    if (few) {
+      // (R + 1/2) / nr never comes within rounding distance of an integer for the less than 2^21 rows there can be here
+      const int R = q.R + rr, g = (int)(((float)R + 0.5f) * inv_nr);
+      return (bh0 + g) * nQb + i0 + (R - g * nr);
     }
-    const int i = q.ph * DS_QROWS + rr;
-    return i < nQs ? (bh0 + q.g) * nQb + i : -1;
+    return rr < q.cut ? q.base + rr : q.next + (rr - q.cut);
   };
   constexpr int NCH = DS_ND * D / 16;              // 16-byte pieces of a row of digits
-  constexpr int QPD = DS_QROWS * NCH / 256;        // ... per thread per pass
+  constexpr int QPD = (DS_ROWS * NCH + 255) / 256;         // ... per thread per step
+  constexpr int QPT = (DS_ROWS * (D / 4) + 255) / 256;     // float4 pieces of the means per thread per step (the other forms)
   float4 qpre[DSD ? 1 : QPT];
   uint4 dpre[DSD ? QPD : 1];
   float spre = 0.0f;
-  auto load_q = [&](PassId p) {
+  // (a step within one head: consecutive rows of the arrays)
+  auto plain_step = [&](const Step& q) { return !few && q.cut >= DS_ROWS && nrow - q.R >= DS_ROWS; };
+  auto load_q = [&](const Step& q) {
     if constexpr (DSD) {
-      if (!flat) {
-        // the pass's rows are consecutive query blocks of one head: one contiguous piece of the digit array
-        const int row0 = (bh0 + p.g) * nQb + p.ph * DS_QROWS, rows = min(DS_QROWS, nQs - p.ph * DS_QROWS);
-        const uint4* src = reinterpret_cast<const uint4*>(q_digits + (size_t)row0 * (DS_ND * D));
+      if (plain_step(q)) {
+        const uint4* src = reinterpret_cast<const uint4*>(q_digits + (size_t)(unsigned)q.base * (DS_ND * D));
 #pragma unroll
         for (int k = 0; k < QPD; ++k) {
-          const int idx = t + k * 256;
-          dpre[k] = idx < rows * NCH ? src[idx] : make_uint4(0u, 0u, 0u, 0u);
+          if ((k + 1) * 256 <= DS_ROWS * NCH || t + k * 256 < DS_ROWS * NCH) dpre[k] = src[(unsigned)(t + k * 256)];
         }
-        if (t < DS_QROWS) spre = t < rows ? q_dscale[row0 + t] : 0.0f;
+        if (t < DS_ROWS) spre = q_dscale[(unsigned)(q.base + t)];
         return;
       }
+      int tt = t;
+      asm volatile("" : "+v"(tt));       // (what this path needs is formed here: kept through the loop, it cost registers)
 #pragma unroll
       for (int k = 0; k < QPD; ++k) {
-        const int idx = t + k * 256, rr = idx / NCH, ch = idx % NCH;
-        const int row = pass_row(p, rr);
+        const int idx = tt + k * 256, rr = idx / NCH, ch = idx % NCH;
+        const int row = rr < DS_ROWS ? step_row(q, rr) : -1;
         dpre[k] = row >= 0 ? *reinterpret_cast<const uint4*>(q_digits + (size_t)row * (DS_ND * D) + 16 * ch)
                            : make_uint4(0u, 0u, 0u, 0u);
       }
-      if (t < DS_QROWS) {
-        const int row = pass_row(p, t);
+      if (t < DS_ROWS) {
+        const int row = step_row(q, t);
         spre = row >= 0 ? q_dscale[row] : 0.0f;
       }
-      return;
-    }
+    } else {
 #pragma unroll
-    for (int k = 0; k < (DSD ? 0 : QPT); ++k) {
-      const int idx = t + k * 256, rr = idx / (D / 4), c4 = idx % (D / 4);
-      const int row = pass_row(p, rr);
-      qpre[k] = row >= 0 ? *reinterpret_cast<const float4*>(q_mean + (size_t)row * D + 4 * c4)
-                         : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int k = 0; k < QPT; ++k) {
+        const int idx = t + k * 256, rr = idx / (D / 4), c4 = idx % (D / 4);
+        const int row = rr < DS_ROWS ? step_row(q, rr) : -1;
+        qpre[k] = row >= 0 ? *reinterpret_cast<const float4*>(q_mean + (size_t)row * D + 4 * c4)
+                           : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
     }
   };
-  auto store_q = [&]() {
+  auto store_q = [&](int half) {                   // into one of the two halves of the LDS buffer
     if constexpr (DSD) {
 #pragma unroll
       for (int k = 0; k < QPD; ++k) {
         const int idx = t + k * 256, rr = idx / NCH, ch = idx % NCH;
-        *reinterpret_cast<uint4*>(&s_qd[rr][16 * ch]) = dpre[k];
+        if (DS_ROWS * NCH % 256 == 0 || rr < DS_ROWS) *reinterpret_cast<uint4*>(&s_qd[half * DS_ROWS + rr][16 * ch]) = dpre[k];
       }
-      if (t < DS_QROWS) s_qs[t] = spre;
-      return;
-    }
+      if (t < DS_ROWS) s_qs[half * DS_ROWS + t] = (double)spre;
+    } else {
 #pragma unroll
-    for (int k = 0; k < (DSD ? 0 : QPT); ++k) {
-      const int idx = t + k * 256, rr = idx / (D / 4), c4 = idx % (D / 4);
-      const int col = 4 * c4 + (D >= 128 ? 16 * ((4 * c4) >> PADSH) : 0);
-      s_q[rr][col + 0] = qpre[k].x; s_q[rr][col + 1] = qpre[k].y;
-      s_q[rr][col + 2] = qpre[k].z; s_q[rr][col + 3] = qpre[k].w;
+      for (int k = 0; k < QPT; ++k) {
+        const int idx = t + k * 256, rr = idx / (D / 4), c4 = idx % (D / 4);
+        const int col = 4 * c4 + (D >= 128 ? 16 * ((4 * c4) >> PADSH) : 0);
+        float* dst = &s_q[half * DS_ROWS + rr][col];
+        dst[0] = qpre[k].x; dst[1] = qpre[k].y; dst[2] = qpre[k].z; dst[3] = qpre[k].w;
+      }
     }
   };
-  if constexpr (INT4) load_q(pass_first);
+  // the first step's block means are requested before the K rows so that both round trips overlap
+  Step step = step_at(0, 0, i0);
+  if constexpr (INT4) load_q(step);
 
   // mean(K) of this head: reduced by the statistics pass, or here
   __shared__ __align__(16) float s_kmean[REDUCE ? D : 4];
@@ -828,23 +826,22 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   float x[CPL];
   float mx = 0.0f;
   const size_t hbase = hp.base + sq.k0 * (size_t)km.sn;
-  if (n0 + r < N) {
+  const unsigned short* krow = K + row_offset(km, hbase, min(n0 + r, N - 1)) + c0;
 #pragma unroll
-    for (int p = 0; p < CPL / 8; ++p) {
-      float x8[8];
-      load8<BF16, false>(K + row_offset(km, hbase, n0 + r) + c0 + 8 * p, x8);
-      const float4 m0 = mean4(c0 + 8 * p), m1 = mean4(c0 + 8 * p + 4);
-      const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
+  for (int p = 0; p < CPL / 8; ++p) {
+    float x8[8];
+    load8<BF16, false>(krow + 8 * p, x8);
+    const float4 m0 = mean4(c0 + 8 * p), m1 = mean4(c0 + 8 * p + 4);
+    const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        x[8 * p + e] = __fsub_rn(x8[e], mean[e]);
-        mx = fmaxf(mx, fabsf(x[8 * p + e]));
-      }
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < CPL; ++e) x[e] = 0.0f;      // padded keys: codes 0, Delta-S 0
+    for (int e = 0; e < 8; ++e) x[8 * p + e] = __fsub_rn(x8[e], mean[e]);
   }
+  if (n0 + BKV > N) {                              // a block with padded keys: their codes and Delta-S are 0
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) x[e] = n0 + r < N ? x[e] : 0.0f;
+  }
+#pragma unroll
+  for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(x[e]));
   // lanes l, l^16, l^32, l^48 hold one key: its maximum first, then (unless every key has its own
   // scale) the run of 4 keys, then (default) the wavefront's run of 16
   mx = butterfly_max<32>(butterfly_max<16>(mx));
@@ -862,7 +859,7 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   if (k4 == 0 && (r16 & (kg - 1)) == 0) k_scale[(bhkv * nKb + kb) * (BKV >> ksh) + ((16 * w + r16) >> ksh)] = delta;
   if (stats_only) return;                // per-tensor scales, first pass: only the block maxima are wanted
   uint8_t* img = reinterpret_cast<uint8_t*>(s_codes);
-  const QuantScale qs = quant_scale<QMAX>(delta);
+  const CodeScale qs = code_scale(delta);
   if constexpr (INT4) {
     // the lane's CPL codes are CPL*6/32 consecutive dwords of one MFMA lane's payload (all 6 of
     // them when d = 128; dwords 0..2 or 3..5 when d = 64), or two whole payloads (d = 256)
@@ -870,11 +867,11 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
 #pragma unroll
     for (int pl = 0; pl < NPL; ++pl) {
       Codes32 cd;
+      if constexpr (CPP < 32) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) { cd.ev[e] = 0.0f; cd.od[e] = 0.0f; }
-#pragma unroll
-      for (int g = 0; g < CPP / 8; ++g)
-        quant_group<8, QMAX>(x + CPP * pl + 8 * g, delta, qs, [&](int e, float c) { cd.set(8 * g + e, c); });
+        for (int e = 0; e < 16; ++e) { cd.ev[e] = 0.0f; cd.od[e] = 0.0f; }
+      }
+      code_group<CPP, QMAX>(x + CPP * pl, delta, qs, [&](int e, float c) { cd.set(e, c); });
       const v6u pw = cd.pack();
       int lane_m, e0;
       const size_t op = k_op6(r, c0 + CPP * pl, D, &lane_m, &e0);
@@ -885,12 +882,13 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
     }
   } else {
 #pragma unroll
-    for (int p = 0; p < CPL / 8; ++p) {
-      int c[8];
-      quant_group<8, QMAX>(x + 8 * p, delta, qs, [&](int e, float cf) { c[e] = (int)cf; });
-      *reinterpret_cast<uint2*>(img + k_code_off(r, c0 + 8 * p, D)) = pack8(c);
+    for (int i = 0; i < CPL / 16; ++i) {
+      unsigned c[16];
+      code_group_bytes<16, QMAX>(x + 16 * i, delta, qs, c);
+      *reinterpret_cast<uint4*>(img + k_code_off(r, c0 + 16 * i, D)) = pack16(c);
     }
   }
+  if constexpr (INT4) store_q(0);
   __syncthreads();
   constexpr int BLK16 = (int)(k_block_bytes(D, INT4) / 16);
   uint4* dst = reinterpret_cast<uint4*>(k_codes + (bhkv * nKb + kb) * k_block_bytes(D, INT4));
@@ -898,11 +896,8 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   for (int i = t; i < BLK16; i += 256) dst[i] = s_codes[i];
 
   if constexpr (INT4) {
-    // FP64 MFMA lane map: lane l supplies A[l%16][l/16] and B[l/16][l%16]; result element v of
-    // lane l is row 4*v + l/16, column l%16
-    // the smoothed keys stay in FP32 registers and are widened per use: CPL more conversions per
-    // pass (a few percent of the pass's MFMA time) instead of 2 CPL more live registers, which is
-    // what lets four workgroups share a CU
+    // the smoothed keys stay in FP32 registers and are widened per use (FP64 form): CPL more conversions per step instead
+    // of 2 CPL more live registers
     const double kap = (double)kappa;
     const int qcol = c0 + (D >= 128 ? 16 * k4 : 0);
     // DS_DIGITS: the digits of this lane's CPL smoothed values as B operands of v_mfma_i32_16x16x64_i8.  An operand is
@@ -912,135 +907,143 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
     v4i bd[DSD ? DS_ND : 1][DSD ? NST : 1];
     double key_up = 0.0;
     if constexpr (DSD) {
-      float down, up;
-      ds_row_scale(mx_key, &down, &up);
-      key_up = (double)up * kap;                   // 2^E of the key, times kappa
+      const DsScale ks = ds_row_scale(mx_key);
+      key_up = (double)ks.up * kap * 0x1p-64;      // 2^E of the key, times kappa; the accumulators are joined times 2^64
 #pragma unroll
       for (int st = 0; st < NST; ++st) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
+          const float y[4] = {x[16 * st + 4 * q4], x[16 * st + 4 * q4 + 1], x[16 * st + 4 * q4 + 2], x[16 * st + 4 * q4 + 3]};
           unsigned dg[DS_ND];
-#pragma unroll
-          for (int a = 0; a < DS_ND; ++a) dg[a] = 0u;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) ds_digits(x[16 * st + 4 * q4 + j] * down, dg, j);
+          ds_digits4(y, ks.magic, dg);
 #pragma unroll
           for (int a = 0; a < DS_ND; ++a) bd[a][st][q4] = (int)dg[a];
         }
       }
-      // (opaque to the compiler from here on: it would otherwise form the digits anew in every pass)
+      // (opaque to the compiler from here on: it would otherwise form the digits anew in every step)
 #pragma unroll
       for (int a = 0; a < DS_ND; ++a) {
 #pragma unroll
         for (int st = 0; st < NST; ++st) asm volatile("" : "+v"(bd[a][st]));
       }
     }
-    bool first_pass = true;
-    for (PassId p = pass_first; pass_ok(p); p = pass_next(p)) {
-      if (!first_pass) __syncthreads();            // everyone is done with the previous pass's rows
-      first_pass = false;
-      store_q();
-      __syncthreads();
-      if (pass_ok(pass_next(p))) load_q(pass_next(p));   // next pass, in flight under the MFMAs
-      // rows 16..31 of the pass all empty (a short last pass): their chain of matrix instructions is left out
-      const bool upper = p.ph * DS_QROWS + 16 < (flat ? nrow : nQs);
-      // (not flat: the pass's rows are consecutive rows of the Delta-S array of one head)
-      const unsigned rowstride = (unsigned)nKb * BKV;
-      float* const out0 = delta_s + (size_t)((bh0 + p.g) * nQb + p.ph * DS_QROWS) * rowstride + (size_t)(n0 + r);
-      const int rows_here = nQs - p.ph * DS_QROWS;
-      const bool full = rows_here >= DS_QROWS;        // (all but a head's last pass)
-      auto put = [&](int rr, float val) {
-        if (!flat) {
-          if (full || rr < rows_here) out0[(size_t)((unsigned)rr * rowstride)] = val;
-          return;
-        }
-        const int row = pass_row(p, rr);
-        if (row >= 0) delta_s[(size_t)row * rowstride + (size_t)(n0 + r)] = val;
-      };
-      if constexpr (DSD) {
-        // accumulators by digit-pair weight: acc[k][rt] collects the pairs with a + b = k for row tile rt; result
-        // element v of lane l is row 4 (l / 16) + v, column l % 16
-        // one 16-row tile at a time (its seven accumulators are live only until its results are out)
+    const unsigned rowstride = (unsigned)nKb * BKV;
+    float* const out = delta_s + n0;
+    int g = 0, i = i0;
+    for (int half = 0; step.R < nrow; half ^= 1) {
+      // the next step's rows are on their way while this one is multiplied, and go to the other half of the buffer
+      i += DS_ROWS;
+      if (i >= nQs) { i -= nr; ++g; }
+      const Step nxt = step_at(step.R + DS_ROWS, g, i);
+      if (nxt.R < nrow) load_q(nxt);
+      const int rows = min(nrow - step.R, DS_ROWS);
+      const bool plain = plain_step(step);
+      float* const out0 = out + (size_t)(unsigned)step.base * rowstride;      // (uniform: the lanes add 32-bit offsets)
+      // the four values of a lane: rows rl + v rs of the step
+      auto put4 = [&](int rl, int rs, const float (&val)[4]) {
+        if (plain) {
+          const unsigned off = (unsigned)rl * rowstride + (unsigned)r;
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-          if (rt == 1 && !upper) break;
-          if (zero_ds) {     // (Q not smoothed: the block means are zero and so is Delta-S)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) put(16 * rt + 4 * k4 + v, 0.0f);
-            continue;
-          }
-          v4i acc[DS_MAXPAIR + 1];
-#pragma unroll
-          for (int a = 0; a < DS_ND; ++a) {
-#pragma unroll
-            for (int st = 0; st < NST; ++st) {
-              const v4i qa = *reinterpret_cast<const v4i*>(&s_qd[16 * rt + r16][a * D + CPL * k4 + 16 * st]);
-#pragma unroll
-              for (int b = 0; b < DS_ND && a + b <= DS_MAXPAIR; ++b) {
-                // the first pair of a weight starts from zero (a constant operand of the instruction)
-                const bool first = st == 0 && a == (a + b >= DS_ND ? a + b - (DS_ND - 1) : 0);
-                acc[a + b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qa, bd[b][st], first ? v4i{0, 0, 0, 0} : acc[a + b], 0, 0, 0);
-              }
-            }
-          }
+          for (int v = 0; v < 4; ++v) (out0 + (size_t)(unsigned)(v * rs) * rowstride)[off] = val[v];
+        } else {
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            const int rr = 16 * rt + 4 * k4 + v;
-            // sum_k acc_k 2^(-7 (k + 2)): neighbours joined as integers first (128 acc_k + acc_{k+1} < 2^31: with the
-            // digit ranges of ds_digits the largest is 128 acc_6 + acc_7 < 2^30.1 at d = 128; at d = 256 that one would
-            // not fit and stays apart), then float64, smallest weights first
-            static_assert(DS_ND == 6 && DS_MAXPAIR == 7, "eight accumulators");
-            const int u0 = acc[0][v] * 128 + acc[1][v], u1 = acc[2][v] * 128 + acc[3][v],
-                      u2 = acc[4][v] * 128 + acc[5][v];
-            double sum;
-            if constexpr (D <= 128) {
-              sum = (double)(acc[6][v] * 128 + acc[7][v]) * 0x1p-63;
-            } else {
-              sum = (double)acc[7][v] * 0x1p-63;
-              sum = __fma_rn((double)acc[6][v], 0x1p-56, sum);
-            }
-            sum = __fma_rn((double)u2, 0x1p-49, sum);
-            sum = __fma_rn((double)u1, 0x1p-35, sum);
-            sum = __fma_rn((double)u0, 0x1p-21, sum);
-            put(rr, (float)(sum * ((double)s_qs[rr] * key_up)));
+            int rr = rl + v * rs;
+            asm volatile("" : "+v"(rr));
+            const int row = step_row(step, rr);
+            if (row >= 0) out[(size_t)(unsigned)row * rowstride + (unsigned)r] = val[v];
           }
         }
+      };
+      float val[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (zero_ds) {                               // (Q not smoothed: the block means are zero and so is Delta-S)
+        put4(4 * k4, 1, val);
+      } else if constexpr (DSD) {
+        // accumulators by digit-pair weight: acc[k] collects the pairs with a + b = k; result element v of lane l is
+        // row 4 (l / 16) + v, column l % 16
+        v4i acc[DS_MAXPAIR + 1];
+#pragma unroll
+        for (int a = 0; a < DS_ND; ++a) {
+#pragma unroll
+          for (int st = 0; st < NST; ++st) {
+            const v4i qa = *reinterpret_cast<const v4i*>(&s_qd[half * DS_ROWS + r16][a * D + CPL * k4 + 16 * st]);
+#pragma unroll
+            for (int b = 0; b < DS_ND && a + b <= DS_MAXPAIR; ++b) {
+              // the first pair of a weight starts from zero (a constant operand of the instruction)
+              const bool first = st == 0 && a == (a + b >= DS_ND ? a + b - (DS_ND - 1) : 0);
+              acc[a + b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qa, bd[b][st], first ? v4i{0, 0, 0, 0} : acc[a + b], 0, 0, 0);
+            }
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          // 2^64 sum_k acc_k 2^(-8 (k + 2)): neighbours joined as integers first, then float64, smallest weights first.
+          // 256 acc_k + acc_{k+1} < 2^31 at d = 128: the largest is k = 4, where the five pairs of digits come to at
+          // most 3.5 2^14 per channel - a number has 24 consecutive significant bits, so that one with n_0 beyond a carry has
+          // n_4 = 0.  At d = 256 that bound does not hold, and all of them are joined in float64.
+          static_assert(DS_ND == 6 && DS_MAXPAIR == 6, "seven accumulators");
+          double sum = (double)acc[6][v];
+          if constexpr (D <= 128) {
+            const int u0 = acc[0][v] * 256 + acc[1][v], u1 = acc[2][v] * 256 + acc[3][v], u2 = acc[4][v] * 256 + acc[5][v];
+            sum = __fma_rn((double)u2, 0x1p8, sum);
+            sum = __fma_rn((double)u1, 0x1p24, sum);
+            sum = __fma_rn((double)u0, 0x1p40, sum);
+          } else {
+            sum = __fma_rn((double)acc[5][v], 0x1p8, sum);
+            sum = __fma_rn((double)acc[4][v], 0x1p16, sum);
+            sum = __fma_rn((double)acc[3][v], 0x1p24, sum);
+            sum = __fma_rn((double)acc[2][v], 0x1p32, sum);
+            sum = __fma_rn((double)acc[1][v], 0x1p40, sum);
+            sum = __fma_rn((double)acc[0][v], 0x1p48, sum);
+          }
+          val[v] = (float)(sum * (s_qs[half * DS_ROWS + 4 * k4 + v] * key_up));
+        }
+        put4(4 * k4, 1, val);
       } else if constexpr (DS32) {
         // Faster, approximate form (an option of the boundary): the same product on the FP32 form of the
         // instruction (result element v of lane l is row 4*(l/16) + v, column l%16).  FP32 accumulation:
         // within (d + 2) 2^-24 kappa sum_c |q_bar_c gamma(K)_c| of the exact value, about half a unit of 2^-24 of
         // that magnitude on average.  It runs at twice the rate and under the vector work of the workgroups
         // that share the CU, so the product costs next to nothing on top of the quantization.
-        v4f acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (!zero_ds) {
+        v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int cs = 0; cs < CPL; ++cs)
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(s_q[half * DS_ROWS + r16][qcol + cs], x[cs], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) val[v] = __fmul_rn(kappa, acc[v]);
+        put4(4 * k4, 1, val);
+      } else if (rows <= 8) {
+        // A few rows: four at a time by v_mfma_f64_4x4x4_4b_f64, four independent 4 x 4 products per instruction (lane l supplies
+        // A[l % 4][l / 16] and B[l / 16][l % 4] of product (l / 4) % 4 and receives D[l / 16][l % 4]): 18 cycles for the step of
+        // four channels that takes the 16-row form 64, and the same order of additions.
+#pragma unroll 1
+        for (int r4 = 0; r4 < rows; r4 += 4) {
+          double acc = 0.0;
 #pragma unroll
           for (int cs = 0; cs < CPL; ++cs) {
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(s_q[r16][qcol + cs], x[cs], acc0, 0, 0, 0);
-            if (upper) acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(s_q[16 + r16][qcol + cs], x[cs], acc1, 0, 0, 0);
+            asm volatile("" : "+v"(x[cs]));        // keeps the widening where it is used
+            acc = __builtin_amdgcn_mfma_f64_4x4x4f64((double)s_q[half * DS_ROWS + r4 + (r16 & 3)][qcol + cs], (double)x[cs], acc, 0, 0, 0);
           }
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          put(4 * k4 + v, __fmul_rn(kappa, acc0[v]));
-          if (upper) put(16 + 4 * k4 + v, __fmul_rn(kappa, acc1[v]));
+          const int row = step_row(step, r4 + k4);
+          if (row >= 0) out[(size_t)(unsigned)row * rowstride + (unsigned)r] = (float)(kap * acc);
         }
       } else {
-        v4d acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
-        if (!zero_ds) {      // (Q not smoothed: the block means are zero and so is Delta-S)
+        // FP64 MFMA lane map: lane l supplies A[l%16][l/16] and B[l/16][l%16]; result element v of lane l is row
+        // 4*v + l/16, column l%16
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-          for (int cs = 0; cs < CPL; ++cs) {
-            asm volatile("" : "+v"(x[cs]));            // keeps the widening inside the pass loop
-            const double bk = (double)x[cs];
-            acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)s_q[r16][qcol + cs], bk, acc0, 0, 0, 0);
-            if (upper) acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)s_q[16 + r16][qcol + cs], bk, acc1, 0, 0, 0);
-          }
+        for (int cs = 0; cs < CPL; ++cs) {
+          asm volatile("" : "+v"(x[cs]));          // keeps the widening inside the loop
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)s_q[half * DS_ROWS + r16][qcol + cs], (double)x[cs], acc, 0, 0, 0);
         }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          put(4 * v + k4, (float)(kap * acc0[v]));
-          if (upper) put(16 + 4 * v + k4, (float)(kap * acc1[v]));
-        }
+        for (int v = 0; v < 4; ++v) val[v] = (float)(kap * acc[v]);
+        put4(k4, 4, val);
       }
+      if (nxt.R >= nrow) break;
+      store_q(half ^ 1);                           // (its last readers met the barrier that opened this step)
+      __syncthreads();
+      step = nxt;
     }
   }
 }
@@ -1135,8 +1138,13 @@ __device__ __forceinline__ void quant_v_block(const BlockPos bp, const QuantKV& 
   }
 }
 
+// Workgroups per CU the K quantizer is built for.  Digits: the six digit planes of a lane's channels and the seven accumulators
+// stay in registers through the steps, 124 registers of 128 at d = 128 (4096 tokens of 128 heads: three workgroups per CU 97 us,
+// four 91; as long as the loads of a step across heads kept their addresses through the loop, seven registers spilled once per
+// workgroup, 58 MB), 96 at d = 64 (four 467 us of a 17776-token call, five 435); d = 256 fits two.
+template <int D, bool INT4, int DSM> constexpr int quant_k_occupancy() { return D == 256 ? 2 : (D == 64 && INT4 && DSM == DS_DIGITS ? 5 : 4); }
 template <bool BF16, bool INT4, int D, int DSM = DS_DIGITS>
-__global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS ? 3 : 4)) k_quant_k(const QuantKV a) {
+__global__ void __launch_bounds__(256, (quant_k_occupancy<D, INT4, DSM>())) k_quant_k(const QuantKV a) {
   quant_k_block<BF16, INT4, D, DSM>(block_pos(a.km), a);
 }
 template <bool BF16, int D, bool SMOOTH_V, int PVF>

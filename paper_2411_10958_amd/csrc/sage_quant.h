@@ -81,7 +81,7 @@ __device__ __forceinline__ float wave_max(float v) { return group_max<64>(v); }
 // where the remainder underflows: quotients below 2^-40, which every 8-bit and 4-bit code rounds to 0.
 __device__ __forceinline__ float div_by(float x, float s, float r) {
   const float q = __fmul_rn(x, r);
-  return __fmaf_rn(__fmaf_rn(-q, s, x), r, q);
+  return __fmaf_rn(__fmaf_rn(q, -s, x), r, q);
 }
 __device__ __forceinline__ bool div_by_ok(float s) {
   return s >= 0x1p-60f && s <= 0x1p60f && (__float_as_uint(s) & 0x7fffffu) != 0x7fffffu;
@@ -127,6 +127,49 @@ __device__ inline void quant_group(const float* x, float delta, const QuantScale
 #pragma unroll
     for (int e = 0; e < NE; ++e) put(e, (float)quant_code(x[e], delta, QMAX));
   }
+}
+
+// psi with the correctly rounded quotient of div_by, for whole wavefronts: `fast` says that every lane's scale is one that
+// div_by accepts, or zero (all its values are then zero and so are their codes).  Four instructions per code instead of the
+// five of quant_group, three of them multiply-adds, and no branch per eight codes.
+struct CodeScale { float r; bool fast; };
+__device__ __forceinline__ CodeScale code_scale(float delta) {
+  CodeScale q;
+  q.fast = __builtin_amdgcn_ballot_w64(!(div_by_ok(delta) || delta == 0.0f)) == 0;
+  q.r = q.fast && delta > 0.0f ? __fdiv_rn(1.0f, delta) : 0.0f;
+  return q;
+}
+// NE codes as integer-valued floats, handed to put(e, code)
+template <int NE, int QMAX, class Put>
+__device__ __forceinline__ void code_group(const float* x, float delta, const CodeScale& qs, Put&& put) {
+  if (qs.fast) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) put(e, rintf(div_by(x[e], delta, qs.r)));
+  } else {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) put(e, (float)quant_code(x[e], delta, QMAX));
+  }
+}
+// ... in the low bytes of c[0..NE) (adding 1.5 * 2^23 rounds to the nearest integer, ties to even, and leaves it in the low
+// mantissa bits)
+template <int NE, int QMAX>
+__device__ __forceinline__ void code_group_bytes(const float* x, float delta, const CodeScale& qs, unsigned (&c)[NE]) {
+  if (qs.fast) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) c[e] = __float_as_uint(div_by(x[e], delta, qs.r) + 12582912.0f);
+  } else {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) c[e] = (unsigned)quant_code(x[e], delta, QMAX);
+  }
+}
+// the low bytes of sixteen words side by side
+__device__ __forceinline__ uint4 pack16(const unsigned (&c)[16]) {
+  unsigned wd[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    wd[q] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(c[4 * q + 3], c[4 * q + 2], 0x0c0c0400u),
+                                  __builtin_amdgcn_perm(c[4 * q + 1], c[4 * q], 0x0c0c0400u), 0x05040100u);
+  return make_uint4(wd[0], wd[1], wd[2], wd[3]);
 }
 
 typedef unsigned v6u __attribute__((ext_vector_type(6)));
