@@ -30,7 +30,7 @@ __device__ __forceinline__ double pair_sum(double (&x)[N]) {
   return x[0];
 }
 
-// One workgroup (8 wavefronts): one chunk of the key blocks of one (batch, KV head).  Column c of the tile is query c % n of
+// One workgroup (4 + raw_attenders wavefronts): one chunk of the key blocks of one (batch, KV head).  Column c of the tile is query c % n of
 // head c / n of the KV head's group (n: the sequence's query count).
 //
 // Wavefronts 0..3 quantize: a block's raw rows are in registers (requested a block ahead, as soon as the previous ones
@@ -48,19 +48,22 @@ __device__ __forceinline__ double pair_sum(double (&x)[N]) {
 // both parts in turn, 168 / 175 us when the two-part form took 128 / 160; more registers per thread, so one workgroup per CU,
 // 153 / 170.  K by 64-byte pieces of four lanes and an exchange in registers pays at d = 256 only, where a lane's own
 // piece is a whole cache line (quad_exchange).
-template <int D, bool INT4, bool CAUSAL, bool BF16>
-__global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnParams p, const RawParams x) {
+template <int D> constexpr int raw_attenders() { return D == 256 ? 4 : 2; }
+template <int D> constexpr int raw_threads() { return 64 * (4 + raw_attenders<D>()); }
+template <int D, bool INT4, bool CAUSAL, bool BF16, int HEADS>
+__global__ void __launch_bounds__(raw_threads<D>(), D == 256 ? 2 : 3) k_attn_raw(const AttnParams p, const RawParams x) {
   constexpr int CPL = D / 4;                                     // K: channels per lane
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BKV / NRG;   // V: 8 channels of RPT consecutive keys per thread
-  constexpr int CT = D / 32, CTW = (CT + 3) / 4;                 // channel tiles of the output, per wavefront
+  constexpr int NATT = raw_attenders<D>(), NT = raw_threads<D>();
+  constexpr int CT = D / 32, CTW = CT / NATT;                    // channel tiles of the output, per attending wavefront
   constexpr int KCK = (int)(k_block_bytes(D, INT4) / 16), KC = D * BKV / 16;
   constexpr int QMAX = INT4 ? 7 : 127;
   constexpr int NP = qk_pieces<D, INT4>();
   constexpr int QMS = CPL + 2;     // doubles per (head, channel quarter) in s_qm: 16 of them start in 16 different bank groups
   __shared__ v4i s_k[2][KCK];
   __shared__ v4i s_v[2][KC];
-  __shared__ __align__(16) float s_ds[INT4 ? 2 : 1][INT4 ? PACK_G : 1][BKV];
-  __shared__ __align__(16) double s_qm[INT4 ? PACK_G * 4 * QMS : 2];
+  __shared__ __align__(16) float s_ds[INT4 ? 2 : 1][INT4 ? HEADS : 1][BKV];
+  __shared__ __align__(16) double s_qm[INT4 ? HEADS * 4 * QMS : 2];
   __shared__ __align__(16) float s_km[D], s_vs[D], s_vi[D];      // mean(K); delta_V and its reciprocal (0: divide)
   __shared__ float s_ks[2][4];
 
@@ -79,7 +82,7 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
   const int hq = col_ok ? col / sq.n : 0, query = col_ok ? col - hq * sq.n : 0;
   if (sq.nk == 0) {                                              // no keys at all: the rows are defined as zeros
     if (split != 0) return;
-    for (int idx = t; idx < cols * (D / 8); idx += 512) {
+    for (int idx = t; idx < cols * (D / 8); idx += NT) {
       const int c = idx / (D / 8), g = c / sq.n, r = c - g * sq.n;
       unsigned short* o = reinterpret_cast<unsigned short*>(p.out) + row_offset(p.om, head_offset(p.om, (unsigned)(bh + g)), (int)sq.q0 + r);
       *reinterpret_cast<uint4*>(o + (idx % (D / 8)) * 8) = make_uint4(0u, 0u, 0u, 0u);
@@ -104,14 +107,14 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
     return;
   }
 
-  for (int c = t; c < D; c += 512) {
+  for (int c = t; c < D; c += NT) {
     s_km[c] = x.k_mean[bhkv * D + c];
     const float vs = p.v_scale[bhkv * D + c];
     s_vs[c] = vs;
     s_vi[c] = div_by_ok(vs) ? __fdiv_rn(1.0f, vs) : 0.0f;
   }
   if constexpr (INT4) {
-    for (int idx = t; idx < PACK_G * D; idx += 512) {
+    for (int idx = t; idx < HEADS * D; idx += NT) {
       const int g = idx / D, c = idx % D;
       // block mean of the head's queries (one block: at most 32), added in k_quant_q4's order
       double mean = 0.0;
@@ -138,20 +141,34 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
     const int cg = t % NCG, vr = RPT * (t / NCG);
     const size_t hbase = head_offset(x.km, (unsigned)bhkv) + sq.k0 * (size_t)x.km.sn;
     uint4 rk[CPL / 8], rv[RPT];
+    // Rows of block j: a uniform base and 32-bit lane offsets, formed once (64 rows of a token-major tensor stay below 2^32
+    // bytes).  Where the sequence ends inside the block its last row stands in for the rows behind it; their
+    // codes are cleared below (K) or meet a P~ of zero (V).
+    const unsigned rowb = 2u * (unsigned)x.km.sn;
+    const unsigned koff = (unsigned)kr * rowb + (D == 256 ? 16 * kk : 2 * c0), voff = (unsigned)vr * rowb + 16 * cg;
+    constexpr int KSTEP = D == 256 ? 64 : 16;              // bytes from one of the lane's loads to the next (256: quad_piece)
     auto fetch_k = [&](int j) {
-      const int key = j * BKV + kr;
+      j = min(j, j1 - 1);                                  // (past the chunk: its last block once more, unused)
+      const char* base = reinterpret_cast<const char*>(x.k + row_offset(x.km, hbase, j * BKV));
+      const int last = sq.nk - 1 - j * BKV;
+      unsigned off = koff;
+      if (last < BKV - 1) off -= (unsigned)max(kr - last, 0) * rowb;
 #pragma unroll
-      for (int i = 0; i < CPL / 8; ++i)
-        rk[i] = j < j1 && key < sq.nk ? *reinterpret_cast<const uint4*>(x.k + row_offset(x.km, hbase, key) +
-                                                                        (D == 256 ? 8 * quad_piece(i, kk) : c0 + 8 * i))
-                                      : make_uint4(0u, 0u, 0u, 0u);
+      for (int i = 0; i < CPL / 8; ++i) rk[i] = *reinterpret_cast<const uint4*>(base + KSTEP * i + off);
     };
     auto fetch_v = [&](int j) {
+      j = min(j, j1 - 1);
+      const char* base = reinterpret_cast<const char*>(x.v + row_offset(x.km, hbase, j * BKV));
+      const int last = sq.nk - 1 - j * BKV;
+      unsigned off[RPT];
 #pragma unroll
-      for (int i = 0; i < RPT; ++i) {
-        const int kv = j * BKV + vr + i;
-        rv[i] = j < j1 && kv < sq.nk ? nt_load16(x.v + row_offset(x.km, hbase, kv) + 8 * cg) : make_uint4(0u, 0u, 0u, 0u);
+      for (int i = 0; i < RPT; ++i) off[i] = voff + (unsigned)i * rowb;
+      if (last < BKV - 1) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) off[i] -= (unsigned)max(vr + i - last, 0) * rowb;
       }
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) rv[i] = nt_load16(reinterpret_cast<const unsigned short*>(base + off[i]));
     };
     fetch_k(j0);
     fetch_v(j0);
@@ -173,6 +190,7 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
 #pragma unroll
           for (int e = 0; e < 8; ++e) xk[8 * i + e] = __fsub_rn(xk[8 * i + e], mean[e]);
         }
+        __builtin_amdgcn_sched_barrier(0);
         fetch_k(j + 1);                    // (the registers are free; in flight under the rest of this block's work)
         if (j * BKV + BKV > sq.nk && j * BKV + kr >= sq.nk) {        // padded keys: codes 0, Delta-S 0
 #pragma unroll
@@ -182,9 +200,7 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
         for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(xk[e]));
         const float delta = __fdiv_rn(wave_max(mx), (float)QMAX);
         if (lane == 0) s_ks[cur][w] = delta;
-        // codes: the wavefront is one group, so one reciprocal and one decision serve all of it
-        const bool fast = __builtin_amdgcn_readfirstlane(div_by_ok(delta));
-        const float rd = fast ? __fdiv_rn(1.0f, delta) : 0.0f;
+        const CodeScale qs = code_scale(delta);
         uint8_t* img = reinterpret_cast<uint8_t*>(&s_k[cur][0]);
         if constexpr (INT4) {
           // Delta-S: q_bar_g . gamma(K)_t in float64, four heads at a time by v_mfma_f64_4x4x4_4b_f64: four independent
@@ -196,31 +212,43 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
           // lies next to the middle of two FP32 values could round to the other one (decode of 32768 keys: 249 us either way).
           const double kap = (double)p.kappa;
           const double* qa = &s_qm[((lane & 3) * 4 + kk) * QMS];
-          auto delta_s = [&](int first) {
-            double acc = 0.0;
+          // The means come out of LDS a chunk of channels ahead of their use: read one by one, each product waited for its own
+          // (32768 keys, 4-bit mode 145 us, now NNN); the two chains of five to eight heads run side by side.
+          constexpr int NCH = HEADS / 4, CH = (D == 256 ? 4 : 8) / NCH;
+          double acc[NCH], qv[2][NCH][CH];
+          auto means = [&](int c, int b) {
 #pragma unroll
-            for (int cs = 0; cs < CPL; ++cs) {
-              float xs = xk[cs];
-              asm volatile("" : "+v"(xs) :: "memory");     // (operands are read and widened as they are used, not all at once)
-              acc = __builtin_amdgcn_mfma_f64_4x4x4f64(qa[4 * first * QMS + cs], (double)xs, acc, 0, 0, 0);
+            for (int i = 0; i < NCH; ++i) {
+#pragma unroll
+              for (int e = 0; e < CH; ++e) qv[b][i][e] = qa[16 * i * QMS + c + e];
             }
-            s_ds[cur][first + kk][kr] = (float)(kap * acc);
           };
-          delta_s(0);
-          if (G > 4) delta_s(4);
+#pragma unroll
+          for (int i = 0; i < NCH; ++i) acc[i] = 0.0;
+          means(0, 0);
+#pragma unroll
+          for (int cs = 0; cs < CPL; cs += CH) {
+            if (cs + CH < CPL) means(cs + CH, (cs / CH + 1) & 1);
+            asm volatile("" ::: "memory");                 // (not all of them at once)
+#pragma unroll
+            for (int e = 0; e < CH; ++e) {
+              asm volatile("" : "+v"(xk[cs + e]));         // (widened as it is used)
+              const double xd = (double)xk[cs + e];
+#pragma unroll
+              for (int i = 0; i < NCH; ++i) acc[i] = __builtin_amdgcn_mfma_f64_4x4x4f64(qv[(cs / CH) & 1][i][e], xd, acc[i], 0, 0, 0);
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < NCH; ++i) s_ds[cur][4 * i + kk][kr] = (float)(kap * acc[i]);
           constexpr int NPL = CPL > 32 ? CPL / 32 : 1, CPP = CPL / NPL;
 #pragma unroll
           for (int pl = 0; pl < NPL; ++pl) {
             Codes32 cd;
+            if constexpr (CPP < 32) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) { cd.ev[e] = 0.0f; cd.od[e] = 0.0f; }
-            if (fast) {
-#pragma unroll
-              for (int e = 0; e < CPP; ++e) cd.set(e, rintf(div_by(xk[CPP * pl + e], delta, rd)));
-            } else {
-#pragma unroll
-              for (int e = 0; e < CPP; ++e) cd.set(e, (float)quant_code(xk[CPP * pl + e], delta, QMAX));
+              for (int e = 0; e < 16; ++e) { cd.ev[e] = 0.0f; cd.od[e] = 0.0f; }
             }
+            code_group<CPP, QMAX>(xk + CPP * pl, delta, qs, [&](int e, float c) { cd.set(e, c); });
             const v6u pw = cd.pack();
             int lane_m, e0;
             const size_t op = k_op6(kr, c0 + CPP * pl, D, &lane_m, &e0);
@@ -230,24 +258,11 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
               *reinterpret_cast<unsigned*>(img + op + op6_byte(lane_m, 4 * (d0 + i))) = pw[i];
           }
         } else {
-          // (adding 1.5 * 2^23 rounds to the nearest integer, ties to even, and leaves it in the low mantissa bits, so the
-          // low byte is the code)
 #pragma unroll
           for (int i = 0; i < CPL / 16; ++i) {
             unsigned c[16];
-            if (fast) {
-#pragma unroll
-              for (int e = 0; e < 16; ++e) c[e] = __float_as_uint(div_by(xk[16 * i + e], delta, rd) + 12582912.0f);
-            } else {
-#pragma unroll
-              for (int e = 0; e < 16; ++e) c[e] = (unsigned)quant_code(xk[16 * i + e], delta, QMAX);
-            }
-            unsigned wd[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              wd[q] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(c[4 * q + 3], c[4 * q + 2], 0x0c0c0400u),
-                                            __builtin_amdgcn_perm(c[4 * q + 1], c[4 * q], 0x0c0c0400u), 0x05040100u);
-            *reinterpret_cast<uint4*>(img + k_code_off(kr, c0 + 16 * i, D)) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+            code_group_bytes<16, QMAX>(xk + 16 * i, delta, qs, c);
+            *reinterpret_cast<uint4*>(img + k_code_off(kr, c0 + 16 * i, D)) = pack16(c);
           }
         }
       }
@@ -260,6 +275,14 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
         for (int e = 0; e < 8; ++e) { vs[e] = s_vs[8 * cg + e]; vi[e] = s_vi[8 * cg + e]; }
 #pragma unroll
         for (int i = 0; i < RPT; ++i) unpack8<BF16>(rv[i], xv[i]);
+        // (unpacked here and not in the two branches below: the rows' registers would not be free for the next block's, and a
+        // copy at the end of the block would wait for those)
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(xv[i][e]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
         fetch_v(j + 1);
         if (v_fast) {
 #pragma unroll
@@ -281,7 +304,8 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
           int wd[(RPT + 3) / 4];
 #pragma unroll
           for (int i = 0; i < RPT; i += 2) {
-            if ((i & 2) == 0) wd[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(xv[i][e], xv[i + 1][e], 0, false);
+            // (the first conversion of a word keeps the other half of any register: one that is free afterwards)
+            if ((i & 2) == 0) wd[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(xv[i][e], xv[i + 1][e], __float_as_int(xv[i][e]), false);
             else wd[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(xv[i][e], xv[i + 1][e], wd[i / 4], true);
           }
           if constexpr (RPT == 2) *reinterpret_cast<unsigned short*>(img + off) = (unsigned short)wd[0];
@@ -383,13 +407,11 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
   st.m_run = -INFINITY;
   st.l_run = 0.0f;
   float m_sub = -INFINITY;
-  const bool working = w * CTW < CT;                             // (d = 64: two wavefronts have no channels)
   int n_plain = min(j1, sq.nk / BKV);                            // blocks that need no mask
   if (CAUSAL) n_plain = min(n_plain, (sq.coff + 1) / BKV);
   const int n_keys_end = min(sq.nk, j1 * BKV);
   for (int j = j0, cur = 0; j < j1; ++j, cur ^= 1) {
     __syncthreads();
-    if (!working) continue;
     v8i pb;
     float alpha;
     auto attend = [&](auto masked_) {
@@ -448,7 +470,7 @@ __global__ void __launch_bounds__(512, D == 256 ? 2 : 4) k_attn_raw(const AttnPa
     pv_step<DW, 0, PV_E4M3>(st, va, pb);
     if constexpr (CTW > 1) pv_step<DW, CTW - 1, PV_E4M3>(st, va, pb);
   }
-  if (!working || !col_ok) return;
+  if (!col_ok) return;
 
   float l_tot = st.l_run;
   {
@@ -537,8 +559,14 @@ static hipError_t launch_raw_t(const Dims& D, const Ptrs& P, hipStream_t s) {
   x.k_mean = P.k_mean; x.q_corr = P.q_corr;
   x.km = make_tensor_map(D.nhd, D.Hkv, D.Nk, D.d, D.seq.cu_q != nullptr);
   const int grid = p.total_tiles * D.splits;
-  if (D.bf16) k_attn_raw<DD, INT4, CAUSAL, true><<<grid, 512, 0, s>>>(p, x);
-  else        k_attn_raw<DD, INT4, CAUSAL, false><<<grid, 512, 0, s>>>(p, x);
+  const bool many = INT4 && D.H / D.Hkv > 4;
+#define SAGE_RAW_LAUNCH(BF) \
+  do { \
+    if (many) k_attn_raw<DD, INT4, CAUSAL, BF, INT4 ? PACK_G : 4><<<grid, raw_threads<DD>(), 0, s>>>(p, x); \
+    else k_attn_raw<DD, INT4, CAUSAL, BF, 4><<<grid, raw_threads<DD>(), 0, s>>>(p, x); \
+  } while (0)
+  if (D.bf16) SAGE_RAW_LAUNCH(true); else SAGE_RAW_LAUNCH(false);
+#undef SAGE_RAW_LAUNCH
   if (D.splits > 1) return launch_merge_packed(D, p, s);
   return hipGetLastError();
 }
