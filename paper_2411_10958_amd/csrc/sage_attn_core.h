@@ -112,6 +112,17 @@ __device__ __forceinline__ void qk_tile(const typename QkOperand<INT4>::type (&k
   }
 }
 
+// The steps of one key tile alone.
+template <int D, bool INT4, int KT, int S = 0>
+__device__ __forceinline__ void qk_key_tile(const typename QkOperand<INT4>::type (&ka)[qk_steps<D, INT4>()],
+                                            const typename QkOperand<INT4>::type (&qreg)[qk_pieces<D, INT4>()],
+                                            v16i (&acc)[2]) {
+  if constexpr (S < qk_pieces<D, INT4>()) {
+    qk_step<D, INT4, 2 * S + KT>(ka, qreg, acc);
+    qk_key_tile<D, INT4, KT, S + 1>(ka, qreg, acc);
+  }
+}
+
 // One (piece, tile) operand out of a packed K^ block or Q^ tile at `base` (LDS or global): INT8
 // mode chunk `op`*64 + lane; INT4 mode the lane's 16 bytes of op's first plane and 8 bytes of its
 // second plane.

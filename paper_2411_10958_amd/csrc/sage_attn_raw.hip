@@ -30,32 +30,30 @@ __device__ __forceinline__ double pair_sum(double (&x)[N]) {
   return x[0];
 }
 
-// One workgroup (4 + raw_attenders wavefronts): one chunk of the key blocks of one (batch, KV head).  Column c of the tile is query c % n of
+// One workgroup (8 wavefronts): one chunk of the key blocks of one (batch, KV head).  Column c of the tile is query c % n of
 // head c / n of the KV head's group (n: the sequence's query count).
 //
-// Wavefronts 0..3 quantize: a block's raw rows are in registers (requested a block ahead, as soon as the previous ones
-// are unpacked), are smoothed, quantized and written to LDS in the order the matrix operands are read in.  Wavefronts 4..7
-// attend: each forms the block's scores and P~ for all 32 columns - the same values in all four - and multiplies them
-// with its own quarter of the channels of V^.  That repeats the softmax piece four times, but in parallel; with one
-// wavefront doing all of it a block would take three times as long.  LDS holds two blocks, one barrier per block.
+// Wavefronts 0..3 quantize K, 4 and 5 V: a block's raw rows are in registers (requested a block ahead, as soon as the previous
+// ones are unpacked), are smoothed, quantized and written to LDS in the order the matrix operands are read in.  Wavefronts 6 and
+// 7 attend: each forms the block's scores and P~ for all 32 columns - the same values in both - and multiplies them
+// with its own half of the channels of V^.  LDS holds two blocks, one barrier per block.
 //
-// Bound: neither the stream of K and V (32 KB per block at d = 128) nor the vector ALU alone; each block is a chain of both
-// halves' work behind one barrier.  4 x 8 KV heads, 32768 keys, d = 128, one query, statistics supplied: 117 us in the 8-bit mode
-// (537 MB: 4.6 TB/s; quantizers + attention kernel 185), 148 in the 4-bit mode (3.6 TB/s; 255), whose Delta-S is FP64 matrix
-// work that no vector work overlaps.  The vector ALU issues in 75 / 71 % of the cycles: 795 / 873 instructions per SIMD and
-// block.  At d = 128 the 128 registers do not hold everything: the 4-bit form spills 16 to 19 (8 to 12 reloads in the two block
-// loops, of values that stay the same), the 8-bit one 11 to 13 (4 reloads); d = 64 and 256 none.  Tried: four wavefronts doing
-// both parts in turn, 168 / 175 us when the two-part form took 128 / 160; more registers per thread, so one workgroup per CU,
-// 153 / 170.  K by 64-byte pieces of four lanes and an exchange in registers pays at d = 256 only, where a lane's own
-// piece is a whole cache line (quad_exchange).
-template <int D> constexpr int raw_attenders() { return D == 256 ? 4 : 2; }
-template <int D> constexpr int raw_threads() { return 64 * (4 + raw_attenders<D>()); }
+// Bound: each block is a chain of its wavefronts' work behind one barrier; the split above is what makes the longest of
+// them short, and keeps every part in 128 registers (d = 64 and 128; d = 256: 189), so that two workgroups share a CU.
+// 4 x 8 KV heads, 32768 keys, d = 128, one query, statistics supplied, whole call: 101 us in the 4-bit mode (537 MB: 5.3 TB/s),
+// 88 in the 8-bit one (6.1 TB/s; quantizers + attention kernel 185).  Four wavefronts quantizing both and four attending, with 16
+// spilled registers, rows addressed and padded lane by lane and every mean of Delta-S waited for by itself: 153 / 122; those mended
+// and two attending wavefronts instead of four: 139 / 103.  16 of 256 channels, 30000 keys, 4-bit: 147, 128, 114.  16 x 16 of 64
+// channels, 5003 keys, 8-bit: 139, 82, 74.  Tried: one attending wavefront (d = 64: 71 -> 69 us on grouped heads, 74 -> 77
+// on ungrouped ones); four for V at d = 256 (128 -> 128, 8-bit 70 -> 82).  K by 64-byte pieces of four lanes and an exchange in
+// registers pays at d = 256 only, where a lane's own piece is a whole cache line (quad_exchange).
+// HEADS: 4, or PACK_G where the 4-bit mode has more than four query heads per KV head (two chains of the Delta-S product).
+constexpr int RAW_V = 2, RAW_ATT = 2, RAW_THREADS = 64 * (4 + RAW_V + RAW_ATT);
 template <int D, bool INT4, bool CAUSAL, bool BF16, int HEADS>
-__global__ void __launch_bounds__(raw_threads<D>(), D == 256 ? 2 : 3) k_attn_raw(const AttnParams p, const RawParams x) {
+__global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(const AttnParams p, const RawParams x) {
   constexpr int CPL = D / 4;                                     // K: channels per lane
-  constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BKV / NRG;   // V: 8 channels of RPT consecutive keys per thread
-  constexpr int NATT = raw_attenders<D>(), NT = raw_threads<D>();
-  constexpr int CT = D / 32, CTW = CT / NATT;                    // channel tiles of the output, per attending wavefront
+  constexpr int NCG = D / 8, NRG = 64 * RAW_V / NCG, RPT = BKV / NRG;   // V: 8 channels of RPT keys per thread
+  constexpr int CT = D / 32, CTW = CT / RAW_ATT;                 // channel tiles of the output, per attending wavefront
   constexpr int KCK = (int)(k_block_bytes(D, INT4) / 16), KC = D * BKV / 16;
   constexpr int QMAX = INT4 ? 7 : 127;
   constexpr int NP = qk_pieces<D, INT4>();
@@ -68,8 +66,9 @@ __global__ void __launch_bounds__(raw_threads<D>(), D == 256 ? 2 : 3) k_attn_raw
   __shared__ float s_ks[2][4];
 
   const int t = threadIdx.x, lane = t & 63;
-  const bool quantizer = __builtin_amdgcn_readfirstlane(t >> 8) == 0;
-  const int w = __builtin_amdgcn_readfirstlane(t >> 6) & 3;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const bool k_wave = wave < 4, v_wave = !k_wave && wave < 4 + RAW_V;
+  const int w = k_wave ? wave : wave - 4 - RAW_V;                // (of the K quantizers, or of the attending wavefronts)
   const int n = lane & 31, half = lane >> 5;
   const int split = blockIdx.x % p.splits, tile = blockIdx.x / p.splits;
   const int G = p.H / p.Hkv;
@@ -82,7 +81,7 @@ __global__ void __launch_bounds__(raw_threads<D>(), D == 256 ? 2 : 3) k_attn_raw
   const int hq = col_ok ? col / sq.n : 0, query = col_ok ? col - hq * sq.n : 0;
   if (sq.nk == 0) {                                              // no keys at all: the rows are defined as zeros
     if (split != 0) return;
-    for (int idx = t; idx < cols * (D / 8); idx += NT) {
+    for (int idx = t; idx < cols * (D / 8); idx += RAW_THREADS) {
       const int c = idx / (D / 8), g = c / sq.n, r = c - g * sq.n;
       unsigned short* o = reinterpret_cast<unsigned short*>(p.out) + row_offset(p.om, head_offset(p.om, (unsigned)(bh + g)), (int)sq.q0 + r);
       *reinterpret_cast<uint4*>(o + (idx % (D / 8)) * 8) = make_uint4(0u, 0u, 0u, 0u);
@@ -107,14 +106,14 @@ __global__ void __launch_bounds__(raw_threads<D>(), D == 256 ? 2 : 3) k_attn_raw
     return;
   }
 
-  for (int c = t; c < D; c += NT) {
+  for (int c = t; c < D; c += RAW_THREADS) {
     s_km[c] = x.k_mean[bhkv * D + c];
     const float vs = p.v_scale[bhkv * D + c];
     s_vs[c] = vs;
     s_vi[c] = div_by_ok(vs) ? __fdiv_rn(1.0f, vs) : 0.0f;
   }
   if constexpr (INT4) {
-    for (int idx = t; idx < HEADS * D; idx += NT) {
+    for (int idx = t; idx < HEADS * D; idx += RAW_THREADS) {
       const int g = idx / D, c = idx % D;
       // block mean of the head's queries (one block: at most 32), added in k_quant_q4's order
       double mean = 0.0;
@@ -134,191 +133,204 @@ __global__ void __launch_bounds__(raw_threads<D>(), D == 256 ? 2 : 3) k_attn_raw
   }
   __syncthreads();
 
-  if (quantizer) {
-    // ---- this thread's share of a block: K as in k_quant_k - lane l of wavefront w holds key 16 w + l % 16, channels
-    // CPL (l / 16) .. - and V by rows
-    const int kk = lane >> 4, c0 = CPL * kk, kr = 16 * w + (lane & 15);
-    const int cg = t % NCG, vr = RPT * (t / NCG);
-    const size_t hbase = head_offset(x.km, (unsigned)bhkv) + sq.k0 * (size_t)x.km.sn;
-    uint4 rk[CPL / 8], rv[RPT];
-    // Rows of block j: a uniform base and 32-bit lane offsets, formed once (64 rows of a token-major tensor stay below 2^32
-    // bytes).  Where the sequence ends inside the block its last row stands in for the rows behind it; their
-    // codes are cleared below (K) or meet a P~ of zero (V).
-    const unsigned rowb = 2u * (unsigned)x.km.sn;
-    const unsigned koff = (unsigned)kr * rowb + (D == 256 ? 16 * kk : 2 * c0), voff = (unsigned)vr * rowb + 16 * cg;
-    constexpr int KSTEP = D == 256 ? 64 : 16;              // bytes from one of the lane's loads to the next (256: quad_piece)
-    auto fetch_k = [&](int j) {
-      j = min(j, j1 - 1);                                  // (past the chunk: its last block once more, unused)
-      const char* base = reinterpret_cast<const char*>(x.k + row_offset(x.km, hbase, j * BKV));
-      const int last = sq.nk - 1 - j * BKV;
-      unsigned off = koff;
-      if (last < BKV - 1) off -= (unsigned)max(kr - last, 0) * rowb;
+  const size_t hbase = head_offset(x.km, (unsigned)bhkv) + sq.k0 * (size_t)x.km.sn;
+  // Rows of block j: a uniform base and 32-bit lane offsets, formed once (64 rows of a token-major tensor stay below 2^32
+  // bytes).  Where the sequence ends inside the block its last row stands in for the rows behind it; their
+  // codes are cleared below (K) or meet a P~ of zero (V).  Past the chunk its last block is read once more, and not used.
+  const unsigned rowb = 2u * (unsigned)x.km.sn;
+  // K as in k_quant_k: lane l of wavefront w holds key 16 w + l % 16, channels CPL (l / 16) ..
+  const int kk = lane >> 4, c0 = CPL * kk, kr = 16 * w + (lane & 15);
+  const unsigned koff = (unsigned)kr * rowb + (D == 256 ? 16 * kk : 2 * c0);
+  constexpr int KSTEP = D == 256 ? 64 : 16;                // bytes from one of the lane's loads to the next (256: quad_piece)
+  uint4 rk[CPL / 8];
+  auto fetch_k = [&](int j) {
+    j = min(j, j1 - 1);
+    const char* base = reinterpret_cast<const char*>(x.k + row_offset(x.km, hbase, j * BKV));
+    const int last = sq.nk - 1 - j * BKV;
+    unsigned off = koff;
+    if (last < BKV - 1) off -= (unsigned)max(kr - last, 0) * rowb;
 #pragma unroll
-      for (int i = 0; i < CPL / 8; ++i) rk[i] = *reinterpret_cast<const uint4*>(base + KSTEP * i + off);
-    };
-    auto fetch_v = [&](int j) {
-      j = min(j, j1 - 1);
-      const char* base = reinterpret_cast<const char*>(x.v + row_offset(x.km, hbase, j * BKV));
-      const int last = sq.nk - 1 - j * BKV;
-      unsigned off[RPT];
+    for (int i = 0; i < CPL / 8; ++i) rk[i] = *reinterpret_cast<const uint4*>(base + KSTEP * i + off);
+  };
+  auto quant_k = [&](int j, int cur) {
+    // smooth, group maximum over the wavefront's 16 keys, codes and scale (k_quant_k's arithmetic)
+    float xk[CPL];
+    float mx = 0.0f;
+    if constexpr (D == 256) quad_exchange(rk);
 #pragma unroll
-      for (int i = 0; i < RPT; ++i) off[i] = voff + (unsigned)i * rowb;
-      if (last < BKV - 1) {
+    for (int i = 0; i < CPL / 8; ++i) {
+      unpack8<BF16>(rk[i], &xk[8 * i]);
+      const float4 m0 = *reinterpret_cast<const float4*>(&s_km[c0 + 8 * i]);
+      const float4 m1 = *reinterpret_cast<const float4*>(&s_km[c0 + 8 * i + 4]);
+      const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) off[i] -= (unsigned)max(vr + i - last, 0) * rowb;
+      for (int e = 0; e < 8; ++e) xk[8 * i + e] = __fsub_rn(xk[8 * i + e], mean[e]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_k(j + 1);                    // (the registers are free; in flight under the rest of this block's work)
+    if (j * BKV + BKV > sq.nk && j * BKV + kr >= sq.nk) {        // padded keys: codes 0, Delta-S 0
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) xk[e] = 0.0f;
+    }
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(xk[e]));
+    const float delta = __fdiv_rn(wave_max(mx), (float)QMAX);
+    if (lane == 0) s_ks[cur][w] = delta;
+    const CodeScale qs = code_scale(delta);
+    uint8_t* img = reinterpret_cast<uint8_t*>(&s_k[cur][0]);
+    if constexpr (INT4) {
+      // Delta-S: q_bar_g . gamma(K)_t in float64, four heads at a time by v_mfma_f64_4x4x4_4b_f64: four independent
+      // 4 x 4 products per instruction, lane l supplies A[l % 4][l / 16] and B[l / 16][l % 4] of product (l / 4) % 4 and
+      // receives D[l / 16][l % 4].  Product i holds keys 16 w + 4 i + 0..3, contraction slot (step cs, l / 16) channel
+      // CPL (l / 16) + cs: the lane's own registers, in order.  (The 16-row form of the
+      // general path spends 2048 matrix cycles per block on rows that a few heads leave empty; this one 512 per 4 heads.)
+      // One chain of accumulations, in the general path's order: with two, which are a little shorter, a Delta-S that
+      // lies next to the middle of two FP32 values could round to the other one (decode of 32768 keys: 249 us either way).
+      const double kap = (double)p.kappa;
+      const double* qa = &s_qm[((lane & 3) * 4 + kk) * QMS];
+      // The means come out of LDS a chunk of channels ahead of their use: read one by one, each product waited for its own
+      // (32768 keys, 4-bit mode 145 us, 139); the two chains of five to eight heads run side by side.
+      constexpr int NCH = HEADS / 4, CH = (D == 256 ? 4 : 8) / NCH;
+      double acc[NCH], qv[2][NCH][CH];
+      auto means = [&](int c, int b) {
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+#pragma unroll
+          for (int e = 0; e < CH; ++e) qv[b][i][e] = qa[16 * i * QMS + c + e];
+        }
+      };
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) acc[i] = 0.0;
+      means(0, 0);
+#pragma unroll
+      for (int cs = 0; cs < CPL; cs += CH) {
+        if (cs + CH < CPL) means(cs + CH, (cs / CH + 1) & 1);
+        asm volatile("" ::: "memory");                 // (not all of them at once)
+#pragma unroll
+        for (int e = 0; e < CH; ++e) {
+          asm volatile("" : "+v"(xk[cs + e]));         // (widened as it is used)
+          const double xd = (double)xk[cs + e];
+#pragma unroll
+          for (int i = 0; i < NCH; ++i) acc[i] = __builtin_amdgcn_mfma_f64_4x4x4f64(qv[(cs / CH) & 1][i][e], xd, acc[i], 0, 0, 0);
+        }
       }
 #pragma unroll
-      for (int i = 0; i < RPT; ++i) rv[i] = nt_load16(reinterpret_cast<const unsigned short*>(base + off[i]));
-    };
+      for (int i = 0; i < NCH; ++i) s_ds[cur][4 * i + kk][kr] = (float)(kap * acc[i]);
+      constexpr int NPL = CPL > 32 ? CPL / 32 : 1, CPP = CPL / NPL;
+#pragma unroll
+      for (int pl = 0; pl < NPL; ++pl) {
+        Codes32 cd;
+        if constexpr (CPP < 32) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) { cd.ev[e] = 0.0f; cd.od[e] = 0.0f; }
+        }
+        code_group<CPP, QMAX>(xk + CPP * pl, delta, qs, [&](int e, float c) { cd.set(e, c); });
+        const v6u pw = cd.pack();
+        int lane_m, e0;
+        const size_t op = k_op6(kr, c0 + CPP * pl, D, &lane_m, &e0);
+        const int d0 = (6 * e0) >> 5;
+#pragma unroll
+        for (int i = 0; i < CPP * 6 / 32; ++i)
+          *reinterpret_cast<unsigned*>(img + op + op6_byte(lane_m, 4 * (d0 + i))) = pw[i];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < CPL / 16; ++i) {
+        unsigned c[16];
+        code_group_bytes<16, QMAX>(xk + 16 * i, delta, qs, c);
+        *reinterpret_cast<uint4*>(img + k_code_off(kr, c0 + 16 * i, D)) = pack16(c);
+      }
+    }
+  };
+  // V: codes of four consecutive keys of a channel side by side, NH such runs per thread
+  constexpr int HR = 4, NH = RPT / HR;
+  const int tv = t - 256, cg = tv % NCG, vr = HR * (tv / NCG);
+  const unsigned voff = (unsigned)vr * rowb + 16 * cg;
+  uint4 rv[NH][HR];
+  bool v_fast = true;
+  auto fetch_v = [&](int j, uint4 (&rows)[HR], int hh) {
+    j = min(j, j1 - 1);
+    const char* base = reinterpret_cast<const char*>(x.v + row_offset(x.km, hbase, j * BKV));
+    const int last = sq.nk - 1 - j * BKV, r0 = HR * NRG * hh;
+    unsigned off[HR], vo = voff;
+    asm volatile("" : "+v"(vo));         // (added up for every block: kept, the offsets cost a register each)
+#pragma unroll
+    for (int i = 0; i < HR; ++i) off[i] = vo + (unsigned)(r0 + i) * rowb;
+    if (last < BKV - 1) {
+#pragma unroll
+      for (int i = 0; i < HR; ++i) off[i] -= (unsigned)max(vr + r0 + i - last, 0) * rowb;
+    }
+#pragma unroll
+    for (int i = 0; i < HR; ++i) rows[i] = nt_load16(reinterpret_cast<const unsigned short*>(base + off[i]));
+  };
+  // Channel c's 16-byte chunks are XOR-ed in their place by (c / 16) % 8, so that the 16 channel groups of a store meet 16
+  // different bank groups; the thread's eight channels are eight neighbouring chunks, XOR-ed alike
+  static_assert(NH == 1 || HR * NRG == 32 || HR * NRG == 16, "a further run of keys is 16 or 32 keys on: 32 or 64 chunks");
+  const unsigned vdst = (unsigned)v_code_off(vr, 8 * cg, D) ^ (unsigned)(((cg >> 1) & 7) * 16);
+  auto quant_v = [&](int j, int cur) {
+    uint8_t* img = reinterpret_cast<uint8_t*>(&s_v[cur][0]);
+    unsigned vd = vdst;
+    asm volatile("" : "+v"(vd));
+    float vs[8], vi[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { vs[e] = s_vs[8 * cg + e]; vi[e] = s_vi[8 * cg + e]; }
+#pragma unroll
+    for (int hh = 0; hh < NH; ++hh) {
+      float xv[HR][8];
+#pragma unroll
+      for (int i = 0; i < HR; ++i) unpack8<BF16>(rv[hh][i], xv[i]);
+      // (unpacked here and not in the two branches below: the rows' registers would not be free for the next block's, and a
+      // copy at the end of the block would wait for those)
+#pragma unroll
+      for (int i = 0; i < HR; ++i) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(xv[i][e]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      fetch_v(j + 1, rv[hh], hh);
+      if (v_fast) {
+#pragma unroll
+        for (int i = 0; i < HR; ++i) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) xv[i][e] = div_by(xv[i][e], vs[e], vi[e]);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < HR; ++i) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            xv[i][e] = vs[e] > 0.0f ? __fdiv_rn(xv[i][e], vs[e]) : 0.0f;
+            asm volatile("" : "+v"(xv[i][e]) :: "memory");     // (one division at a time)
+          }
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const unsigned off = (vd ^ (16u * e)) + 32u * HR * NRG * hh;
+        // (the first conversion of the word keeps the other half of any register: one that is free afterwards)
+        int wd = __builtin_amdgcn_cvt_pk_fp8_f32(xv[0][e], xv[1][e], __float_as_int(xv[0][e]), false);
+        wd = __builtin_amdgcn_cvt_pk_fp8_f32(xv[2][e], xv[3][e], wd, true);
+        *reinterpret_cast<int*>(img + off) = wd;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // (one barrier per block: block j is in LDS, and the other wavefronts are done with block j - 1)
+  if (k_wave) {
     fetch_k(j0);
-    fetch_v(j0);
-    bool v_fast = true;
+    for (int j = j0, cur = 0; j < j1; ++j, cur ^= 1) { quant_k(j, cur); __syncthreads(); }
+    return;
+  }
+  if (v_wave) {
+#pragma unroll
+    for (int hh = 0; hh < NH; ++hh) fetch_v(j0, rv[hh], hh);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v_fast = v_fast && (s_vi[8 * cg + e] != 0.0f || s_vs[8 * cg + e] == 0.0f);   // (an all-zero channel: 0 * 0 = 0 either way)
-    for (int j = j0, cur = 0; j < j1; ++j, cur ^= 1) {
-      // ---- K: smooth, group maximum over the wavefront's 16 keys, codes and scale (k_quant_k's arithmetic)
-      {
-        float xk[CPL];
-        float mx = 0.0f;
-        if constexpr (D == 256) quad_exchange(rk);
-#pragma unroll
-        for (int i = 0; i < CPL / 8; ++i) {
-          unpack8<BF16>(rk[i], &xk[8 * i]);
-          const float4 m0 = *reinterpret_cast<const float4*>(&s_km[c0 + 8 * i]);
-          const float4 m1 = *reinterpret_cast<const float4*>(&s_km[c0 + 8 * i + 4]);
-          const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
-#pragma unroll
-          for (int e = 0; e < 8; ++e) xk[8 * i + e] = __fsub_rn(xk[8 * i + e], mean[e]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_k(j + 1);                    // (the registers are free; in flight under the rest of this block's work)
-        if (j * BKV + BKV > sq.nk && j * BKV + kr >= sq.nk) {        // padded keys: codes 0, Delta-S 0
-#pragma unroll
-          for (int e = 0; e < CPL; ++e) xk[e] = 0.0f;
-        }
-#pragma unroll
-        for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(xk[e]));
-        const float delta = __fdiv_rn(wave_max(mx), (float)QMAX);
-        if (lane == 0) s_ks[cur][w] = delta;
-        const CodeScale qs = code_scale(delta);
-        uint8_t* img = reinterpret_cast<uint8_t*>(&s_k[cur][0]);
-        if constexpr (INT4) {
-          // Delta-S: q_bar_g . gamma(K)_t in float64, four heads at a time by v_mfma_f64_4x4x4_4b_f64: four independent
-          // 4 x 4 products per instruction, lane l supplies A[l % 4][l / 16] and B[l / 16][l % 4] of product (l / 4) % 4 and
-          // receives D[l / 16][l % 4].  Product i holds keys 16 w + 4 i + 0..3, contraction slot (step cs, l / 16) channel
-          // CPL (l / 16) + cs: the lane's own registers, in order.  (The 16-row form of the
-          // general path spends 2048 matrix cycles per block on rows that a few heads leave empty; this one 512 per 4 heads.)
-          // One chain of accumulations, in the general path's order: with two, which are a little shorter, a Delta-S that
-          // lies next to the middle of two FP32 values could round to the other one (decode of 32768 keys: 249 us either way).
-          const double kap = (double)p.kappa;
-          const double* qa = &s_qm[((lane & 3) * 4 + kk) * QMS];
-          // The means come out of LDS a chunk of channels ahead of their use: read one by one, each product waited for its own
-          // (32768 keys, 4-bit mode 145 us, now NNN); the two chains of five to eight heads run side by side.
-          constexpr int NCH = HEADS / 4, CH = (D == 256 ? 4 : 8) / NCH;
-          double acc[NCH], qv[2][NCH][CH];
-          auto means = [&](int c, int b) {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-#pragma unroll
-              for (int e = 0; e < CH; ++e) qv[b][i][e] = qa[16 * i * QMS + c + e];
-            }
-          };
-#pragma unroll
-          for (int i = 0; i < NCH; ++i) acc[i] = 0.0;
-          means(0, 0);
-#pragma unroll
-          for (int cs = 0; cs < CPL; cs += CH) {
-            if (cs + CH < CPL) means(cs + CH, (cs / CH + 1) & 1);
-            asm volatile("" ::: "memory");                 // (not all of them at once)
-#pragma unroll
-            for (int e = 0; e < CH; ++e) {
-              asm volatile("" : "+v"(xk[cs + e]));         // (widened as it is used)
-              const double xd = (double)xk[cs + e];
-#pragma unroll
-              for (int i = 0; i < NCH; ++i) acc[i] = __builtin_amdgcn_mfma_f64_4x4x4f64(qv[(cs / CH) & 1][i][e], xd, acc[i], 0, 0, 0);
-            }
-          }
-#pragma unroll
-          for (int i = 0; i < NCH; ++i) s_ds[cur][4 * i + kk][kr] = (float)(kap * acc[i]);
-          constexpr int NPL = CPL > 32 ? CPL / 32 : 1, CPP = CPL / NPL;
-#pragma unroll
-          for (int pl = 0; pl < NPL; ++pl) {
-            Codes32 cd;
-            if constexpr (CPP < 32) {
-#pragma unroll
-              for (int e = 0; e < 16; ++e) { cd.ev[e] = 0.0f; cd.od[e] = 0.0f; }
-            }
-            code_group<CPP, QMAX>(xk + CPP * pl, delta, qs, [&](int e, float c) { cd.set(e, c); });
-            const v6u pw = cd.pack();
-            int lane_m, e0;
-            const size_t op = k_op6(kr, c0 + CPP * pl, D, &lane_m, &e0);
-            const int d0 = (6 * e0) >> 5;
-#pragma unroll
-            for (int i = 0; i < CPP * 6 / 32; ++i)
-              *reinterpret_cast<unsigned*>(img + op + op6_byte(lane_m, 4 * (d0 + i))) = pw[i];
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < CPL / 16; ++i) {
-            unsigned c[16];
-            code_group_bytes<16, QMAX>(xk + 16 * i, delta, qs, c);
-            *reinterpret_cast<uint4*>(img + k_code_off(kr, c0 + 16 * i, D)) = pack16(c);
-          }
-        }
-      }
-      // ---- V: codes of RPT consecutive keys of a channel side by side.  Channel c's 16-byte chunks are XOR-ed in their
-      // place by (c / 16) % 8, so that the 16 channel groups of a store meet 16 different bank groups
-      {
-        uint8_t* img = reinterpret_cast<uint8_t*>(&s_v[cur][0]);
-        float xv[RPT][8], vs[8], vi[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { vs[e] = s_vs[8 * cg + e]; vi[e] = s_vi[8 * cg + e]; }
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) unpack8<BF16>(rv[i], xv[i]);
-        // (unpacked here and not in the two branches below: the rows' registers would not be free for the next block's, and a
-        // copy at the end of the block would wait for those)
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(xv[i][e]));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_v(j + 1);
-        if (v_fast) {
-#pragma unroll
-          for (int i = 0; i < RPT; ++i) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) xv[i][e] = div_by(xv[i][e], vs[e], vi[e]);
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < RPT; ++i) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) xv[i][e] = vs[e] > 0.0f ? __fdiv_rn(xv[i][e], vs[e]) : 0.0f;
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int c = 8 * cg + e;
-          const size_t off = v_code_off(vr, c, D) ^ (size_t)(((c >> 4) & 7) * 16);
-          int wd[(RPT + 3) / 4];
-#pragma unroll
-          for (int i = 0; i < RPT; i += 2) {
-            // (the first conversion of a word keeps the other half of any register: one that is free afterwards)
-            if ((i & 2) == 0) wd[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(xv[i][e], xv[i + 1][e], __float_as_int(xv[i][e]), false);
-            else wd[i / 4] = __builtin_amdgcn_cvt_pk_fp8_f32(xv[i][e], xv[i + 1][e], wd[i / 4], true);
-          }
-          if constexpr (RPT == 2) *reinterpret_cast<unsigned short*>(img + off) = (unsigned short)wd[0];
-          else if constexpr (RPT == 4) *reinterpret_cast<int*>(img + off) = wd[0];
-          else *reinterpret_cast<int2*>(img + off) = make_int2(wd[0], wd[RPT / 4 - 1]);
-        }
-      }
-      __syncthreads();                     // block j is in LDS; the other wavefronts are done with block j - 1
-    }
+    for (int j = j0, cur = 0; j < j1; ++j, cur ^= 1) { quant_v(j, cur); __syncthreads(); }
     return;
   }
 
-  // ---- the wavefront's Q^ operands: all four hold the same 32 columns and quantize them themselves (a separate launch for so
+  // ---- the wavefront's Q^ operands: both hold the same 32 columns and quantize them themselves (a separate launch for so
   // few rows costs 7 us: 16 x 8 KV heads, 5003 keys, 8-bit mode 85 / 79 us, 4 x 8, 32768 keys, 4-bit 263 / 243; 16 of 256 channels,
   // 30000 keys, 4-bit 238 / 231).  Lane (n, half)
   // supplies, of its column's query, PC consecutive channels per operand: smoothed
@@ -416,37 +428,38 @@ __global__ void __launch_bounds__(raw_threads<D>(), D == 256 ? 2 : 3) k_attn_raw
     float alpha;
     auto attend = [&](auto masked_) {
       constexpr bool MASKED = decltype(masked_)::value;
-      typename KBlockRegs<D, INT4>::type ka;
-      read_k_block<D, INT4>(&s_k[cur][0], lane, ka);
       KeyScales<0> ks;
       ks.s[0] = s_ks[cur][half];
       ks.s[1] = s_ks[cur][2 + half];
+      Factors<0> fac;
+      fac.set(dq, p.kappa, ks);
+      const int key0 = j * BKV, last = query + sq.coff;
       v16i raw[2], sc[2];
-      qk_tile<D, INT4>(ka, qreg, raw);
-      asm volatile("" ::: "memory");     // Delta-S is read after the operands of the product, into registers they leave
-      if constexpr (INT4) {
+      // one key tile after the other, so that one tile's operands and raw scores are live at a time
+      auto key_tile = [&](auto kt_) {
+        constexpr int KT = decltype(kt_)::value;
+        typename KBlockRegs<D, INT4>::type ka;
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-          const v4f* dsv = reinterpret_cast<const v4f*>(&s_ds[cur][hq][32 * kt + 16 * half]);
+        for (int sp = 0; sp < NP; ++sp) ka[2 * sp + KT] = load_qk_operand<INT4>(&s_k[cur][0], 2 * sp + KT, lane);
+        qk_key_tile<D, INT4, KT>(ka, qreg, raw);
+        asm volatile("" ::: "memory");     // Delta-S is read after the operands of the product, into registers they leave
+        if constexpr (INT4) {
+          const v4f* dsv = reinterpret_cast<const v4f*>(&s_ds[cur][hq][32 * KT + 16 * half]);
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
             const v4f t4 = dsv[g];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) sc[kt][4 * g + r] = __float_as_int(t4[r]);
+            for (int r = 0; r < 4; ++r) sc[KT][4 * g + r] = __float_as_int(t4[r]);
           }
         }
-      }
-      Factors<0> fac;
-      fac.set(dq, p.kappa, ks);
-      const int key0 = j * BKV, last = query + sq.coff;
-      dequant_group<INT4, CAUSAL, MASKED, 0, 0, 0>(raw, sc, fac, half, key0, last, n_keys_end);
-      dequant_group<INT4, CAUSAL, MASKED, 0, 0, 1>(raw, sc, fac, half, key0, last, n_keys_end);
-      dequant_group<INT4, CAUSAL, MASKED, 0, 0, 2>(raw, sc, fac, half, key0, last, n_keys_end);
-      dequant_group<INT4, CAUSAL, MASKED, 0, 0, 3>(raw, sc, fac, half, key0, last, n_keys_end);
-      dequant_group<INT4, CAUSAL, MASKED, 0, 1, 0>(raw, sc, fac, half, key0, last, n_keys_end);
-      dequant_group<INT4, CAUSAL, MASKED, 0, 1, 1>(raw, sc, fac, half, key0, last, n_keys_end);
-      dequant_group<INT4, CAUSAL, MASKED, 0, 1, 2>(raw, sc, fac, half, key0, last, n_keys_end);
-      dequant_group<INT4, CAUSAL, MASKED, 0, 1, 3>(raw, sc, fac, half, key0, last, n_keys_end);
+        dequant_group<INT4, CAUSAL, MASKED, 0, KT, 0>(raw, sc, fac, half, key0, last, n_keys_end);
+        dequant_group<INT4, CAUSAL, MASKED, 0, KT, 1>(raw, sc, fac, half, key0, last, n_keys_end);
+        dequant_group<INT4, CAUSAL, MASKED, 0, KT, 2>(raw, sc, fac, half, key0, last, n_keys_end);
+        dequant_group<INT4, CAUSAL, MASKED, 0, KT, 3>(raw, sc, fac, half, key0, last, n_keys_end);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      key_tile(std::integral_constant<int, 0>{});
+      key_tile(std::integral_constant<int, 1>{});
       alpha = update_max<DW, INT4, 0, PV_E4M3>(st, sc, fac, m_sub);
       float ls = 0.0f;
       exp_group<INT4, MASKED, 0, PV_E4M3, 0, 0>(sc, fac, m_sub, pb, ls);
@@ -468,7 +481,8 @@ __global__ void __launch_bounds__(raw_threads<D>(), D == 256 ? 2 : 3) k_attn_raw
       va[i] = s_v[cur][(ct * 2 + (i & 1)) * 64 + (lane ^ ((2 * ct + (n >> 4)) & 7))];
     }
     pv_step<DW, 0, PV_E4M3>(st, va, pb);
-    if constexpr (CTW > 1) pv_step<DW, CTW - 1, PV_E4M3>(st, va, pb);
+    if constexpr (CTW > 1) pv_step<DW, (CTW > 1 ? 1 : 0), PV_E4M3>(st, va, pb);
+    if constexpr (CTW > 2) { pv_step<DW, (CTW > 2 ? 2 : 0), PV_E4M3>(st, va, pb); pv_step<DW, (CTW > 2 ? 3 : 0), PV_E4M3>(st, va, pb); }
   }
   if (!col_ok) return;
 
@@ -562,8 +576,8 @@ static hipError_t launch_raw_t(const Dims& D, const Ptrs& P, hipStream_t s) {
   const bool many = INT4 && D.H / D.Hkv > 4;
 #define SAGE_RAW_LAUNCH(BF) \
   do { \
-    if (many) k_attn_raw<DD, INT4, CAUSAL, BF, INT4 ? PACK_G : 4><<<grid, raw_threads<DD>(), 0, s>>>(p, x); \
-    else k_attn_raw<DD, INT4, CAUSAL, BF, 4><<<grid, raw_threads<DD>(), 0, s>>>(p, x); \
+    if (many) k_attn_raw<DD, INT4, CAUSAL, BF, INT4 ? PACK_G : 4><<<grid, RAW_THREADS, 0, s>>>(p, x); \
+    else k_attn_raw<DD, INT4, CAUSAL, BF, 4><<<grid, RAW_THREADS, 0, s>>>(p, x); \
   } while (0)
   if (D.bf16) SAGE_RAW_LAUNCH(true); else SAGE_RAW_LAUNCH(false);
 #undef SAGE_RAW_LAUNCH

@@ -147,7 +147,11 @@ __device__ __forceinline__ void code_group(const float* x, float delta, const Co
     for (int e = 0; e < NE; ++e) put(e, rintf(div_by(x[e], delta, qs.r)));
   } else {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) put(e, (float)quant_code(x[e], delta, QMAX));
+    for (int e = 0; e < NE; ++e) {
+      float c = (float)quant_code(x[e], delta, QMAX);
+      asm volatile("" : "+v"(c) :: "memory");          // (one division at a time: together they want more registers than the loop has)
+      put(e, c);
+    }
   }
 }
 // ... in the low bytes of c[0..NE) (adding 1.5 * 2^23 rounds to the nearest integer, ties to even, and leaves it in the low
@@ -159,7 +163,10 @@ __device__ __forceinline__ void code_group_bytes(const float* x, float delta, co
     for (int e = 0; e < NE; ++e) c[e] = __float_as_uint(div_by(x[e], delta, qs.r) + 12582912.0f);
   } else {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) c[e] = (unsigned)quant_code(x[e], delta, QMAX);
+    for (int e = 0; e < NE; ++e) {
+      c[e] = (unsigned)quant_code(x[e], delta, QMAX);
+      asm volatile("" : "+v"(c[e]) :: "memory");
+    }
   }
 }
 // the low bytes of sixteen words side by side
