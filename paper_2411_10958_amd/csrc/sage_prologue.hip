@@ -730,7 +730,7 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   const int i0 = causal ? min(max(n0 - coff, 0) / BQ, nQs) : 0;
   const int nr = nQs - i0, nrow = INT4 ? G * nr : 0;
   const int bh0 = (int)bhkv * G;
-  const float inv_nr = 1.0f / (float)max(nr, 1);
+  const float inv_nr = __builtin_amdgcn_rcpf((float)max(nr, 1));
   // A step's rows: nr >= 16 leaves room for one change of head, `cut` rows of the current one and then the next one's;
   // shorter heads are told apart by a division per row.
   struct Step { int R, base, next, cut; };         // first row, its place in the [B H][nQb] arrays, that of the next head's first row, cut
@@ -805,7 +805,12 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
       }
     }
   };
-  // the first step's block means are requested before the K rows so that both round trips overlap
+  // the K rows are requested first, then the first step's block means, so that the round trips overlap
+  const size_t hbase = hp.base + sq.k0 * (size_t)km.sn;
+  const unsigned short* krow = K + row_offset(km, hbase, min(n0 + r, N - 1)) + c0;
+  uint4 kraw[CPL / 8];
+#pragma unroll
+  for (int p = 0; p < CPL / 8; ++p) kraw[p] = *reinterpret_cast<const uint4*>(krow + 8 * p);
   Step step = step_at(0, 0, i0);
   if constexpr (INT4) load_q(step);
 
@@ -825,12 +830,10 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
 
   float x[CPL];
   float mx = 0.0f;
-  const size_t hbase = hp.base + sq.k0 * (size_t)km.sn;
-  const unsigned short* krow = K + row_offset(km, hbase, min(n0 + r, N - 1)) + c0;
 #pragma unroll
   for (int p = 0; p < CPL / 8; ++p) {
     float x8[8];
-    load8<BF16, false>(krow + 8 * p, x8);
+    unpack8<BF16>(kraw[p], x8);
     const float4 m0 = mean4(c0 + 8 * p), m1 = mean4(c0 + 8 * p + 4);
     const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
 #pragma unroll
