@@ -553,14 +553,20 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
 // Calls the kernel above serves: the 32 columns of a tile hold all queries that meet a KV head (beyond 32 the softmax piece
 // would be repeated for columns that another wavefront holds on the general path), with the default groups, data types
 // and smoothing; in the 4-bit mode Delta-S in float64 (the library's own choice for so few block means).  A workgroup works
-// through its chunk block by block, about 2 us each, where the general path spreads the quantizers over the chip: with few
-// workgroups that serial chain is longer than the launches it saves.  Whole calls of 96 to 104 workgroups, 1 to 8 heads per KV
-// head, both modes, general path / this one: 64 channels 1.06 to 1.64, 128 1.09 to 1.71, 256 1.12 to 1.91 (one block per chunk
-// gains most).  64 workgroups: 1.02 to 1.36, so the line is on the safe side.  Larger: 16 x 8 KV heads, 5003 keys, statistics
-// supplied, 8-bit 131 us / 79; 4 x 8, 32768 keys 357 / 243; 16 of 256 channels, 30000 keys 383 / 231.
+// through its chunk block by block, 0.7 to 2.8 us each, where the general path spreads the quantizers over the chip: with few
+// workgroups and long chunks that serial chain is longer than the launches it saves.  Whole calls, general path / this one, 64
+// to 104 workgroups: 1.02 to 1.91 at any length (64, chunks of 128 blocks: 1.02 to 1.21).  4 workgroups, one chunk each: of 12
+// blocks 1.00 (256 channels, 4-bit) to 1.30, of 20 0.86 (256, 4-bit), 1.00 (128) and 1.11 (64), in the 8-bit mode 1.02, 1.16, 1.19; of
+// 32 0.78, 0.87, 0.97 and 0.92, 1.06, 1.07.  With five to eight heads in a group, 4-bit: one workgroup of 8 blocks of 256 channels 0.94, 4
+// of 12 of 128 channels 1.06, of 20 0.90.  16 workgroups: chunks of 20 blocks of 256 channels 0.97 (4-bit) and 1.16, of 32 of 128 0.96 and
+// 1.14, of 32 of 64 1.06 and 1.12.  Automatic chunks are of 8 to 15 blocks until there are 512 workgroups or 64 chunks.
 bool attention_raw_ok(const Dims& D) {
   const int G = D.H / D.Hkv;
-  return G <= PACK_G && (long long)G * D.N <= 32 && (long long)D.B * D.Hkv * D.splits >= 96 && D.kg == KGROUP && !D.block_groups && D.pvf == PV_E4M3 &&
+  const long long groups = (long long)D.B * D.Hkv * D.splits;
+  const int chunk = (D.nKb + D.splits - 1) / D.splits;
+  int longest = D.int4 ? (G <= 4 ? 4 : 0) + 1024 / D.d : 8 + 1536 / D.d;
+  if (groups >= 16) longest += longest / 2;
+  return G <= PACK_G && (long long)G * D.N <= 32 && (groups >= 64 || chunk <= longest) && D.kg == KGROUP && !D.block_groups && D.pvf == PV_E4M3 &&
          D.smooth_k && D.smooth_q && !D.smooth_v && (!D.int4 || D.ds_mode == 2);
 }
 
