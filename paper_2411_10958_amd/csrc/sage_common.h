@@ -98,7 +98,7 @@ inline dim3 block_grid(const TensorMap& m, int pieces, int heads) {
 inline TensorMap make_tensor_map(int nhd, int heads, int tokens, int d, bool varlen = false) {
   TensorMap m;
   m.heads = heads;
-  m.heads_inner = (nhd || varlen) && heads * d >= 4096 && tokens <= 65535 * 64;   // (y of a grid is 16 bits; pieces have 64 tokens or more)
+  m.heads_inner = (nhd || varlen) && heads * d >= 4096 && tokens <= 65535 * 32;   // (y of a grid is 16 bits; pieces have 64 tokens or more, K and V side by side two for 64)
   if (varlen) { m.sb = 0; m.sh = d; m.sn = (long long)heads * d; return m; }   // packed [tokens, heads, d]
   if (nhd) { m.sb = (long long)tokens * heads * d; m.sh = d; m.sn = (long long)heads * d; }
   else     { m.sb = (long long)heads * tokens * d; m.sh = (long long)tokens * d; m.sn = d; }

@@ -20,15 +20,19 @@ constexpr int STAT_UNROLL = 4; // rows per thread in flight
 
 // With the smooth-V option the first pass takes the exact token sums of V instead of max|V| (the
 // maximum must be taken of the centred values, which needs the mean first: k_v_absmax below).
+// (The bodies of the preprocessing kernels take their LDS from the kernel: one that runs two of them side by side overlays it.)
+template <int D, bool SMOOTH_V> struct StatsLds {
+  static constexpr int NRG = 256 / (D / 8);
+  double sum[NRG][D], vsum[SMOOTH_V ? NRG : 1][D];
+  float max[SMOOTH_V ? 1 : NRG][D];
+};
 template <bool BF16, int D, bool SMOOTH_V>
-__device__ __forceinline__ void col_stats_block(const BlockPos bp, const unsigned short* __restrict__ K,
+__device__ __forceinline__ void col_stats_block(StatsLds<D, SMOOTH_V>& lds, const BlockPos bp, const unsigned short* __restrict__ K,
                                                 const unsigned short* __restrict__ V, double* __restrict__ k_sum,
                                                 double* __restrict__ v_sum, unsigned* __restrict__ v_max, int Nq, int N,
                                                 const TensorMap& km, const SeqMap& sm) {
   constexpr int NCG = D / 8, NRG = 256 / NCG;
-  __shared__ double s_sum[NRG][D];
-  __shared__ double s_vsum[SMOOTH_V ? NRG : 1][D];
-  __shared__ float s_max[SMOOTH_V ? 1 : NRG][D];
+  auto& s_sum = lds.sum; auto& s_vsum = lds.vsum; auto& s_max = lds.max;
   const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
   const HeadPos hp = head_pos(km, bp.y);
   const Seq sq = seq_of(sm, hp.b, Nq, N);
@@ -92,7 +96,8 @@ __global__ void __launch_bounds__(256) k_col_stats(const unsigned short* __restr
                                                    double* __restrict__ k_sum, double* __restrict__ v_sum,
                                                    unsigned* __restrict__ v_max, int Nq, int N, TensorMap km,
                                                    SeqMap sm) {
-  col_stats_block<BF16, D, SMOOTH_V>(block_pos(km), K, V, k_sum, v_sum, v_max, Nq, N, km, sm);
+  __shared__ StatsLds<D, SMOOTH_V> lds;
+  col_stats_block<BF16, D, SMOOTH_V>(lds, block_pos(km), K, V, k_sum, v_sum, v_max, Nq, N, km, sm);
 }
 
 // Smooth-V option, second pass over V: per-channel max |fl32(V - mean(V))|.
@@ -364,8 +369,12 @@ struct QuantQ {
 // Q, 8-bit variant: pair-group quantization psi_Q(Q_i), no smoothing (the 8-bit kernel of the
 // paper's "two kernel implementations" leaves Q as it is).  One workgroup per 128 queries of one
 // (batch, head).
+template <int D, bool INT4> struct QuantQLds {               // (8-bit mode)
+  uint4 codes[BQ * D / 16];
+  float bmax[4];
+};
 template <bool BF16, int D>
-__device__ __forceinline__ void quant_q8_block(const BlockPos bp, const QuantQ& a) {
+__device__ __forceinline__ void quant_q8_block(QuantQLds<D, false>& lds, const BlockPos bp, const QuantQ& a) {
   SAGE_QUANT_Q_ARGS;
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BQ / NRG;  // RPT rows per thread (8 or 4)
   constexpr int QMAX = 127;
@@ -393,8 +402,7 @@ __device__ __forceinline__ void quant_q8_block(const BlockPos bp, const QuantQ& 
                                          k_mean + kv_head(qm, bp.y, G) * D + cg * 8, kappa, cg);
   // codes go to LDS in the packed order of this 128-query slab (contiguous in the workspace) and
   // leave as coalesced 16-byte stores
-  __shared__ uint4 s_codes[BQ * D / 16];
-  __shared__ float s_bmax[4];
+  auto& s_codes = lds.codes; auto& s_bmax = lds.bmax;
   uint8_t* img = reinterpret_cast<uint8_t*>(s_codes);
   float block_max = 0.0f;
   if (block_groups) {       // per-block granularity: one scale for the whole 128-query block
@@ -453,8 +461,15 @@ __device__ __forceinline__ void quant_q8_block(const BlockPos bp, const QuantQ& 
 // LDS: the raw rows (32 KB at d = 128), which the packed code image takes over once every thread holds its values in
 // registers, and one row of column sums per wavefront (the row groups of a wavefront are summed by lane exchanges
 // first) - 37 KB, so that four workgroups share a CU and their loads, arithmetic and stores overlap.
+template <int D> struct QuantQLds<D, true> {
+  uint4 raw[BQ * (D / 8)];           // the raw rows; later the packed code image of the slab
+  double sum[4][D];                  // column sums, one row per wavefront
+  alignas(16) float mean[D];
+  alignas(16) float kbar[D];         // mean(K) of the KV head (log-sum-exp output only)
+  float bmax[4];
+};
 template <bool BF16, int D>
-__device__ __forceinline__ void quant_q4_block(const BlockPos bp, const QuantQ& a) {
+__device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const BlockPos bp, const QuantQ& a) {
   SAGE_QUANT_Q_ARGS;
   float *__restrict__ q_mean = a.q_mean, *__restrict__ q_dscale = a.q_dscale;
   unsigned char* __restrict__ q_digits = a.q_digits;
@@ -463,12 +478,8 @@ __device__ __forceinline__ void quant_q4_block(const BlockPos bp, const QuantQ& 
   constexpr int CPL = D / 4, CPC = CPL / 8;                      // quantization map: 2 rows x CPL channels
   constexpr int QMAX = 7;
   constexpr int SLAB = (int)q_slab_bytes(D, true);
-  __shared__ uint4 s_raw[BQ * NCG];           // the raw rows; later the packed code image of the slab
+  auto& s_raw = lds.raw; auto& s_sum = lds.sum; auto& s_mean = lds.mean; auto& s_kbar = lds.kbar; auto& s_bmax = lds.bmax;
   static_assert(SLAB <= (int)sizeof(uint4) * BQ * NCG, "the code image fits where the raw rows were");
-  __shared__ double s_sum[4][D];              // column sums, one row per wavefront
-  __shared__ __align__(16) float s_mean[D];
-  __shared__ __align__(16) float s_kbar[D];   // mean(K) of the KV head (log-sum-exp output only)
-  __shared__ float s_bmax[4];
   const int t = threadIdx.x;
   const int qb = bp.x;
   const size_t bh = bp.y;
@@ -608,14 +619,18 @@ __device__ __forceinline__ void quant_q4_block(const BlockPos bp, const QuantQ& 
 }
 
 template <bool BF16, bool INT4, int D>
-__device__ __forceinline__ void quant_q_block(const BlockPos bp, const QuantQ& a) {
-  if constexpr (INT4) quant_q4_block<BF16, D>(bp, a); else quant_q8_block<BF16, D>(bp, a);
+__device__ __forceinline__ void quant_q_block(QuantQLds<D, INT4>& lds, const BlockPos bp, const QuantQ& a) {
+  if constexpr (INT4) quant_q4_block<BF16, D>(lds, bp, a); else quant_q8_block<BF16, D>(lds, bp, a);
 }
 template <bool BF16, int D>
-__global__ void __launch_bounds__(256) k_quant_q8(const QuantQ a) { quant_q8_block<BF16, D>(block_pos(a.qm), a); }
+__global__ void __launch_bounds__(256) k_quant_q8(const QuantQ a) {
+  __shared__ QuantQLds<D, false> lds;
+  quant_q8_block<BF16, D>(lds, block_pos(a.qm), a);
+}
 template <bool BF16, int D>
 __global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q4(const QuantQ a) {
-  quant_q4_block<BF16, D>(block_pos(a.qm), a);
+  __shared__ QuantQLds<D, true> lds;
+  quant_q4_block<BF16, D>(lds, block_pos(a.qm), a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -687,8 +702,23 @@ struct QuantKV {
   float code_max;
 };
 
+template <int D, bool INT4, int DSM, bool REDUCE> struct QuantKLds {
+  static constexpr bool DSD = INT4 && DSM == DS_DIGITS;
+  // LDS row of staged block means: channel c sits at column c + 16*(c / 32) when D = 128, so the
+  // 32 lanes of a half-wavefront (16 rows x 2 channel groups) hit 32 different banks (odd stride)
+  static constexpr int SQW = D + (D >= 128 ? 48 : 0) + 1;
+  // DS_DIGITS: a staged row is its DS_ND digit planes of D bytes; 16 bytes of padding make the 16 rows of an operand read
+  // start in 16 different bank groups
+  static constexpr int ROWB = DS_ND * D + 16;
+  uint4 codes[k_block_bytes(D, INT4) / 16];        // the block's packed image
+  float q[INT4 && !DSD ? 2 * DS_ROWS : 1][SQW];
+  alignas(16) unsigned char qd[DSD ? 2 * DS_ROWS : 1][DSD ? ROWB : 16];
+  double qs[DSD ? 2 * DS_ROWS : 1];                // 2^E of the staged rows
+  alignas(16) float kmean[REDUCE ? D : 4];
+  float bmax[4];
+};
 template <bool BF16, bool INT4, int D, int DSM = DS_DIGITS, bool REDUCE = false>
-__device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& a) {
+__device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& lds, const BlockPos bp, const QuantKV& a) {
   const unsigned short* __restrict__ K = a.k;
   float* __restrict__ k_scale = a.k_scale; int8_t* __restrict__ k_codes = a.k_codes;
   const float* __restrict__ q_mean = a.q_mean; float* __restrict__ delta_s = a.delta_s;
@@ -699,17 +729,8 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   constexpr bool DS32 = DSM == DS_FP32, DSD = INT4 && DSM == DS_DIGITS;
   constexpr int CPL = D / 4;                       // channels per lane (32 or 16)
   constexpr int QMAX = INT4 ? 7 : 127;
-  // LDS row of staged block means: channel c sits at column c + 16*(c / 32) when D = 128, so the
-  // 32 lanes of a half-wavefront (16 rows x 2 channel groups) hit 32 different banks (odd stride)
-  constexpr int SQW = D + (D >= 128 ? 48 : 0) + 1;
   constexpr int PADSH = D == 256 ? 6 : 5;          // 16 columns of padding after every 32 (d = 128) / 64 (d = 256) channels
-  __shared__ uint4 s_codes[k_block_bytes(D, INT4) / 16];   // the block's packed image
-  __shared__ float s_q[INT4 && !DSD ? 2 * DS_ROWS : 1][SQW];
-  // DS_DIGITS: a staged row is its DS_ND digit planes of D bytes; 16 bytes of padding make the 16 rows of an operand read
-  // start in 16 different bank groups
-  constexpr int ROWB = DS_ND * D + 16;
-  __shared__ __align__(16) unsigned char s_qd[DSD ? 2 * DS_ROWS : 1][DSD ? ROWB : 16];
-  __shared__ double s_qs[DSD ? 2 * DS_ROWS : 1];   // 2^E of the staged rows
+  auto& s_codes = lds.codes; auto& s_q = lds.q; auto& s_qd = lds.qd; auto& s_qs = lds.qs; auto& s_kmean = lds.kmean; auto& s_bmax = lds.bmax;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int r16 = lane & 15, k4 = lane >> 4;
   const int kb = bp.x;
@@ -815,7 +836,6 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   if constexpr (INT4) load_q(step);
 
   // mean(K) of this head: reduced by the statistics pass, or here
-  __shared__ __align__(16) float s_kmean[REDUCE ? D : 4];
   if constexpr (REDUCE) {
     if (t < D) {
       const float m = a.smooth_k ? (float)(sum_partials(a.k_sum, (size_t)bhkv, a.nchunk, D, t) / (double)N) : 0.0f;
@@ -851,7 +871,6 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
   const float mx_key = mx;                         // this key's largest magnitude (DS_DIGITS: its fixed-point exponent)
   if (kg >= 4) mx = group_max<4>(mx);
   if (kg == 16) mx = butterfly_max<8>(butterfly_max<4>(mx));
-  __shared__ float s_bmax[4];
   if (block_groups) {       // per-block granularity: one scale for the whole 64-key block
     if (lane == 0) s_bmax[w] = mx;
     __syncthreads();
@@ -1056,14 +1075,18 @@ __device__ __forceinline__ void quant_k_block(const BlockPos bp, const QuantKV& 
 // order of the P~V product
 // (Sec. 3.3; Algorithm 1 "Preprocessing": (delta_V, V^) = psi_V(V)).  v_mean is null, or the token
 // mean to subtract first (smooth-V option, SMOOTH_V).
+template <int D, bool REDUCE> struct QuantVLds {
+  uint8_t tile[BKV][D + 16];
+  float vscale[REDUCE ? D : 1];                    // delta_V of this head, reduced here
+};
 template <bool BF16, int D, bool SMOOTH_V, int PVF, bool REDUCE = false>
-__device__ __forceinline__ void quant_v_block(const BlockPos bp, const QuantKV& a) {
+__device__ __forceinline__ void quant_v_block(QuantVLds<D, REDUCE>& lds, const BlockPos bp, const QuantKV& a) {
   const unsigned short* __restrict__ V = a.v;
   const float* __restrict__ v_mean = a.v_mean; uint8_t* __restrict__ v_codes = a.v_codes;
   const int Nq = a.Nq, Nmax = a.Nk, nKb = a.nKb;
   const TensorMap& km = a.km; const SeqMap& sm = a.sm;
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BKV / NRG;
-  __shared__ uint8_t tile[BKV][D + 16];
+  auto& tile = lds.tile; auto& s_vscale = lds.vscale;
   const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
   const int kb = bp.x;
   const size_t bh = bp.y;
@@ -1073,7 +1096,6 @@ __device__ __forceinline__ void quant_v_block(const BlockPos bp, const QuantKV& 
   const int N = sq.nk;
   if (n0 >= N) return;                             // a block past the end of a shorter sequence
   const size_t hbase = hp.base + sq.k0 * (size_t)km.sn;
-  __shared__ float s_vscale[REDUCE ? D : 1];       // delta_V of this head, reduced here
   if constexpr (REDUCE) {
     if (t < D) {
       float vm = 0.0f;
@@ -1148,11 +1170,13 @@ __device__ __forceinline__ void quant_v_block(const BlockPos bp, const QuantKV& 
 template <int D, bool INT4, int DSM> constexpr int quant_k_occupancy() { return D == 256 ? 2 : (D == 64 && INT4 && DSM == DS_DIGITS ? 5 : 4); }
 template <bool BF16, bool INT4, int D, int DSM = DS_DIGITS>
 __global__ void __launch_bounds__(256, (quant_k_occupancy<D, INT4, DSM>())) k_quant_k(const QuantKV a) {
-  quant_k_block<BF16, INT4, D, DSM>(block_pos(a.km), a);
+  __shared__ QuantKLds<D, INT4, DSM, false> lds;
+  quant_k_block<BF16, INT4, D, DSM>(lds, block_pos(a.km), a);
 }
 template <bool BF16, int D, bool SMOOTH_V, int PVF>
 __global__ void __launch_bounds__(256) k_quant_v(const QuantKV a) {
-  quant_v_block<BF16, D, SMOOTH_V, PVF>(block_pos(a.km), a);
+  __shared__ QuantVLds<D, false> lds;
+  quant_v_block<BF16, D, SMOOTH_V, PVF>(lds, block_pos(a.km), a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1168,20 +1192,28 @@ struct SmallStats {
   int nchunk;
   TensorMap km;
 };
+template <class A, class B> union Overlay { A a; B b; __device__ Overlay() {} };
 template <bool BF16, bool INT4, int D>
-__global__ void __launch_bounds__(256) k_quant_q_and_stats(const QuantQ q, const SmallStats st) {
+__global__ void __launch_bounds__(256, D == 256 || !INT4 ? 2 : 4) k_quant_q_and_stats(const QuantQ q, const SmallStats st) {
+  __shared__ Overlay<QuantQLds<D, INT4>, StatsLds<D, false>> lds;
   // grid: (query blocks, then chunks of keys; query heads) - the chunks of the first B H_kv rows count as KV heads
   if ((int)blockIdx.x < q.nQb) {
-    quant_q_block<BF16, INT4, D>(BlockPos{blockIdx.x, blockIdx.y, (unsigned)q.nQb}, q);
+    quant_q_block<BF16, INT4, D>(lds.a, BlockPos{blockIdx.x, blockIdx.y, (unsigned)q.nQb}, q);
   } else if ((int)blockIdx.y < (int)gridDim.y / q.G) {
-    col_stats_block<BF16, D, false>(BlockPos{blockIdx.x - q.nQb, blockIdx.y, (unsigned)st.nchunk}, st.k, st.v, st.k_sum, nullptr,
+    col_stats_block<BF16, D, false>(lds.b, BlockPos{blockIdx.x - q.nQb, blockIdx.y, (unsigned)st.nchunk}, st.k, st.v, st.k_sum, nullptr,
                                     st.v_max, q.N, q.Nk, st.km, q.sm);
   }
 }
-template <bool BF16, bool INT4, int D, int DSM, bool REDUCE>
-__global__ void __launch_bounds__(256, D == 256 ? 2 : (INT4 && DSM == DS_DIGITS ? 3 : 4)) k_quant_kv(const QuantKV a) {
-  if ((int)blockIdx.x < a.nKb) quant_k_block<BF16, INT4, D, DSM, REDUCE>(BlockPos{blockIdx.x, blockIdx.y, (unsigned)a.nKb}, a);
-  else quant_v_block<BF16, D, false, PV_E4M3, REDUCE>(BlockPos{blockIdx.x - a.nKb, blockIdx.y, (unsigned)a.nKb}, a);
+// K and V side by side: even pieces are key blocks for K, odd ones for V, so that the one's arithmetic runs under the other's
+// loads and stores whatever the length.
+template <bool BF16, bool INT4, int D, int DSM, bool SMOOTH_V, bool REDUCE>
+__global__ void __launch_bounds__(256, (quant_k_occupancy<D, INT4, DSM>())) k_quant_kv(const QuantKV a) {
+  __shared__ Overlay<QuantKLds<D, INT4, DSM, REDUCE>, QuantVLds<D, REDUCE>> lds;
+  BlockPos bp = block_pos(a.km);
+  const bool is_v = bp.x & 1;
+  bp.x >>= 1; bp.nx >>= 1;
+  if (is_v) quant_v_block<BF16, D, SMOOTH_V, PV_E4M3, REDUCE>(lds.b, bp, a);
+  else quant_k_block<BF16, INT4, D, DSM, REDUCE>(lds.a, bp, a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1264,24 +1296,31 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
 }
 
 // Calls that the three-launch sequence serves (k_quant_q_and_stats, k_quant_kv): E4M3, exact Delta-S, no row constants (they
-// need mean(K) before Q), at most 8 chunks of keys to be reduced in every workgroup, and at most two workgroups per CU in
-// any of the kernels it replaces.  Whole calls, us, six launches / three: 2 heads of 64 channels, 256 tokens 26.5 / 18.7;
-// 32 heads on 8, 300 tokens 34.5 / 23.6; 8 heads, 2000 tokens 58 / 47; 32 of 256 channels on 16, 700 tokens 73 / 59; 64,
-// 500 tokens, 8-bit mode (512 workgroups) 51 / 39.  Beyond: 128 heads, 1024 tokens (2048 workgroups) 99 / 109, 64 of 64
-// channels, 2000 tokens (2048) 84 / 86.
-// A pair holds the LDS of both its bodies, so in the 4-bit mode fewer of its workgroups fit a CU than of the Q quantizer alone
-// (d = 128: two instead of four; d = 256: one instead of two): the Q blocks and statistics chunks together are held to
-// what still gained.  32 sequences' heads of 60 tokens, d = 128: 768 workgroups 38.3 / 33.2, 896 39.0 / 39.0, 1024 41.0 / 41.9;
-// d = 256: 576 72.9 / 64.7, 640 55.6 / 60.1, 896 64.6 / 72.8.  And the K quantizer's digits at d = 256 leave one
-// K / V pair per CU: 128 key blocks 85.6 / 78.1, 256 127.7 / 134.2, 512 126.1 / 145.0.
-constexpr int SMALL_CALL_WG = 512;
+// need mean(K) before Q).  What it costs is the reduction of the statistics, which every workgroup does for its head: the workgroups
+// of the general sequence's Q and K launches times the chunks of a head.  Whole calls, us, general sequence (K and V as kv_pair says) / three
+// launches: 2 heads of 64 channels, 256 tokens 26.5 / 17.4; 128 of 128, 500 tokens (1536 workgroups, 2 chunks) 57 / 46; 512 of 200
+// (3072, 1) 79 / 71; 128 of 1024 (3072, 4) 94.8 / 92.8; 32 on 8 of 3000 (1144, 12) 98 / 93; 8 of 5000 (952, 20) 111 / 108; at the line and
+// beyond: 8 on 1 of 8000 (629, 32) 151.4 / 150.7, 64 on 16 of 2048 (3072, 8) 153.8 / 154.6, 2 of 12000 (564, 47) 114 / 119.
+// The bodies of a pair share its LDS (side by side it held pairs of d >= 128 to fewer workgroups), but its registers are the larger
+// body's, which tells at 256 channels where the chip is full: the 4-bit mode gains to 768 key blocks (64 heads of 750 tokens 90 / 85, 16 of
+// 3000 145.5 / 146.6, 64 of 1000 with 1024 blocks 107.7 / 108.6, 256 of 512 with 2048 156 / 167), the 8-bit mode at any size except
+// that heads of a single key block give Q's registers to half of the workgroups for little (512 heads of 60 tokens 70.1 / 70.0, 768
+// 98.8 / 101, 1536 165 / 179; 768 of 100 132 / 126).
+constexpr int SMALL_CALL_WORK = 20480, SMALL_CALL_CHUNKS = 32;
 static bool small_call(const Dims& Dm) {
   const long long nk = (long long)Dm.B * Dm.Hkv * Dm.nKb, nq = (long long)Dm.B * Dm.H * Dm.nQb;
-  const long long stats = Dm.stats_given ? 0 : (long long)Dm.B * Dm.Hkv * ((Dm.Nk + STAT_ROWS - 1) / STAT_ROWS);
-  if (Dm.int4 && Dm.d >= 128 && nq + stats > (Dm.d == 256 ? 576 : 768)) return false;
-  if (Dm.int4 && Dm.d == 256 && Dm.ds_mode == DS_DIGITS && nk > 128) return false;
+  const int nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS;
+  if (Dm.d == 256 && (Dm.int4 ? nk > 768 : Dm.nKb == 1 && nq > 512)) return false;
   return !Dm.want_lse && !Dm.smooth_v && !Dm.tensor_groups && Dm.pvf == PV_E4M3 && !Dm.ds32 && !Dm.seq.cu_q &&
-         Dm.Nk <= 8 * STAT_ROWS && nk <= SMALL_CALL_WG && nq <= SMALL_CALL_WG;
+         nchunk <= SMALL_CALL_CHUNKS && (nk + nq) * nchunk <= SMALL_CALL_WORK;
+}
+
+// K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  In the 8-bit mode, whose two
+// quantizers are alike, at any length (16 heads of 20000 tokens, 64 channels 781 / 777 us, 32 of 8192, 128 channels 402 / 400, 4 of 30000
+// 82 / 79); with Delta-S, or 256 channels, K's registers leave V's workgroups too few on a CU once they fill the chip: 632
+// key blocks of 256 channels 193 / 190, 752 of 64 70 / 69, but 1128 of 128 300 / 308, 2048 of 256 389 / 409, 8192 770 / 796.
+static bool kv_pair(const Dims& Dm) {
+  return !Dm.tensor_groups && Dm.pvf == PV_E4M3 && !Dm.ds32 && ((!Dm.int4 && Dm.d < 256) || (long long)Dm.B * Dm.Hkv * Dm.nKb <= 768);
 }
 
 template <bool BF16, bool INT4, int D>
@@ -1312,6 +1351,19 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   ka.head_scale = nullptr; ka.stats_only = 0; ka.zero_ds = !Dm.smooth_q; ka.q_digits = P.q_digits; ka.q_dscale = P.q_dscale;
   ka.k_sum = P.k_sum; ka.v_max = P.v_max; ka.nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS; ka.smooth_k = Dm.smooth_k;
   ka.code_max = E4M3_MAX;
+  // K and V in one launch; `reduced`: mean(K) and delta_V are in place
+  auto quant_kv = [&](bool reduced) {
+    const dim3 grid = block_grid(km, 2 * Dm.nKb, BHkv);
+#define SAGE_QKV(DSM_)                                                                                                  \
+  do {                                                                                                                  \
+    if (Dm.smooth_v) k_quant_kv<BF16, INT4, D, DSM_, true, false><<<grid, 256, 0, s>>>(ka);                              \
+    else if (reduced) k_quant_kv<BF16, INT4, D, DSM_, false, false><<<grid, 256, 0, s>>>(ka);                            \
+    else k_quant_kv<BF16, INT4, D, DSM_, false, true><<<grid, 256, 0, s>>>(ka);                                          \
+  } while (0)
+    if (INT4 && Dm.ds_mode == DS_FP64) SAGE_QKV(INT4 ? DS_FP64 : DS_DIGITS);
+    else SAGE_QKV(DS_DIGITS);
+#undef SAGE_QKV
+  };
   if (small_call(Dm)) {
     if (Dm.stats_given) {
       k_quant_q_and_stats<BF16, INT4, D><<<dim3(Dm.nQb, BH), 256, 0, s>>>(qa, SmallStats{});
@@ -1319,15 +1371,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
       const SmallStats st = {k, v, P.k_sum, P.v_max, ka.nchunk, km};
       k_quant_q_and_stats<BF16, INT4, D><<<dim3(Dm.nQb + ka.nchunk, BH), 256, 0, s>>>(qa, st);
     }
-    const dim3 gkv(2 * Dm.nKb, BHkv);
-#define SAGE_QKV(DSM_)                                                                                      \
-  do {                                                                                                      \
-    if (Dm.stats_given) k_quant_kv<BF16, INT4, D, DSM_, false><<<gkv, 256, 0, s>>>(ka);                      \
-    else k_quant_kv<BF16, INT4, D, DSM_, true><<<gkv, 256, 0, s>>>(ka);                                      \
-  } while (0)
-    if (INT4 && Dm.ds_mode == DS_FP64) SAGE_QKV(INT4 ? DS_FP64 : DS_DIGITS);
-    else SAGE_QKV(DS_DIGITS);
-#undef SAGE_QKV
+    quant_kv(Dm.stats_given);
     return hipGetLastError();
   }
   auto quant_q_pass = [&](float* corr, const float* head_scale, int stats_only) {
@@ -1362,6 +1406,10 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   if (!Dm.want_lse) quant_q();
   if (!Dm.stats_given) launch_stats_t<BF16, D>(Dm, P, s);     // else P.k_mean and P.v_scale are the caller's arrays
   if (Dm.want_lse) quant_q();
+  if (kv_pair(Dm)) {
+    quant_kv(true);
+    return hipGetLastError();
+  }
   if (Dm.tensor_groups) {
     quant_k_pass(nullptr, 1);
     k_head_scale<<<BHkv, 256, 0, s>>>(P.k_scale, P.k_head_scale, BKV / Dm.kg, Dm.nKb * (BKV / Dm.kg), BKV, Dm.Hkv, 1,

@@ -1,0 +1,43 @@
+"""K and V quantized by one launch or by two (kv_pair in csrc/sage_prologue.hip): a head quantized in a call on one side of the line
+has the codes and scales that it has in a call on the other."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _pa():
+    import paper_2411_10958_amd as pa
+    return pa
+
+
+# sequences, N, N_kv, d, H, Hkv, mode, smooth_v: 768 key blocks and 800 (the 4-bit line, and the 8-bit one of 256 channels)
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode,smooth_v", [
+    (25, 100, 2047, 64, 2, 1, "int4_fp8", False), (25, 129, 1985, 128, 1, 1, "int4_fp8", True), (25, 70, 2000, 256, 3, 1, "int4_fp8", False),
+    (25, 300, 2048, 256, 1, 1, "int8_fp8", True), (25, 67, 2047, 256, 1, 1, "int8_fp8", False), (25, 64, 2001, 128, 2, 1, "int8_fp8", False)])
+def test_one_launch_equals_two(B, N, Nk, d, H, Hkv, mode, smooth_v):
+    pa = _pa()
+    print(f"K/V pair: B={B} N={N} N_kv={Nk} d={d} H={H}/{Hkv} {mode} smooth_v={smooth_v}", flush=True)
+    g = torch.Generator().manual_seed(B + N + Nk + d)
+    q, k, v = (torch.randn(B, h, n, d, generator=g).to(torch.bfloat16).cuda() for h, n in ((H, N), (Hkv, Nk), (Hkv, Nk)))
+    kw = dict(mode=mode, smooth_v=smooth_v, return_lse=True, kv_splits=1)      # (the log-sum-exp keeps both calls off the small-call sequence)
+    two, lse_two = pa.sage_attn_fwd_ex(q, k, v, **kw)
+    one, lse_one = pa.sage_attn_fwd_ex(q[:24], k[:24], v[:24], **kw)
+    torch.cuda.synchronize()
+    assert torch.isfinite(two).all()
+    assert torch.equal(one, two[:24]) and torch.equal(lse_one, lse_two[:24])
+
+
+# the lines of small_call: 32 chunks of 256 keys, 20480 workgroups times chunks, 768 key blocks and one-block heads at 256 channels
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode", [
+    (1, 130, 8192, 128, 3, 1, "int4_fp8"), (1, 130, 8193, 64, 3, 1, "int8_fp8"), (128, 128, 256, 64, 32, 32, "int4_fp8"), (241, 128, 256, 64, 17, 17, "int8_fp8"),
+    (24, 70, 2048, 256, 1, 1, "int4_fp8"), (25, 70, 2048, 256, 1, 1, "int4_fp8"), (32, 60, 64, 256, 16, 4, "int8_fp8"), (27, 60, 64, 256, 19, 1, "int8_fp8")])
+def test_three_launches_equal_the_general_sequence(B, N, Nk, d, H, Hkv, mode):
+    pa = _pa()
+    print(f"three launches: B={B} N={N} N_kv={Nk} d={d} H={H}/{Hkv} {mode}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(B + N + Nk + d)
+    q, k, v = (torch.randn(B, h, n, d, generator=g, device="cuda").half() for h, n in ((H, N), (Hkv, Nk), (Hkv, Nk)))
+    out = pa.sage_attn_fwd_ex(q, k, v, mode=mode, kv_splits=1)
+    general, _ = pa.sage_attn_fwd_ex(q, k, v, mode=mode, kv_splits=1, return_lse=True)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out).all() and torch.equal(out, general)
