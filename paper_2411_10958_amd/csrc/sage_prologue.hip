@@ -141,48 +141,63 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ part, 
   return s;
 }
 
+// The LDS of two bodies of which a workgroup runs one.
+template <class A, class B> union Overlay { A a; B b; __device__ Overlay() {} };
+
 // k_mean = fl32(sum / N) (Eq. 2), delta_V = fl32(max|V| / 448) (Sec. 3.3); with the smooth-V option
 // this call produces v_mean = fl32(sum / N) instead of delta_V, which k_finalize_vscale adds later.
-constexpr int FIN_ENT = 16, FIN_PARTS = 16;     // k_finalize_stats: entries per workgroup, threads per entry (256 threads)
-__global__ void k_finalize_stats(const double* __restrict__ k_sum, const double* __restrict__ v_sum,
-                                 const unsigned* __restrict__ v_max, float* __restrict__ k_mean,
-                                 float* __restrict__ v_mean, float* __restrict__ v_scale, int n, int Nq, int N,
-                                 int d, int Hkv, int nchunk, SeqMap sm, float code_max, int smooth_k) {
-  // FIN_ENT (head, channel) entries per workgroup, FIN_PARTS threads each: thread part p sums chunks p, p + FIN_PARTS,
-  // ... (the sums are exact in float64, so their order does not matter) and the parts meet in LDS.  Many threads per
-  // entry because a long key range leaves many chunks (128 at 32 k keys) and a thread's loads are one round trip each.
-  __shared__ double s_k[FIN_PARTS][FIN_ENT], s_v[FIN_PARTS][FIN_ENT];
-  __shared__ float s_m[FIN_PARTS][FIN_ENT];
+// FIN_ENT (head, channel) entries per workgroup, FIN_PARTS threads each (256): thread part p sums chunks p, p + FIN_PARTS,
+// ... (the sums are exact in float64, so their order does not matter) and the parts meet in LDS.  Many threads per
+// entry because a long key range leaves many chunks (128 at 32 k keys) and a thread's loads are one round trip each.
+constexpr int FIN_ENT = 16, FIN_PARTS = 16;
+struct Finalize {
+  const double *k_sum, *v_sum;
+  const unsigned* v_max;
+  float *k_mean, *v_mean, *v_scale;
+  int n, Nq, N, d, Hkv, nchunk;
+  SeqMap sm;
+  float code_max;
+  int smooth_k;
+};
+struct FinalizeLds {
+  double k[FIN_PARTS][FIN_ENT], v[FIN_PARTS][FIN_ENT];
+  float m[FIN_PARTS][FIN_ENT];
+};
+__device__ __forceinline__ void finalize_stats_block(FinalizeLds& lds, unsigned block, const Finalize& a) {
   const int e = threadIdx.x % FIN_ENT, part = threadIdx.x / FIN_ENT;
-  const int i = blockIdx.x * FIN_ENT + e;
+  const int i = block * FIN_ENT + e;
   double ks = 0.0, vs = 0.0;
   float vm = 0.0f;
-  if (i < n) {
-    const int head = i / d, c = i - head * d;
-    const size_t p0 = (size_t)head * nchunk * d + c;
+  if (i < a.n) {
+    const int head = i / a.d, c = i - head * a.d;
+    const size_t p0 = (size_t)head * a.nchunk * a.d + c;
 #pragma unroll 4
-    for (int ch = part; ch < nchunk; ch += FIN_PARTS) {
-      ks += k_sum[p0 + (size_t)ch * d];
-      if (v_sum) vs += v_sum[p0 + (size_t)ch * d];
-      else vm = fmaxf(vm, __uint_as_float(v_max[p0 + (size_t)ch * d]));
+    for (int ch = part; ch < a.nchunk; ch += FIN_PARTS) {
+      ks += a.k_sum[p0 + (size_t)ch * a.d];
+      if (a.v_sum) vs += a.v_sum[p0 + (size_t)ch * a.d];
+      else vm = fmaxf(vm, __uint_as_float(a.v_max[p0 + (size_t)ch * a.d]));
     }
   }
-  s_k[part][e] = ks; s_v[part][e] = vs; s_m[part][e] = vm;
+  lds.k[part][e] = ks; lds.v[part][e] = vs; lds.m[part][e] = vm;
   __syncthreads();
-  if (part == 0 && i < n) {
-    const int head = i / d;
-    const int nk = seq_of(sm, (unsigned)(head / Hkv), Nq, N).nk;      // this sequence's key count
+  if (part == 0 && i < a.n) {
+    const int head = i / a.d;
+    const int nk = seq_of(a.sm, (unsigned)(head / a.Hkv), a.Nq, a.N).nk;      // this sequence's key count
     ks = 0.0; vs = 0.0; vm = 0.0f;
 #pragma unroll
     for (int q = 0; q < FIN_PARTS; ++q) {
-      ks += s_k[q][e];
-      vs += s_v[q][e];
-      vm = fmaxf(vm, s_m[q][e]);
+      ks += lds.k[q][e];
+      vs += lds.v[q][e];
+      vm = fmaxf(vm, lds.m[q][e]);
     }
-    k_mean[i] = nk > 0 && smooth_k ? (float)(ks / (double)nk) : 0.0f;   // smoothing of K off: mean 0
-    if (v_sum) v_mean[i] = nk > 0 ? (float)(vs / (double)nk) : 0.0f;
-    else v_scale[i] = __fdiv_rn(vm, code_max);
+    a.k_mean[i] = nk > 0 && a.smooth_k ? (float)(ks / (double)nk) : 0.0f;   // smoothing of K off: mean 0
+    if (a.v_sum) a.v_mean[i] = nk > 0 ? (float)(vs / (double)nk) : 0.0f;
+    else a.v_scale[i] = __fdiv_rn(vm, a.code_max);
   }
+}
+__global__ void __launch_bounds__(256) k_finalize_stats(const Finalize a) {
+  __shared__ FinalizeLds lds;
+  finalize_stats_block(lds, blockIdx.x, a);
 }
 // Running statistics of a growing K / V (a KV cache that is appended to): the exact column sums of K and the column
 // maxima of |V| are kept as state, a new chunk's partial results are added to them, and mean(K), delta_V of the whole
@@ -358,19 +373,28 @@ struct QuantQ {
   int stats_only, smooth_q;
   unsigned char* q_digits;
   float* q_dscale;
+  const double* k_sum;       // not null: mean(K) is not there yet, these are the partial sums of its chunks
+  int nchunk, smooth_k;
 };
+// mean(K) of one channel, from k_mean or from the partial sums
+template <int D>
+__device__ __forceinline__ float q_kbar(const QuantQ& a, unsigned kv_head, int nk, int c) {
+  if (!a.k_sum) return a.k_mean[(size_t)kv_head * D + c];
+  return nk > 0 && a.smooth_k ? (float)(sum_partials(a.k_sum, kv_head, a.nchunk, D, c) / (double)nk) : 0.0f;
+}
 #define SAGE_QUANT_Q_ARGS                                                                                              \
   const unsigned short* __restrict__ Q = a.q; float* __restrict__ q_scale = a.q_scale;                                 \
   int8_t* __restrict__ q_codes = a.q_codes;                                                                            \
   const int N = a.N, Nk = a.Nk, nQb = a.nQb, block_groups = a.block_groups, qg = a.qg, G = a.G, stats_only = a.stats_only; \
   const TensorMap& qm = a.qm; const SeqMap& sm = a.sm; float* __restrict__ q_corr = a.q_corr;                          \
-  const float* __restrict__ k_mean = a.k_mean; const float* __restrict__ head_scale = a.head_scale; const float kappa = a.kappa
+  const float* __restrict__ head_scale = a.head_scale; const float kappa = a.kappa
 
 // Q, 8-bit variant: pair-group quantization psi_Q(Q_i), no smoothing (the 8-bit kernel of the
 // paper's "two kernel implementations" leaves Q as it is).  One workgroup per 128 queries of one
 // (batch, head).
 template <int D, bool INT4> struct QuantQLds {               // (8-bit mode)
   uint4 codes[BQ * D / 16];
+  alignas(16) float kbar[D];         // mean(K) of the KV head (log-sum-exp output only)
   float bmax[4];
 };
 template <bool BF16, int D>
@@ -398,8 +422,11 @@ __device__ __forceinline__ void quant_q8_block(QuantQLds<D, false>& lds, const B
       for (int e = 0; e < 8; ++e) x[i][e] = 0.0f;
     }
   }
-  if (q_corr) row_constants<D, NCG, RPT>(x, q_corr + (bh * nQb + qb) * BQ + rg * RPT, valid - rg * RPT,
-                                         k_mean + kv_head(qm, bp.y, G) * D + cg * 8, kappa, cg);
+  if (q_corr) {
+    if (t < D) lds.kbar[t] = q_kbar<D>(a, kv_head(qm, bp.y, G), sq.nk, t);
+    __syncthreads();
+    row_constants<D, NCG, RPT>(x, q_corr + (bh * nQb + qb) * BQ + rg * RPT, valid - rg * RPT, lds.kbar + cg * 8, kappa, cg);
+  }
   // codes go to LDS in the packed order of this 128-query slab (contiguous in the workspace) and
   // leave as coalesced 16-byte stores
   auto& s_codes = lds.codes; auto& s_bmax = lds.bmax;
@@ -489,9 +516,6 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const Bl
   const int valid = min(BQ, sq.n - n0);
   if (valid <= 0) return;                     // a block past the end of a shorter sequence
   const size_t hbase = hp.base + sq.q0 * (size_t)qm.sn;
-  // (fetched now, under the loads of the rows: read from global memory where it is used, in front of every 8 channels of
-  // every row, it was a round trip each)
-  if (q_corr && t < D) s_kbar[t] = k_mean[kv_head(qm, bp.y, G) * D + t];
   auto swz = [](int r) { return (r >> 1) & (D >= 128 ? 3 : 1); };
   {
     const int cg = t % NCG, rg = t / NCG;
@@ -505,6 +529,9 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const Bl
       raw[i] = r < valid ? nt_load16(Q + row_offset(qm, hbase, n0 + r) + cg * 8)
                          : make_uint4(0u, 0u, 0u, 0u);                  // padded rows are zero
     }
+    // (fetched now, under the loads of the rows: read from global memory where it is used, in front of every 8 channels of
+    // every row, it was a round trip each)
+    if (q_corr && t < D) s_kbar[t] = q_kbar<D>(a, kv_head(qm, bp.y, G), sq.nk, t);
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
       const int r = rg * RPT + i;
@@ -622,15 +649,16 @@ template <bool BF16, bool INT4, int D>
 __device__ __forceinline__ void quant_q_block(QuantQLds<D, INT4>& lds, const BlockPos bp, const QuantQ& a) {
   if constexpr (INT4) quant_q4_block<BF16, D>(lds, bp, a); else quant_q8_block<BF16, D>(lds, bp, a);
 }
-template <bool BF16, int D>
-__global__ void __launch_bounds__(256) k_quant_q8(const QuantQ a) {
-  __shared__ QuantQLds<D, false> lds;
-  quant_q8_block<BF16, D>(lds, block_pos(a.qm), a);
-}
-template <bool BF16, int D>
-__global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q4(const QuantQ a) {
-  __shared__ QuantQLds<D, true> lds;
-  quant_q4_block<BF16, D>(lds, block_pos(a.qm), a);
+// The first fin_rows rows of the grid finish the statistics (finalize_stats_block) under the quantization of Q.
+template <bool BF16, bool INT4, int D>
+__global__ void __launch_bounds__(256, D == 256 || !INT4 ? 2 : 4) k_quant_q(const QuantQ a, const Finalize f, const unsigned fin_rows) {
+  __shared__ Overlay<QuantQLds<D, INT4>, FinalizeLds> lds;
+  if (blockIdx.y < fin_rows) {
+    finalize_stats_block(lds.b, blockIdx.y * gridDim.x + blockIdx.x, f);
+    return;
+  }
+  const unsigned y = blockIdx.y - fin_rows, ny = gridDim.y - fin_rows;
+  quant_q_block<BF16, INT4, D>(lds.a, a.qm.heads_inner ? BlockPos{y, blockIdx.x, ny} : BlockPos{blockIdx.x, y, gridDim.x}, a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1192,7 +1220,6 @@ struct SmallStats {
   int nchunk;
   TensorMap km;
 };
-template <class A, class B> union Overlay { A a; B b; __device__ Overlay() {} };
 template <bool BF16, bool INT4, int D>
 __global__ void __launch_bounds__(256, D == 256 || !INT4 ? 2 : 4) k_quant_q_and_stats(const QuantQ q, const SmallStats st) {
   __shared__ Overlay<QuantQLds<D, INT4>, StatsLds<D, false>> lds;
@@ -1271,27 +1298,25 @@ __global__ void k_unpack_rows(const float* __restrict__ src, float* __restrict__
 
 // ------------------------------------------------------------------------------------------
 // The statistics pass: mean(K) and delta_V (and mean(V) with the smooth-V option) into P.k_mean, P.v_scale, P.v_mean.
+static Finalize finalize_args(const Dims& Dm, const Ptrs& P) {
+  return {P.k_sum, Dm.smooth_v ? P.v_sum : nullptr, P.v_max, P.k_mean, P.v_mean, P.v_scale, Dm.B * Dm.Hkv * Dm.d, Dm.N, Dm.Nk, Dm.d, Dm.Hkv,
+          (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS, Dm.seq, Dm.pvf == PV_INT8 ? INT8_PV_MAX : (Dm.pvf == PV_E5M2 ? E5M2_MAX : E4M3_MAX), Dm.smooth_k};
+}
+// finalize = false: the caller's next launch does it (no smooth_v)
 template <bool BF16, int D>
-static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
-  const int BHkv = Dm.B * Dm.Hkv;
+static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s, bool finalize = true) {
   const unsigned short* k = (const unsigned short*)P.k;
   const unsigned short* v = (const unsigned short*)P.v;
-  const int nstat = BHkv * Dm.d;
   const TensorMap km = make_tensor_map(Dm.nhd, Dm.Hkv, Dm.Nk, Dm.d, Dm.seq.cu_q != nullptr);
-  const SeqMap sm = Dm.seq;
-  const int nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS;
-  const dim3 gstat = block_grid(km, nchunk, BHkv);
-  const float code_max = Dm.pvf == PV_INT8 ? INT8_PV_MAX : (Dm.pvf == PV_E5M2 ? E5M2_MAX : E4M3_MAX);
+  const Finalize f = finalize_args(Dm, P);
+  const dim3 gstat = block_grid(km, f.nchunk, Dm.B * Dm.Hkv);
+  const int fin = (f.n + FIN_ENT - 1) / FIN_ENT;
+  if (Dm.smooth_v) k_col_stats<BF16, D, true><<<gstat, 256, 0, s>>>(k, v, P.k_sum, P.v_sum, P.v_max, Dm.N, Dm.Nk, km, Dm.seq);
+  else k_col_stats<BF16, D, false><<<gstat, 256, 0, s>>>(k, v, P.k_sum, nullptr, P.v_max, Dm.N, Dm.Nk, km, Dm.seq);
+  if (finalize) k_finalize_stats<<<fin, FIN_ENT * FIN_PARTS, 0, s>>>(f);
   if (Dm.smooth_v) {
-    k_col_stats<BF16, D, true><<<gstat, 256, 0, s>>>(k, v, P.k_sum, P.v_sum, P.v_max, Dm.N, Dm.Nk, km, sm);
-    k_finalize_stats<<<(nstat + FIN_ENT - 1) / FIN_ENT, FIN_ENT * FIN_PARTS, 0, s>>>(P.k_sum, P.v_sum, P.v_max, P.k_mean, P.v_mean, P.v_scale,
-                                                        nstat, Dm.N, Dm.Nk, Dm.d, Dm.Hkv, nchunk, sm, code_max, Dm.smooth_k);
-    k_v_absmax<BF16, D><<<gstat, 256, 0, s>>>(v, P.v_mean, P.v_max, Dm.N, Dm.Nk, km, sm);
-    k_finalize_vscale<<<(nstat + FIN_ENT - 1) / FIN_ENT, FIN_ENT * FIN_PARTS, 0, s>>>(P.v_max, P.v_scale, nstat, Dm.d, nchunk, code_max);
-  } else {
-    k_col_stats<BF16, D, false><<<gstat, 256, 0, s>>>(k, v, P.k_sum, nullptr, P.v_max, Dm.N, Dm.Nk, km, sm);
-    k_finalize_stats<<<(nstat + FIN_ENT - 1) / FIN_ENT, FIN_ENT * FIN_PARTS, 0, s>>>(P.k_sum, nullptr, P.v_max, P.k_mean, nullptr, P.v_scale,
-                                                        nstat, Dm.N, Dm.Nk, Dm.d, Dm.Hkv, nchunk, sm, code_max, Dm.smooth_k);
+    k_v_absmax<BF16, D><<<gstat, 256, 0, s>>>(v, P.v_mean, P.v_max, Dm.N, Dm.Nk, km, Dm.seq);
+    k_finalize_vscale<<<fin, FIN_ENT * FIN_PARTS, 0, s>>>(P.v_max, P.v_scale, f.n, Dm.d, f.nchunk, f.code_max);
   }
 }
 
@@ -1334,14 +1359,11 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
                   km = make_tensor_map(Dm.nhd, Dm.Hkv, Dm.Nk, Dm.d, varlen);
   const SeqMap sm = Dm.seq;
   const float* v_mean = Dm.smooth_v ? P.v_mean : nullptr;
-  // Q goes first: it depends on nothing, and with the statistics pass next to the K and V quantizers
-  // those re-read K and V while the chip's memory-side cache still holds most of them.  Only when
-  // the log-sum-exp output is wanted does Q wait for mean(K) (its row constants need it).
   QuantQ qa;
   qa.q = q; qa.q_mean = P.q_mean; qa.q_scale = P.q_scale; qa.q_codes = P.q_codes;
   qa.N = Dm.N; qa.Nk = Dm.Nk; qa.nQb = Dm.nQb; qa.block_groups = Dm.block_groups; qa.qg = Dm.qg;
   qa.qm = qm; qa.sm = sm; qa.q_corr = nullptr; qa.k_mean = P.k_mean; qa.G = Dm.H / Dm.Hkv; qa.kappa = Dm.kappa;
-  qa.head_scale = nullptr; qa.stats_only = 0; qa.smooth_q = Dm.smooth_q;
+  qa.head_scale = nullptr; qa.stats_only = 0; qa.smooth_q = Dm.smooth_q; qa.k_sum = nullptr; qa.nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS; qa.smooth_k = Dm.smooth_k;
   qa.q_digits = Dm.ds_mode == DS_DIGITS && Dm.smooth_q ? P.q_digits : nullptr; qa.q_dscale = P.q_dscale;
   QuantKV ka;
   ka.k = k; ka.v = v; ka.k_mean = P.k_mean; ka.v_scale = P.v_scale; ka.v_mean = v_mean;
@@ -1374,21 +1396,24 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
     quant_kv(Dm.stats_given);
     return hipGetLastError();
   }
-  auto quant_q_pass = [&](float* corr, const float* head_scale, int stats_only) {
+  auto quant_q_pass = [&](float* corr, const float* head_scale, int stats_only, const Finalize* f = nullptr) {
     QuantQ x = qa;
     x.q_corr = corr; x.head_scale = head_scale; x.stats_only = stats_only;
-    if constexpr (INT4) k_quant_q4<BF16, D><<<block_grid(qm, Dm.nQb, BH), 256, 0, s>>>(x);
-    else                k_quant_q8<BF16, D><<<block_grid(qm, Dm.nQb, BH), 256, 0, s>>>(x);
+    dim3 grid = block_grid(qm, Dm.nQb, BH);
+    unsigned rows = 0;
+    if (f) rows = ((f->n + FIN_ENT - 1) / FIN_ENT + grid.x - 1) / grid.x;
+    grid.y += rows;
+    k_quant_q<BF16, INT4, D><<<grid, 256, 0, s>>>(x, f ? *f : Finalize{}, rows);
   };
-  auto quant_q = [&]() {
+  auto quant_q = [&](const Finalize* f = nullptr) {
     float* corr = Dm.want_lse ? P.q_corr : nullptr;
     if (Dm.tensor_groups) {     // block scales, their maximum per head, then the codes with that one scale
-      quant_q_pass(nullptr, nullptr, 1);
+      quant_q_pass(nullptr, nullptr, 1, f);
       k_head_scale<<<BH, 256, 0, s>>>(P.q_scale, P.q_head_scale, BQ / Dm.qg, Dm.nQb * (BQ / Dm.qg), BQ, Dm.H, 0, Dm.N,
                                      Dm.Nk, sm);
       quant_q_pass(corr, P.q_head_scale, 0);
     } else {
-      quant_q_pass(corr, nullptr, 0);
+      quant_q_pass(corr, nullptr, 0, f);
     }
   };
   auto quant_k_pass = [&](const float* head_scale, int stats_only) {
@@ -1403,9 +1428,16 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
     }
 #undef SAGE_QK
   };
-  if (!Dm.want_lse) quant_q();
-  if (!Dm.stats_given) launch_stats_t<BF16, D>(Dm, P, s);     // else P.k_mean and P.v_scale are the caller's arrays
-  if (Dm.want_lse) quant_q();
+  // The partial statistics are finished under the quantization of Q (5 us as a launch of its own: 64 heads of 2048 tokens
+  // 114.2 / 111.8 us, 64 on 8 of 3000 153.6 / 150.1, 32 of 8192, 8-bit mode 400 / 397).  With the log-sum-exp Q needs mean(K) itself and sums
+  // the chunks in every workgroup: 4 chunks 39.4 / 37.2, 8 89.9 / 88.7, but 16 (512 queries) 84.7 / 85.5, 64 138 / 149.
+  // Smooth V needs the sums before its second pass.  (With the statistics given, P.k_mean and P.v_scale are the caller's arrays.)
+  const Finalize fin = finalize_args(Dm, P);
+  const bool fin_with_q = !Dm.stats_given && !Dm.smooth_v && (!Dm.want_lse || fin.nchunk <= 8) && (long long)BH + fin.n / FIN_ENT + 2 <= 65535;
+  if (fin_with_q && Dm.want_lse) qa.k_sum = P.k_sum;
+  if (!Dm.stats_given && (fin_with_q || Dm.want_lse)) launch_stats_t<BF16, D>(Dm, P, s, !fin_with_q);
+  quant_q(fin_with_q ? &fin : nullptr);
+  if (!Dm.stats_given && !fin_with_q && !Dm.want_lse) launch_stats_t<BF16, D>(Dm, P, s);
   if (kv_pair(Dm)) {
     quant_kv(true);
     return hipGetLastError();

@@ -41,3 +41,24 @@ def test_three_launches_equal_the_general_sequence(B, N, Nk, d, H, Hkv, mode):
     general, _ = pa.sage_attn_fwd_ex(q, k, v, mode=mode, kv_splits=1, return_lse=True)
     torch.cuda.synchronize()
     assert torch.isfinite(out).all() and torch.equal(out, general)
+
+
+# statistics finished under Q (up to 8 chunks with the log-sum-exp; 9 are finished before Q) or given; ragged lengths and token-major rows
+@pytest.mark.parametrize("smooth_k", [True, False])
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,layout", [(1, 65, 1, 64, 2, 1, "HND"), (3, 130, 2048, 128, 4, 2, "HND"), (2, 129, 2049, 128, 2, 2, "HND"),
+                                                   (2, 300, 2047, 128, 32, 32, "NHD"), (1, 257, 1000, 256, 17, 17, "NHD"), (5, 1500, 1500, 64, 33, 33, "HND")])
+def test_statistics_finished_under_q(B, N, Nk, d, H, Hkv, layout, mode, smooth_k):
+    pa = _pa()
+    print(f"statistics under Q: B={B} N={N} N_kv={Nk} d={d} H={H}/{Hkv} {mode} {layout} smooth_k={smooth_k}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(B + N + Nk + d)
+    q, k, v = (torch.randn((B, h, n, d) if layout == "HND" else (B, n, h, d), generator=g, device="cuda").bfloat16() + 1 for h, n in ((H, N), (Hkv, Nk), (Hkv, Nk)))
+    kw = dict(mode=mode, layout=layout, kv_splits=1, smooth_k=smooth_k)
+    out, lse = pa.sage_attn_fwd_ex(q, k, v, return_lse=True, **kw)
+    plain = pa.sage_attn_fwd_ex(q, k, v, **kw)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out).all() and torch.equal(out, plain)
+    if smooth_k:
+        given, lse_given = pa.sage_attn_fwd_ex(q, k, v, return_lse=True, kv_stats=pa.sage_attn_kv_stats(k, v, layout=layout), **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(out, given) and torch.equal(lse, lse_given)
