@@ -51,16 +51,14 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
   D->smooth_k = (a->flags & SAGE_FLAG_NO_SMOOTH_K) == 0;
   D->smooth_q = (a->flags & SAGE_FLAG_NO_SMOOTH_Q) == 0;
   D->ds32 = (a->flags & SAGE_FLAG_FP32_DELTA_S) != 0;
-  // Delta-S: digit products on the INT8 matrix unit, unless a key block meets at most 8 rows of block means (a decode
-  // step, a short chunk): two chains of the 4-row FP64 matrix instruction are then cheaper than cutting the keys into digits
-  // (K quantizer, 4 x 32 heads of 1024 tokens, 8 rows: 20.1 us FP64, 21.4 digits; 16 rows of 512 queries of 4 heads on 16384
-  // keys: 41.3 and 40.7).  Up to 16 rows where the key blocks do not fill the chip and the shorter chain counts: whole calls, 64
-  // heads on 8 of 192 tokens 17.0 / 17.2, 32 on 8 of 300 22.5 / 22.7, but 12 heads of 2000 (384 blocks) 55.1 / 54.2.
-  const long long ds_rows = (long long)(D->H / D->Hkv) * D->nQb;
+  // Delta-S: digit products on the INT8 matrix unit, unless a key block meets at most 16 rows of block means (a decode
+  // step, a short chunk): one chain of FP64 matrix instructions then costs about what cutting the keys into digits does (K
+  // quantizer, 4 x 32 heads of 1024 tokens, 8 rows: 20.1 us FP64, 21.4 digits; 16 rows of 512 queries of 4 heads on 16384 keys: 41.3
+  // and 40.7), and a NaN of K or Q reaches Delta-S through it, which it does not through digits.
   D->ds_mode = D->ds32 ? 1
              : (a->flags & SAGE_FLAG_FP64_DELTA_S) != 0 ? 2
              : (a->flags & SAGE_FLAG_DIGIT_DELTA_S) != 0 ? 0
-             : (ds_rows <= 8 || (ds_rows <= 16 && (long long)D->B * D->Hkv * D->nKb <= 256) ? 2 : 0);
+             : ((long long)(D->H / D->Hkv) * D->nQb <= 16 ? 2 : 0);
 
   D->stats_given = a->k_mean_in != nullptr;
   D->tensor_groups = a->group_map == SAGE_GROUPS_TENSOR;

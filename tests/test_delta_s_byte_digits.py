@@ -95,3 +95,17 @@ def test_attention_reads_only_rows_that_were_formed(H, Hkv, N, Nk, d, causal, fo
     other = run("fp64" if form == "digits" else "digits")
     assert (out != other).any(-1).float().mean() <= 1e-2
     assert (out.float() - ref.float()).norm() <= 2e-3 * ref.float().norm()    # FP32 sums move a few codes of P~ by one step
+
+
+@pytest.mark.gpu
+def test_a_nan_key_reaches_the_output_where_few_rows_meet_many_key_blocks():
+    """16 rows of block means on 384 key blocks: Delta-S in float64, whose products carry a NaN of K (through its mean) to every
+    query of that head."""
+    import torch
+    import paper_2411_10958_amd as pa
+    g = torch.Generator(device="cuda").manual_seed(0)
+    q, k, v = (torch.randn((1, 12, 2000, 128), generator=g, device="cuda").bfloat16() for _ in range(3))
+    k[0, 3, 77, 5] = float("nan")
+    out = pa.sage_attn_fwd_ex(q, k, v, causal=False, kv_splits=1)
+    assert out[0, 3].isnan().any(-1).all()
+    assert torch.isfinite(out[0, [i for i in range(12) if i != 3]]).all()
