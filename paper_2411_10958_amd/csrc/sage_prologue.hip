@@ -686,7 +686,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int DS_ROWS = 16;     // block means per step of the Delta-S product: one tile of the 16-row matrix instructions
 
 // How the Delta-S product is formed (template parameter DSM of k_quant_k):
-//   DS_DIGITS  both factors cut into 7-bit digits of a fixed-point number and multiplied digit by digit on the INT8
+//   DS_DIGITS  both factors cut into signed bytes of a fixed-point number and multiplied byte by byte on the INT8
 //              matrix instruction: exact integer sums, recombined in float64 (the default),
 //   DS_FP32    v_mfma_f32_16x16x4_f32: faster still, approximate (an option of the boundary),
 //   DS_FP64    v_mfma_f64_16x16x4_f64: the reference form (an option of the boundary).
