@@ -92,13 +92,14 @@ __device__ inline BlockPos block_pos(const TensorMap& m) {
   if (m.heads_inner) { p.x = blockIdx.y; p.y = blockIdx.x; p.nx = gridDim.y; }
   return p;
 }
+constexpr int GRID_Y_MAX = 65535;      // y of a grid is 16 bits
 inline dim3 block_grid(const TensorMap& m, int pieces, int heads) {
   return m.heads_inner ? dim3(heads, pieces) : dim3(pieces, heads);
 }
 inline TensorMap make_tensor_map(int nhd, int heads, int tokens, int d, bool varlen = false) {
   TensorMap m;
   m.heads = heads;
-  m.heads_inner = (nhd || varlen) && heads * d >= 4096 && tokens <= 65535 * 32;   // (y of a grid is 16 bits; pieces have 64 tokens or more, K and V side by side two for 64)
+  m.heads_inner = (nhd || varlen) && heads * d >= 4096 && tokens <= GRID_Y_MAX * 64;   // (pieces have 64 tokens or more)
   if (varlen) { m.sb = 0; m.sh = d; m.sn = (long long)heads * d; return m; }   // packed [tokens, heads, d]
   if (nhd) { m.sb = (long long)tokens * heads * d; m.sh = d; m.sn = (long long)heads * d; }
   else     { m.sb = (long long)heads * tokens * d; m.sh = (long long)tokens * d; m.sn = d; }

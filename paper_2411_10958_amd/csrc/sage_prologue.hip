@@ -1344,7 +1344,10 @@ static bool small_call(const Dims& Dm) {
 // quantizers are alike, at any length (16 heads of 20000 tokens, 64 channels 781 / 777 us, 32 of 8192, 128 channels 402 / 400, 4 of 30000
 // 82 / 79); with Delta-S, or 256 channels, K's registers leave V's workgroups too few on a CU once they fill the chip: 632
 // key blocks of 256 channels 193 / 190, 752 of 64 70 / 69, but 1128 of 128 300 / 308, 2048 of 256 389 / 409, 8192 770 / 796.
-static bool kv_pair(const Dims& Dm) {
+// Its grid has two pieces per key block, which a token-major tensor of long rows has in y (heads_inner): beyond 32767 blocks the
+// two launches remain.
+static bool kv_pair(const Dims& Dm, const TensorMap& km) {
+  if (km.heads_inner && 2 * Dm.nKb > GRID_Y_MAX) return false;
   return !Dm.tensor_groups && Dm.pvf == PV_E4M3 && !Dm.ds32 && ((!Dm.int4 && Dm.d < 256) || (long long)Dm.B * Dm.Hkv * Dm.nKb <= 768);
 }
 
@@ -1438,7 +1441,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   if (!Dm.stats_given && (fin_with_q || Dm.want_lse)) launch_stats_t<BF16, D>(Dm, P, s, !fin_with_q);
   quant_q(fin_with_q ? &fin : nullptr);
   if (!Dm.stats_given && !fin_with_q && !Dm.want_lse) launch_stats_t<BF16, D>(Dm, P, s);
-  if (kv_pair(Dm)) {
+  if (kv_pair(Dm, km)) {
     quant_kv(true);
     return hipGetLastError();
   }
