@@ -1340,15 +1340,19 @@ static bool small_call(const Dims& Dm) {
          nchunk <= SMALL_CALL_CHUNKS && (nk + nq) * nchunk <= SMALL_CALL_WORK;
 }
 
-// K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  In the 8-bit mode, whose two
-// quantizers are alike, at any length (16 heads of 20000 tokens, 64 channels 781 / 777 us, 32 of 8192, 128 channels 402 / 400, 4 of 30000
-// 82 / 79); with Delta-S, or 256 channels, K's registers leave V's workgroups too few on a CU once they fill the chip: 632
-// key blocks of 256 channels 193 / 190, 752 of 64 70 / 69, but 1128 of 128 300 / 308, 2048 of 256 389 / 409, 8192 770 / 796.
-// Its grid has two pieces per key block, which a token-major tensor of long rows has in y (heads_inner): beyond 32767 blocks the
-// two launches remain.
-static bool kv_pair(const Dims& Dm, const TensorMap& km) {
-  if (km.heads_inner && 2 * Dm.nKb > GRID_Y_MAX) return false;
-  return !Dm.tensor_groups && Dm.pvf == PV_E4M3 && !Dm.ds32 && ((!Dm.int4 && Dm.d < 256) || (long long)Dm.B * Dm.Hkv * Dm.nKb <= 768);
+// K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  A V workgroup has its rows in
+// flight one at a time and in the pair K's registers, so where K fills the chip by itself, or its workgroups are long (many rows of
+// block means), V's are better off in a launch of their own.  Whole calls, two launches / one, us, by key blocks and rows per KV head:
+// 4-bit, 64 channels 598 blocks, 2 rows 1.07 times as fast, 524, 128 rows 1.00, 724 to 784, 96 to 120 rows 0.96 to 0.97; 128 channels 582,
+// 124 rows 1.00, 608, 32 rows 1.01, 656 to 768, 88 to 160 rows 0.97 to 0.98, 746, 24 rows 1.00, 704, 2 rows 1.08; 256 channels 250, 39
+// rows 1.04, 328 to 432, 48 to 72 rows 0.99, 500, 56 rows 0.97, 640, 24 rows 1.00, 752, 48 rows 0.995, 960, 2 rows 0.95.  8-bit, 64 and 128
+// channels, 1536 blocks 119.3 / 118.2, 3912 142.5 / 140.6, 4928 165.8 / 165.0, 5056 139.4 / 140.9, 7360 315.3 / 320.0, 13496 234.4 / 238.3; 256
+// channels 584 179.4 / 176.4, 768 74.9 / 74.2, 2048 389 / 409.  (So two pieces per key block always fit y of a grid.)
+static bool kv_pair(const Dims& Dm) {
+  if (Dm.tensor_groups || Dm.pvf != PV_E4M3 || Dm.ds32) return false;
+  const bool few_rows = (long long)(Dm.H / Dm.Hkv) * Dm.nQb <= 24;
+  const int line = !Dm.int4 ? (Dm.d == 256 ? 768 : 4608) : (Dm.d == 256 ? (few_rows ? 640 : 320) : (few_rows ? 768 : 640));
+  return (long long)Dm.B * Dm.Hkv * Dm.nKb <= line;
 }
 
 template <bool BF16, bool INT4, int D>
@@ -1441,7 +1445,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   if (!Dm.stats_given && (fin_with_q || Dm.want_lse)) launch_stats_t<BF16, D>(Dm, P, s, !fin_with_q);
   quant_q(fin_with_q ? &fin : nullptr);
   if (!Dm.stats_given && !fin_with_q && !Dm.want_lse) launch_stats_t<BF16, D>(Dm, P, s);
-  if (kv_pair(Dm, km)) {
+  if (kv_pair(Dm)) {
     quant_kv(true);
     return hipGetLastError();
   }

@@ -1,7 +1,10 @@
 """Which kernels a call launches and on what grids, from the library's own launches with the HIP runtime replaced: no GPU."""
 import itertools
 
+import pytest
+
 from launch_recorder import launches
+from test_gpu_kv_pair import PAIR_CASES
 
 POINTER = 4096
 BASE = dict(B=1, H=32, H_kv=32, d=128, dtype=1, mode=1, layout=1)
@@ -25,3 +28,29 @@ def test_no_grid_has_more_than_65535_rows():
         for x in seq:
             assert max(x.grid[1:]) <= 65535, (kw, x)
     assert ran > len(calls) * 0.9
+
+
+def _names(**kw):
+    (status, seq), = launches([("sage_attn_fwd_ex", kw)])
+    assert status == 0, kw
+    return [x.kernel for x in seq]
+
+
+def _mode(mode):
+    return 0 if mode == "int4_fp8" else 1
+
+
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode,smooth_v", PAIR_CASES)
+def test_one_sequence_more_takes_two_launches(B, N, Nk, d, H, Hkv, mode, smooth_v):
+    call = dict(N=N, N_kv=Nk, d=d, H=H, H_kv=Hkv, dtype=1, mode=_mode(mode), flags=int(smooth_v), lse=POINTER, kv_splits=1)
+    assert "k_quant_kv" in _names(B=B - 1, **call)
+    two = _names(B=B, **call)
+    assert "k_quant_kv" not in two and "k_quant_k" in two and "k_quant_v" in two
+
+
+# calls that K and V in one launch made slower: B, H, Hkv, N, N_kv, d, mode, layout, causal (256.8 -> 262.9 us, 269.0 -> 279.1, 367.3 ->
+# 374.4, 315.3 -> 320.0)
+@pytest.mark.parametrize("B,H,Hkv,N,Nk,d,mode,layout,causal", [(2, 8, 1, 1408, 21988, 128, 0, 0, 1), (4, 16, 2, 2221, 5799, 64, 0, 1, 0),
+                                                               (1, 16, 2, 1464, 15104, 256, 0, 0, 1), (4, 32, 16, 512, 29440, 128, 1, 1, 1)])
+def test_large_calls_quantize_k_and_v_in_two_launches(B, H, Hkv, N, Nk, d, mode, layout, causal):
+    assert "k_quant_kv" not in _names(B=B, H=H, H_kv=Hkv, N=N, N_kv=Nk, d=d, mode=mode, layout=layout, causal=causal, dtype=1, lse=POINTER)
