@@ -96,6 +96,16 @@ constexpr int GRID_Y_MAX = 65535;      // y of a grid is 16 bits
 inline dim3 block_grid(const TensorMap& m, int pieces, int heads) {
   return m.heads_inner ? dim3(heads, pieces) : dim3(pieces, heads);
 }
+// Two kinds of pieces in one launch, M of each: which kind and piece workgroup L of 2 M works on.  Workgroups go to the 8 XCDs in
+// turn, so the kinds take turns every 8: taken one by one, each kind would have every other XCD to itself.
+struct PairPiece { unsigned piece; bool second; };
+__host__ __device__ inline PairPiece pair_piece(unsigned L, unsigned M) {
+  const unsigned tail = M & ~7u;
+  if (L < 2 * tail) return {(L >> 4) * 8 + (L & 7), ((L >> 3) & 1) != 0};
+  L -= 2 * tail;
+  const unsigned r = M - tail;
+  return L < r ? PairPiece{tail + L, false} : PairPiece{tail + L - r, true};
+}
 inline TensorMap make_tensor_map(int nhd, int heads, int tokens, int d, bool varlen = false) {
   TensorMap m;
   m.heads = heads;

@@ -1231,15 +1231,15 @@ __global__ void __launch_bounds__(256, D == 256 || !INT4 ? 2 : 4) k_quant_q_and_
                                     st.v_max, q.N, q.Nk, st.km, q.sm);
   }
 }
-// K and V side by side: even pieces are key blocks for K, odd ones for V, so that the one's arithmetic runs under the other's
-// loads and stores whatever the length.
+// K and V side by side (pair_piece), so that the one's arithmetic runs under the other's loads and stores whatever the length.
 template <bool BF16, bool INT4, int D, int DSM, bool SMOOTH_V, bool REDUCE>
 __global__ void __launch_bounds__(256, (quant_k_occupancy<D, INT4, DSM>())) k_quant_kv(const QuantKV a) {
   __shared__ Overlay<QuantKLds<D, INT4, DSM, REDUCE>, QuantVLds<D, REDUCE>> lds;
-  BlockPos bp = block_pos(a.km);
-  const bool is_v = bp.x & 1;
-  bp.x >>= 1; bp.nx >>= 1;
-  if (is_v) quant_v_block<BF16, D, SMOOTH_V, PV_E4M3, REDUCE>(lds.b, bp, a);
+  const unsigned M = gridDim.x >> 1, nKb = (unsigned)a.nKb;
+  const PairPiece pp = pair_piece(blockIdx.x, M);
+  const unsigned per = a.km.heads_inner ? M / nKb : nKb, hi = pp.piece / per, lo = pp.piece - hi * per;
+  const BlockPos bp = a.km.heads_inner ? BlockPos{hi, lo, nKb} : BlockPos{lo, hi, nKb};
+  if (pp.second) quant_v_block<BF16, D, SMOOTH_V, PV_E4M3, REDUCE>(lds.b, bp, a);
   else quant_k_block<BF16, INT4, D, DSM, REDUCE>(lds.a, bp, a);
 }
 
@@ -1340,18 +1340,17 @@ static bool small_call(const Dims& Dm) {
          nchunk <= SMALL_CALL_CHUNKS && (nk + nq) * nchunk <= SMALL_CALL_WORK;
 }
 
-// K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  A V workgroup has its rows in
-// flight one at a time and in the pair K's registers, so where K fills the chip by itself, or its workgroups are long (many rows of
-// block means), V's are better off in a launch of their own.  Whole calls, two launches / one, us, by key blocks and rows per KV head:
-// 4-bit, 64 channels 598 blocks, 2 rows 1.07 times as fast, 524, 128 rows 1.00, 724 to 784, 96 to 120 rows 0.96 to 0.97; 128 channels 582,
-// 124 rows 1.00, 608, 32 rows 1.01, 656 to 768, 88 to 160 rows 0.97 to 0.98, 746, 24 rows 1.00, 704, 2 rows 1.08; 256 channels 250, 39
-// rows 1.04, 328 to 432, 48 to 72 rows 0.99, 500, 56 rows 0.97, 640, 24 rows 1.00, 752, 48 rows 0.995, 960, 2 rows 0.95.  8-bit, 64 and 128
-// channels, 1536 blocks 119.3 / 118.2, 3912 142.5 / 140.6, 4928 165.8 / 165.0, 5056 139.4 / 140.9, 7360 315.3 / 320.0, 13496 234.4 / 238.3; 256
-// channels 584 179.4 / 176.4, 768 74.9 / 74.2, 2048 389 / 409.  (So two pieces per key block always fit y of a grid.)
+// K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  The registers are the larger body's,
+// K's with Delta-S, so where K fills the chip by itself and its workgroups are long (many rows of block means) V's are better off in a
+// launch of their own.  Whole calls, time of two launches / one, by key blocks and rows per KV head.  4-bit: 64 channels 240 blocks, 16 rows 1.07,
+// 592, 148 rows 1.00, 728, 144 rows 0.96, 768, 8 rows 1.04; 128 channels 392, 52 rows 1.02, 448 to 520, 64 to 132 rows 0.97
+// to 0.98, 668, 108 rows 0.94, 706, 16 rows 1.02, 984, 22 rows 1.00; 256 channels 368, 32 rows 1.01, 420, 80 rows 0.97, 520 to 672, 2 rows 0.99 to
+// 1.00, 768, 12 to 24 rows 1.01 to 1.02, 784, 4 rows 0.97.  8-bit, whose two quantizers are alike: 64 channels 656 blocks 1.06, 4160 1.01, 7872
+// 1.02, 14632 1.02, 15700 0.99; 128 channels 640 1.06, 3716 1.01, 7936 1.01, 13984 1.00; 256 channels 768 1.01 to 1.04 (2048 0.95).
 static bool kv_pair(const Dims& Dm) {
   if (Dm.tensor_groups || Dm.pvf != PV_E4M3 || Dm.ds32) return false;
   const bool few_rows = (long long)(Dm.H / Dm.Hkv) * Dm.nQb <= 24;
-  const int line = !Dm.int4 ? (Dm.d == 256 ? 768 : 4608) : (Dm.d == 256 ? (few_rows ? 640 : 320) : (few_rows ? 768 : 640));
+  const int line = !Dm.int4 ? (Dm.d == 256 ? 768 : 16384) : (few_rows ? 768 : (Dm.d == 64 ? 640 : 400));
   return (long long)Dm.B * Dm.Hkv * Dm.nKb <= line;
 }
 
@@ -1382,7 +1381,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   ka.code_max = E4M3_MAX;
   // K and V in one launch; `reduced`: mean(K) and delta_V are in place
   auto quant_kv = [&](bool reduced) {
-    const dim3 grid = block_grid(km, 2 * Dm.nKb, BHkv);
+    const unsigned grid = 2u * (unsigned)Dm.nKb * (unsigned)BHkv;
 #define SAGE_QKV(DSM_)                                                                                                  \
   do {                                                                                                                  \
     if (Dm.smooth_v) k_quant_kv<BF16, INT4, D, DSM_, true, false><<<grid, 256, 0, s>>>(ka);                              \

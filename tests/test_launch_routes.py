@@ -46,11 +46,3 @@ def test_one_sequence_more_takes_two_launches(B, N, Nk, d, H, Hkv, mode, smooth_
     assert "k_quant_kv" in _names(B=B - 1, **call)
     two = _names(B=B, **call)
     assert "k_quant_kv" not in two and "k_quant_k" in two and "k_quant_v" in two
-
-
-# calls that K and V in one launch made slower: B, H, Hkv, N, N_kv, d, mode, layout, causal (256.8 -> 262.9 us, 269.0 -> 279.1, 367.3 ->
-# 374.4, 315.3 -> 320.0)
-@pytest.mark.parametrize("B,H,Hkv,N,Nk,d,mode,layout,causal", [(2, 8, 1, 1408, 21988, 128, 0, 0, 1), (4, 16, 2, 2221, 5799, 64, 0, 1, 0),
-                                                               (1, 16, 2, 1464, 15104, 256, 0, 0, 1), (4, 32, 16, 512, 29440, 128, 1, 1, 1)])
-def test_large_calls_quantize_k_and_v_in_two_launches(B, H, Hkv, N, Nk, d, mode, layout, causal):
-    assert "k_quant_kv" not in _names(B=B, H=H, H_kv=Hkv, N=N, N_kv=Nk, d=d, mode=mode, layout=layout, causal=causal, dtype=1, lse=POINTER)
