@@ -1212,22 +1212,28 @@ __global__ void __launch_bounds__(256) k_quant_v(const QuantKV a) {
 // launches of the general sequence become three: Q and the statistics side by side, then K and V side by side with
 // the reduction of the statistics in front (each workgroup for its own head), then the attention kernel.
 // Where a kernel of the sequence fills the chip by itself the pair is slower than the two (the workgroups of one
-// take the slots and registers of the other): see the rule in launch_prologue_t.
+// take the slots and registers of the other): see the rule, small_call.
 struct SmallStats {
   const unsigned short *k, *v;
   double* k_sum;
   unsigned* v_max;
   int nchunk;
   TensorMap km;
+  unsigned q_blocks;         // query blocks of all heads: that many workgroups, then one per chunk of keys of a KV head
 };
 template <bool BF16, bool INT4, int D>
 __global__ void __launch_bounds__(256, D == 256 || !INT4 ? 2 : 4) k_quant_q_and_stats(const QuantQ q, const SmallStats st) {
   __shared__ Overlay<QuantQLds<D, INT4>, StatsLds<D, false>> lds;
-  // grid: (query blocks, then chunks of keys; query heads) - the chunks of the first B H_kv rows count as KV heads
-  if ((int)blockIdx.x < q.nQb) {
-    quant_q_block<BF16, INT4, D>(lds.a, BlockPos{blockIdx.x, blockIdx.y, (unsigned)q.nQb}, q);
-  } else if ((int)blockIdx.y < (int)gridDim.y / q.G) {
-    col_stats_block<BF16, D, false>(lds.b, BlockPos{blockIdx.x - q.nQb, blockIdx.y, (unsigned)st.nchunk}, st.k, st.v, st.k_sum, nullptr,
+  // Numbered through the heads.  Workgroups go to the eight XCDs in turn: on a grid of (query blocks and chunks, heads) the query blocks
+  // fell on some of them only wherever such a row has 2, 4 or 8 of both, and the chunks that grouped heads leave empty on the others (39 x
+  // 64 heads on 8 of 58 queries and 586 keys, 256 channels, 8-bit: 383 us, a whole call 610 -> 372).
+  const unsigned nQb = (unsigned)q.nQb, nchunk = (unsigned)st.nchunk;
+  if (blockIdx.x < st.q_blocks) {
+    const unsigned head = blockIdx.x / nQb;
+    quant_q_block<BF16, INT4, D>(lds.a, BlockPos{blockIdx.x - head * nQb, head, nQb}, q);
+  } else {
+    const unsigned c = blockIdx.x - st.q_blocks, head = c / nchunk;
+    col_stats_block<BF16, D, false>(lds.b, BlockPos{c - head * nchunk, head, nchunk}, st.k, st.v, st.k_sum, nullptr,
                                     st.v_max, q.N, q.Nk, st.km, q.sm);
   }
 }
@@ -1322,22 +1328,22 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s, bool fi
 
 // Calls that the three-launch sequence serves (k_quant_q_and_stats, k_quant_kv): E4M3, exact Delta-S, no row constants (they
 // need mean(K) before Q).  What it costs is the reduction of the statistics, which every workgroup does for its head: the workgroups
-// of the general sequence's Q and K launches times the chunks of a head.  Whole calls, us, general sequence (K and V as kv_pair says) / three
-// launches: 2 heads of 64 channels, 256 tokens 26.5 / 17.4; 128 of 128, 500 tokens (1536 workgroups, 2 chunks) 57 / 46; 512 of 200
-// (3072, 1) 79 / 71; 128 of 1024 (3072, 4) 94.8 / 92.8; 32 on 8 of 3000 (1144, 12) 98 / 93; 8 of 5000 (952, 20) 111 / 108; at the line and
-// beyond: 8 on 1 of 8000 (629, 32) 151.4 / 150.7, 64 on 16 of 2048 (3072, 8) 153.8 / 154.6, 2 of 12000 (564, 47) 114 / 119.
+// of the general sequence's Q and K launches times the chunks of a head.  Whole calls, full attention, us, general sequence (K and V as kv_pair
+// says) / three launches, 4-bit then 8-bit: 2 heads of 64 channels, 256 tokens 19.1 / 15.9, 19.6 / 16.3; 128 of 128, 500 tokens (1536 workgroups, 2
+// chunks) 62.6 / 51.0, 61.8 / 53.9; 512 of 200 (3072, 1) 83.6 / 75.1, 81.8 / 71.7; 128 of 1024 (3072, 4) 115.3 / 113.8, 117.3 / 112.5; 32 on 8 of
+// 3000 (1144, 12) 137.5 / 134.1, 146.4 / 143.1; 8 of 5000 (952, 20) 151.4 / 149.5, 150.0 / 148.0; 8 on 1 of 8000 (629, 32) 232.3 / 233.5, 212.5 /
+// 211.8; 2 of 12000 (564, 47) 162.3 / 165.9, 164.8 / 171.5.  By workgroups times chunks, general / three: 4-bit 10000 to 14336, 64 channels 1.00 to
+// 1.03, 128 1.01 to 1.04, 15000 to 20480 0.99 to 1.01, 0.96 to 1.02; 8-bit 15000 to 20480 0.99 to 1.09, 30000 to 40000 0.96 to 1.01.
 // The bodies of a pair share its LDS (side by side it held pairs of d >= 128 to fewer workgroups), but its registers are the larger
-// body's, which tells at 256 channels where the chip is full: the 4-bit mode gains to 768 key blocks (64 heads of 750 tokens 90 / 85, 16 of
-// 3000 145.5 / 146.6, 64 of 1000 with 1024 blocks 107.7 / 108.6, 256 of 512 with 2048 156 / 167), the 8-bit mode at any size except
-// that heads of a single key block give Q's registers to half of the workgroups for little (512 heads of 60 tokens 70.1 / 70.0, 768
-// 98.8 / 101, 1536 165 / 179; 768 of 100 132 / 126).
-constexpr int SMALL_CALL_WORK = 20480, SMALL_CALL_CHUNKS = 32;
+// body's, which tells in the 4-bit mode at 256 channels where the chip is full: it gains to 768 key blocks (64 heads of 750 tokens 103.2 /
+// 99.2, 64 of 1000 with 1024 blocks 121.7 / 123.9, 256 of 512 with 2048 183 / 194; 8-bit 99.1 / 88.2, 121.5 / 112.0, 190 / 174).
+constexpr int SMALL_CALL_WORK_INT4 = 14336, SMALL_CALL_WORK_INT8 = 20480, SMALL_CALL_CHUNKS = 32;
 static bool small_call(const Dims& Dm) {
   const long long nk = (long long)Dm.B * Dm.Hkv * Dm.nKb, nq = (long long)Dm.B * Dm.H * Dm.nQb;
   const int nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS;
-  if (Dm.d == 256 && (Dm.int4 ? nk > 768 : Dm.nKb == 1 && nq > 512)) return false;
+  if (Dm.d == 256 && Dm.int4 && nk > 768) return false;
   return !Dm.want_lse && !Dm.smooth_v && !Dm.tensor_groups && Dm.pvf == PV_E4M3 && !Dm.ds32 && !Dm.seq.cu_q &&
-         nchunk <= SMALL_CALL_CHUNKS && (nk + nq) * nchunk <= SMALL_CALL_WORK;
+         nchunk <= SMALL_CALL_CHUNKS && (nk + nq) * nchunk <= (Dm.int4 ? SMALL_CALL_WORK_INT4 : SMALL_CALL_WORK_INT8);
 }
 
 // K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  The registers are the larger body's,
@@ -1393,12 +1399,9 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
 #undef SAGE_QKV
   };
   if (small_call(Dm)) {
-    if (Dm.stats_given) {
-      k_quant_q_and_stats<BF16, INT4, D><<<dim3(Dm.nQb, BH), 256, 0, s>>>(qa, SmallStats{});
-    } else {
-      const SmallStats st = {k, v, P.k_sum, P.v_max, ka.nchunk, km};
-      k_quant_q_and_stats<BF16, INT4, D><<<dim3(Dm.nQb + ka.nchunk, BH), 256, 0, s>>>(qa, st);
-    }
+    const unsigned q_blocks = (unsigned)(Dm.nQb * BH), chunks = Dm.stats_given ? 0u : (unsigned)(ka.nchunk * BHkv);
+    const SmallStats st = {k, v, P.k_sum, P.v_max, ka.nchunk, km, q_blocks};
+    k_quant_q_and_stats<BF16, INT4, D><<<q_blocks + chunks, 256, 0, s>>>(qa, st);
     quant_kv(Dm.stats_given);
     return hipGetLastError();
   }

@@ -33,11 +33,16 @@ def test_one_launch_equals_two(B, N, Nk, d, H, Hkv, mode, smooth_v):
     assert torch.equal(one, two[:-1]) and torch.equal(lse_one, lse_two[:-1])
 
 
-# the lines of small_call: 32 chunks of 256 keys, 20480 workgroups times chunks, 768 key blocks and one-block heads at 256 channels
-@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode", [
-    (1, 130, 8192, 128, 3, 1, "int4_fp8"), (1, 130, 8193, 64, 3, 1, "int8_fp8"), (128, 128, 256, 64, 32, 32, "int4_fp8"), (241, 128, 256, 64, 17, 17, "int8_fp8"),
-    (24, 70, 2048, 256, 1, 1, "int4_fp8"), (25, 70, 2048, 256, 1, 1, "int4_fp8"), (32, 60, 64, 256, 16, 4, "int8_fp8"), (27, 60, 64, 256, 19, 1, "int8_fp8")])
-def test_three_launches_equal_the_general_sequence(B, N, Nk, d, H, Hkv, mode):
+# the lines of small_call: 32 chunks of 256 keys, 14336 (4-bit) or 20480 workgroups times chunks, 768 key blocks at 256 channels; last: whether the
+# three launches serve it
+SMALL_CASES = [
+    (1, 130, 8192, 128, 3, 1, "int4_fp8", True), (1, 130, 8193, 64, 3, 1, "int8_fp8", False), (112, 128, 192, 64, 32, 32, "int4_fp8", True), (113, 128, 192, 64, 32, 32, "int4_fp8", False),
+    (128, 128, 256, 64, 32, 32, "int8_fp8", True), (241, 128, 256, 64, 17, 17, "int8_fp8", False), (24, 70, 2048, 256, 1, 1, "int4_fp8", True), (25, 70, 2048, 256, 1, 1, "int4_fp8", False),
+    (32, 60, 64, 256, 16, 4, "int8_fp8", True), (27, 60, 64, 256, 19, 1, "int8_fp8", True)]
+
+
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode,three", SMALL_CASES)
+def test_three_launches_equal_the_general_sequence(B, N, Nk, d, H, Hkv, mode, three):
     pa = _pa()
     print(f"three launches: B={B} N={N} N_kv={Nk} d={d} H={H}/{Hkv} {mode}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(B + N + Nk + d)

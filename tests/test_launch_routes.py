@@ -4,7 +4,7 @@ import itertools
 import pytest
 
 from launch_recorder import launches
-from test_gpu_kv_pair import PAIR_CASES
+from test_gpu_kv_pair import PAIR_CASES, SMALL_CASES
 
 POINTER = 4096
 BASE = dict(B=1, H=32, H_kv=32, d=128, dtype=1, mode=1, layout=1)
@@ -46,3 +46,17 @@ def test_one_sequence_more_takes_two_launches(B, N, Nk, d, H, Hkv, mode, smooth_
     assert "k_quant_kv" in _names(B=B - 1, **call)
     two = _names(B=B, **call)
     assert "k_quant_kv" not in two and "k_quant_k" in two and "k_quant_v" in two
+
+
+@pytest.mark.parametrize("B,H,Hkv,N,Nk,d,mode", [(1, 2, 2, 256, 256, 64, 0), (39, 64, 8, 58, 586, 256, 1), (2, 8, 1, 300, 300, 128, 0), (18, 64, 8, 217, 435, 128, 1)])
+def test_quantizer_of_q_and_statistics_leave_no_workgroup_empty(B, H, Hkv, N, Nk, d, mode):
+    call = dict(B=B, H=H, H_kv=Hkv, N=N, N_kv=Nk, d=d, mode=mode, dtype=1)
+    for stats, chunks in ((dict(), (Nk + 255) // 256), (dict(k_mean_in=POINTER, v_scale_in=POINTER), 0)):
+        (_, seq), = launches([("sage_attn_fwd_ex", {**call, **stats})])
+        assert seq[0].kernel == "k_quant_q_and_stats" and seq[0].grid == (B * (H * ((N + 127) // 128) + Hkv * chunks), 1, 1)
+
+
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode,three", SMALL_CASES)
+def test_small_calls_take_the_side_their_case_means(B, N, Nk, d, H, Hkv, mode, three):
+    names = _names(B=B, N=N, N_kv=Nk, d=d, H=H, H_kv=Hkv, mode=_mode(mode), kv_splits=1)
+    assert (names[:2] == ["k_quant_q_and_stats", "k_quant_kv"]) == three and ("k_col_stats" in names) == (not three)
