@@ -728,6 +728,8 @@ struct QuantKV {
   const unsigned* v_max;
   int nchunk, smooth_k;
   float code_max;
+  unsigned pair_row;         // K and V in one launch: pieces before the slower of (key block, head) goes on, and its reciprocal
+  float inv_pair_row;
 };
 
 template <int D, bool INT4, int DSM, bool REDUCE> struct QuantKLds {
@@ -1219,31 +1221,41 @@ struct SmallStats {
   unsigned* v_max;
   int nchunk;
   TensorMap km;
-  unsigned q_blocks;         // query blocks of all heads: that many workgroups, then one per chunk of keys of a KV head
+  unsigned row, turn_shift;  // workgroups per KV head; rows that begin on the same XCD are 2^turn_shift apart (31: no chunks, no turning)
+  float inv_row, inv_nQb;
 };
+// L / n from 1 / n, for the few workgroups of a paired launch: (L + 1/2) / n is at least 1 / (2 n) from an integer, and its error below
+// 2^-22 L / n, so L < 2^20 is enough.  (The integer division in front of every workgroup's loads cost 0.3 us of a small launch's 6.)
+__device__ __forceinline__ unsigned quotient(unsigned L, float inv) {
+  return (unsigned)__builtin_amdgcn_readfirstlane((int)(((float)L + 0.5f) * inv));
+}
 template <bool BF16, bool INT4, int D>
 __global__ void __launch_bounds__(256, D == 256 || !INT4 ? 2 : 4) k_quant_q_and_stats(const QuantQ q, const SmallStats st) {
   __shared__ Overlay<QuantQLds<D, INT4>, StatsLds<D, false>> lds;
-  // Numbered through the heads.  Workgroups go to the eight XCDs in turn: on a grid of (query blocks and chunks, heads) the query blocks
-  // fell on some of them only wherever such a row has 2, 4 or 8 of both, and the chunks that grouped heads leave empty on the others (39 x
-  // 64 heads on 8 of 58 queries and 586 keys, 256 channels, 8-bit: 383 us, a whole call 610 -> 372).
-  const unsigned nQb = (unsigned)q.nQb, nchunk = (unsigned)st.nchunk;
-  if (blockIdx.x < st.q_blocks) {
-    const unsigned head = blockIdx.x / nQb;
-    quant_q_block<BF16, INT4, D>(lds.a, BlockPos{blockIdx.x - head * nQb, head, nQb}, q);
+  // Row by row of a KV head: the query blocks of its heads, then its chunks.  Workgroups go to the eight XCDs in turn, so that in rows of
+  // 2, 4 or 8 the query blocks would fall on some of them only: each row that begins where an earlier one did is turned by one more.  (On a
+  // grid of (query blocks and chunks, heads), the places of the grouped heads' chunks empty, 39 x 64 heads on 8 of 58 queries and 586
+  // keys, 256 channels, 8-bit took 378 us, here 133; the whole call 598, here 353, six launches 370.  All query blocks in front of all
+  // chunks: 128 heads of 1024 tokens 23.4, here 21.6; 44 x 64 on 16 of 158 queries and 316 keys, 64 channels, 8-bit 51.3, here 40.9.)
+  const unsigned nQb = (unsigned)q.nQb, y = quotient(blockIdx.x, st.inv_row), turn = y >> st.turn_shift;
+  unsigned x = blockIdx.x - y * st.row + (turn - quotient(turn, st.inv_row) * st.row);
+  if (x >= st.row) x -= st.row;
+  const unsigned nq = nQb * (unsigned)q.G;
+  if (x < nq) {
+    const unsigned g = quotient(x, st.inv_nQb);
+    quant_q_block<BF16, INT4, D>(lds.a, BlockPos{x - g * nQb, y * (unsigned)q.G + g, nQb}, q);
   } else {
-    const unsigned c = blockIdx.x - st.q_blocks, head = c / nchunk;
-    col_stats_block<BF16, D, false>(lds.b, BlockPos{c - head * nchunk, head, nchunk}, st.k, st.v, st.k_sum, nullptr,
-                                    st.v_max, q.N, q.Nk, st.km, q.sm);
+    col_stats_block<BF16, D, false>(lds.b, BlockPos{x - nq, y, (unsigned)st.nchunk}, st.k, st.v, st.k_sum, nullptr, st.v_max, q.N, q.Nk, st.km,
+                                    q.sm);
   }
 }
 // K and V side by side (pair_piece), so that the one's arithmetic runs under the other's loads and stores whatever the length.
 template <bool BF16, bool INT4, int D, int DSM, bool SMOOTH_V, bool REDUCE>
 __global__ void __launch_bounds__(256, (quant_k_occupancy<D, INT4, DSM>())) k_quant_kv(const QuantKV a) {
   __shared__ Overlay<QuantKLds<D, INT4, DSM, REDUCE>, QuantVLds<D, REDUCE>> lds;
-  const unsigned M = gridDim.x >> 1, nKb = (unsigned)a.nKb;
-  const PairPiece pp = pair_piece(blockIdx.x, M);
-  const unsigned per = a.km.heads_inner ? M / nKb : nKb, hi = pp.piece / per, lo = pp.piece - hi * per;
+  const unsigned nKb = (unsigned)a.nKb, per = a.pair_row;
+  const PairPiece pp = pair_piece(blockIdx.x, gridDim.x >> 1);
+  const unsigned hi = quotient(pp.piece, a.inv_pair_row), lo = pp.piece - hi * per;
   const BlockPos bp = a.km.heads_inner ? BlockPos{hi, lo, nKb} : BlockPos{lo, hi, nKb};
   if (pp.second) quant_v_block<BF16, D, SMOOTH_V, PV_E4M3, REDUCE>(lds.b, bp, a);
   else quant_k_block<BF16, INT4, D, DSM, REDUCE>(lds.a, bp, a);
@@ -1338,7 +1350,7 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s, bool fi
 // body's, which tells in the 4-bit mode at 256 channels where the chip is full: it gains to 768 key blocks (64 heads of 750 tokens 103.2 /
 // 99.2, 64 of 1000 with 1024 blocks 121.7 / 123.9, 256 of 512 with 2048 183 / 194; 8-bit 99.1 / 88.2, 121.5 / 112.0, 190 / 174).
 constexpr int SMALL_CALL_WORK_INT4 = 14336, SMALL_CALL_WORK_INT8 = 20480, SMALL_CALL_CHUNKS = 32;
-static bool small_call(const Dims& Dm) {
+bool small_call(const Dims& Dm) {
   const long long nk = (long long)Dm.B * Dm.Hkv * Dm.nKb, nq = (long long)Dm.B * Dm.H * Dm.nQb;
   const int nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS;
   if (Dm.d == 256 && Dm.int4 && nk > 768) return false;
@@ -1385,6 +1397,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   ka.head_scale = nullptr; ka.stats_only = 0; ka.zero_ds = !Dm.smooth_q; ka.q_digits = P.q_digits; ka.q_dscale = P.q_dscale;
   ka.k_sum = P.k_sum; ka.v_max = P.v_max; ka.nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS; ka.smooth_k = Dm.smooth_k;
   ka.code_max = E4M3_MAX;
+  ka.pair_row = (unsigned)(km.heads_inner ? BHkv : Dm.nKb); ka.inv_pair_row = 1.0f / (float)ka.pair_row;
   // K and V in one launch; `reduced`: mean(K) and delta_V are in place
   auto quant_kv = [&](bool reduced) {
     const unsigned grid = 2u * (unsigned)Dm.nKb * (unsigned)BHkv;
@@ -1399,9 +1412,10 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
 #undef SAGE_QKV
   };
   if (small_call(Dm)) {
-    const unsigned q_blocks = (unsigned)(Dm.nQb * BH), chunks = Dm.stats_given ? 0u : (unsigned)(ka.nchunk * BHkv);
-    const SmallStats st = {k, v, P.k_sum, P.v_max, ka.nchunk, km, q_blocks};
-    k_quant_q_and_stats<BF16, INT4, D><<<q_blocks + chunks, 256, 0, s>>>(qa, st);
+    const unsigned row = (unsigned)(qa.G * Dm.nQb + (Dm.stats_given ? 0 : ka.nchunk));
+    const SmallStats st = {k, v, P.k_sum, P.v_max, ka.nchunk, km, row, Dm.stats_given ? 31u : (row % 8 == 0 ? 0u : (row % 4 == 0 ? 1u : (row % 2 == 0 ? 2u : 3u))),
+                           1.0f / (float)row, 1.0f / (float)Dm.nQb};
+    k_quant_q_and_stats<BF16, INT4, D><<<row * (unsigned)BHkv, 256, 0, s>>>(qa, st);
     quant_kv(Dm.stats_given);
     return hipGetLastError();
   }

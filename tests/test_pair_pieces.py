@@ -1,8 +1,9 @@
 """pair_piece (csrc/sage_common.h): which piece of K or V a workgroup of the paired launch works on, run on the host.  Workgroup L runs on
-XCD L % 8."""
+XCD L % 8, and the workgroups of an XCD go to its 32 CUs in turn."""
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 from paper_2411_10958_amd import build
@@ -19,7 +20,7 @@ int main() {
     }
 }
 """
-SIZES = [1, 2, 7, 8, 9, 15, 16, 17, 63, 64, 100, 768, 1001]
+SIZES = [1, 2, 7, 8, 9, 15, 16, 17, 63, 64, 100, 768, 1001, 2048]
 
 
 @pytest.fixture(scope="module")
@@ -43,3 +44,16 @@ def test_every_piece_once_and_both_kinds_on_every_xcd(pieces, M):
     for xcd in range(8):
         kinds = [kind for L, (_, kind) in enumerate(pieces[M]) if L % 8 == xcd]
         assert abs(2 * sum(kinds) - len(kinds)) <= 2
+    if M >= 512:
+        for cu in range(256):
+            kinds = [kind for L, (_, kind) in enumerate(pieces[M]) if L % 256 == cu]
+            assert abs(2 * sum(kinds) - len(kinds)) <= 2
+
+
+def test_quotients_of_the_paired_launches():
+    """quotient() in csrc/sage_prologue.hip, (L + 1/2) (1 / n) in float32, cut to an integer: every L of the launches that use it (at most
+    two pieces for each of 20480 workgroups)."""
+    L = np.arange(1 << 16, dtype=np.uint32)
+    for n in [*range(1, 2050), 3000, 4096, 5461, 8191, 8192, 16384, 20480, 40960]:
+        inv = np.float32(1.0) / np.float32(n)
+        assert np.array_equal(((L.astype(np.float32) + np.float32(0.5)) * inv).astype(np.int32), L // n), n
