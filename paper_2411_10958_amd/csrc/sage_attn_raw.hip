@@ -554,19 +554,33 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
 // would be repeated for columns that another wavefront holds on the general path), with the default groups, data types
 // and smoothing; in the 4-bit mode Delta-S in float64 (the library's own choice for so few block means).  A workgroup works
 // through its chunk block by block, 0.7 to 2.8 us each, where the general path spreads the quantizers over the chip: with few
-// workgroups and long chunks that serial chain is longer than the launches it saves.  Whole calls, general path / this one, 64
-// to 104 workgroups: 1.02 to 1.91 at any length (64, chunks of 128 blocks: 1.02 to 1.21).  4 workgroups, one chunk each: of 12
+// workgroups and long chunks that serial chain is longer than the launches it saves.  Whole calls whose general path has more than
+// two preprocessing launches, or with the statistics supplied, general path / this one, 64 to 104 workgroups: 1.02 to 1.91 at any length (64, chunks of 128 blocks: 1.02 to 1.21).  4 workgroups, one chunk each: of 12
 // blocks 1.00 (256 channels, 4-bit) to 1.30, of 20 0.86 (256, 4-bit), 1.00 (128) and 1.11 (64), in the 8-bit mode 1.02, 1.16, 1.19; of
 // 32 0.78, 0.87, 0.97 and 0.92, 1.06, 1.07.  With five to eight heads in a group, 4-bit: one workgroup of 8 blocks of 256 channels 0.94, 4
 // of 12 of 128 channels 1.06, of 20 0.90.  16 workgroups: chunks of 20 blocks of 256 channels 0.97 (4-bit) and 1.16, of 32 of 128 0.96 and
 // 1.14, of 32 of 64 1.06 and 1.12.  Automatic chunks are of 8 to 15 blocks until there are 512 workgroups or 64 chunks.
+// Where the general path has two (small_call) and the statistics are not supplied this kernel saves none: it comes after the statistics
+// and their reduction.  4-bit, up to 8 queries, 48 workgroups and more 0.99 to 2.05 at any length; 32 to 47, chunks of up to 3 blocks 1.04 to 1.35, of
+// more 0.90 to 1.21; fewer, of 4 blocks of 64 channels 0.99 to 1.08, of 2 of 128 1.01 to 1.15, of 3 of 256 1.02 to 1.09, then 0.95 (6 blocks of
+// 64), 0.90 (6 of 128), 0.86 (5 of 256), 0.66 to 0.90 (20 and more).  It adds up the block means of more queries one by one: 20 to 32 queries,
+// 48 to 95 workgroups 0.88 to 1.10, fewer 0.72 to 1.00, but 1 or 2 blocks of 256 channels 1.00 to 1.13.  8-bit, 32 workgroups and more 0.98 to
+// 2.00; 16 to 31, chunks of up to 9 / 6 / 4 blocks 0.98 to 1.70; fewer, of 6 blocks of 64 channels 0.99 to 1.04, of 4 of 128 1.01 to 1.17, of 3 of
+// 256 1.13 to 1.23, then 0.97 (10 to 12 of 64), 0.95 (7 of
+// 128), 0.83 (12 of 256).
 bool attention_raw_ok(const Dims& D) {
   const int G = D.H / D.Hkv;
   const long long groups = (long long)D.B * D.Hkv * D.splits;
   const int chunk = (D.nKb + D.splits - 1) / D.splits;
   int longest = D.int4 ? (G <= 4 ? 4 : 0) + 1024 / D.d : 8 + 1536 / D.d;
   if (groups >= 16) longest += longest / 2;
-  return G <= PACK_G && (long long)G * D.N <= 32 && (groups >= 64 || chunk <= longest) && D.kg == KGROUP && !D.block_groups && D.pvf == PV_E4M3 &&
+  int many = 64;
+  if (small_call(D) && !D.stats_given) {
+    if (!D.int4) { longest = D.d == 64 ? 6 : (D.d == 128 ? 4 : 3); if (groups >= 16) longest += longest / 2; many = 32; }
+    else if (D.N <= 8) { longest = D.d == 64 ? 4 : (D.d == 128 ? 2 : 3); many = 48; }
+    else { longest = D.d == 256 ? 2 : 0; many = 96; }
+  }
+  return G <= PACK_G && (long long)G * D.N <= 32 && (groups >= many || chunk <= longest) && D.kg == KGROUP && !D.block_groups && D.pvf == PV_E4M3 &&
          D.smooth_k && D.smooth_q && !D.smooth_v && (!D.int4 || D.ds_mode == 2);
 }
 

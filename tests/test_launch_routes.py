@@ -4,6 +4,7 @@ import itertools
 import pytest
 
 from launch_recorder import launches
+from test_gpu_few_workgroups import CASES, THREE_LAUNCHES
 from test_gpu_kv_pair import PAIR_CASES, SMALL_CASES
 
 POINTER = 4096
@@ -60,3 +61,28 @@ def test_quantizer_of_q_and_statistics_leave_no_workgroup_empty(B, H, Hkv, N, Nk
 def test_small_calls_take_the_side_their_case_means(B, N, Nk, d, H, Hkv, mode, three):
     names = _names(B=B, N=N, N_kv=Nk, d=d, H=H, H_kv=Hkv, mode=_mode(mode), kv_splits=1)
     assert (names[:2] == ["k_quant_q_and_stats", "k_quant_kv"]) == three and ("k_col_stats" in names) == (not three)
+
+
+# decode-shaped calls that the attention kernel with the quantizers in it made slower, where the general path is three launches: B, H, Hkv,
+# N, N_kv, d, mode (29.2 -> 34.2 us, 37.6 -> 45.6, 26.3 -> 30.4, 34.7 -> 36.9, 30.1 -> 33.0)
+@pytest.mark.parametrize("B,H,Hkv,N,Nk,d,mode", [(9, 2, 1, 2, 746, 128, 0), (1, 8, 8, 4, 454, 256, 0), (3, 32, 4, 4, 409, 128, 0), (9, 16, 2, 1, 1178, 64, 0),
+                                                 (5, 4, 1, 4, 863, 128, 1)])
+def test_few_workgroups_keep_the_three_launches(B, H, Hkv, N, Nk, d, mode):
+    call = dict(B=B, H=H, H_kv=Hkv, N=N, N_kv=Nk, d=d, mode=mode, causal=1, kv_splits=1)
+    assert _names(**call) == ["k_quant_q_and_stats", "k_quant_kv", "k_attn_fwd"]
+    # ... and the kernel stays where it saves launches: statistics supplied, or the log-sum-exp wanted
+    assert _names(**call, k_mean_in=POINTER, v_scale_in=POINTER) == ["k_attn_raw"]
+    assert _names(**call, lse=POINTER) == ["k_col_stats", "k_finalize_stats", "k_attn_raw"]
+
+
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,splits,raw4,raw8", CASES)
+def test_few_workgroups_take_the_side_their_case_means(B, N, Nk, d, H, Hkv, splits, raw4, raw8):
+    for mode, raw in ((0, raw4), (1, raw8)):
+        call = dict(B=B, N=N, N_kv=Nk, d=d, H=H, H_kv=Hkv, kv_splits=splits, mode=mode, causal=Nk >= N and H % 2 == 0, layout=Nk % 2, lse=POINTER)
+        assert ("k_attn_raw" in _names(**call)) == bool(raw), mode
+
+
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode,raw", THREE_LAUNCHES)
+def test_three_launches_take_the_side_their_case_means(B, N, Nk, d, H, Hkv, mode, raw):
+    names = _names(B=B, N=N, N_kv=Nk, d=d, H=H, H_kv=Hkv, kv_splits=1, mode=_mode(mode), dtype=1, causal=1)
+    assert names == (["k_col_stats", "k_finalize_stats", "k_attn_raw"] if raw else ["k_quant_q_and_stats", "k_quant_kv", "k_attn_fwd"])
