@@ -96,17 +96,11 @@ constexpr int GRID_Y_MAX = 65535;      // y of a grid is 16 bits
 inline dim3 block_grid(const TensorMap& m, int pieces, int heads) {
   return m.heads_inner ? dim3(heads, pieces) : dim3(pieces, heads);
 }
-// Two kinds of pieces in one launch, M of each: which kind and piece workgroup L of 2 M works on.  Workgroups go to the 8 XCDs in
-// turn and there to its 32 CUs in turn, so the kinds take turns every 8, and change places every 256: taken one by one each kind would
-// have every other XCD to itself, and without the change every other CU (24 heads of 20 key blocks of 64 channels, 4-bit 9.0 us for 7.7).
-struct PairPiece { unsigned piece; bool second; };
-__host__ __device__ inline PairPiece pair_piece(unsigned L, unsigned M) {
-  const unsigned tail = M & ~7u;
-  if (L < 2 * tail) return {(L >> 4) * 8 + (L & 7), (((L >> 3) ^ (L >> 8)) & 1) != 0};
-  L -= 2 * tail;
-  const unsigned r = M - tail;
-  return L < r ? PairPiece{tail + L, false} : PairPiece{tail + L - r, true};
-}
+// Two kinds of pieces in one launch, side by side in pairs, mixed: whether workgroup L (in the order they start, L ^ 1 the other of its
+// pair) takes the second kind.  Workgroups go to the 8 XCDs in turn and there to the 32 CUs in turn, so the kinds change places every 8
+// and every 256: without, each would have every other XCD to itself (2 x 344 key blocks, 96 rows of block means, 128 channels, a whole
+// call 0.98 times as fast as with two launches, with 1.00), or every other CU (24 heads of 20 blocks of 64 channels 9.0 us, with 7.7).
+__host__ __device__ inline bool pair_second(unsigned L) { return (__builtin_popcount(L & 0x109u) & 1) != 0; }
 inline TensorMap make_tensor_map(int nhd, int heads, int tokens, int d, bool varlen = false) {
   TensorMap m;
   m.heads = heads;

@@ -728,8 +728,7 @@ struct QuantKV {
   const unsigned* v_max;
   int nchunk, smooth_k;
   float code_max;
-  unsigned pair_row;         // K and V in one launch: pieces before the slower of (key block, head) goes on, and its reciprocal
-  float inv_pair_row;
+  int mixed;                 // K and V in one launch: both on every XCD
 };
 
 template <int D, bool INT4, int DSM, bool REDUCE> struct QuantKLds {
@@ -1221,43 +1220,37 @@ struct SmallStats {
   unsigned* v_max;
   int nchunk;
   TensorMap km;
-  unsigned row, turn_shift;  // workgroups per KV head; rows that begin on the same XCD are 2^turn_shift apart (31: no chunks, no turning)
-  float inv_row, inv_nQb;
+  int turn_shift, turn_mask;
+  float inv_nQb;
 };
-// L / n from 1 / n, for the few workgroups of a paired launch: (L + 1/2) / n is at least 1 / (2 n) from an integer, and its error below
-// 2^-22 L / n, so L < 2^20 is enough.  (The integer division in front of every workgroup's loads cost 0.3 us of a small launch's 6.)
-__device__ __forceinline__ unsigned quotient(unsigned L, float inv) {
-  return (unsigned)__builtin_amdgcn_readfirstlane((int)(((float)L + 0.5f) * inv));
-}
 template <bool BF16, bool INT4, int D>
 __global__ void __launch_bounds__(256, D == 256 || !INT4 ? 2 : 4) k_quant_q_and_stats(const QuantQ q, const SmallStats st) {
   __shared__ Overlay<QuantQLds<D, INT4>, StatsLds<D, false>> lds;
-  // Row by row of a KV head: the query blocks of its heads, then its chunks.  Workgroups go to the eight XCDs in turn, so that in rows of
-  // 2, 4 or 8 the query blocks would fall on some of them only: each row that begins where an earlier one did is turned by one more.  (On a
-  // grid of (query blocks and chunks, heads), the places of the grouped heads' chunks empty, 39 x 64 heads on 8 of 58 queries and 586
-  // keys, 256 channels, 8-bit took 378 us, here 133; the whole call 598, here 353, six launches 370.  All query blocks in front of all
-  // chunks: 128 heads of 1024 tokens 23.4, here 21.6; 44 x 64 on 16 of 158 queries and 316 keys, 64 channels, 8-bit 51.3, here 40.9.)
-  const unsigned nQb = (unsigned)q.nQb, y = quotient(blockIdx.x, st.inv_row), turn = y >> st.turn_shift;
-  unsigned x = blockIdx.x - y * st.row + (turn - quotient(turn, st.inv_row) * st.row);
-  if (x >= st.row) x -= st.row;
-  const unsigned nq = nQb * (unsigned)q.G;
+  // A row of the grid: the query blocks of a KV head's heads, then its chunks.  Workgroups go to the eight XCDs in turn, so that in rows of an
+  // even length the query blocks would fall on some of them only: a row that begins where an earlier one did is turned.  (On a grid of
+  // (query blocks and chunks, heads), the places of the grouped heads' chunks empty, 39 x 64 heads on 8 of 58 queries and 586 keys, 256
+  // channels, 8-bit took 378 us, turned 133; the whole call 598, now 353, six launches 370.  All query blocks in front of all chunks: 128
+  // heads of 1024 tokens 23.4, here 21.6; 44 x 64 on 16 of 158 queries and 316 keys, 64 channels, 8-bit 51.3, here 40.9.)
+  const unsigned nQb = (unsigned)q.nQb, nq = nQb * (unsigned)q.G;
+  unsigned x = blockIdx.x + ((blockIdx.y >> st.turn_shift) & (unsigned)st.turn_mask);
+  if (x >= gridDim.x) x -= gridDim.x;
   if (x < nq) {
-    const unsigned g = quotient(x, st.inv_nQb);
-    quant_q_block<BF16, INT4, D>(lds.a, BlockPos{x - g * nQb, y * (unsigned)q.G + g, nQb}, q);
+    // x / nQb: (x + 1/2) / nQb is at least 1 / (2 nQb) from an integer, and the error of its FP32 value below 2^-22 x / nQb
+    const unsigned g = q.G == 1 ? 0u : (unsigned)__builtin_amdgcn_readfirstlane((int)(((float)x + 0.5f) * st.inv_nQb));
+    quant_q_block<BF16, INT4, D>(lds.a, BlockPos{x - g * nQb, blockIdx.y * (unsigned)q.G + g, nQb}, q);
   } else {
-    col_stats_block<BF16, D, false>(lds.b, BlockPos{x - nq, y, (unsigned)st.nchunk}, st.k, st.v, st.k_sum, nullptr, st.v_max, q.N, q.Nk, st.km,
-                                    q.sm);
+    col_stats_block<BF16, D, false>(lds.b, BlockPos{x - nq, blockIdx.y, (unsigned)st.nchunk}, st.k, st.v, st.k_sum, nullptr, st.v_max, q.N, q.Nk,
+                                    st.km, q.sm);
   }
 }
-// K and V side by side (pair_piece), so that the one's arithmetic runs under the other's loads and stores whatever the length.
+// K and V of a key block side by side, so that the one's arithmetic runs under the other's loads and stores whatever the length.
 template <bool BF16, bool INT4, int D, int DSM, bool SMOOTH_V, bool REDUCE>
 __global__ void __launch_bounds__(256, (quant_k_occupancy<D, INT4, DSM>())) k_quant_kv(const QuantKV a) {
   __shared__ Overlay<QuantKLds<D, INT4, DSM, REDUCE>, QuantVLds<D, REDUCE>> lds;
-  const unsigned nKb = (unsigned)a.nKb, per = a.pair_row;
-  const PairPiece pp = pair_piece(blockIdx.x, gridDim.x >> 1);
-  const unsigned hi = quotient(pp.piece, a.inv_pair_row), lo = pp.piece - hi * per;
-  const BlockPos bp = a.km.heads_inner ? BlockPos{hi, lo, nKb} : BlockPos{lo, hi, nKb};
-  if (pp.second) quant_v_block<BF16, D, SMOOTH_V, PV_E4M3, REDUCE>(lds.b, bp, a);
+  BlockPos bp = block_pos(a.km);
+  const bool is_v = a.mixed ? pair_second(blockIdx.y * gridDim.x + blockIdx.x) : (bp.x & 1) != 0;
+  bp.x >>= 1; bp.nx >>= 1;
+  if (is_v) quant_v_block<BF16, D, SMOOTH_V, PV_E4M3, REDUCE>(lds.b, bp, a);
   else quant_k_block<BF16, INT4, D, DSM, REDUCE>(lds.a, bp, a);
 }
 
@@ -1344,31 +1337,36 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s, bool fi
 // says) / three launches, 4-bit then 8-bit: 2 heads of 64 channels, 256 tokens 19.1 / 15.9, 19.6 / 16.3; 128 of 128, 500 tokens (1536 workgroups, 2
 // chunks) 62.6 / 51.0, 61.8 / 53.9; 512 of 200 (3072, 1) 83.6 / 75.1, 81.8 / 71.7; 128 of 1024 (3072, 4) 115.3 / 113.8, 117.3 / 112.5; 32 on 8 of
 // 3000 (1144, 12) 137.5 / 134.1, 146.4 / 143.1; 8 of 5000 (952, 20) 151.4 / 149.5, 150.0 / 148.0; 8 on 1 of 8000 (629, 32) 232.3 / 233.5, 212.5 /
-// 211.8; 2 of 12000 (564, 47) 162.3 / 165.9, 164.8 / 171.5.  By workgroups times chunks, general / three: 4-bit 10000 to 14336, 64 channels 1.00 to
-// 1.03, 128 1.01 to 1.04, 15000 to 20480 0.99 to 1.01, 0.96 to 1.02; 8-bit 15000 to 20480 0.99 to 1.09, 30000 to 40000 0.96 to 1.01.
+// 211.8; 2 of 12000 (564, 47) 162.3 / 165.9, 164.8 / 171.5; 32 on 8 of 3362 (1288, 14), 4-bit 113.3 / 106.6.  By workgroups times chunks, general /
+// three: 4-bit 10000 to 14336, 64 channels 1.00 to 1.03, 128 1.01 to 1.04, 15000 to 20480 0.99 to 1.01, 0.96 (many key blocks) to 1.06 (many rows
+// of block means); 8-bit 15000 to 20480 0.99 to 1.09; 21000 to 40000 0.92 to 1.02.
 // The bodies of a pair share its LDS (side by side it held pairs of d >= 128 to fewer workgroups), but its registers are the larger
-// body's, which tells in the 4-bit mode at 256 channels where the chip is full: it gains to 768 key blocks (64 heads of 750 tokens 103.2 /
-// 99.2, 64 of 1000 with 1024 blocks 121.7 / 123.9, 256 of 512 with 2048 183 / 194; 8-bit 99.1 / 88.2, 121.5 / 112.0, 190 / 174).
-constexpr int SMALL_CALL_WORK_INT4 = 14336, SMALL_CALL_WORK_INT8 = 20480, SMALL_CALL_CHUNKS = 32;
+// body's, which tells in the 4-bit mode at 256 channels where the chip is full: it gains to 768 key blocks, with many rows of block means to 384 (64 on 8 heads of
+// 1607 queries and 3214 keys, 408 blocks, 104 rows, statistics supplied 317 / 325; 64 heads of 750 tokens 103.2 / 99.2, 64 of 1000 with 1024 blocks 121.7 / 123.9, 256 of 512 with 2048 183 / 194; 8-bit 99.1 / 88.2, 121.5 / 112.0, 190 / 174).
+constexpr int SMALL_CALL_WORK = 20480, SMALL_CALL_CHUNKS = 32;
+// Rows of block means that a key block meets: up to 24, two steps of the Delta-S product, K's workgroups are about as long as V's.
+static bool few_rows(const Dims& Dm) { return (long long)(Dm.H / Dm.Hkv) * Dm.nQb <= 24; }
 bool small_call(const Dims& Dm) {
   const long long nk = (long long)Dm.B * Dm.Hkv * Dm.nKb, nq = (long long)Dm.B * Dm.H * Dm.nQb;
   const int nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS;
-  if (Dm.d == 256 && Dm.int4 && nk > 768) return false;
+  if (Dm.d == 256 && Dm.int4 && nk > (few_rows(Dm) ? 768 : 384)) return false;
   return !Dm.want_lse && !Dm.smooth_v && !Dm.tensor_groups && Dm.pvf == PV_E4M3 && !Dm.ds32 && !Dm.seq.cu_q &&
-         nchunk <= SMALL_CALL_CHUNKS && (nk + nq) * nchunk <= (Dm.int4 ? SMALL_CALL_WORK_INT4 : SMALL_CALL_WORK_INT8);
+         nchunk <= SMALL_CALL_CHUNKS && (nk + nq) * nchunk <= SMALL_CALL_WORK;
 }
 
 // K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  The registers are the larger body's,
 // K's with Delta-S, so where K fills the chip by itself and its workgroups are long (many rows of block means) V's are better off in a
 // launch of their own.  Whole calls, time of two launches / one, by key blocks and rows per KV head.  4-bit: 64 channels 240 blocks, 16 rows 1.07,
 // 592, 148 rows 1.00, 728, 144 rows 0.96, 768, 8 rows 1.04; 128 channels 392, 52 rows 1.02, 448 to 520, 64 to 132 rows 0.97
-// to 0.98, 668, 108 rows 0.94, 706, 16 rows 1.02, 984, 22 rows 1.00; 256 channels 368, 32 rows 1.01, 420, 80 rows 0.97, 520 to 672, 2 rows 0.99 to
-// 1.00, 768, 12 to 24 rows 1.01 to 1.02, 784, 4 rows 0.97.  8-bit, whose two quantizers are alike: 64 channels 656 blocks 1.06, 4160 1.01, 7872
-// 1.02, 14632 1.02, 15700 0.99; 128 channels 640 1.06, 3716 1.01, 7936 1.01, 13984 1.00; 256 channels 768 1.01 to 1.04 (2048 0.95).
+// to 0.98, 668, 108 rows 0.94, 706, 16 rows 1.02, 984, 22 rows 1.00; 256 channels 250, 39 rows 1.04, 328 to 432, 48 to 72 rows 0.99, 500, 56 rows
+// 0.97, 512 to 640, 1 to 24 rows 1.00 to 1.04, 736, 12 rows 0.99, 960, 2 rows 0.95.  8-bit, whose two quantizers are alike, 64 and 128 channels,
+// us: 1536 blocks 119.3 / 118.2, 3912 142.5 / 140.6, 4928 165.8 / 165.0, 5056 139.4 / 140.9, 7360 315.3 / 320.0, 13496 234.4 / 238.3; 256 channels 584
+// 179.4 / 176.4, 768 74.9 / 74.2, 2048 389 / 409.  A packed batch has fewer blocks and rows than its longest sequence says: 8 sequences of up to 3456 tokens, one head, 440 blocks and 27
+// rows by that count, 67 / 62 us.
 static bool kv_pair(const Dims& Dm) {
   if (Dm.tensor_groups || Dm.pvf != PV_E4M3 || Dm.ds32) return false;
-  const bool few_rows = (long long)(Dm.H / Dm.Hkv) * Dm.nQb <= 24;
-  const int line = !Dm.int4 ? (Dm.d == 256 ? 768 : 16384) : (few_rows ? 768 : (Dm.d == 64 ? 640 : 400));
+  const int line = !Dm.int4 ? (Dm.d == 256 ? 768 : 4608)
+                 : Dm.seq.cu_q ? 768 : Dm.d == 256 ? (few_rows(Dm) ? 640 : 320) : (few_rows(Dm) ? 768 : (Dm.d == 64 ? 640 : 400));
   return (long long)Dm.B * Dm.Hkv * Dm.nKb <= line;
 }
 
@@ -1397,10 +1395,13 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   ka.head_scale = nullptr; ka.stats_only = 0; ka.zero_ds = !Dm.smooth_q; ka.q_digits = P.q_digits; ka.q_dscale = P.q_dscale;
   ka.k_sum = P.k_sum; ka.v_max = P.v_max; ka.nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS; ka.smooth_k = Dm.smooth_k;
   ka.code_max = E4M3_MAX;
-  ka.pair_row = (unsigned)(km.heads_inner ? BHkv : Dm.nKb); ka.inv_pair_row = 1.0f / (float)ka.pair_row;
+  // Taken one by one, K and V have every other XCD to themselves, on a grid that runs through the key blocks first.  That is the better
+  // order (two kinds of code and of registers kept apart: 24 heads of 493 tokens, 8-bit, K and V 7.7 us mixed, 6.8 apart; 16 on 8 heads of
+  // 1261 tokens of 256 channels, 4-bit, whole call 81.6, 80.2) unless K takes much longer than V and the chip is full.
+  ka.mixed = INT4 && D < 256 && !km.heads_inner && (!few_rows(Dm) || (long long)BHkv * Dm.nKb >= 256);
   // K and V in one launch; `reduced`: mean(K) and delta_V are in place
   auto quant_kv = [&](bool reduced) {
-    const unsigned grid = 2u * (unsigned)Dm.nKb * (unsigned)BHkv;
+    const dim3 grid = block_grid(km, 2 * Dm.nKb, BHkv);
 #define SAGE_QKV(DSM_)                                                                                                  \
   do {                                                                                                                  \
     if (Dm.smooth_v) k_quant_kv<BF16, INT4, D, DSM_, true, false><<<grid, 256, 0, s>>>(ka);                              \
@@ -1412,10 +1413,10 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
 #undef SAGE_QKV
   };
   if (small_call(Dm)) {
-    const unsigned row = (unsigned)(qa.G * Dm.nQb + (Dm.stats_given ? 0 : ka.nchunk));
-    const SmallStats st = {k, v, P.k_sum, P.v_max, ka.nchunk, km, row, Dm.stats_given ? 31u : (row % 8 == 0 ? 0u : (row % 4 == 0 ? 1u : (row % 2 == 0 ? 2u : 3u))),
-                           1.0f / (float)row, 1.0f / (float)Dm.nQb};
-    k_quant_q_and_stats<BF16, INT4, D><<<row * (unsigned)BHkv, 256, 0, s>>>(qa, st);
+    // rows of 8 n workgroups all begin on the same XCD, of 8 n + 4 every other one, of an even number every fourth
+    const int row = qa.G * Dm.nQb + (Dm.stats_given ? 0 : ka.nchunk), even = Dm.stats_given ? 1 : row & -row;
+    const SmallStats st = {k, v, P.k_sum, P.v_max, ka.nchunk, km, even >= 8 ? 0 : (even == 4 ? 1 : 2), even >= 8 ? 7 : even - 1, 1.0f / (float)Dm.nQb};
+    k_quant_q_and_stats<BF16, INT4, D><<<dim3(row, BHkv), 256, 0, s>>>(qa, st);
     quant_kv(Dm.stats_given);
     return hipGetLastError();
   }

@@ -14,9 +14,9 @@ def _pa():
 # sequences, N, N_kv, d, H, Hkv, mode, smooth_v: one sequence more than the pair takes (tests/test_launch_routes.py holds the launches to
 # that).  4-bit with few rows of block means, with many; 8-bit
 PAIR_CASES = [
-    (25, 100, 2047, 64, 2, 1, "int4_fp8", False), (25, 129, 1985, 128, 1, 1, "int4_fp8", True), (25, 70, 2000, 256, 3, 1, "int4_fp8", False),
-    (21, 500, 2001, 64, 7, 1, "int4_fp8", True), (13, 3201, 2048, 128, 1, 1, "int4_fp8", False), (13, 520, 2040, 256, 5, 1, "int4_fp8", False),
-    (25, 300, 2048, 256, 1, 1, "int8_fp8", True), (25, 67, 2047, 256, 1, 1, "int8_fp8", False), (129, 2, 70, 128, 64, 64, "int8_fp8", True), (129, 33, 5, 64, 128, 128, "int8_fp8", False)]
+    (25, 100, 2047, 64, 2, 1, "int4_fp8", False), (25, 129, 1985, 128, 1, 1, "int4_fp8", True), (21, 70, 2000, 256, 3, 1, "int4_fp8", False),
+    (21, 500, 2001, 64, 7, 1, "int4_fp8", True), (13, 3201, 2048, 128, 1, 1, "int4_fp8", False), (11, 520, 2040, 256, 5, 1, "int4_fp8", False),
+    (25, 300, 2048, 256, 1, 1, "int8_fp8", True), (25, 67, 2047, 256, 1, 1, "int8_fp8", False), (145, 64, 2001, 128, 2, 1, "int8_fp8", False), (145, 33, 2048, 64, 1, 1, "int8_fp8", True)]
 
 
 @pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode,smooth_v", PAIR_CASES)
@@ -33,11 +33,12 @@ def test_one_launch_equals_two(B, N, Nk, d, H, Hkv, mode, smooth_v):
     assert torch.equal(one, two[:-1]) and torch.equal(lse_one, lse_two[:-1])
 
 
-# the lines of small_call: 32 chunks of 256 keys, 14336 (4-bit) or 20480 workgroups times chunks, 768 key blocks at 256 channels; last: whether the
+# the lines of small_call: 32 chunks of 256 keys, 20480 workgroups times chunks, 768 key blocks (384 with many rows of block means) at 256 channels; last: whether the
 # three launches serve it
 SMALL_CASES = [
-    (1, 130, 8192, 128, 3, 1, "int4_fp8", True), (1, 130, 8193, 64, 3, 1, "int8_fp8", False), (112, 128, 192, 64, 32, 32, "int4_fp8", True), (113, 128, 192, 64, 32, 32, "int4_fp8", False),
+    (1, 130, 8192, 128, 3, 1, "int4_fp8", True), (1, 130, 8193, 64, 3, 1, "int8_fp8", False), (128, 128, 256, 64, 32, 32, "int4_fp8", True), (129, 128, 256, 64, 32, 32, "int4_fp8", False),
     (128, 128, 256, 64, 32, 32, "int8_fp8", True), (241, 128, 256, 64, 17, 17, "int8_fp8", False), (24, 70, 2048, 256, 1, 1, "int4_fp8", True), (25, 70, 2048, 256, 1, 1, "int4_fp8", False),
+    (12, 600, 2048, 256, 5, 1, "int4_fp8", True), (13, 600, 2048, 256, 5, 1, "int4_fp8", False),
     (32, 60, 64, 256, 16, 4, "int8_fp8", True), (27, 60, 64, 256, 19, 1, "int8_fp8", True)]
 
 

@@ -54,7 +54,7 @@ def test_quantizer_of_q_and_statistics_leave_no_workgroup_empty(B, H, Hkv, N, Nk
     call = dict(B=B, H=H, H_kv=Hkv, N=N, N_kv=Nk, d=d, mode=mode, dtype=1)
     for stats, chunks in ((dict(), (Nk + 255) // 256), (dict(k_mean_in=POINTER, v_scale_in=POINTER), 0)):
         (_, seq), = launches([("sage_attn_fwd_ex", {**call, **stats})])
-        assert seq[0].kernel == "k_quant_q_and_stats" and seq[0].grid == (B * (H * ((N + 127) // 128) + Hkv * chunks), 1, 1)
+        assert seq[0].kernel == "k_quant_q_and_stats" and seq[0].grid == (H // Hkv * ((N + 127) // 128) + chunks, B * Hkv, 1)
 
 
 @pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode,three", SMALL_CASES)
