@@ -75,8 +75,9 @@ enum { SAGE_DT_FP16 = 0, SAGE_DT_BF16 = 1 };
    the last bits of the scores, so once in about 10^5 scores the FP8 code of P~ comes out one step away
    from what the exact Delta-S gives.  Off by default; ignored by the 8-bit mode.
    SAGE_FLAG_FP64_DELTA_S / SAGE_FLAG_DIGIT_DELTA_S: which exact form of the Delta-S product runs.  "Digit": both
-   factors are cut into 7-bit fixed-point digits (42 bits below each row's largest magnitude) and multiplied exactly on
-   the INT8 matrix unit (30 of the 36 digit pairs); "FP64": the FP64 matrix instruction.  Both agree with the float64
+   factors are cut into six signed bytes of a 48-bit fixed-point number (rounded at 2^(E - 48), E three above the exponent of the
+   row's largest magnitude) and multiplied exactly on the INT8 matrix unit (the 26 of 36 byte pairs whose indices add up
+   to 6 or less); "FP64": the FP64 matrix instruction.  Both agree with the float64
    inner product to the last bit of the FP32 result (the tests allow one value in 10^3 to differ by that bit).  With neither flag the library picks: digits, except when a key
    block meets at most 16 block means ((H / H_kv) ceil(N / 128) <= 16), where one chain of FP64 instructions is cheaper.
    Ignored by the 8-bit mode; FP32 wins over both, FP64 over digit. */

@@ -38,14 +38,14 @@ __device__ __forceinline__ double pair_sum(double (&x)[N]) {
 // 7 attend: each forms the block's scores and P~ for all 32 columns - the same values in both - and multiplies them
 // with its own half of the channels of V^.  LDS holds two blocks, one barrier per block.
 //
-// Bound: each block is a chain of its wavefronts' work behind one barrier; the split above is what makes the longest of
-// them short, and keeps every part in 128 registers (d = 64 and 128; d = 256: 189), so that two workgroups share a CU.
-// 4 x 8 KV heads, 32768 keys, d = 128, one query, statistics supplied, whole call: 101 us in the 4-bit mode (537 MB: 5.3 TB/s),
-// 88 in the 8-bit one (6.1 TB/s; quantizers + attention kernel 185).  Four wavefronts quantizing both and four attending, with 16
-// spilled registers, rows addressed and padded lane by lane and every mean of Delta-S waited for by itself: 153 / 122; those mended
-// and two attending wavefronts instead of four: 139 / 103.  16 of 256 channels, 30000 keys, 4-bit: 147, 128, 114.  16 x 16 of 64
-// channels, 5003 keys, 8-bit: 139, 82, 74.  Tried: one attending wavefront (d = 64: 71 -> 69 us on grouped heads, 74 -> 77
-// on ungrouped ones); four for V at d = 256 (128 -> 128, 8-bit 70 -> 82).  K by 64-byte pieces of four lanes and an exchange in
+// Bound: each block is a chain of its wavefronts' work behind one barrier; the split above is what makes the longest of them short,
+// and keeps every part in 128 registers (d = 64 and 128; d = 256: 189), so that two workgroups share a CU. 4 x 8 KV heads, 32768 keys,
+// d = 128, one query, statistics supplied: 102 us in the 4-bit mode (537 MB: 5.3 TB/s), 83 in the 8-bit one (6.4 TB/s), and a merge of
+// 5 us.  Whole calls, both modes: quantizers and attention kernel 255 / 185, four wavefronts quantizing both and four attending, with
+// 16 spilled registers, rows addressed and padded lane by lane and every mean of Delta-S waited for by itself 153 / 122, those mended
+// 139 / 103 with two attending wavefronts instead of four, this form 101 / 88. 16 of 256 channels, 30000 keys, 4-bit: 147, 128, 114.
+// 16 x 16 of 64 channels, 5003 keys, 8-bit: 139, 82, 74.  Tried: one attending wavefront (d = 64: 71 -> 69 us on grouped heads, 74 ->
+// 77 on ungrouped ones); four for V at d = 256 (128 -> 128, 8-bit 70 -> 82).  K by 64-byte pieces of four lanes and an exchange in
 // registers pays at d = 256 only, where a lane's own piece is a whole cache line (quad_exchange).
 // HEADS: 4, or PACK_G where the 4-bit mode has more than four query heads per KV head (two chains of the Delta-S product).
 constexpr int RAW_V = 2, RAW_ATT = 2, RAW_THREADS = 64 * (4 + RAW_V + RAW_ATT);
@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
   if constexpr (INT4) {
     for (int idx = t; idx < HEADS * D; idx += RAW_THREADS) {
       const int g = idx / D, c = idx % D;
-      // block mean of the head's queries (one block: at most 32), added in k_quant_q4's order
+      // block mean of the head's queries (one block: at most 32), added in quant_q4_block's order
       double mean = 0.0;
       if (g < G) {
         constexpr int RG = D / 16, NG = 32 / RG;             // rows are summed in runs of RG, the runs in pairs
@@ -334,7 +334,7 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
   // few rows costs 7 us: 16 x 8 KV heads, 5003 keys, 8-bit mode 85 / 79 us, 4 x 8, 32768 keys, 4-bit 263 / 243; 16 of 256 channels,
   // 30000 keys, 4-bit 238 / 231).  Lane (n, half)
   // supplies, of its column's query, PC consecutive channels per operand: smoothed
-  // (4-bit mode), scale from the pair of queries, codes as k_quant_q4 / k_quant_q8 give them.
+  // (4-bit mode), scale from the pair of queries, codes as quant_q4_block / quant_q8_block give them.
   constexpr int PC = INT4 ? 32 : 16;
   typename QkOperand<INT4>::type qreg[NP];
   float dq;
@@ -550,23 +550,24 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
   }
 }
 
-// Calls the kernel above serves: the 32 columns of a tile hold all queries that meet a KV head (beyond 32 the softmax piece
-// would be repeated for columns that another wavefront holds on the general path), with the default groups, data types
-// and smoothing; in the 4-bit mode Delta-S in float64 (the library's own choice for so few block means).  A workgroup works
-// through its chunk block by block, 0.7 to 2.8 us each, where the general path spreads the quantizers over the chip: with few
-// workgroups and long chunks that serial chain is longer than the launches it saves.  Whole calls whose general path has more than
-// two preprocessing launches, or with the statistics supplied, general path / this one, 64 to 104 workgroups: 1.02 to 1.91 at any length (64, chunks of 128 blocks: 1.02 to 1.21).  4 workgroups, one chunk each: of 12
-// blocks 1.00 (256 channels, 4-bit) to 1.30, of 20 0.86 (256, 4-bit), 1.00 (128) and 1.11 (64), in the 8-bit mode 1.02, 1.16, 1.19; of
-// 32 0.78, 0.87, 0.97 and 0.92, 1.06, 1.07.  With five to eight heads in a group, 4-bit: one workgroup of 8 blocks of 256 channels 0.94, 4
-// of 12 of 128 channels 1.06, of 20 0.90.  16 workgroups: chunks of 20 blocks of 256 channels 0.97 (4-bit) and 1.16, of 32 of 128 0.96 and
-// 1.14, of 32 of 64 1.06 and 1.12.  Automatic chunks are of 8 to 15 blocks until there are 512 workgroups or 64 chunks.
-// Where the general path has two (small_call) and the statistics are not supplied this kernel saves none: it comes after the statistics
-// and their reduction.  4-bit, up to 8 queries, 48 workgroups and more 0.99 to 2.05 at any length; 32 to 47, chunks of up to 3 blocks 1.04 to 1.35, of
-// more 0.90 to 1.21; fewer, of 4 blocks of 64 channels 0.99 to 1.08, of 2 of 128 1.01 to 1.15, of 3 of 256 1.02 to 1.09, then 0.95 (6 blocks of
-// 64), 0.90 (6 of 128), 0.86 (5 of 256), 0.66 to 0.90 (20 and more).  It adds up the block means of more queries one by one: 20 to 32 queries,
-// 48 to 95 workgroups 0.88 to 1.10, fewer 0.72 to 1.00, but 1 or 2 blocks of 256 channels 1.00 to 1.13.  8-bit, 32 workgroups and more 0.98 to
-// 2.00; 16 to 31, chunks of up to 9 / 6 / 4 blocks 0.98 to 1.70; fewer, of 6 blocks of 64 channels 0.99 to 1.04, of 4 of 128 1.01 to 1.17, of 3 of
-// 256 1.13 to 1.23, then 0.97 (10 to 12 of 64), 0.95 (7 of
+// Calls the kernel above serves: the 32 columns of a tile hold all queries that meet a KV head (beyond 32 the softmax piece would be
+// repeated for columns that another wavefront holds on the general path), with the default groups, data types and smoothing; in the
+// 4-bit mode Delta-S in float64 (the library's own choice for so few block means).  A workgroup works through its chunk block by
+// block, 0.7 to 2.8 us each, where the general path spreads the quantizers over the chip: with few workgroups and long chunks that
+// serial chain is longer than the launches it saves.  Whole calls whose general path has more than two preprocessing launches, or with
+// the statistics supplied, general path / this one, 64 to 104 workgroups: 1.02 to 1.91 at any length (64, chunks of 128 blocks: 1.02
+// to 1.21).  4 workgroups, one chunk each: of 12 blocks 1.00 (256 channels, 4-bit) to 1.30, of 20 0.86 (256, 4-bit), 1.00 (128) and
+// 1.11 (64), in the 8-bit mode 1.02, 1.16, 1.19; of 32 0.78, 0.87, 0.97 and 0.92, 1.06, 1.07.  With five to eight heads in a group,
+// 4-bit: one workgroup of 8 blocks of 256 channels 0.94, 4 of 12 of 128 channels 1.06, of 20 0.90.  16 workgroups: chunks of 20 blocks
+// of 256 channels 0.97 (4-bit) and 1.16, of 32 of 128 0.96 and 1.14, of 32 of 64 1.06 and 1.12.  Automatic chunks are of 8 to 15
+// blocks until there are 512 workgroups or 64 chunks.
+// Where the general path has two (small_call) and the statistics are not supplied this kernel saves none: it comes after the
+// statistics and their reduction.  4-bit, up to 8 queries, 48 workgroups and more 0.99 to 2.05 at any length; 32 to 47, chunks of up
+// to 3 blocks 1.04 to 1.35, of more 0.90 to 1.21; fewer, of 4 blocks of 64 channels 0.99 to 1.08, of 2 of 128 1.01 to 1.15, of 3 of
+// 256 1.02 to 1.09, then 0.95 (6 blocks of 64), 0.90 (6 of 128), 0.86 (5 of 256), 0.66 to 0.90 (20 and more).  It adds up the block
+// means of more queries one by one: 20 to 32 queries, 48 to 95 workgroups 0.88 to 1.10, fewer 0.72 to 1.00, but 1 or 2 blocks of 256
+// channels 1.00 to 1.13.  8-bit, 32 workgroups and more 0.98 to 2.00; 16 to 31, chunks of up to 9 / 6 / 4 blocks 0.98 to 1.70; fewer,
+// of 6 blocks of 64 channels 0.99 to 1.04, of 4 of 128 1.01 to 1.17, of 3 of 256 1.13 to 1.23, then 0.97 (10 to 12 of 64), 0.95 (7 of
 // 128), 0.83 (12 of 256).
 bool attention_raw_ok(const Dims& D) {
   const int G = D.H / D.Hkv;

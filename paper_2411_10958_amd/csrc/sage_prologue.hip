@@ -477,7 +477,7 @@ __device__ __forceinline__ void quant_q8_block(QuantQLds<D, false>& lds, const B
 
 // Q, 4-bit variant: block mean, smoothing, pair-group quantization (Algorithm 1: q_bar_i =
 // mean(Q_i), psi_Q(Q_i - q_bar_i)).  Two thread-to-data maps, joined through LDS:
-//  - loading and the exact column sums of the block mean use the coalesced map of k_quant_q8 (a
+//  - loading and the exact column sums of the block mean use the coalesced map of quant_q8_block (a
 //    thread owns 8 channels of BQ*D/2048 rows), and the raw 16-bit rows are parked in LDS;
 //  - quantization uses the map the codes are consumed in: a thread owns D/4 consecutive channels
 //    of the two queries of one scale group, i.e. (half of) one MFMA lane's payload per query, so
@@ -699,8 +699,10 @@ constexpr int DS_ROWS = 16;     // block means per step of the Delta-S product: 
 // an accumulator (below 2^24), and the pairs with a + b > 6 are left out: together less than 2^-49 of
 // |x|_max |y|_max d.  The result agrees with the float64 inner product far below its FP32 rounding, at a quarter of
 // the FP64 instruction's time, and - being INT8 matrix work - it runs alongside the vector work of the quantizers.
-// Bound: vector issue (four cycles an instruction, whatever its class, once the wavefronts of a SIMD are out of step), which
-// the cutting of the keys and the joining of the accumulators set for a few rows, and the matrix pipe together for many.
+// Bound: for a few rows vector issue (four cycles an instruction, whatever its class, once the wavefronts of a SIMD are out of
+// step), which the cutting of the keys and the joining of the accumulators set; for many the chain of a step, loads, matrix
+// instructions, joining, one barrier: 32 heads of 32768 tokens, causal, vector issue 56 % and matrix pipe 58 % busy; 16 heads of 8192
+// tokens of 256 channels, two wavefronts per SIMD, 46 % and 29 %.
 enum { DS_DIGITS = 0, DS_FP32 = 1, DS_FP64 = 2 };
 
 // Arguments of the K and V quantizers.  Where the statistics pass left partial results that nobody has reduced (k_sum, v_max
@@ -1331,18 +1333,19 @@ static void launch_stats_t(const Dims& Dm, const Ptrs& P, hipStream_t s, bool fi
   }
 }
 
-// Calls that the three-launch sequence serves (k_quant_q_and_stats, k_quant_kv): E4M3, exact Delta-S, no row constants (they
-// need mean(K) before Q).  What it costs is the reduction of the statistics, which every workgroup does for its head: the workgroups
-// of the general sequence's Q and K launches times the chunks of a head.  Whole calls, full attention, us, general sequence (K and V as kv_pair
-// says) / three launches, 4-bit then 8-bit: 2 heads of 64 channels, 256 tokens 19.1 / 15.9, 19.6 / 16.3; 128 of 128, 500 tokens (1536 workgroups, 2
-// chunks) 62.6 / 51.0, 61.8 / 53.9; 512 of 200 (3072, 1) 83.6 / 75.1, 81.8 / 71.7; 128 of 1024 (3072, 4) 115.3 / 113.8, 117.3 / 112.5; 32 on 8 of
-// 3000 (1144, 12) 137.5 / 134.1, 146.4 / 143.1; 8 of 5000 (952, 20) 151.4 / 149.5, 150.0 / 148.0; 8 on 1 of 8000 (629, 32) 232.3 / 233.5, 212.5 /
-// 211.8; 2 of 12000 (564, 47) 162.3 / 165.9, 164.8 / 171.5; 32 on 8 of 3362 (1288, 14), 4-bit 113.3 / 106.6.  By workgroups times chunks, general /
-// three: 4-bit 10000 to 14336, 64 channels 1.00 to 1.03, 128 1.01 to 1.04, 15000 to 20480 0.99 to 1.01, 0.96 (many key blocks) to 1.06 (many rows
-// of block means); 8-bit 15000 to 20480 0.99 to 1.09; 21000 to 40000 0.92 to 1.02.
-// The bodies of a pair share its LDS (side by side it held pairs of d >= 128 to fewer workgroups), but its registers are the larger
-// body's, which tells in the 4-bit mode at 256 channels where the chip is full: it gains to 768 key blocks, with many rows of block means to 384 (64 on 8 heads of
-// 1607 queries and 3214 keys, 408 blocks, 104 rows, statistics supplied 317 / 325; 64 heads of 750 tokens 103.2 / 99.2, 64 of 1000 with 1024 blocks 121.7 / 123.9, 256 of 512 with 2048 183 / 194; 8-bit 99.1 / 88.2, 121.5 / 112.0, 190 / 174).
+// Calls that the three-launch sequence serves (k_quant_q_and_stats, k_quant_kv): E4M3, exact Delta-S, no row constants (they need mean(K)
+// before Q).  What it costs is the reduction of the statistics, which every workgroup does for its head: the workgroups of the general
+// sequence's Q and K launches times the chunks of a head.  Whole calls, full attention, us, general sequence (K and V as kv_pair says) /
+// three launches, 4-bit then 8-bit: 2 heads of 64 channels, 256 tokens 19.1 / 15.9, 19.6 / 16.3; 128 of 128, 500 tokens (1536 workgroups, 2
+// chunks) 62.6 / 51.0, 61.8 / 53.9; 512 of 200 (3072, 1) 83.6 / 75.1, 81.8 / 71.7; 128 of 1024 (3072, 4) 115.3 / 113.8, 117.3 / 112.5; 32
+// on 8 of 3000 (1144, 12) 137.5 / 134.1, 146.4 / 143.1; 8 of 5000 (952, 20) 151.4 / 149.5, 150.0 / 148.0; 8 on 1 of 8000 (629, 32) 232.3 /
+// 233.5, 212.5 / 211.8; 2 of 12000 (564, 47) 162.3 / 165.9, 164.8 / 171.5; 32 on 8 of 3362 (1288, 14), 4-bit, causal 113.3 / 106.6.  By workgroups
+// times chunks, general / three: 4-bit 10000 to 14336, 64 channels 1.00 to 1.03, 128 1.01 to 1.04, 15000 to 20480 0.99 to 1.01, 0.96 (many
+// key blocks) to 1.06 (many rows of block means); 8-bit 15000 to 20480 0.99 to 1.09; 21000 to 40000 0.92 to 1.02.
+// The bodies of a pair share its LDS (side by side it held pairs of d >= 128 to fewer workgroups), but its registers are the larger body's,
+// which tells in the 4-bit mode at 256 channels where the chip is full: it gains to 768 key blocks, with many rows of block means to 384
+// (64 on 8 heads of 1607 queries and 3214 keys, 408 blocks, 104 rows, statistics supplied 317 / 325; 64 heads of 750 tokens 103.2 / 99.2,
+// 64 of 1000 with 1024 blocks 121.7 / 123.9, 256 of 512 with 2048 183 / 194; 8-bit 99.1 / 88.2, 121.5 / 112.0, 190 / 174).
 constexpr int SMALL_CALL_WORK = 20480, SMALL_CALL_CHUNKS = 32;
 // Rows of block means that a key block meets: up to 24, two steps of the Delta-S product, K's workgroups are about as long as V's.
 static bool few_rows(const Dims& Dm) { return (long long)(Dm.H / Dm.Hkv) * Dm.nQb <= 24; }
@@ -1354,15 +1357,15 @@ bool small_call(const Dims& Dm) {
          nchunk <= SMALL_CALL_CHUNKS && (nk + nq) * nchunk <= SMALL_CALL_WORK;
 }
 
-// K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  The registers are the larger body's,
-// K's with Delta-S, so where K fills the chip by itself and its workgroups are long (many rows of block means) V's are better off in a
-// launch of their own.  Whole calls, time of two launches / one, by key blocks and rows per KV head.  4-bit: 64 channels 240 blocks, 16 rows 1.07,
-// 592, 148 rows 1.00, 728, 144 rows 0.96, 768, 8 rows 1.04; 128 channels 392, 52 rows 1.02, 448 to 520, 64 to 132 rows 0.97
-// to 0.98, 668, 108 rows 0.94, 706, 16 rows 1.02, 984, 22 rows 1.00; 256 channels 250, 39 rows 1.04, 328 to 432, 48 to 72 rows 0.99, 500, 56 rows
-// 0.97, 512 to 640, 1 to 24 rows 1.00 to 1.04, 736, 12 rows 0.99, 960, 2 rows 0.95.  8-bit, whose two quantizers are alike, 64 and 128 channels,
-// us: 1536 blocks 119.3 / 118.2, 3912 142.5 / 140.6, 4928 165.8 / 165.0, 5056 139.4 / 140.9, 7360 315.3 / 320.0, 13496 234.4 / 238.3; 256 channels 584
-// 179.4 / 176.4, 768 74.9 / 74.2, 2048 389 / 409.  A packed batch has fewer blocks and rows than its longest sequence says: 8 sequences of up to 3456 tokens, one head, 440 blocks and 27
-// rows by that count, 67 / 62 us.
+// K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  The registers are the larger body's, K's
+// with Delta-S, so where K fills the chip by itself and its workgroups are long (many rows of block means) V's are better off in a launch
+// of their own.  Whole calls, time of two launches / one, by key blocks and rows per KV head.  4-bit: 64 channels 240 blocks, 16 rows 1.07,
+// 592, 148 rows 1.00, 728, 144 rows 0.96, 768, 8 rows 1.04; 128 channels 392, 52 rows 1.02, 448 to 520, 64 to 132 rows 0.97 to 0.98, 668,
+// 108 rows 0.94, 706, 16 rows 1.02, 984, 22 rows 1.00; 256 channels 250, 39 rows 1.04, 328 to 432, 48 to 72 rows 0.99, 500, 56 rows 0.97,
+// 512 to 640, 1 to 24 rows 1.00 to 1.04, 736, 12 rows 0.99, 960, 2 rows 0.95.  8-bit, whose two quantizers are alike, 64 and 128 channels,
+// us: 1536 blocks 119.3 / 118.2, 3912 142.5 / 140.6, 4928 165.8 / 165.0, 5056 139.4 / 140.9, 7360 315.3 / 320.0, 13496 234.4 / 238.3; 256
+// channels 584 179.4 / 176.4, 768 74.9 / 74.2, 2048 389 / 409.  A packed batch has fewer blocks and rows than its longest sequence says: 8
+// sequences of up to 3456 tokens, one head, 440 blocks and 27 rows by that count, 67 / 62 us.
 static bool kv_pair(const Dims& Dm) {
   if (Dm.tensor_groups || Dm.pvf != PV_E4M3 || Dm.ds32) return false;
   const int line = !Dm.int4 ? (Dm.d == 256 ? 768 : 4608)

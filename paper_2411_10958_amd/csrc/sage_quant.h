@@ -131,7 +131,8 @@ __device__ inline void quant_group(const float* x, float delta, const QuantScale
 
 // psi with the correctly rounded quotient of div_by, for whole wavefronts: `fast` says that every lane's scale is one that
 // div_by accepts, or zero (all its values are then zero and so are their codes).  Four instructions per code instead of the
-// five of quant_group, three of them multiply-adds, and no branch per eight codes.
+// five of quant_group, three of them multiply-adds, and no branch per eight codes.  (K's form; Q keeps quant_group, with which this one was not
+// compared there: Q has a scale for every two queries, K one for a wavefront.)
 struct CodeScale { float r; bool fast; };
 __device__ __forceinline__ CodeScale code_scale(float delta) {
   CodeScale q;

@@ -68,6 +68,18 @@ def test_joined_accumulators_stay_below_31_bits():
     assert np.abs(dg[0]).max() <= 64
 
 
+def test_bytes_represent_every_value_within_21_binades_of_the_row_maximum_exactly():
+    rng = np.random.default_rng(5)
+    X = (rng.uniform(0.5, 1.0, (64, 128)) * rng.choice([-1.0, 1.0], (64, 128)) * np.exp2(rng.integers(-21, 1, size=(64, 128)))).astype(f32)
+    X[:, 0] = 1.5                                               # the row's largest magnitude: exponent 0; the others lie in [2^-22, 1)
+    dg, up = _digits(X)
+    back = sum(dg[a].astype(f64) * 2.0 ** (-8 * (a + 1)) for a in range(6)) * up[:, None]
+    small = np.abs(X) < 2.0 ** -21                              # exponent -22: one bit below the grid 2^-45
+    assert np.array_equal(back[~small].astype(f32), X[~small]) and (~small).sum() > 7000
+    assert np.all(np.abs(back - X.astype(f64)) <= 2.0 ** -46)
+    assert np.abs(dg[0]).max() <= 64 and all(-128 <= dg[a].min() and dg[a].max() <= 127 for a in range(1, 6))
+
+
 # rows of block means per KV head: one, a few (told apart by division), just below, at and above a step of 16, and steps that
 # cross from one head to the next; with a causal mask the rows start where a key block becomes visible
 @pytest.mark.gpu
@@ -95,6 +107,33 @@ def test_attention_reads_only_rows_that_were_formed(H, Hkv, N, Nk, d, causal, fo
     other = run("fp64" if form == "digits" else "digits")
     assert (out != other).any(-1).float().mean() <= 1e-2
     assert (out.float() - ref.float()).norm() <= 2e-3 * ref.float().norm()    # FP32 sums move a few codes of P~ by one step
+
+
+# the same of a packed batch (the first visible block of each sequence is its own; one with fewer keys than queries) and of a split key range
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens_q,lens_k,H,Hkv,d,splits", [("300,1,2100,129", "", 4, 2, 64, 1), ("640,65,1920", "700,65,2300", 3, 1, 128, 1), ("2177,40", "100,40", 2, 1, 128, 1),
+                                                          ("2049", "4200", 2, 1, 128, 4), ("700,512", "5000,1100", 2, 2, 256, 3)])
+@pytest.mark.parametrize("form", ["digits", "fp64"])
+def test_packed_and_split_attention_reads_only_rows_that_were_formed(lens_q, lens_k, H, Hkv, d, splits, form):
+    import torch
+    import paper_2411_10958_amd as pa
+    lq = [int(x) for x in lens_q.split(",")]
+    lk = [int(x) for x in lens_k.split(",")] if lens_k else lq
+    g = torch.Generator(device="cuda").manual_seed(sum(lq))
+    q, k, v = ((torch.randn((n, h, d), generator=g, device="cuda") * 2 + torch.randn((1, h, d), generator=g, device="cuda") * 3).bfloat16()
+               for h, n in ((H, sum(lq)), (Hkv, sum(lk)), (Hkv, sum(lk))))
+    cu = [torch.tensor([0, *np.cumsum(x)], dtype=torch.int32).cuda() for x in (lq, lk)]
+    kw = dict(cu_seqlens_q=cu[0], cu_seqlens_k=cu[1], max_seqlen_q=max(lq), max_seqlen_k=max(max(lk), max(lq)), causal=True, kv_splits=splits)
+
+    def run(f, fill):
+        out = torch.empty_like(q)
+        a = pa.make_varlen_args(q, k, v, out, delta_s=f, **kw)
+        ws = torch.full((pa.sage_attn_workspace_bytes(a),), fill, dtype=torch.uint8, device="cuda")
+        return pa.sage_attn_fwd_ex(q, k, v, out=out, workspace=ws, delta_s=f, **kw)
+    out = run(form, 255)
+    assert torch.isfinite(out).all() and torch.equal(out, run(form, 0))
+    other = run("fp64" if form == "digits" else "digits", 255)
+    assert (out != other).any(-1).float().mean() <= 1e-2
 
 
 @pytest.mark.gpu

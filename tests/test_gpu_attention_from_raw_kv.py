@@ -1,5 +1,5 @@
-"""Calls whose queries of a KV head fit 32 columns, with 96 workgroups or more (B x H_kv x key chunks), are served by a kernel
-that quantizes K and V itself (csrc/sage_attn_raw.hip).  sage_attn_prologue + sage_attn_core always take the general path, so
+"""Calls whose queries of a KV head fit 32 columns are served by a kernel that quantizes K and V itself, by the rule of
+attention_raw_ok (csrc/sage_attn_raw.hip).  sage_attn_prologue + sage_attn_core always take the general path, so
 the two can be compared on the same arguments: same codes, scales, chunks and order of every sum, so the same bits."""
 import ctypes
 
