@@ -438,6 +438,21 @@ __device__ __forceinline__ void dma_b32(const void* gbase, unsigned voff, unsign
                : "={m0}"(m0_after) : "s"(lds_byte), "v"(voff), "s"(gbase) : "memory");
 }
 
+// The 16-byte form for the lanes of `mask` alone (wavefront-uniform; none is allowed: then nothing is copied).
+__device__ __forceinline__ void dma_b128_lanes(const void* gbase, unsigned voff, unsigned lds_byte, unsigned long long mask) {
+  unsigned m0_after;
+  unsigned long long all;
+  asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 %1, exec\n\ts_mov_b64 exec, %5\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %3, %4\n\ts_mov_b64 exec, %1"
+               : "={m0}"(m0_after), "=&s"(all) : "s"(lds_byte), "v"(voff), "s"(gbase), "s"(mask) : "memory");
+}
+// A pointer that is the same in every lane, in scalar registers.
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  const unsigned long long u = (unsigned long long)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)u), hi = __builtin_amdgcn_readfirstlane((unsigned)(u >> 32));
+  return reinterpret_cast<const char*>((unsigned long long)hi << 32 | lo);
+}
+
 // An empty use of a register: the compiler must have the value complete (its load waited for) here.
 __device__ __forceinline__ void use_now(int x) { asm volatile("" :: "v"(x)); }
 __device__ __forceinline__ void use_now(float x) { asm volatile("" :: "v"(x)); }

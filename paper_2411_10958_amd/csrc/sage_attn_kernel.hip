@@ -32,8 +32,6 @@ __global__ void __launch_bounds__(256, (attn_occupancy<D, GM, PVF>())) k_attn_fw
   constexpr int KC = D * BKV / 16;    // 16-byte chunks of one V^ block
   constexpr int KCK = (int)(k_block_bytes(D, INT4) / 16);   // 16-byte chunks of one K^ block
   constexpr int CPT = KC / 256;       // V^ chunks per thread per block copy (2 or 1)
-  constexpr int CPTK = (KCK + 255) / 256;   // K^ copy rounds (the last one may skip some wavefronts)
-  constexpr int MINC = KCK / 256 + CPT;     // copies every wavefront issues per block, at least
   // LDS stages: block j is read while j+1 and j+2 arrive (d = 256 without the software pipeline: two stages of
   // 29 KB, so that two workgroups fit a CU)
   constexpr int NST = (D == 256 && attn_occupancy<D, GM, PVF>() >= 2) ? 2 : 3;
@@ -144,37 +142,63 @@ __global__ void __launch_bounds__(256, (attn_occupancy<D, GM, PVF>())) k_attn_fw
     }
   }
 
-  // Block copies: every wavefront moves its quarter of the K^ and V^ chunks (the copy is the
-  // identity on chunk indices), wavefront 0 the block's Delta-S row, wavefront 1 the 4 scales.
+  // Block copies, in pieces of 64 chunks (1 KB, one copy instruction): whole rounds of four K^ and V^ pieces, one per
+  // wavefront, then what is left - K^ pieces, the Delta-S row, the key scales - as a round of one "rest" piece per
+  // wavefront, fewer lanes where it is shorter (and a single piece by one wavefront where that leaves one over).
+  // Which rest piece a wavefront has is settled here, once per tile, so the loop has no branches by wavefront: the
+  // copies bound it beside the vector issue (without them it takes 11 % less at 128 channels, 16 % at 256).  Against a
+  // branch per piece: 256 channels, 16 heads of 8192 tokens, causal 261 -> 249 us (4-bit mode; its spilled registers
+  // went as well) and 298 -> 293 (8-bit), 128 channels, 128 heads of 4096 tokens, 4-bit 575 -> 565; 64 channels and the
+  // 8-bit mode at 128, which had one branch less to lose, the same.
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)&lds[0][0];
+  constexpr int KG = KCK / 64, KR = KG / 4, KL = KG % 4;
+  constexpr int NREST = KL + (INT4 ? 1 : 0) + 1;            // K^ pieces, Delta-S, scales
+  constexpr bool REST = !PACK && NREST >= 2;                // a round of rest pieces (packed tiles: several Delta-S rows)
+  constexpr int SC_W = NREST - 1;                           // the rest piece that holds the scales
+  const char* rest_p = nullptr;
+  unsigned rest_step = 0, rest_lds = 0, rest_lanes = 0;
+  if constexpr (REST) {
+    const char* pk = reinterpret_cast<const char*>(gk + (KR * 4 + w) * 64);
+    if (w < KL) {
+      rest_p = pk; rest_step = KCK * 16; rest_lds = (KR * 4 + w) * 1024; rest_lanes = 64;
+    } else if (INT4 && w == KL) {
+      rest_p = reinterpret_cast<const char*>(gd); rest_step = BKV * 4; rest_lds = (KCK + KC) * 16; rest_lanes = 16;
+    } else if (w == SC_W) {
+      rest_p = reinterpret_cast<const char*>(gs); rest_step = KSC * 4; rest_lds = (KCK + KC) * 16 + 256; rest_lanes = KSC / 4;
+    }
+    rest_p = uniform_ptr(rest_p);
+    rest_step = __builtin_amdgcn_readfirstlane(rest_step);
+    rest_lds = __builtin_amdgcn_readfirstlane(rest_lds);
+    rest_lanes = __builtin_amdgcn_readfirstlane(rest_lanes);
+  }
+  const unsigned long long rest_mask = rest_lanes == 64 ? ~0ull : (1ull << rest_lanes) - 1;
   auto issue = [&](int j, int st) {
     const unsigned sb = lds0 + (unsigned)st * (STAGE * 16);
+    const unsigned v16 = (unsigned)lane * 16;
+    const char* k0 = reinterpret_cast<const char*>(gk) + (size_t)j * (KCK * 16) + w * 1024;
+    const char* v0 = reinterpret_cast<const char*>(gv) + (size_t)j * (KC * 16) + w * 1024;
 #pragma unroll
-    for (int i = 0; i < CPTK; ++i) {
-      if (i * 256 + 64 * w < KCK)
-        dma_b128(gk + (size_t)j * KCK + i * 256, (unsigned)t * 16, sb + (unsigned)(i * 256 + 64 * w) * 16);
-    }
+    for (int i = 0; i < KR; ++i) dma_b128(k0 + i * 4096, v16, sb + w * 1024 + i * 4096);
 #pragma unroll
-    for (int i = 0; i < CPT; ++i)
-      dma_b128(gv + (size_t)j * KC + i * 256, (unsigned)t * 16, sb + (unsigned)(KCK + i * 256 + 64 * w) * 16);
-    if (w == 0) {
-      if constexpr (INT4) {
-        if constexpr (PACK) {          // one Delta-S row per query head of the group (consecutive heads, one row each)
-          const int G = p.H / p.Hkv;
-          for (int g = 0; g < G; ++g)
-            dma_b32(gd + (size_t)g * p.nKb * BKV + (size_t)j * BKV, (unsigned)lane * 4, sb + (KCK + KC) * 16 + 256u * g);
-        } else {
-          dma_b32(gd + (size_t)j * BKV, (unsigned)lane * 4, sb + (KCK + KC) * 16);
-        }
+    for (int i = 0; i < CPT; ++i) dma_b128(v0 + i * 4096, v16, sb + KCK * 16 + w * 1024 + i * 4096);
+    if constexpr (REST) dma_b128_lanes(rest_p + (size_t)j * rest_step, v16, sb + rest_lds, rest_mask);
+    if constexpr (PACK) {
+      if constexpr (KL > 0) { if (w < KL) dma_b128(k0 + KR * 4096, v16, sb + w * 1024 + KR * 4096); }
+      if (INT4 && w == 2) {            // one Delta-S row per query head of the group (consecutive heads, one row each)
+        const int G = p.H / p.Hkv;
+        for (int g = 0; g < G; ++g)
+          dma_b32(gd + (size_t)g * p.nKb * BKV + (size_t)j * BKV, (unsigned)lane * 4, sb + (KCK + KC) * 16 + 256u * g);
       }
-    } else if (w == 1) {
-      if (lane < KSC) dma_b32(gs + (size_t)j * KSC, (unsigned)lane * 4, sb + (KCK + KC) * 16 + 256 * DSR);
+    }
+    if constexpr (!REST || NREST > 4) {
+      if (w == 3 && lane < KSC) dma_b32(gs + (size_t)j * KSC, (unsigned)lane * 4, sb + (KCK + KC) * 16 + 256 * DSR);
     }
   };
   // Every wavefront issues at least MINC copies per block, in block order, and loads complete in
   // order: "at most MINC outstanding" therefore means every block but the newest has landed.
+  constexpr int MINC = KR + CPT + (REST ? 1 : 0);
   auto wait_all_but_newest = [&]() {
-    static_assert(MINC >= 1 && MINC <= 8, "copy count per block");
+    static_assert(MINC >= 1 && MINC <= 12, "copy count per block");
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(MINC) : "memory");
   };
   auto wait_all = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); };
