@@ -13,6 +13,12 @@ __device__ inline uint4 nt_load16(const unsigned short* p) {
   return make_uint4(r[0], r[1], r[2], r[3]);
 }
 
+__device__ inline uint2 nt_load8(const unsigned short* p) {
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  const v2u r = __builtin_nontemporal_load(reinterpret_cast<const v2u*>(p));
+  return make_uint2(r[0], r[1]);
+}
+
 template <bool BF16, bool NT = true>
 __device__ inline void load8(const unsigned short* p, float (&x)[8]) {
   const uint4 raw = NT ? nt_load16(p) : *reinterpret_cast<const uint4*>(p);

@@ -1,0 +1,37 @@
+"""The V quantizer's codes byte for byte against the CPU oracle, where its rows, its transposition in LDS and its two forms of the
+quotient can go wrong: lengths around the 64 keys of a block and the rows of a thread, every width, channels of zeros (scale 0:
+the dividing form), values of either zero and far below the channel's scale."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from oracle import sage_oracle as so
+from test_gpu_parity import _pa
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("zeros", [False, True])
+@pytest.mark.parametrize("nk", [1, 3, 4, 5, 63, 64, 65, 131])
+@pytest.mark.parametrize("d,dtype,smooth_v", [(64, "bf16", False), (64, "fp16", True), (128, "fp16", False), (128, "bf16", True), (256, "bf16", False),
+                                              (256, "fp16", True)])
+def test_v_codes(d, dtype, smooth_v, nk, zeros):
+    pa = _pa()
+    print(f"V codes: d={d} {dtype} N_kv={nk} smooth_v={smooth_v} zeros={zeros}", flush=True)
+    rng = np.random.default_rng(d + nk)
+    x = (rng.standard_normal((2, nk, d)) * 2.0 ** rng.integers(-6, 7, (2, 1, d))).astype(np.float32)
+    x[rng.random(x.shape) < 0.05] = -0.0
+    x[rng.random(x.shape) < 0.05] *= np.float32(2.0 ** -14)
+    if zeros:
+        x[:, :, rng.integers(d, size=3)] = 0.0
+    dev = torch.device("cuda:0")
+    tt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    v = torch.from_numpy(x[None]).to(tt).to(dev)
+    vn = v[0].float().cpu().numpy()
+    got, _, _ = pa.sage_attn_quant(v, v, v, mode="int8_fp8", smooth_v=smooth_v, want=("v_codes", "v_scale"))
+    torch.cuda.synchronize()
+    for h in range(2):
+        pro = so.quantize_head(vn[h], vn[h], vn[h], mode="int8_fp8", smooth_v_on=smooth_v)
+        assert np.array_equal(got["v_scale"][0, h].cpu().numpy(), pro["v_scale"])
+        assert np.array_equal(got["v_codes"][0, h].cpu().numpy(), pro["v_codes"])
