@@ -1386,20 +1386,28 @@ bool small_call(const Dims& Dm) {
          nchunk <= SMALL_CALL_CHUNKS && (nk + nq) * nchunk <= SMALL_CALL_WORK;
 }
 
-// K and V in one launch (k_quant_kv) for larger calls too: the one's tail runs under the other.  The registers are the larger body's, K's
-// with Delta-S, so where K fills the chip by itself and its workgroups are long (many rows of block means) V's are better off in a launch
-// of their own.  Whole calls, time of two launches / one, by key blocks and rows per KV head.  4-bit: 64 channels 240 blocks, 16 rows 1.07,
-// 592, 148 rows 1.00, 728, 144 rows 0.96, 768, 8 rows 1.04; 128 channels 392, 52 rows 1.02, 448 to 520, 64 to 132 rows 0.97 to 0.98, 668,
-// 108 rows 0.94, 706, 16 rows 1.02, 984, 22 rows 1.00; 256 channels 250, 39 rows 1.04, 328 to 432, 48 to 72 rows 0.99, 500, 56 rows 0.97,
+// K and V in one launch (k_quant_kv) for larger calls too: the one's loads and stores run under the other's arithmetic, and one launch
+// and one tail are saved.  The registers are the larger body's, K's with Delta-S, so where K fills the chip by itself and its workgroups are
+// long (many rows of block means) V's are better off in a launch of their own.  4-bit mode, preprocessing alone on inputs in turn, one launch
+// over two, by key blocks and rows per KV head: 64 channels 576 to 1056 blocks, 2 to 132 rows 0.89 to 0.96, 2048, 2 to 132 rows 0.91 to 0.98, 4096, 2
+// to 100 rows 0.92 to 0.99, 8192, 2 to 64 rows 0.96 to 0.99; 128 channels 400 to 1056, 2 to 300 rows 0.89 to 0.98, 2048, 2 to 132 rows 0.90 to
+// 0.98, 4096, 2 to 132 rows 0.95 to 0.99, 8192 and 12000, 28 to 64 rows 0.98 to 1.00, but 6000 to 12000, 2 to 16 rows 0.99 to 1.02; beyond the
+// product of the lines below 2000, 200 rows 1.00 and 1.01, 1200, 200 and 300 rows 0.97 to 1.06, 6000, 100 rows 0.99 and 1.01, 4096, 128 rows
+// 1.04 (causal), 16384, 128 rows 1.08.  (Between the first line and the second, 25 to 31 rows or 769 to 800 blocks, two launches: 0.90 to 0.94 would
+// be had there.)  256 channels, whole calls, time of two launches / one: 250, 39 rows 1.04, 328 to 432, 48 to 72 rows 0.99, 500, 56 rows 0.97,
 // 512 to 640, 1 to 24 rows 1.00 to 1.04, 736, 12 rows 0.99, 960, 2 rows 0.95.  8-bit, whose two quantizers are alike, 64 and 128 channels,
 // us: 1536 blocks 119.3 / 118.2, 3912 142.5 / 140.6, 4928 165.8 / 165.0, 5056 139.4 / 140.9, 7360 315.3 / 320.0, 13496 234.4 / 238.3; 256
 // channels 584 179.4 / 176.4, 768 74.9 / 74.2, 2048 389 / 409.  A packed batch has fewer blocks and rows than its longest sequence says: 8
-// sequences of up to 3456 tokens, one head, 440 blocks and 27 rows by that count, 67 / 62 us.
+// sequences of up to 4096 tokens, 12321 in all, 32 on 8 heads, 4096 blocks and 128 rows by that count, preprocessing 113.5 / 105.8 us.
 static bool kv_pair(const Dims& Dm) {
   if (Dm.tensor_groups || Dm.pvf != PV_E4M3 || Dm.ds32) return false;
-  const int line = !Dm.int4 ? (Dm.d == 256 ? 768 : 4608)
-                 : Dm.seq.cu_q ? 768 : Dm.d == 256 ? (few_rows(Dm) ? 640 : 320) : (few_rows(Dm) ? 768 : (Dm.d == 64 ? 640 : 400));
-  return (long long)Dm.B * Dm.Hkv * Dm.nKb <= line;
+  const long long blocks = (long long)Dm.B * Dm.Hkv * Dm.nKb, rows = (long long)(Dm.H / Dm.Hkv) * Dm.nQb;
+  if (!Dm.int4) return blocks <= (Dm.d == 256 ? 768 : 4608);
+  const int line = Dm.seq.cu_q ? 768 : Dm.d == 256 ? (few_rows(Dm) ? 640 : 320) : (few_rows(Dm) ? 768 : (Dm.d == 64 ? 640 : 400));
+  if (blocks <= line || Dm.d == 256) return blocks <= line;
+  if (Dm.seq.cu_q) return blocks * rows <= 1 << 19;
+  if (few_rows(Dm)) return blocks > 800 && blocks <= 4096;
+  return (rows >= 32 || blocks > 800) && (rows <= 160 || blocks <= 800) && blocks * rows <= 3 << 17;
 }
 
 template <bool BF16, bool INT4, int D>

@@ -33,6 +33,26 @@ def test_one_launch_equals_two(B, N, Nk, d, H, Hkv, mode, smooth_v):
     assert torch.equal(one, two[:-1]) and torch.equal(lse_one, lse_two[:-1])
 
 
+# the 4-bit lines for larger calls, one sequence more than the pair takes: blocks for few rows, the product of blocks and rows, blocks for more than
+# 160 rows; and (last) one sequence more than two launches take, from 801 blocks on
+LARGE_PAIR_CASES = [(129, 100, 2047, 64, 1, 1, True), (129, 129, 1985, 128, 2, 1, True), (77, 900, 2001, 64, 20, 1, True), (385, 250, 2048, 128, 16, 1, True),
+                    (26, 800, 2010, 128, 24, 1, True), (26, 100, 2000, 128, 1, 1, False), (26, 400, 2040, 64, 7, 1, False)]
+
+
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,more_is_two", LARGE_PAIR_CASES)
+def test_one_launch_equals_two_on_larger_calls(B, N, Nk, d, H, Hkv, more_is_two):
+    pa = _pa()
+    print(f"K/V pair, larger: B={B} N={N} N_kv={Nk} d={d} H={H}/{Hkv}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(B + N + Nk + d)
+    q, k, v = (torch.randn(B, h, n, d, generator=g, device="cuda").to(torch.bfloat16) for h, n in ((H, N), (Hkv, Nk), (Hkv, Nk)))
+    kw = dict(return_lse=True, kv_splits=1)
+    more, lse_more = pa.sage_attn_fwd_ex(q, k, v, **kw)
+    less, lse_less = pa.sage_attn_fwd_ex(q[:-1], k[:-1], v[:-1], **kw)
+    torch.cuda.synchronize()
+    assert torch.isfinite(more).all()
+    assert torch.equal(less, more[:-1]) and torch.equal(lse_less, lse_more[:-1])
+
+
 # the lines of small_call: 32 chunks of 256 keys, 20480 workgroups times chunks, 768 key blocks (384 with many rows of block means) at 256 channels; last: whether the
 # three launches serve it
 SMALL_CASES = [

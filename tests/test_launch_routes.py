@@ -5,7 +5,7 @@ import pytest
 
 from launch_recorder import launches
 from test_gpu_few_workgroups import CASES, THREE_LAUNCHES
-from test_gpu_kv_pair import PAIR_CASES, SMALL_CASES
+from test_gpu_kv_pair import LARGE_PAIR_CASES, PAIR_CASES, SMALL_CASES
 
 POINTER = 4096
 BASE = dict(B=1, H=32, H_kv=32, d=128, dtype=1, mode=1, layout=1)
@@ -47,6 +47,14 @@ def test_one_sequence_more_takes_two_launches(B, N, Nk, d, H, Hkv, mode, smooth_
     assert "k_quant_kv" in _names(B=B - 1, **call)
     two = _names(B=B, **call)
     assert "k_quant_kv" not in two and "k_quant_k" in two and "k_quant_v" in two
+
+
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,more_is_two", LARGE_PAIR_CASES)
+def test_the_lines_of_the_pair_on_larger_calls(B, N, Nk, d, H, Hkv, more_is_two):
+    call = dict(N=N, N_kv=Nk, d=d, H=H, H_kv=Hkv, dtype=1, mode=0, lse=POINTER, kv_splits=1)
+    for b, two in ((B, more_is_two), (B - 1, not more_is_two)):
+        names = _names(B=b, **call)
+        assert ("k_quant_kv" in names) == (not two) and ("k_quant_v" in names) == two, (b, names)
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,Nk,d,mode", [(1, 2, 2, 256, 256, 64, 0), (39, 64, 8, 58, 586, 256, 1), (2, 8, 1, 300, 300, 128, 0), (18, 64, 8, 217, 435, 128, 1)])
