@@ -48,9 +48,15 @@ __device__ __forceinline__ double pair_sum(double (&x)[N]) {
 // 77 on ungrouped ones); four for V at d = 256 (128 -> 128, 8-bit 70 -> 82).  K by 64-byte pieces of four lanes and an exchange in
 // registers pays at d = 256 only, where a lane's own piece is a whole cache line (quad_exchange).
 // HEADS: 4, or PACK_G where the 4-bit mode has more than four query heads per KV head (two chains of the Delta-S product).
+// LONE: one query per head in the 4-bit mode.  It is its own block mean, gamma(Q) = 0, so all of its codes are 0 and so is
+// their product with K's: the score is Delta-S, and neither codes nor scales of Q and K are formed.  Same bits; whole calls, the kernel with
+// the codes / this one, on inputs in turn: 4 x 8 KV heads of 32768 keys 194 / 182 us, statistics supplied 107 / 92 (6.2 TB/s), 16 x 16
+// of 64 channels, 5003 keys 94 / 73, 16 of 256, 30000 keys 117 / 99, 8 of 4000 keys 34 / 30.  (A branch in the one kernel spilled 38 registers
+// of the calls with more queries: 70 / 87.)
 constexpr int RAW_V = 2, RAW_ATT = 2, RAW_THREADS = 64 * (4 + RAW_V + RAW_ATT);
-template <int D, bool INT4, bool CAUSAL, bool BF16, int HEADS>
+template <int D, bool INT4, bool CAUSAL, bool BF16, int HEADS, bool LONE = false>
 __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(const AttnParams p, const RawParams x) {
+  static_assert(!LONE || (INT4 && !CAUSAL), "one query sees every key");
   constexpr int CPL = D / 4;                                     // K: channels per lane
   constexpr int NCG = D / 8, NRG = 64 * RAW_V / NCG, RPT = BKV / NRG;   // V: 8 channels of RPT keys per thread
   constexpr int CT = D / 32, CTW = CT / RAW_ATT;                 // channel tiles of the output, per attending wavefront
@@ -172,11 +178,15 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
 #pragma unroll
       for (int e = 0; e < CPL; ++e) xk[e] = 0.0f;
     }
+    float delta = 0.0f;
+    CodeScale qs;
+    if constexpr (!LONE) {
 #pragma unroll
-    for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(xk[e]));
-    const float delta = __fdiv_rn(wave_max(mx), (float)QMAX);
-    if (lane == 0) s_ks[cur][w] = delta;
-    const CodeScale qs = code_scale(delta);
+      for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(xk[e]));
+      delta = __fdiv_rn(wave_max(mx), (float)QMAX);
+      if (lane == 0) s_ks[cur][w] = delta;
+      qs = code_scale(delta);
+    }
     uint8_t* img = reinterpret_cast<uint8_t*>(&s_k[cur][0]);
     if constexpr (INT4) {
       // Delta-S: q_bar_g . gamma(K)_t in float64, four heads at a time by v_mfma_f64_4x4x4_4b_f64: four independent
@@ -216,6 +226,7 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
       }
 #pragma unroll
       for (int i = 0; i < NCH; ++i) s_ds[cur][4 * i + kk][kr] = (float)(kap * acc[i]);
+      if constexpr (LONE) return;
       constexpr int NPL = CPL > 32 ? CPL / 32 : 1, CPP = CPL / NPL;
 #pragma unroll
       for (int pl = 0; pl < NPL; ++pl) {
@@ -337,8 +348,10 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
   // (4-bit mode), scale from the pair of queries, codes as quant_q4_block / quant_q8_block give them.
   constexpr int PC = INT4 ? 32 : 16;
   typename QkOperand<INT4>::type qreg[NP];
-  float dq;
-  {
+  float dq = 0.0f;
+#pragma unroll
+  for (int s = 0; s < NP; ++s) qreg[s] = typename QkOperand<INT4>::type{};
+  if constexpr (!LONE) {
     const unsigned short* qrow = x.q + row_offset(p.om, head_offset(p.om, (unsigned)(bh + hq)), (int)sq.q0 + query);
     float mx = 0.0f;
     // one operand's channels at a time, fetched once for the maximum and again for the codes: kept, the row would cost a
@@ -428,13 +441,21 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
     float alpha;
     auto attend = [&](auto masked_) {
       constexpr bool MASKED = decltype(masked_)::value;
-      KeyScales<0> ks;
-      ks.s[0] = s_ks[cur][half];
-      ks.s[1] = s_ks[cur][2 + half];
       Factors<0> fac;
-      fac.set(dq, p.kappa, ks);
+      fac.c[0] = fac.c[1] = 0.0f;
       const int key0 = j * BKV, last = query + sq.coff;
       v16i raw[2], sc[2];
+      auto lone_tile = [&](auto kt_) {
+        constexpr int KT = decltype(kt_)::value;
+        const float* dsr = &s_ds[cur][hq][32 * KT + 16 * half];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          float s = dsr[v];
+          const int key = key0 + 32 * KT + 16 * half + v;
+          if (MASKED && (key >= n_keys_end || (CAUSAL && key > last))) s = -INFINITY;
+          sc[KT][v] = __float_as_int(s);
+        }
+      };
       // one key tile after the other, so that one tile's operands and raw scores are live at a time
       auto key_tile = [&](auto kt_) {
         constexpr int KT = decltype(kt_)::value;
@@ -458,8 +479,17 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
         dequant_group<INT4, CAUSAL, MASKED, 0, KT, 3>(raw, sc, fac, half, key0, last, n_keys_end);
         __builtin_amdgcn_sched_barrier(0);
       };
-      key_tile(std::integral_constant<int, 0>{});
-      key_tile(std::integral_constant<int, 1>{});
+      if constexpr (LONE) {
+        lone_tile(std::integral_constant<int, 0>{});
+        lone_tile(std::integral_constant<int, 1>{});
+      } else {
+        KeyScales<0> ks;
+        ks.s[0] = s_ks[cur][half];
+        ks.s[1] = s_ks[cur][2 + half];
+        fac.set(dq, p.kappa, ks);
+        key_tile(std::integral_constant<int, 0>{});
+        key_tile(std::integral_constant<int, 1>{});
+      }
       alpha = update_max<DW, INT4, 0, PV_E4M3>(st, sc, fac, m_sub);
       float ls = 0.0f;
       exp_group<INT4, MASKED, 0, PV_E4M3, 0, 0>(sc, fac, m_sub, pb, ls);
@@ -595,6 +625,15 @@ static hipError_t launch_raw_t(const Dims& D, const Ptrs& P, hipStream_t s) {
   x.km = make_tensor_map(D.nhd, D.Hkv, D.Nk, D.d, D.seq.cu_q != nullptr);
   const int grid = p.total_tiles * D.splits;
   const bool many = INT4 && D.H / D.Hkv > 4;
+  if constexpr (INT4) {
+    if (D.N == 1) {                // (of a packed batch: the longest sequence's; without a mask: one query sees every key)
+#define SAGE_RAW_LONE(BF, HEADS) k_attn_raw<DD, true, false, BF, HEADS, true><<<grid, RAW_THREADS, 0, s>>>(p, x)
+      if (D.bf16) { if (many) SAGE_RAW_LONE(true, PACK_G); else SAGE_RAW_LONE(true, 4); }
+      else        { if (many) SAGE_RAW_LONE(false, PACK_G); else SAGE_RAW_LONE(false, 4); }
+#undef SAGE_RAW_LONE
+      return D.splits > 1 ? launch_merge_packed(D, p, s) : hipGetLastError();
+    }
+  }
 #define SAGE_RAW_LAUNCH(BF) \
   do { \
     if (many) k_attn_raw<DD, INT4, CAUSAL, BF, INT4 ? PACK_G : 4><<<grid, RAW_THREADS, 0, s>>>(p, x); \

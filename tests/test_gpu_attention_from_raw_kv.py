@@ -86,6 +86,26 @@ def test_equals_the_general_path(B, N, Nk, d, dtype, H, Hkv, causal, layout, spl
     _compare(_both(pa, q, k, v, a))
 
 
+@pytest.mark.parametrize("special", ["", "nan key", "zero query", "loud query"])
+@pytest.mark.parametrize("B,Nk,d,dtype,H,Hkv,causal,layout,splits", [(40, 129, 64, "bf16", 8, 2, True, "NHD", 0), (100, 640, 128, "fp16", 4, 1, False, "HND", 1),
+                                                                     (20, 1999, 128, "bf16", 10, 2, True, "HND", 0), (64, 65, 256, "fp16", 8, 1, True, "NHD", 0),
+                                                                     (24, 1000, 256, "bf16", 4, 4, False, "HND", 2)])
+def test_one_query_in_the_4_bit_mode_equals_the_general_path(B, Nk, d, dtype, H, Hkv, causal, layout, splits, special):
+    """A single query's codes are all zero, and the kernel for it forms neither them nor K's."""
+    pa = _pa()
+    q, k, v = _inputs(B, 1, Nk, d, H, Hkv, dtype, layout, 3)
+    print(f"raw K, V, one query: B={B} N_kv={Nk} d={d} {dtype} H={H}/{Hkv} causal={causal} {layout} {special}", flush=True)
+    if special == "nan key":
+        k.view(-1)[(Nk // 2) * d * (Hkv if layout == "NHD" else 1) + 5] = float("nan")
+    elif special:
+        q *= 0.0 if special == "zero query" else 64.0
+    a = pa.make_args(q, k, v, None, causal=causal, mode="int4_fp8", layout=layout, kv_splits=splits)
+    assert B * Hkv * pa.sage_attn_kv_splits(a) >= 64
+    (x, lx), (y, ly) = _both(pa, q, k, v, a)
+    assert torch.equal(x.isnan(), y.isnan()) and bool(x.isnan().any()) == (special == "nan key")
+    assert torch.equal(x.nan_to_num(0.5), y.nan_to_num(0.5)) and torch.equal(lx.nan_to_num(0.5), ly.nan_to_num(0.5))
+
+
 @pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
 def test_packed_batch_equals_the_general_path(mode):
     """Sequences without queries, without keys, with fewer keys than queries, and of very different lengths."""
