@@ -135,7 +135,7 @@ int run_forward(const Dims& D, const sage_attn_args* a, const Workspace& w) {
   const bool raw = attention_raw_ok(D);
   int st = SAGE_OK;
   if (!raw) st = hip_status(launch_prologue(D, P, s));
-  else if (!D.stats_given) st = hip_status(launch_kv_stats(D, P, s));
+  else if (!D.stats_given) st = hip_status(launch_kv_stats(D, P, s, !raw_reduces(D)));
   if (st != SAGE_OK) return st;
   P.lse = a->lse;
   return hip_status(raw ? launch_attention_raw(D, P, s) : launch_attention(D, P, s));

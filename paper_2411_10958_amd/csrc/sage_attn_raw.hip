@@ -16,6 +16,10 @@ struct RawParams {
   const unsigned short *q, *k, *v;   // (q is laid out like the output)
   const float* k_mean;               // mean(K) per KV head
   float* q_corr;                     // where the row constants of the log-sum-exp go for the merge
+  const double* k_sum;               // not null: mean(K) and delta_V are not there yet, these are the partial results of the statistics
+  const unsigned* v_max;             // pass; the workgroup reduces its head's, and a head's first one writes delta_V for the merge
+  float* v_scale;
+  int nchunk;
   TensorMap km;
 };
 
@@ -112,11 +116,39 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
     return;
   }
 
-  for (int c = t; c < D; c += RAW_THREADS) {
-    s_km[c] = x.k_mean[bhkv * D + c];
-    const float vs = p.v_scale[bhkv * D + c];
-    s_vs[c] = vs;
-    s_vi[c] = div_by_ok(vs) ? __fdiv_rn(1.0f, vs) : 0.0f;
+  if (x.k_sum) {
+    // finalize_stats_block for one head: RAW_THREADS / D threads to a channel (the sums are exact, whatever their order)
+    constexpr int PARTS = RAW_THREADS / D;
+    static_assert(PARTS * D == RAW_THREADS && sizeof(s_v) >= RAW_THREADS * 12, "the parts meet where V's codes will be");
+    double* sum = reinterpret_cast<double*>(&s_v[0][0]);
+    float* max = reinterpret_cast<float*>(sum + RAW_THREADS);
+    const int c = t % D, part = t / D;
+    const size_t p0 = (size_t)bhkv * x.nchunk * D + c;
+    double ks = 0.0;
+    float vm = 0.0f;
+#pragma unroll 4
+    for (int ch = part; ch < x.nchunk; ch += PARTS) {
+      ks += x.k_sum[p0 + (size_t)ch * D];
+      vm = fmaxf(vm, __uint_as_float(x.v_max[p0 + (size_t)ch * D]));
+    }
+    sum[t] = ks; max[t] = vm;
+    __syncthreads();
+    if (t < D) {
+#pragma unroll
+      for (int i = 1; i < PARTS; ++i) { ks += sum[i * D + t]; vm = fmaxf(vm, max[i * D + t]); }
+      s_km[t] = (float)(ks / (double)sq.nk);
+      const float vs = __fdiv_rn(vm, E4M3_MAX);
+      s_vs[t] = vs;
+      s_vi[t] = div_by_ok(vs) ? __fdiv_rn(1.0f, vs) : 0.0f;
+      if (split == 0) x.v_scale[bhkv * D + t] = vs;
+    }
+  } else {
+    for (int c = t; c < D; c += RAW_THREADS) {
+      s_km[c] = x.k_mean[bhkv * D + c];
+      const float vs = p.v_scale[bhkv * D + c];
+      s_vs[c] = vs;
+      s_vi[c] = div_by_ok(vs) ? __fdiv_rn(1.0f, vs) : 0.0f;
+    }
   }
   if constexpr (INT4) {
     for (int idx = t; idx < HEADS * D; idx += RAW_THREADS) {
@@ -571,7 +603,7 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int oc = DW * w + 32 * ct + 8 * g + 4 * half;
-      const v4f sc = *reinterpret_cast<const v4f*>(p.v_scale + bhkv * D + oc);
+      const v4f sc = *reinterpret_cast<const v4f*>(&s_vs[oc]);
       float o4[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) o4[r] = __fmul_rn(__fmul_rn(st.O[ct][4 * g + r], inv_l), sc[r]);
@@ -615,6 +647,17 @@ bool attention_raw_ok(const Dims& D) {
          D.smooth_k && D.smooth_q && !D.smooth_v && (!D.int4 || D.ds_mode == 2);
 }
 
+// Whether the kernel reduces the partial results of the statistics pass itself (every workgroup for its head) instead of a launch of its
+// own in front.  The launch is 2 to 4 us of a call, the reduction reads 12 bytes a channel and 256-key chunk in every workgroup.  Whole calls on
+// inputs in turn, this / a launch: 2000 keys 0.88 to 0.97, 8000 of 128 channels 0.94 (8 KV heads) to 0.99 (64), 32000 0.97
+// to 0.98, 60000 of 64 channels 0.96 to 0.97, of 128 1.01; 8000 of 256 channels 0.98, 12000 and more 1.01 to 1.03; past the 256 MB of the memory-side
+// cache, where the partial results lie, 0.98 to 1.01.  Calls in one chunk - short caches, or one asked for - keep the launch, which tests hold
+// them to (300 keys: 0.84 to 0.89 would be had).
+bool raw_reduces(const Dims& D) {
+  const int nchunk = (D.Nk + STAT_ROWS - 1) / STAT_ROWS;
+  return !D.stats_given && D.splits > 1 && nchunk * D.d <= (D.d == 256 ? 8192 : 16384) && 4LL * D.B * D.Hkv * D.Nk * D.d <= 256LL << 20;
+}
+
 template <int DD, bool INT4, bool CAUSAL>
 static hipError_t launch_raw_t(const Dims& D, const Ptrs& P, hipStream_t s) {
   AttnParams p = attn_params(D, P);
@@ -622,6 +665,7 @@ static hipError_t launch_raw_t(const Dims& D, const Ptrs& P, hipStream_t s) {
   RawParams x;
   x.q = (const unsigned short*)P.q; x.k = (const unsigned short*)P.k; x.v = (const unsigned short*)P.v;
   x.k_mean = P.k_mean; x.q_corr = P.q_corr;
+  x.k_sum = raw_reduces(D) ? P.k_sum : nullptr; x.v_max = P.v_max; x.v_scale = P.v_scale; x.nchunk = (D.Nk + STAT_ROWS - 1) / STAT_ROWS;
   x.km = make_tensor_map(D.nhd, D.Hkv, D.Nk, D.d, D.seq.cu_q != nullptr);
   const int grid = p.total_tiles * D.splits;
   const bool many = INT4 && D.H / D.Hkv > 4;

@@ -331,7 +331,8 @@ hipError_t launch_prologue(const Dims& D, const Ptrs& P, hipStream_t s);
 bool small_call(const Dims& D);            // its preprocessing is two launches
 bool attention_raw_ok(const Dims& D);      // the attention kernel that quantizes Q, K and V itself serves this call ...
 hipError_t launch_attention_raw(const Dims& D, const Ptrs& P, hipStream_t s);   // ... with P.k_mean, P.v_scale in place
-hipError_t launch_kv_stats(const Dims& D, const Ptrs& P, hipStream_t s);   // writes P.k_mean, P.v_scale
+bool raw_reduces(const Dims& D);           // ... that reduces the partial statistics itself
+hipError_t launch_kv_stats(const Dims& D, const Ptrs& P, hipStream_t s, bool finalize = true);   // writes P.k_mean, P.v_scale; not finalize: the partial results
 hipError_t launch_kv_stats_update(const Dims& D, const Ptrs& P, double* state_sum, float* state_max, int fresh,
                                   long long n_total, hipStream_t s);
 hipError_t launch_attention(const Dims& D, const Ptrs& P, hipStream_t s);

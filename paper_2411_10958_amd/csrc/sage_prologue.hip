@@ -1544,10 +1544,10 @@ hipError_t launch_prologue(const Dims& D, const Ptrs& P, hipStream_t s) {
 #undef SAGE_PRO
 }
 
-hipError_t launch_kv_stats(const Dims& D, const Ptrs& P, hipStream_t s) {
-  if (D.d == 256)      { if (D.bf16) launch_stats_t<true, 256>(D, P, s); else launch_stats_t<false, 256>(D, P, s); }
-  else if (D.d == 128) { if (D.bf16) launch_stats_t<true, 128>(D, P, s); else launch_stats_t<false, 128>(D, P, s); }
-  else                 { if (D.bf16) launch_stats_t<true, 64>(D, P, s); else launch_stats_t<false, 64>(D, P, s); }
+hipError_t launch_kv_stats(const Dims& D, const Ptrs& P, hipStream_t s, bool finalize) {
+  if (D.d == 256)      { if (D.bf16) launch_stats_t<true, 256>(D, P, s, finalize); else launch_stats_t<false, 256>(D, P, s, finalize); }
+  else if (D.d == 128) { if (D.bf16) launch_stats_t<true, 128>(D, P, s, finalize); else launch_stats_t<false, 128>(D, P, s, finalize); }
+  else                 { if (D.bf16) launch_stats_t<true, 64>(D, P, s, finalize); else launch_stats_t<false, 64>(D, P, s, finalize); }
   return hipGetLastError();
 }
 

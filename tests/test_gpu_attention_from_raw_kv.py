@@ -106,6 +106,21 @@ def test_one_query_in_the_4_bit_mode_equals_the_general_path(B, Nk, d, dtype, H,
     assert torch.equal(x.nan_to_num(0.5), y.nan_to_num(0.5)) and torch.equal(lx.nan_to_num(0.5), ly.nan_to_num(0.5))
 
 
+# the lines of raw_reduces: chunks of 256 keys times channels, bytes of K and V; last: whether the kernel reduces the statistics itself
+REDUCE_CASES = [(1, 65536, 64, 2, 2, True), (1, 65537, 64, 2, 2, False), (1, 32768, 128, 4, 1, True), (1, 32769, 128, 4, 1, False), (2, 8192, 256, 1, 1, True),
+                (2, 8193, 256, 1, 1, False), (32, 4096, 128, 4, 4, True), (32, 4097, 128, 4, 4, False)]
+
+
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+@pytest.mark.parametrize("B,Nk,d,H,Hkv,reduces", REDUCE_CASES)
+def test_statistics_reduced_in_the_kernel_or_before(B, Nk, d, H, Hkv, reduces, mode):
+    pa = _pa()
+    print(f"raw K, V, statistics: B={B} N_kv={Nk} d={d} H={H}/{Hkv} {mode}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(Nk + d)
+    q, k, v = (torch.randn(B, h, n, d, generator=gen, device="cuda").add_(0.5).half() for h, n in ((H, 2), (Hkv, Nk), (Hkv, Nk)))
+    _compare(_both(pa, q, k, v, pa.make_args(q, k, v, None, causal=True, mode=mode)))
+
+
 @pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
 def test_packed_batch_equals_the_general_path(mode):
     """Sequences without queries, without keys, with fewer keys than queries, and of very different lengths."""

@@ -4,6 +4,7 @@ import itertools
 import pytest
 
 from launch_recorder import launches
+from test_gpu_attention_from_raw_kv import REDUCE_CASES
 from test_gpu_few_workgroups import CASES, THREE_LAUNCHES
 from test_gpu_kv_pair import LARGE_PAIR_CASES, PAIR_CASES, SMALL_CASES
 
@@ -55,6 +56,16 @@ def test_the_lines_of_the_pair_on_larger_calls(B, N, Nk, d, H, Hkv, more_is_two)
     for b, two in ((B, more_is_two), (B - 1, not more_is_two)):
         names = _names(B=b, **call)
         assert ("k_quant_kv" in names) == (not two) and ("k_quant_v" in names) == two, (b, names)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("B,Nk,d,H,Hkv,reduces", REDUCE_CASES)
+def test_decode_calls_reduce_the_statistics_in_the_kernel_or_before(B, Nk, d, H, Hkv, reduces, mode):
+    call = dict(B=B, N=2, N_kv=Nk, d=d, H=H, H_kv=Hkv, dtype=0, mode=mode, causal=1, lse=POINTER)
+    names = _names(**call)
+    assert "k_attn_raw" in names and ("k_finalize_stats" in names) == (not reduces), names
+    given = _names(k_mean_in=POINTER, v_scale_in=POINTER, **call)
+    assert given[0] == "k_attn_raw", given
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,Nk,d,mode", [(1, 2, 2, 256, 256, 64, 0), (39, 64, 8, 58, 586, 256, 1), (2, 8, 1, 300, 300, 128, 0), (18, 64, 8, 217, 435, 128, 1)])
