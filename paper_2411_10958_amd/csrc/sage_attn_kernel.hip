@@ -16,6 +16,15 @@
 
 namespace sage {
 
+// Blocks left at which a workgroup of the last round lowers its priority for the (i + 1)-th time (in the kernel): the last step is what
+// two of them may end apart.
+template <int D> __device__ constexpr int tail_left(int i) { return D == 64 ? (i == 0 ? 40 : i == 1 ? 20 : 8) : (i == 0 ? 28 : i == 1 ? 12 : 4); }
+__device__ __forceinline__ void set_priority(int p) {     // (the instruction takes a constant)
+  if (p == 3) __builtin_amdgcn_s_setprio(3);
+  else if (p == 2) __builtin_amdgcn_s_setprio(2);
+  else if (p == 1) __builtin_amdgcn_s_setprio(1);
+  else __builtin_amdgcn_s_setprio(0);
+}
 // Tile order of packed batches (in the kernel).
 constexpr int BAND_LEVELS = 4, BAND_TILES = 8192;
 
@@ -491,8 +500,35 @@ __global__ void __launch_bounds__(256, (attn_occupancy<D, GM, PVF>())) k_attn_fw
     cur = nx1;                                                                                       \
   } while (0)
   int j = j_begin;
+  // The workgroups of a CU do not advance alike: the SIMDs serve the oldest wavefront first (128 channels, three workgroups: 1.2 us a
+  // block for the first, 2.5 for the last), so that the last of a launch end one after the other, each with more of its CU to itself than it can use.  Those that
+  // start in the last round therefore begin at the highest priority and lower it as their keys run out: of workgroups that share
+  // a CU the one with more left to do goes first, and they end together.  (Earlier rounds are better off uneven, their ends fall between the
+  // others' blocks: 4096 tiles of 128 channels 572 -> 568 us, with every round 593.  Under a causal mask the tiles go out heaviest
+  // first, and the oldest is the right one to be first: 8192 tokens, 64 channels 217 -> 222.)  Attention alone, us, without / with, 4096 keys, no mask:
+  // 128 channels 512 tiles 94 / 87, 640 126 / 112, 768 132 / 121, 1024 173 / 164, 2048 328 / 316, 8-bit 768 141 / 133; 256 channels 512 138
+  // / 132, 1024 266 / 261; 64 channels 1024 129 / 117, 4096 430 / 422; 256 tiles in three chunks of 88 blocks 167 / 156.
+  constexpr bool EVEN_TAIL = !PACK && (!CAUSAL || SPLIT);
+  constexpr unsigned SLOTS = 256 * attn_occupancy<D, GM, PVF>();
   if constexpr (OCC3) {
-    for (; j < n_plain; ++j) SAGE_BODY3(false);
+    if constexpr (EVEN_TAIL) {
+      // (in stretches between the changes of priority; the loop itself knows nothing of them)
+      int level = 0;
+      if (blockIdx.x + SLOTS >= (unsigned)n_wg && n_wg > 256) {
+        while (level < 3 && nblk - j <= tail_left<D>(level)) ++level;
+        set_priority(3 - level);
+      } else {
+        level = 3;
+      }
+      for (;;) {
+        const int stop = level < 3 ? min(n_plain, nblk - tail_left<D>(level)) : n_plain;
+        for (; j < stop; ++j) SAGE_BODY3(false);
+        if (j >= n_plain) break;
+        set_priority(3 - ++level);
+      }
+    } else {
+      for (; j < n_plain; ++j) SAGE_BODY3(false);
+    }
     for (; j < n_act; ++j) SAGE_BODY3(true);
   } else {
     for (; j + 1 < n_plain; ++j) SAGE_BODY(false, false);
