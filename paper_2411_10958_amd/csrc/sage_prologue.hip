@@ -134,10 +134,21 @@ __global__ void __launch_bounds__(256) k_v_absmax(const unsigned short* __restri
   }
 }
 
+// Partial results requested together where a workgroup reduces its head's (one round trip per batch instead of per chunk: whole calls of 128
+// heads of 1024 tokens 94.7 -> 92.2 us, 16 of 3000 of 64 channels 66.2 -> 62.7, 8 of 5000 108.5 -> 102.8; batches of 8 and 16 the same, but
+// 192 heads of 500 43.5 -> 42.4 with 4, 42.8 with 8, 43.5 with 16).
+constexpr int SUM_BATCH = 4;
 // the sum over a head's chunks of one channel (exact, whatever the order)
 __device__ __forceinline__ double sum_partials(const double* __restrict__ part, size_t head, int nchunk, int d, int c) {
+  const double* p = part + head * nchunk * d + c;
   double s = 0.0;
-  for (int ch = 0; ch < nchunk; ++ch) s += part[(head * nchunk + ch) * d + c];
+  for (int ch = 0; ch < nchunk; ch += SUM_BATCH) {
+    double x[SUM_BATCH];
+#pragma unroll
+    for (int i = 0; i < SUM_BATCH; ++i) x[i] = p[(size_t)min(ch + i, nchunk - 1) * d];
+#pragma unroll
+    for (int i = 0; i < SUM_BATCH; ++i) s += ch + i < nchunk ? x[i] : 0.0;
+  }
   return s;
 }
 
@@ -1155,7 +1166,13 @@ __device__ __forceinline__ void quant_v_block(QuantVLds<D, REDUCE>& lds, const B
   if constexpr (REDUCE) {
     if (t < D) {
       float vm = 0.0f;
-      for (int ch = 0; ch < a.nchunk; ++ch) vm = fmaxf(vm, __uint_as_float(a.v_max[(bh * a.nchunk + ch) * D + t]));
+      for (int ch = 0; ch < a.nchunk; ch += SUM_BATCH) {
+        float x[SUM_BATCH];
+#pragma unroll
+        for (int i = 0; i < SUM_BATCH; ++i) x[i] = __uint_as_float(a.v_max[(bh * a.nchunk + min(ch + i, a.nchunk - 1)) * D + t]);
+#pragma unroll
+        for (int i = 0; i < SUM_BATCH; ++i) vm = fmaxf(vm, x[i]);
+      }
       const float v = __fdiv_rn(vm, a.code_max);
       s_vscale[t] = v;
       if (kb == 0) a.v_scale[bh * D + t] = v;
