@@ -257,7 +257,13 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
         }
       }
 #pragma unroll
-      for (int i = 0; i < NCH; ++i) s_ds[cur][4 * i + kk][kr] = (float)(kap * acc[i]);
+      for (int i = 0; i < NCH; ++i) {
+        double s = kap * acc[i];
+        // (an infinite key, which supplied statistics allow, makes its group's scale infinite and 0 codes times that NaN: so must the
+        // score be that leaves both out)
+        if constexpr (LONE) s = __builtin_fma(0.0, acc[i], s);
+        s_ds[cur][4 * i + kk][kr] = (float)s;
+      }
       if constexpr (LONE) return;
       constexpr int NPL = CPL > 32 ? CPL / 32 : 1, CPP = CPL / NPL;
 #pragma unroll

@@ -106,6 +106,24 @@ def test_one_query_in_the_4_bit_mode_equals_the_general_path(B, Nk, d, dtype, H,
     assert torch.equal(x.nan_to_num(0.5), y.nan_to_num(0.5)) and torch.equal(lx.nan_to_num(0.5), ly.nan_to_num(0.5))
 
 
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("B,Nk,d,dtype,H,Hkv,layout,splits", [(40, 129, 64, "bf16", 8, 2, "NHD", 0), (100, 640, 128, "fp16", 4, 1, "HND", 1),
+                                                              (24, 1000, 256, "bf16", 4, 4, "HND", 2)])
+def test_one_query_and_a_key_that_is_not_finite(B, Nk, d, dtype, H, Hkv, layout, splits, value):
+    """With the statistics supplied an infinite key leaves mean(K) finite: the general path's scale of the key's group is infinite and its
+    rows NaN, and so they are where no codes are formed."""
+    pa = _pa()
+    q, k, v = _inputs(B, 1, Nk, d, H, Hkv, dtype, layout, 3)
+    print(f"raw K, V, one query, a key of {value}: B={B} N_kv={Nk} d={d} {dtype} H={H}/{Hkv} {layout}", flush=True)
+    stats = pa.sage_attn_kv_stats(k, v, layout=layout)
+    (k if layout == "HND" else k.transpose(1, 2))[1, 0, Nk // 2, 5] = value
+    (x, lx), (y, ly) = _both(pa, q, k, v, pa.make_args(q, k, v, None, mode="int4_fp8", layout=layout, kv_splits=splits, kv_stats=stats))
+    hit = (x if layout == "HND" else x.transpose(1, 2))[1, :H // Hkv]
+    assert bool(hit.isnan().all()) and int(x.isnan().sum()) == hit.numel() and int(lx.isnan().sum()) == H // Hkv
+    assert torch.equal(x.isnan(), y.isnan()) and torch.equal(lx.isnan(), ly.isnan())
+    assert torch.equal(x.nan_to_num(0.5), y.nan_to_num(0.5)) and torch.equal(lx.nan_to_num(0.5), ly.nan_to_num(0.5))
+
+
 # the lines of raw_reduces: chunks of 256 keys times channels, bytes of K and V; last: whether the kernel reduces the statistics itself
 REDUCE_CASES = [(1, 65536, 64, 2, 2, True), (1, 65537, 64, 2, 2, False), (1, 32768, 128, 4, 1, True), (1, 32769, 128, 4, 1, False), (2, 8192, 256, 1, 1, True),
                 (2, 8193, 256, 1, 1, False), (32, 4096, 128, 4, 4, True), (32, 4097, 128, 4, 4, False)]
