@@ -1209,9 +1209,13 @@ __device__ __forceinline__ void quant_v_block(QuantVLds<D, REDUCE>& lds, const B
         for (int i = 0; i < 4; ++i) x[i] = n0 + key0 + i < N ? x[i] : 0.0f;
       }
       if (fast) {
-        // (div_by makes +0 of -0; the sign is the dividend's)
+        // div_by, except that its remainder is kept finite: an infinite quotient (a supplied scale bounds nothing) has none, and the
+        // conversion tells infinities from NaN.  And it makes +0 of -0; the sign is the dividend's.
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = copysignf(div_by(x[i], sc[e], rc[e]), x[i]);
+        for (int i = 0; i < 4; ++i) {
+          const float q = __fmul_rn(x[i], rc[e]), rem = __builtin_amdgcn_fmed3f(__fmaf_rn(q, -sc[e], x[i]), -0x1.fffffep127f, 0x1.fffffep127f);
+          x[i] = copysignf(__fmaf_rn(rem, rc[e], q), x[i]);
+        }
       } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {

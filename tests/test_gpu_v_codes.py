@@ -35,3 +35,22 @@ def test_v_codes(d, dtype, smooth_v, nk, zeros):
         pro = so.quantize_head(vn[h], vn[h], vn[h], mode="int8_fp8", smooth_v_on=smooth_v)
         assert np.array_equal(got["v_scale"][0, h].cpu().numpy(), pro["v_scale"])
         assert np.array_equal(got["v_codes"][0, h].cpu().numpy(), pro["v_codes"])
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "fp16"), (128, "bf16"), (256, "bf16")])
+def test_v_codes_beyond_a_supplied_scale(d, dtype):
+    """A supplied scale bounds nothing: infinite values and quotients (bfloat16: a quotient past the largest float32) and NaN have the codes
+    that the dividing form gives them, which a last channel with a scale of all mantissa bits calls for."""
+    pa = _pa()
+    print(f"V codes beyond the scale: d={d} {dtype}", flush=True)
+    inf, big = float("inf"), 3e38 if dtype == "bf16" else 6e4
+    g = torch.Generator(device="cuda").manual_seed(d)
+    v = torch.randn(1, 2, 131, d, generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float16)
+    for key, x in ((0, inf), (5, -inf), (66, float("nan")), (67, big), (68, -big), (130, inf)):
+        v[:, :, key, 3] = v[:, :, key, d - 9] = x
+    scale = torch.full((1, 2, d), 2.0 ** -8, device="cuda")
+    divided = scale.clone()
+    divided[:, :, d - 1] = float.fromhex("0x1.fffffep-9")
+    codes = [pa.sage_attn_quant(v, v, v, mode="int8_fp8", kv_stats=(torch.zeros_like(scale), s), want=("v_codes",))[0]["v_codes"] for s in (scale, divided)]
+    torch.cuda.synchronize()
+    assert torch.equal(codes[0][..., :d - 1], codes[1][..., :d - 1])
