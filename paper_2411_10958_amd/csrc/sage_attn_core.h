@@ -46,6 +46,23 @@ inline AttnParams attn_params(const Dims& Dm, const Ptrs& P) {
 // merge of the chunks of packed tiles (p.total_tiles of them: one per batch and KV head)
 hipError_t launch_merge_packed(const Dims& Dm, const AttnParams& p, hipStream_t s);
 
+// Whether the tiles of a packed batch of B sequences of at most N queries, `tokens` in all, go out in bands (in k_attn_fwd) or in the order
+// of a fixed-length batch.  What the bands mend is raggedness, so the rule asks for it: a batch of (nearly) equal sequences has the
+// heavy tiles of all of them first in the old order too, and its groups of heads share more.  Attention alone, us, old order / bands.
+// No mask, by the part of B N that is there: 1 (41 of 500, 32 heads) 155 / 161, (8 of 8192, 32 heads) 5088 / 5459, 0.96 (16 of
+// 2000, 64 channels) 239 / 246, 0.94 (8 of 4096, 32 heads) 1301 / 1268, 0.88 1266 / 1169, 0.75 1238 / 931, 0.36 1127 / 433; (31 of
+// 6000) 0.19 2710 / 928; over 116 batches bands take 0.81 of the time, with the line at 0.9 or at 1 too, the worst under it 1.15 (64 of
+// up to 662, 2 heads of 256 channels).  Causal: 1 (8 of 4096, 8 heads of 256 channels) 297 / 314, (12 of 2000) 132 / 144, (8 of 8192, 32
+// heads) 2735 / 2807, 0.90 (16 of 2000) 155 / 161, 0.75 (8 of 4096, 16 heads of 64 channels) 167 / 172, 0.62 (16 of 2000, 8 heads of 256
+// channels) 144 / 102, 0.36 (8 of 4096, 32 heads) 223 / 206, 0.29 (61 of 2500, 32 heads) 399 / 374, 0.19 (31 of 6000, 16 heads) 258 / 238, but with 32 heads 445 / 462; over 188
+// batches of 600 to 40000 tiles 0.96, the worst under the line 1.08.  One band is no order: causal batches of up to BAND_LEVELS positions
+// lose (41 of 500, 8 heads of 256 channels 59 / 68, 32 of up to 407 17.8 / 20.7).
+constexpr int BAND_LEVELS = 4;
+__host__ __device__ inline bool packed_in_bands(bool causal, int tokens, int B, int N) {
+  const long long full = (long long)B * N;
+  return causal ? N > BAND_LEVELS * BQ && 16LL * tokens < 13 * full : 32LL * tokens < 31 * full;
+}
+
 // Split of a tile's key blocks [0, nblk) into chunks, one workgroup each (Sec. 2.1, Eq. 1: the running maximum / sum /
 // output of disjoint key sets combine by the same rule that combines consecutive blocks).  Every chunk must start
 // with a block in which every query of the tile sees a key, so the chunks divide the first n_vis blocks - those

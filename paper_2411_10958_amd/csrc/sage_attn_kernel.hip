@@ -25,8 +25,6 @@ __device__ __forceinline__ void set_priority(int p) {     // (the instruction ta
   else if (p == 1) __builtin_amdgcn_s_setprio(1);
   else __builtin_amdgcn_s_setprio(0);
 }
-// Tile order of packed batches (in the kernel).
-constexpr int BAND_LEVELS = 4, BAND_TILES = 8192;
 
 // PACK (with SPLIT; short queries, grouped KV heads): a tile holds ALL queries of the G = H / H_kv query heads that
 // share one KV head - column c of the tile is query c % n of head c / n of the group, n the sequence's query count
@@ -68,22 +66,16 @@ __global__ void __launch_bounds__(256, (attn_occupancy<D, GM, PVF>())) k_attn_fw
   // interleaved heads no longer share an XCD's L2 there (N = 32768: 1.5 % slower), and the equal shares still
   // count when 8 does not divide the head count (28 heads of 32768 tokens: +4.5 %).
   // A packed batch: sequence by sequence, a long one late in the batch would start its heavy tiles when the short ones are
-  // nearly done, and in contiguous ranges (no mask) each XCD would work on sequences of its own.  Its tiles go out in bands of
-  // BAND_LEVELS positions instead, from the last position of the longest sequence down, in a band sequence by sequence, heaviest
-  // first - so that the tiles of a head still run close together.  Attention alone, us, before / in bands: no mask, 8 sequences of up to
-  // 4096 tokens, 32 on 8 heads 1123 / 457, 60 of 1000 and one of 3000, 32 heads 1319 / 933, 10 of 2000 and one of 16000, 64 channels
-  // 13314 / 2593, 16 of 4096 2720 / 2736, 8 of 8192 4784 / 4946, 41 of 500 151 / 157; causal, 8 of up to 4096, 32 on 8 heads 214 /
-  // 199, 8 heads of 256 channels 141 / 116; 300, 5000, 2000, 512 and 6000 tokens, 8 on 2 heads of 256 channels 308 / 158; 12000, 3000,
-  // 100 and 9000, 16 on 4 922 / 587; 8 of 2048, 32 heads 204 / 206, 3 of 3000 153 / 156, 4 of 8192, 16 heads of 256 channels 1053 / 1074.
-  // Under a mask from BAND_TILES tiles on the last tiles weigh little and the heads' codes no longer meet in the caches (12 of 4096,
-  // 32 heads 1082 / 1099, 8 of 8192 2622 / 2735).
+  // nearly done, and in contiguous ranges (no mask) each XCD would work on sequences of its own.  The tiles of a ragged one
+  // (packed_in_bands) go out in bands of BAND_LEVELS positions instead, from the last position of the longest sequence down, in a band
+  // sequence by sequence, heaviest first - so that the tiles of a head still run close together.
   const int n_wg = SPLIT ? p.total_tiles * p.splits : p.total_tiles;
   const int per_xcd = (n_wg + 7) / 8;
   const int in_xcd = blockIdx.x / 8;
   int tile = (blockIdx.x % 8) * per_xcd + in_xcd;
   int split = 0;
   int bh, qb;
-  const bool bands = !SPLIT && p.seq.cu_q && (!CAUSAL || p.total_tiles <= BAND_TILES);
+  const bool bands = !SPLIT && p.seq.cu_q && packed_in_bands(CAUSAL, p.seq.cu_q[p.B] - p.seq.cu_q[0], p.B, p.N);
   if (!SPLIT && (CAUSAL || bands)) {
     tile = blockIdx.x;
     if (tile >= n_wg) return;
