@@ -1409,26 +1409,23 @@ bool small_call(const Dims& Dm) {
 
 // K and V in one launch (k_quant_kv) for larger calls too: the one's loads and stores run under the other's arithmetic, and one launch
 // and one tail are saved.  The registers are the larger body's, K's with Delta-S, so where K fills the chip by itself and its workgroups are
-// long (many rows of block means) V's are better off in a launch of their own.  4-bit mode, preprocessing alone on inputs in turn, one launch
-// over two, by key blocks and rows per KV head: 64 channels 576 to 1056 blocks, 2 to 132 rows 0.89 to 0.96, 2048, 2 to 132 rows 0.91 to 0.98, 4096, 2
-// to 100 rows 0.92 to 0.99, 8192, 2 to 64 rows 0.96 to 0.99; 128 channels 400 to 1056, 2 to 300 rows 0.89 to 0.98, 2048, 2 to 132 rows 0.90 to
-// 0.98, 4096, 2 to 132 rows 0.95 to 0.99, 8192 and 12000, 28 to 64 rows 0.98 to 1.00, but 6000 to 12000, 2 to 16 rows 0.99 to 1.02; beyond the
-// product of the lines below 2000, 200 rows 1.00 and 1.01, 1200, 200 and 300 rows 0.97 to 1.06, 6000, 100 rows 0.99 and 1.01, 4096, 128 rows
-// 1.04 (causal), 16384, 128 rows 1.08.  (Between the first line and the second, 25 to 31 rows or 769 to 800 blocks, two launches: 0.90 to 0.94 would
-// be had there.)  256 channels, whole calls, time of two launches / one: 250, 39 rows 1.04, 328 to 432, 48 to 72 rows 0.99, 500, 56 rows 0.97,
+// long (many rows of block means) V's are better off in a launch of their own.  A packed batch is counted by its longest sequence, which is all
+// that is known here; the lines hold for it as they do for a batch of fixed length.
+// 4-bit mode, 64 and 128 channels, preprocessing alone on inputs in turn, one launch over two, some 1400 calls of both kinds and layouts by key
+// blocks and rows per KV head, lowest to highest (mean): up to 800 blocks 0.84 to 1.03 (0.92; 250 to 2200 rows 0.91 to 1.01).  Up to 24
+// rows, 801 to 4608 blocks 0.86 to 1.02 (0.96), 4609 to 7000 of 64 channels 0.94 to 1.00 (0.98), of 128 0.98 to 1.04 (1.00), more of 64
+// channels 0.92 to 1.07 (1.00), of 128 0.96 to 1.08 (1.03).  More rows by their product with the blocks: 25 to 256 rows, up to 393216 0.88 to 1.02 (0.97), to 600000 0.90 to 1.05 (0.99), to
+// 900000 0.96 to 1.03 (1.00), more 0.97 to 1.09 (1.02); more than 256 rows and 800 blocks 0.92 to 1.12 (1.00).
+// 256 channels, whole calls, time of two launches / one: 250, 39 rows 1.04, 328 to 432, 48 to 72 rows 0.99, 500, 56 rows 0.97,
 // 512 to 640, 1 to 24 rows 1.00 to 1.04, 736, 12 rows 0.99, 960, 2 rows 0.95.  8-bit, whose two quantizers are alike, 64 and 128 channels,
 // us: 1536 blocks 119.3 / 118.2, 3912 142.5 / 140.6, 4928 165.8 / 165.0, 5056 139.4 / 140.9, 7360 315.3 / 320.0, 13496 234.4 / 238.3; 256
-// channels 584 179.4 / 176.4, 768 74.9 / 74.2, 2048 389 / 409.  A packed batch has fewer blocks and rows than its longest sequence says: 8
-// sequences of up to 4096 tokens, 12321 in all, 32 on 8 heads, 4096 blocks and 128 rows by that count, preprocessing 113.5 / 105.8 us.
+// channels 584 179.4 / 176.4, 768 74.9 / 74.2, 2048 389 / 409.
 static bool kv_pair(const Dims& Dm) {
   if (Dm.tensor_groups || Dm.pvf != PV_E4M3 || Dm.ds32) return false;
   const long long blocks = (long long)Dm.B * Dm.Hkv * Dm.nKb, rows = (long long)(Dm.H / Dm.Hkv) * Dm.nQb;
-  if (!Dm.int4) return blocks <= (Dm.d == 256 ? 768 : 4608);
-  const int line = Dm.seq.cu_q ? 768 : Dm.d == 256 ? (few_rows(Dm) ? 640 : 320) : (few_rows(Dm) ? 768 : (Dm.d == 64 ? 640 : 400));
-  if (blocks <= line || Dm.d == 256) return blocks <= line;
-  if (Dm.seq.cu_q) return blocks * rows <= 1 << 19;
-  if (few_rows(Dm)) return blocks > 800 && blocks <= 4096;
-  return (rows >= 32 || blocks > 800) && (rows <= 160 || blocks <= 800) && blocks * rows <= 3 << 17;
+  if (Dm.d == 256) return blocks <= (!Dm.int4 || Dm.seq.cu_q ? 768 : few_rows(Dm) ? 640 : 320);
+  if (!Dm.int4 || few_rows(Dm)) return blocks <= 4608;
+  return blocks <= 800 || (rows <= 256 && blocks * rows <= 600000);
 }
 
 template <bool BF16, bool INT4, int D>

@@ -14,8 +14,8 @@ def _pa():
 # sequences, N, N_kv, d, H, Hkv, mode, smooth_v: one sequence more than the pair takes (tests/test_launch_routes.py holds the launches to
 # that).  4-bit with few rows of block means, with many; 8-bit
 PAIR_CASES = [
-    (25, 100, 2047, 64, 2, 1, "int4_fp8", False), (25, 129, 1985, 128, 1, 1, "int4_fp8", True), (21, 70, 2000, 256, 3, 1, "int4_fp8", False),
-    (21, 500, 2001, 64, 7, 1, "int4_fp8", True), (13, 3201, 2048, 128, 1, 1, "int4_fp8", False), (11, 520, 2040, 256, 5, 1, "int4_fp8", False),
+    (145, 100, 2047, 64, 2, 1, "int4_fp8", False), (145, 129, 1985, 128, 1, 1, "int4_fp8", True), (21, 70, 2000, 256, 3, 1, "int4_fp8", False),
+    (26, 1000, 2001, 64, 35, 1, "int4_fp8", True), (26, 700, 2048, 128, 44, 1, "int4_fp8", False), (11, 520, 2040, 256, 5, 1, "int4_fp8", False),
     (25, 300, 2048, 256, 1, 1, "int8_fp8", True), (25, 67, 2047, 256, 1, 1, "int8_fp8", False), (145, 64, 2001, 128, 2, 1, "int8_fp8", False), (145, 33, 2048, 64, 1, 1, "int8_fp8", True)]
 
 
@@ -33,14 +33,14 @@ def test_one_launch_equals_two(B, N, Nk, d, H, Hkv, mode, smooth_v):
     assert torch.equal(one, two[:-1]) and torch.equal(lse_one, lse_two[:-1])
 
 
-# the 4-bit lines for larger calls, one sequence more than the pair takes: blocks for few rows, the product of blocks and rows, blocks for more than
-# 160 rows; and (last) one sequence more than two launches take, from 801 blocks on
-LARGE_PAIR_CASES = [(129, 100, 2047, 64, 1, 1, True), (129, 129, 1985, 128, 2, 1, True), (77, 900, 2001, 64, 20, 1, True), (385, 250, 2048, 128, 16, 1, True),
-                    (26, 800, 2010, 128, 24, 1, True), (26, 100, 2000, 128, 1, 1, False), (26, 400, 2040, 64, 7, 1, False)]
+# the 4-bit lines for larger calls, one sequence more than the pair takes: blocks for up to 24 rows, the product of blocks and rows, blocks for more
+# than 256 rows.  No case of fewer blocks or rows takes two launches (tests/test_launch_routes.py)
+LARGE_PAIR_CASES = [(145, 100, 2047, 64, 1, 1), (145, 129, 1985, 128, 12, 1), (94, 1200, 2001, 64, 20, 1), (670, 400, 2048, 128, 7, 1),
+                    (74, 1024, 2040, 128, 32, 1), (26, 1100, 2010, 128, 29, 1)]
 
 
-@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,more_is_two", LARGE_PAIR_CASES)
-def test_one_launch_equals_two_on_larger_calls(B, N, Nk, d, H, Hkv, more_is_two):
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv", LARGE_PAIR_CASES)
+def test_one_launch_equals_two_on_larger_calls(B, N, Nk, d, H, Hkv):
     pa = _pa()
     print(f"K/V pair, larger: B={B} N={N} N_kv={Nk} d={d} H={H}/{Hkv}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(B + N + Nk + d)
@@ -51,6 +51,28 @@ def test_one_launch_equals_two_on_larger_calls(B, N, Nk, d, H, Hkv, more_is_two)
     torch.cuda.synchronize()
     assert torch.isfinite(more).all()
     assert torch.equal(less, more[:-1]) and torch.equal(lse_less, lse_more[:-1])
+
+
+# packed batches, counted by their longest sequence: one sequence more than the pair takes
+PACKED_PAIR_CASES = [(145, 100, 2047, 64, 1, 1, "int4_fp8"), (145, 300, 2000, 128, 8, 1, "int4_fp8"), (94, 1200, 2001, 64, 20, 1, "int4_fp8"), (26, 1100, 2010, 128, 29, 1, "int4_fp8"),
+                     (25, 100, 2048, 256, 1, 1, "int4_fp8"), (25, 900, 2000, 256, 8, 1, "int4_fp8"), (145, 64, 2001, 128, 2, 1, "int8_fp8"), (25, 67, 2047, 256, 1, 1, "int8_fp8")]
+
+
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode", PACKED_PAIR_CASES)
+def test_one_launch_equals_two_on_packed_batches(B, N, Nk, d, H, Hkv, mode):
+    pa = _pa()
+    print(f"K/V pair, packed: B={B} N={N} N_kv={Nk} d={d} H={H}/{Hkv} {mode}", flush=True)
+    nq, nk = ([n] + [max(1, n * (7 * i % 11) // 10 % (n + 1)) for i in range(1, B)] for n in (N, Nk))
+    g = torch.Generator(device="cuda").manual_seed(B + N + Nk + d)
+    q, k, v = (torch.randn(sum(n), h, d, generator=g, device="cuda").half() for h, n in ((H, nq), (Hkv, nk), (Hkv, nk)))
+    cq, ck = (torch.tensor([0] + n).cumsum(0).to(torch.int32).cuda() for n in (nq, nk))
+    kw = dict(mode=mode, max_seqlen_q=N, max_seqlen_k=Nk, return_lse=True, kv_splits=1)
+    more, lse_more = pa.sage_attn_fwd_ex(q, k, v, cu_seqlens_q=cq, cu_seqlens_k=ck, **kw)
+    a, b = sum(nq[:-1]), sum(nk[:-1])
+    less, lse_less = pa.sage_attn_fwd_ex(q[:a], k[:b], v[:b], cu_seqlens_q=cq[:-1], cu_seqlens_k=ck[:-1], **kw)
+    torch.cuda.synchronize()
+    assert torch.isfinite(more).all()
+    assert torch.equal(less, more[:a]) and torch.equal(lse_less, lse_more[:, :a])
 
 
 # the lines of small_call: 32 chunks of 256 keys, 20480 workgroups times chunks, 768 key blocks (384 with many rows of block means) at 256 channels; last: whether the

@@ -6,7 +6,7 @@ import pytest
 from launch_recorder import launches
 from test_gpu_attention_from_raw_kv import REDUCE_CASES
 from test_gpu_few_workgroups import CASES, THREE_LAUNCHES
-from test_gpu_kv_pair import LARGE_PAIR_CASES, PAIR_CASES, SMALL_CASES
+from test_gpu_kv_pair import LARGE_PAIR_CASES, PACKED_PAIR_CASES, PAIR_CASES, SMALL_CASES
 
 POINTER = 4096
 BASE = dict(B=1, H=32, H_kv=32, d=128, dtype=1, mode=1, layout=1)
@@ -50,12 +50,35 @@ def test_one_sequence_more_takes_two_launches(B, N, Nk, d, H, Hkv, mode, smooth_
     assert "k_quant_kv" not in two and "k_quant_k" in two and "k_quant_v" in two
 
 
-@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,more_is_two", LARGE_PAIR_CASES)
-def test_the_lines_of_the_pair_on_larger_calls(B, N, Nk, d, H, Hkv, more_is_two):
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv", LARGE_PAIR_CASES)
+def test_the_lines_of_the_pair_on_larger_calls(B, N, Nk, d, H, Hkv):
     call = dict(N=N, N_kv=Nk, d=d, H=H, H_kv=Hkv, dtype=1, mode=0, lse=POINTER, kv_splits=1)
-    for b, two in ((B, more_is_two), (B - 1, not more_is_two)):
+    for b, two in ((B, True), (B - 1, False)):
         names = _names(B=b, **call)
         assert ("k_quant_kv" in names) == (not two) and ("k_quant_v" in names) == two, (b, names)
+
+
+@pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode", PACKED_PAIR_CASES)
+def test_the_lines_of_the_pair_on_packed_batches(B, N, Nk, d, H, Hkv, mode):
+    call = dict(N=N, N_kv=Nk, d=d, H=H, H_kv=Hkv, dtype=0, mode=_mode(mode), layout=1, lse=POINTER, kv_splits=1, cu_seqlens_q=POINTER, cu_seqlens_k=POINTER)
+    for b, two in ((B, True), (B - 1, False)):
+        names = _names(B=b, **call)
+        assert ("k_quant_kv" in names) == (not two) and ("k_quant_v" in names) == two, (b, names)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("packed", [dict(), dict(layout=1, cu_seqlens_q=POINTER, cu_seqlens_k=POINTER)])
+def test_the_pair_has_no_holes(d, packed):
+    """With more blocks, or more rows, the pair is left for good."""
+    sizes = [1, 2, 8, 16, 24, 25, 26, 31, 32, 64, 128, 160, 256, 257, 300, 400, 600, 700, 768, 769, 800, 801, 1000, 2000, 3000, 4096, 4608, 4609, 6000, 12000, 24000, 24001, 40000]
+    calls = [("sage_attn_fwd_ex", dict(B=b, N=1, N_kv=64, d=d, H=r, H_kv=1, dtype=1, mode=0, lse=POINTER, kv_splits=1, k_mean_in=POINTER, v_scale_in=POINTER, flags=32, **packed))
+             for r in [x for x in sizes if x <= 400] for b in sizes if b * r <= 65535]
+    res = launches(calls)
+    pair = {(kw["H"], kw["B"]): "k_quant_kv" in [x.kernel for x in seq] for (_, kw), (_, seq) in zip(calls, res)}
+    assert all(status == 0 for status, _ in res)
+    for (r, b), p in pair.items():
+        if p:
+            assert all(q for (r2, b2), q in pair.items() if r2 == r and b2 < b or b2 == b and 24 < r2 < r or b2 == b and r2 < r <= 24), (r, b)
 
 
 @pytest.mark.parametrize("mode", [0, 1])
