@@ -629,8 +629,8 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
 // 4-bit: one workgroup of 8 blocks of 256 channels 0.94, 4 of 12 of 128 channels 1.06, of 20 0.90.  16 workgroups: chunks of 20 blocks
 // of 256 channels 0.97 (4-bit) and 1.16, of 32 of 128 0.96 and 1.14, of 32 of 64 1.06 and 1.12.  Automatic chunks are of 8 to 15
 // blocks until there are 512 workgroups or 64 chunks.
-// Where the general path has two (small_call) and the statistics are not supplied this kernel saves none: it comes after the
-// statistics and their reduction.  4-bit, up to 8 queries, 48 workgroups and more 0.99 to 2.05 at any length; 32 to 47, chunks of up
+// Where the general path has two (small_call) and the statistics are not supplied this kernel came after the statistics and their
+// reduction and saved none; these figures are of that form, 2 to 4 us a call before raw_reduces.  4-bit, up to 8 queries, 48 workgroups and more 0.99 to 2.05 at any length; 32 to 47, chunks of up
 // to 3 blocks 1.04 to 1.35, of more 0.90 to 1.21; fewer, of 4 blocks of 64 channels 0.99 to 1.08, of 2 of 128 1.01 to 1.15, of 3 of
 // 256 1.02 to 1.09, then 0.95 (6 blocks of 64), 0.90 (6 of 128), 0.86 (5 of 256), 0.66 to 0.90 (20 and more).  It adds up the block
 // means of more queries one by one: 20 to 32 queries, 48 to 95 workgroups 0.88 to 1.10, fewer 0.72 to 1.00, but 1 or 2 blocks of 256
@@ -655,13 +655,12 @@ bool attention_raw_ok(const Dims& D) {
 
 // Whether the kernel reduces the partial results of the statistics pass itself (every workgroup for its head) instead of a launch of its
 // own in front.  The launch is 2 to 4 us of a call, the reduction reads 12 bytes a channel and 256-key chunk in every workgroup.  Whole calls on
-// inputs in turn, this / a launch: 2000 keys 0.88 to 0.97, 8000 of 128 channels 0.94 (8 KV heads) to 0.99 (64), 32000 0.97
-// to 0.98, 60000 of 64 channels 0.96 to 0.97, of 128 1.01; 8000 of 256 channels 0.98, 12000 and more 1.01 to 1.03; past the 256 MB of the memory-side
-// cache, where the partial results lie, 0.98 to 1.01.  Calls in one chunk - short caches, or one asked for - keep the launch, which tests hold
-// them to (300 keys: 0.84 to 0.89 would be had).
+// inputs in turn, this / a launch: 100 keys 0.82 to 0.84, 300 0.88 to 0.92, 500 to 1000 0.89 to 0.97, 2000 0.88 to 0.97, 8000 of 128 channels
+// 0.94 (8 KV heads) to 0.99 (64), 32000 0.97 to 0.98, 60000 of 64 channels 0.96 to 0.97, of 128 1.01; 8000 of 256 channels 0.98, 12000 and
+// more 1.01 to 1.03; past the 256 MB of the memory-side cache, where the partial results lie, 0.98 to 1.01.
 bool raw_reduces(const Dims& D) {
   const int nchunk = (D.Nk + STAT_ROWS - 1) / STAT_ROWS;
-  return !D.stats_given && D.splits > 1 && nchunk * D.d <= (D.d == 256 ? 8192 : 16384) && 4LL * D.B * D.Hkv * D.Nk * D.d <= 256LL << 20;
+  return !D.stats_given && nchunk * D.d <= (D.d == 256 ? 8192 : 16384) && 4LL * D.B * D.Hkv * D.Nk * D.d <= 256LL << 20;
 }
 
 template <int DD, bool INT4, bool CAUSAL>

@@ -126,7 +126,7 @@ def test_one_query_and_a_key_that_is_not_finite(B, Nk, d, dtype, H, Hkv, layout,
 
 # the lines of raw_reduces: chunks of 256 keys times channels, bytes of K and V; last: whether the kernel reduces the statistics itself
 REDUCE_CASES = [(1, 65536, 64, 2, 2, True), (1, 65537, 64, 2, 2, False), (1, 32768, 128, 4, 1, True), (1, 32769, 128, 4, 1, False), (2, 8192, 256, 1, 1, True),
-                (2, 8193, 256, 1, 1, False), (32, 4096, 128, 4, 4, True), (32, 4097, 128, 4, 4, False)]
+                (2, 8193, 256, 1, 1, False), (32, 4096, 128, 4, 4, True), (32, 4097, 128, 4, 4, False), (64, 2, 128, 4, 1, True), (64, 257, 256, 2, 2, True)]
 
 
 @pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
@@ -136,7 +136,8 @@ def test_statistics_reduced_in_the_kernel_or_before(B, Nk, d, H, Hkv, reduces, m
     print(f"raw K, V, statistics: B={B} N_kv={Nk} d={d} H={H}/{Hkv} {mode}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(Nk + d)
     q, k, v = (torch.randn(B, h, n, d, generator=gen, device="cuda").add_(0.5).half() for h, n in ((H, 2), (Hkv, Nk), (Hkv, Nk)))
-    _compare(_both(pa, q, k, v, pa.make_args(q, k, v, None, causal=True, mode=mode)))
+    for splits in ((0, 1) if B * Hkv >= 64 else (0,)):           # (in several chunks, and in one)
+        _compare(_both(pa, q, k, v, pa.make_args(q, k, v, None, causal=True, mode=mode, kv_splits=splits)))
 
 
 @pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])

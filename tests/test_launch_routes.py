@@ -1,5 +1,6 @@
 """Which kernels a call launches and on what grids, from the library's own launches with the HIP runtime replaced: no GPU."""
 import itertools
+import re
 
 import pytest
 
@@ -89,6 +90,19 @@ def test_decode_calls_reduce_the_statistics_in_the_kernel_or_before(B, Nk, d, H,
     assert "k_attn_raw" in names and ("k_finalize_stats" in names) == (not reduces), names
     given = _names(k_mean_in=POINTER, v_scale_in=POINTER, **call)
     assert given[0] == "k_attn_raw", given
+    if B * Hkv >= 64:                      # ... in one chunk as in several
+        one = _names(kv_splits=1, **call)
+        assert "k_attn_raw" in one and "k_merge_splits" not in one and ("k_finalize_stats" in one) == (not reduces), one
+
+
+@pytest.mark.parametrize("extra", [dict(), dict(causal=1), dict(kv_splits=1), dict(layout=1, cu_seqlens_q=POINTER, cu_seqlens_k=POINTER), dict(k_mean_in=POINTER, v_scale_in=POINTER)])
+@pytest.mark.parametrize("d,H", [(64, 8), (128, 32), (256, 64)])
+@pytest.mark.parametrize("mode,N,lone", [(0, 1, True), (0, 2, False), (1, 1, False)])
+def test_one_query_in_the_4_bit_mode_has_a_kernel_of_its_own(mode, N, lone, d, H, extra):
+    """(the last template argument of k_attn_raw)"""
+    (status, seq), = launches([("sage_attn_fwd_ex", {**dict(B=16, N=N, N_kv=3000, d=d, H=H, H_kv=8, dtype=1, mode=mode, lse=POINTER), **extra})])
+    raw = [x.mangled for x in seq if x.kernel == "k_attn_raw"]
+    assert status == 0 and len(raw) == 1 and re.search(r"ILi%dE.*Lb([01])EEE" % d, raw[0])[1] == str(int(lone)), raw
 
 
 @pytest.mark.parametrize("B,H,Hkv,N,Nk,d,mode", [(1, 2, 2, 256, 256, 64, 0), (39, 64, 8, 58, 586, 256, 1), (2, 8, 1, 300, 300, 128, 0), (18, 64, 8, 217, 435, 128, 1)])
@@ -114,7 +128,7 @@ def test_few_workgroups_keep_the_three_launches(B, H, Hkv, N, Nk, d, mode):
     assert _names(**call) == ["k_quant_q_and_stats", "k_quant_kv", "k_attn_fwd"]
     # ... and the kernel stays where it saves launches: statistics supplied, or the log-sum-exp wanted
     assert _names(**call, k_mean_in=POINTER, v_scale_in=POINTER) == ["k_attn_raw"]
-    assert _names(**call, lse=POINTER) == ["k_col_stats", "k_finalize_stats", "k_attn_raw"]
+    assert _names(**call, lse=POINTER) == ["k_col_stats", "k_attn_raw"]
 
 
 @pytest.mark.parametrize("B,N,Nk,d,H,Hkv,splits,raw4,raw8", CASES)
@@ -127,4 +141,4 @@ def test_few_workgroups_take_the_side_their_case_means(B, N, Nk, d, H, Hkv, spli
 @pytest.mark.parametrize("B,N,Nk,d,H,Hkv,mode,raw", THREE_LAUNCHES)
 def test_three_launches_take_the_side_their_case_means(B, N, Nk, d, H, Hkv, mode, raw):
     names = _names(B=B, N=N, N_kv=Nk, d=d, H=H, H_kv=Hkv, kv_splits=1, mode=_mode(mode), dtype=1, causal=1)
-    assert names == (["k_col_stats", "k_finalize_stats", "k_attn_raw"] if raw else ["k_quant_q_and_stats", "k_quant_kv", "k_attn_fwd"])
+    assert names == (["k_col_stats", "k_attn_raw"] if raw else ["k_quant_q_and_stats", "k_quant_kv", "k_attn_fwd"])
