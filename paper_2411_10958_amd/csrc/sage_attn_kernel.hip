@@ -217,8 +217,10 @@ __global__ void __launch_bounds__(256, (attn_occupancy<D, GM, PVF>())) k_attn_fw
     }
   };
   // Every wavefront issues at least MINC copies per block, in block order, and loads complete in
-  // order: "at most MINC outstanding" therefore means every block but the newest has landed.
+  // order: "at most MINC outstanding" therefore means every block but the newest has landed.  (A copy of no lanes may not
+  // count as outstanding: a form that waits by number - causal, with the software pipeline - has a rest piece for every wavefront.)
   constexpr int MINC = KR + CPT + (REST ? 1 : 0);
+  static_assert(OCC3 || !CAUSAL || !REST || NREST >= 4, "a wavefront without a rest piece does not issue MINC copies");
   auto wait_all_but_newest = [&]() {
     static_assert(MINC >= 1 && MINC <= 12, "copy count per block");
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(MINC) : "memory");
