@@ -12,13 +12,14 @@ from test_gpu_parity import _pa
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("pv", ["e4m3", "e5m2", "int8"])
 @pytest.mark.parametrize("zeros", [False, True])
 @pytest.mark.parametrize("nk", [1, 3, 4, 5, 63, 64, 65, 131])
 @pytest.mark.parametrize("d,dtype,smooth_v", [(64, "bf16", False), (64, "fp16", True), (128, "fp16", False), (128, "bf16", True), (256, "bf16", False),
                                               (256, "fp16", True)])
-def test_v_codes(d, dtype, smooth_v, nk, zeros):
+def test_v_codes(d, dtype, smooth_v, nk, zeros, pv):
     pa = _pa()
-    print(f"V codes: d={d} {dtype} N_kv={nk} smooth_v={smooth_v} zeros={zeros}", flush=True)
+    print(f"V codes: d={d} {dtype} N_kv={nk} smooth_v={smooth_v} zeros={zeros} {pv}", flush=True)
     rng = np.random.default_rng(d + nk)
     x = (rng.standard_normal((2, nk, d)) * 2.0 ** rng.integers(-6, 7, (2, 1, d))).astype(np.float32)
     x[rng.random(x.shape) < 0.05] = -0.0
@@ -29,12 +30,12 @@ def test_v_codes(d, dtype, smooth_v, nk, zeros):
     tt = torch.bfloat16 if dtype == "bf16" else torch.float16
     v = torch.from_numpy(x[None]).to(tt).to(dev)
     vn = v[0].float().cpu().numpy()
-    got, _, _ = pa.sage_attn_quant(v, v, v, mode="int8_fp8", smooth_v=smooth_v, want=("v_codes", "v_scale"))
+    got, _, _ = pa.sage_attn_quant(v, v, v, mode="int8_fp8", smooth_v=smooth_v, pv_format=pv, want=("v_codes", "v_scale"))
     torch.cuda.synchronize()
     for h in range(2):
-        pro = so.quantize_head(vn[h], vn[h], vn[h], mode="int8_fp8", smooth_v_on=smooth_v)
+        pro = so.quantize_head(vn[h], vn[h], vn[h], mode="int8_fp8", smooth_v_on=smooth_v, pv_fmt=pv)
         assert np.array_equal(got["v_scale"][0, h].cpu().numpy(), pro["v_scale"])
-        assert np.array_equal(got["v_codes"][0, h].cpu().numpy(), pro["v_codes"])
+        assert np.array_equal(got["v_codes"][0, h].cpu().numpy(), pro["v_codes"].view(np.uint8))
 
 
 @pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "fp16"), (128, "bf16"), (256, "bf16")])
