@@ -44,8 +44,8 @@ __device__ __forceinline__ double pair_sum(double (&x)[N]) {
 //
 // Bound: each block is a chain of its wavefronts' work behind one barrier; the split above is what makes the longest of them short,
 // and keeps every part in 128 registers (d = 64 and 128; d = 256: 189), so that two workgroups share a CU. 4 x 8 KV heads, 32768 keys,
-// d = 128, one query, statistics supplied: 102 us in the 4-bit mode (537 MB: 5.3 TB/s), 83 in the 8-bit one (6.4 TB/s), and a merge of
-// 5 us.  Whole calls, both modes: quantizers and attention kernel 255 / 185, four wavefronts quantizing both and four attending, with
+// d = 128, one query, statistics supplied, the kernel alone: 81 us in the 4-bit mode (LONE; 537 MB: 6.6 TB/s), 83 in the 8-bit one (6.5 TB/s),
+// and a merge of 5 us; whole calls 94 and 98, with two queries 116 and 98.  Whole calls of earlier forms, both modes: quantizers and attention kernel 255 / 185, four wavefronts quantizing both and four attending, with
 // 16 spilled registers, rows addressed and padded lane by lane and every mean of Delta-S waited for by itself 153 / 122, those mended
 // 139 / 103 with two attending wavefronts instead of four, this form 101 / 88. 16 of 256 channels, 30000 keys, 4-bit: 147, 128, 114.
 // 16 x 16 of 64 channels, 5003 keys, 8-bit: 139, 82, 74.  Tried: one attending wavefront (d = 64: 71 -> 69 us on grouped heads, 74 ->
@@ -54,8 +54,8 @@ __device__ __forceinline__ double pair_sum(double (&x)[N]) {
 // HEADS: 4, or PACK_G where the 4-bit mode has more than four query heads per KV head (two chains of the Delta-S product).
 // LONE: one query per head in the 4-bit mode.  It is its own block mean, gamma(Q) = 0, so all of its codes are 0 and so is
 // their product with K's: the score is Delta-S, and neither codes nor scales of Q and K are formed.  Same bits; whole calls, the kernel with
-// the codes / this one, on inputs in turn: 4 x 8 KV heads of 32768 keys 194 / 182 us, statistics supplied 107 / 92 (6.2 TB/s), 16 x 16
-// of 64 channels, 5003 keys 94 / 73, 16 of 256, 30000 keys 117 / 99, 8 of 4000 keys 34 / 30.  (A branch in the one kernel spilled 38 registers
+// the codes / this one, on inputs in turn: 4 x 8 KV heads of 32768 keys 194 / 182 us, statistics supplied 115 / 94, 16 x 16
+// of 64 channels, 5003 keys 95 / 74, 16 of 256, 30000 keys 119 / 100, 8 of 4000 keys, statistics not supplied, 34 / 30.  (A branch in the one kernel spilled 38 registers
 // of the calls with more queries: 70 / 87.)
 constexpr int RAW_V = 2, RAW_ATT = 2, RAW_THREADS = 64 * (4 + RAW_V + RAW_ATT);
 template <int D, bool INT4, bool CAUSAL, bool BF16, int HEADS, bool LONE = false>
