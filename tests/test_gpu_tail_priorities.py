@@ -1,4 +1,4 @@
-"""Workgroups of a launch's last round change their priority as their keys run out (tail_left in csrc/sage_attn_kernel.hip), in stretches of the
+"""Workgroups that end a launch change their priority as their keys run out (tail_left in csrc/sage_attn_kernel.hip), in stretches of the
 block loop: around every change, with whole and ragged last blocks, with and without a mask, the bits are those of calls too small to have it."""
 import pytest
 import torch
@@ -25,7 +25,7 @@ def _equal_parts(pa, heads, N, Nk, d, **kw):
 def test_without_a_mask(d, blocks, mode):
     import paper_2411_10958_amd as pa
     for Nk in (64 * blocks, 64 * blocks - 17):                  # 3 tiles a head: 360 workgroups, the parts 120
-        print(f"last round: d={d} N_kv={Nk} {mode}", flush=True)
+        print(f"tail: d={d} N_kv={Nk} {mode}", flush=True)
         _equal_parts(pa, 120, 300, Nk, d, mode=mode, kv_splits=1)
 
 
@@ -35,5 +35,5 @@ def test_causal_in_chunks(d, blocks, mode):
     """The wavefronts of a tile meet the mask at different blocks of its last chunk."""
     import paper_2411_10958_amd as pa
     for Nk in (128 * blocks, 128 * blocks + 45):                # 2 tiles a head in 2 chunks: 480 workgroups, the parts 160
-        print(f"last round, causal: d={d} N_kv={Nk} {mode}", flush=True)
+        print(f"tail, causal: d={d} N_kv={Nk} {mode}", flush=True)
         _equal_parts(pa, 120, 230, Nk, d, mode=mode, causal=True, kv_splits=2)
