@@ -156,8 +156,9 @@ typedef struct sage_attn_args {
                               chunks by the rule that combines consecutive blocks in Eq. 1 (Sec. 2.1).  For calls with
                               few query tiles and many keys - a decode step, a short chunk of queries against a long
                               cache - where one workgroup per tile would leave most of the chip idle.  0: the library
-                              decides (it splits when there are fewer than 256 tiles, and 256 to 384 tiles over keys
-                              long enough for chunks of 48 key blocks; sage_attn_kv_splits tells; sage_attn_fwd_static
+                              decides (it splits when there are fewer than 256 tiles, into whole rounds of workgroups, and
+                              256 to 384 tiles - of 64 channels 511 - over keys long enough for chunks of 48 key
+                              blocks; sage_attn_kv_splits tells; sage_attn_fwd_static takes fewer chunks of the former and
                               leaves the latter unsplit where only their partial results would not fit);
                               1: never; 2..64: this many (cut to one chunk per 8 key blocks at most).  Default groups
                               (SAGE_GROUPS_LANE, _BLOCK, _TENSOR) and SAGE_PV_E4M3 only, else 1.

@@ -3,11 +3,42 @@
 #include "sage_attn.h"
 #include "sage_common.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace {
 
 using namespace sage;
+
+// Chunks per tile for a launch of fewer than 256 tiles: about 512 workgroups, in whole rounds.  A chunk is one workgroup's chain from beginning
+// to end, so a few workgroups more than the chip holds at once - two per CU of the kernel that reads K and V itself and of 256-wide heads -
+// run a second round, which ceil(512 / tiles) chunks had wherever 512 is no multiple of the tiles.  Us, ceil / floor.
+// Whole calls that read K and V themselves, statistics supplied: 26 tiles of 17000 keys 61.9 / 44.9, 48 94.5 / 71.2, 72 135 / 102, 102 of 5000
+// 58.2 / 46.8, 120 207 / 168, 150 253 / 220, 232 338 / 326; of 64 channels 96 of 12000 77.9 / 63.9; of 256 88 of 7000 154 / 118.
+// Where that leaves much of the chip idle, two or three full rounds that save an eighth of its time (a sixth where a chunk has 15 key
+// blocks or fewer): 140 tiles, three / seven chunks 217 / 197, 172, two / five 296 / 258, 210, two / seven 313 / 291, but 146 of 5000 keys, three /
+// seven 65.9 / 71.0, and 110, four / nine / thirteen, 165 / 160 / 171 and of 256 channels 147 / 155 / 173.
+// Attention alone: packed tiles of 80 columns, 24 of 20000 keys 44.5 / 38.2, of 256 channels 71.0 / 55.4, 90 of 8000 54.8 / 48.6; 256 channels, 144
+// of 9000 127 / 104, 45 of 30000 154 / 114, 200 of 6000 118 / 106, 180 of 3800 88.8 / 76.9, causal 61.4 / 63.3.
+// Other tiles of 128 (64) channels, of which three (four) workgroups fit a CU: floor where that is 480 workgroups and more (45 of 30000 91.0 /
+// 81.5, 30 of 10000 35.4 / 33.2, 100 of 4000 39.7 / 38.4), else as many as fit the chip while a chunk keeps more than 15 key blocks (144 of 9000, four
+// / five chunks 74.9 / 70.1, of 20000 142 / 126; 64 channels, four / seven 64.2 / 55.7 and 117 / 97; with fewer the partial results cost
+// the gain: 180 of 3800, three / four 41.3 / 42.7).  A packed batch, whose tiles are counted by its longest sequence, has fewer than that and keeps
+// ceil (3 of up to 4736 tokens, 222 tiles, three / four 60.0 / 60.3).
+long long chunks_of_few_tiles(long long tiles, long long nKb, int d, bool short_queries, bool packed_batch) {
+  const long long up = (512 + tiles - 1) / tiles, down = 512 / tiles;
+  if (short_queries) {
+    long long S = down, rounds = 1;
+    for (long long r = 2; r <= 3 && 512 * r / tiles < 9; ++r) {
+      const long long s = 512 * r / tiles;
+      const int part = nKb > 15 * s ? 8 : 6;
+      if (r * S * part <= rounds * s * (part - 1)) { S = s; rounds = r; }
+    }
+    return S;
+  }
+  if (d == 256 || (down >= 3 && down * tiles >= 480)) return down;
+  return packed_batch ? up : std::max(up, std::min((d == 64 ? 1024 : 768) / tiles, (nKb - 1) / 15));
+}
 
 int validate(const sage_attn_args* a, Dims* D, bool need_io) {
   if (!a) return SAGE_ERR_INVALID_ARG;
@@ -78,7 +109,7 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
     const int G = a->H / a->H_kv;
     D->pack = G >= 2 && G <= PACK_G && (long long)G * a->N <= BQ;     // (a->N: the longest sequence's queries)
     const long long tiles = D->pack ? (long long)a->B * a->H_kv : (long long)a->B * a->H * nQb;
-    long long S = a->kv_splits > 1 ? a->kv_splits : (tiles < 256 ? (512 + tiles - 1) / tiles : 1);
+    long long S = a->kv_splits > 1 ? a->kv_splits : (tiles < 256 ? chunks_of_few_tiles(tiles, nKb, a->d, D->pack || (long long)G * a->N <= 32, a->cu_seqlens_q != nullptr) : 1);
     if (a->kv_splits == 0 && !D->pack && tiles >= 256) {
       // One or two workgroups per CU, of the three that fit: a lone wavefront issues far fewer vector instructions than
       // two or three that share the SIMD.  Three chunks per tile while they make four workgroups per CU at most, two while they
@@ -89,7 +120,9 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
       // chunks up to 341 tiles 0.67 - 0.98, two up to 384 0.74 - 1.01; past the lines three at 352 - 384 tiles up to 1.06
       // (256-wide 1.16), two at 392 - 504 tiles up to 1.25 (10 heads of 6400 tokens, causal: 145 us, 183), two of 256-wide
       // heads at 264 - 384 tiles up to 1.17.
-      S = tiles <= 341 ? 3 : (tiles <= 384 ? 2 : 1);
+      // 64-wide heads, of which four workgroups fit a CU, take two chunks up to 511 tiles (attention alone, one / two: 400 tiles on 8192 keys 139 /
+      // 122 us, on 20000 334 / 268, 450 on 10000 170 / 152, 480 on 8000 140 / 127).
+      S = tiles <= 341 ? 3 : (tiles <= (a->d == 64 ? 511 : 384) ? 2 : 1);
       if (S > nKb / 48) S = nKb / 48;
       if (a->d == 256 && S == 2 && tiles > 256) S = 1;
     }
@@ -102,6 +135,7 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
   return SAGE_OK;
 }
 
+long long auto_tiles(const Dims& D) { return D.pack ? (long long)D.B * D.Hkv : (long long)D.B * D.H * D.nQb; }
 // A split that the library picked for a launch of 256 tiles or more (see validate).
 bool splits_by_choice(const Dims& D) { return !D.pack && D.splits > 1 && (long long)D.B * D.H * D.nQb >= 256; }
 
@@ -245,8 +279,10 @@ int sage_attn_fwd_static(const sage_attn_args* args) {
   int st = validate(args, &D, true);
   if (st != SAGE_OK) return st;
   Workspace w = make_workspace(D);
-  if (w.total > (size_t)SAGE_STATIC_WORKSPACE_BYTES && args->kv_splits == 0 && splits_by_choice(D)) {
-    D.splits = 1;                           // fits without the partial results of a split that is only there for speed
+  if (w.total > (size_t)SAGE_STATIC_WORKSPACE_BYTES && args->kv_splits == 0 && D.splits > 1) {
+    // fits without the partial results of a split that is only there for speed, or with those of 512 workgroups
+    if (splits_by_choice(D)) D.splits = 1;
+    else D.splits = std::min(D.splits, (int)((512 + auto_tiles(D) - 1) / auto_tiles(D)));
     w = make_workspace(D);
   }
   if (w.total > (size_t)SAGE_STATIC_WORKSPACE_BYTES) return SAGE_ERR_WORKSPACE;   // beyond the built-in workspace
