@@ -85,7 +85,7 @@ __host__ __device__ inline KeyChunk key_chunk(int s, int S, int nblk, int n_vis)
 // 32*kt + 16*(lane/32) + v of the block and to query lane%32 of the wavefront.
 // INT8 mode: v_mfma_i32_32x32x32_i8, int32 accumulators.  INT4 mode: the codes are 6-bit FP6 E2M3
 // values and feed v_mfma_f32_32x32x64_f8f6f4 in its FP6 operand format (twice the rate of the 8-bit
-// formats); the FP32 accumulators hold the exact integers.  Either way the result is returned as
+// formats) as eighths; the FP32 accumulators hold the integers' sixty-fourths, exactly.  Either way the result is returned as
 // raw 32-bit lanes.
 // The product is issued one MFMA ("step") at a time so that the steps can be spread between
 // pieces of vector work: step I works on key tile I % 2 and contraction piece I / 2 (64 channels

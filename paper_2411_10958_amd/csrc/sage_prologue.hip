@@ -8,6 +8,7 @@
 // copies.
 #include "sage_quant.h"
 #include "sage_attn.h"
+#include <type_traits>
 
 namespace sage {
 
@@ -350,24 +351,6 @@ __device__ inline size_t kv_head(const TensorMap& qm, unsigned bh, int G) {
   const unsigned b = bh / (unsigned)qm.heads, h = bh - b * (unsigned)qm.heads;
   return (size_t)b * (qm.heads / G) + h / G;
 }
-// kappa * <q_r, mean(K)> for the rows of one thread group (the row constant that smoothing K drops
-// from the scores, Sec. 3.1; needed only for the log-sum-exp output): float64 products and sums,
-// one rounding.  x: this thread's 8 channels of RPT rows; NCG consecutive lanes share a row.
-template <int D, int NCG, int RPT>
-__device__ inline void row_constants(const float (&x)[RPT][8], float* out, int n_valid, const float* kbar8,
-                                     float kappa, int cg) {
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    double dot = 0.0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) dot += (double)x[i][e] * (double)kbar8[e];
-    dot = butterfly_sum<4>(butterfly_sum<2>(butterfly_sum<1>(dot)));
-    if constexpr (NCG > 8) dot = butterfly_sum<8>(dot);
-    if constexpr (NCG > 16) dot = butterfly_sum<16>(dot);
-    if (cg == 0 && i < n_valid) out[i] = (float)((double)kappa * dot);
-  }
-}
-
 // Arguments of the Q quantizers (the 8-bit one leaves the last five alone).
 struct QuantQ {
   const unsigned short* q;
@@ -400,139 +383,166 @@ __device__ __forceinline__ float q_kbar(const QuantQ& a, unsigned kv_head, int n
   const TensorMap& qm = a.qm; const SeqMap& sm = a.sm; float* __restrict__ q_corr = a.q_corr;                          \
   const float* __restrict__ head_scale = a.head_scale; const float kappa = a.kappa
 
+// The rows of a 128-query block as the Q quantizers hold them: wavefront w has rows 32 w .. 32 w + 31, in passes, and the lanes of a pass take
+// the place of the lanes of the matrix operand that the codes are for, so that a wavefront's codes leave in runs of 128 and 256 bytes straight
+// from its registers.  (As an image put together in LDS they cost a barrier, a pass through LDS and the LDS itself.)
+struct QBlock { unsigned qb, bh; int n0, valid; size_t hbase; int nk; };
+__device__ __forceinline__ QBlock q_block(const QuantQ& a, unsigned qb, unsigned bh) {
+  QBlock b;
+  b.qb = qb; b.bh = bh; b.n0 = (int)qb * BQ;
+  const HeadPos hp = head_pos(a.qm, bh);
+  const Seq sq = seq_of(a.sm, hp.b, a.N, a.Nk);
+  b.valid = min(BQ, sq.n - b.n0);              // (none: a block past the end of a shorter sequence)
+  b.hbase = hp.base + sq.q0 * (size_t)a.qm.sn;
+  b.nk = sq.nk;
+  return b;
+}
+
 // Q, 8-bit variant: pair-group quantization psi_Q(Q_i), no smoothing (the 8-bit kernel of the
 // paper's "two kernel implementations" leaves Q as it is).  One workgroup per 128 queries of one
-// (batch, head).
+// (batch, head); a wavefront quantizes by itself.  Lane l of a pass holds row l % 16 and the 16-channel pieces l / 16 + 4 m, 32 bytes
+// each: four lanes read 128 consecutive bytes, and a piece is 16 bytes of codes.  Both passes' rows are requested together.
+// Against codes laid out in LDS, rows as 8 channels of 4 to 8 rows per thread and a byte extract per code: 32 heads of 8192 tokens 33 -> 25 us (100 MB:
+// 4.0 TB/s).  Bound: the loads in flight - a workgroup loads, computes and stores in turn, and a chip's worth of them starts together
+// (walking several blocks with the next one's rows requested ahead gained nothing: the 4-bit form 45 -> 51 us on 4096 blocks).
 template <int D, bool INT4> struct QuantQLds {               // (8-bit mode)
-  uint4 codes[BQ * D / 16];
   alignas(16) float kbar[D];         // mean(K) of the KV head (log-sum-exp output only)
   float bmax[4];
 };
 template <bool BF16, int D>
-__device__ __forceinline__ void quant_q8_block(QuantQLds<D, false>& lds, const BlockPos bp, const QuantQ& a) {
+__device__ __forceinline__ void quant_q8_block(QuantQLds<D, false>& lds, const QBlock bl, const QuantQ& a) {
   SAGE_QUANT_Q_ARGS;
-  constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BQ / NRG;  // RPT rows per thread (8 or 4)
+  constexpr int NM = D / 64;                    // pieces of a row per lane
   constexpr int QMAX = 127;
-  const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
-  const int qb = bp.x;
-  const size_t bh = bp.y;
-  const int n0 = qb * BQ;
-  const HeadPos hp = head_pos(qm, bp.y);
-  const Seq sq = seq_of(sm, hp.b, N, Nk);
-  const int valid = min(BQ, sq.n - n0);
+  const int t = threadIdx.x, w = t >> 6, r16 = t & 15, k4 = (t >> 4) & 3;
+  const int qb = bl.qb, n0 = bl.n0, valid = bl.valid;
+  const size_t bh = bl.bh, hbase = bl.hbase;
   if (valid <= 0) return;                     // a block past the end of a shorter sequence
-  const size_t hbase = hp.base + sq.q0 * (size_t)qm.sn;
-  float x[RPT][8];
+  uint4 raw[2][NM][2];
 #pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int r = rg * RPT + i;
-    if (r < valid) {
-      load8<BF16>(Q + row_offset(qm, hbase, n0 + r) + cg * 8, x[i]);
-    } else {
+  for (int p = 0; p < 2; ++p) {
+    const int r = 32 * w + 16 * p + r16;
+    const unsigned short* src = Q + row_offset(qm, hbase, n0 + min(r, valid - 1)) + 16 * k4;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) x[i][e] = 0.0f;
+    for (int m = 0; m < NM; ++m) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) raw[p][m][i] = nt_load16(src + 64 * m + 8 * i);
     }
   }
   if (q_corr) {
-    if (t < D) lds.kbar[t] = q_kbar<D>(a, kv_head(qm, bp.y, G), sq.nk, t);
+    if (t < D) lds.kbar[t] = q_kbar<D>(a, kv_head(qm, (unsigned)bh, G), bl.nk, t);
     __syncthreads();
-    row_constants<D, NCG, RPT>(x, q_corr + (bh * nQb + qb) * BQ + rg * RPT, valid - rg * RPT, lds.kbar + cg * 8, kappa, cg);
   }
-  // codes go to LDS in the packed order of this 128-query slab (contiguous in the workspace) and
-  // leave as coalesced 16-byte stores
-  auto& s_codes = lds.codes; auto& s_bmax = lds.bmax;
-  uint8_t* img = reinterpret_cast<uint8_t*>(s_codes);
+  // a row's largest magnitude: its pieces, then the lanes that share it
+  auto row_max = [&](int p) {
+    float mx = 0.0f;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        float x[8];
+        unpack8<BF16>(raw[p][m][i], x);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(x[e]));
+      }
+    }
+    mx = butterfly_max<32>(butterfly_max<16>(mx));
+    return 32 * w + 16 * p + r16 < valid ? mx : 0.0f;      // (the rows past the end are copies of the last one: their codes are 0)
+  };
   float block_max = 0.0f;
   if (block_groups) {       // per-block granularity: one scale for the whole 128-query block
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) block_max = fmaxf(block_max, fabsf(x[i][e]));
-    }
-    block_max = wave_max(block_max);
-    if ((t & 63) == 0) s_bmax[t >> 6] = block_max;
+    block_max = group_max<16>(fmaxf(row_max(0), row_max(1)));
+    if ((t & 63) == 0) lds.bmax[w] = block_max;
     __syncthreads();
-    block_max = fmaxf(fmaxf(s_bmax[0], s_bmax[1]), fmaxf(s_bmax[2], s_bmax[3]));
+    block_max = fmaxf(fmaxf(lds.bmax[0], lds.bmax[1]), fmaxf(lds.bmax[2], lds.bmax[3]));
   }
+  uint4* const slab = reinterpret_cast<uint4*>(q_codes + (bh * nQb + qb) * q_slab_bytes(D, false));
 #pragma unroll
-  for (int p = 0; p < RPT / 2; ++p) {
-    float mxr[2];                       // per query; the pair shares the larger one unless qg == 1
+  for (int p = 0; p < 2; ++p) {
+    const int r = 32 * w + 16 * p + r16;
+    if (q_corr) {
+      // kappa * <q_r, mean(K)>, the row constant that smoothing K drops from the scores (Sec. 3.1; needed only for the log-sum-exp
+      // output): float64 products and sums, one rounding; runs of 8 channels, then neighbours in pairs
+      double part[NM];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      mxr[i] = 0.0f;
+      for (int m = 0; m < NM; ++m) {
+        double run[2];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) mxr[i] = fmaxf(mxr[i], fabsf(x[2 * p + i][e]));
-      mxr[i] = group_max<NCG>(mxr[i]);
+        for (int i = 0; i < 2; ++i) {
+          float x[8];
+          unpack8<BF16>(raw[p][m][i], x);
+          run[i] = 0.0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) run[i] += (double)x[e] * (double)lds.kbar[16 * k4 + 64 * m + 8 * i + e];
+        }
+        part[m] = butterfly_sum<32>(butterfly_sum<16>(run[0] + run[1]));
+      }
+      double dot = part[0];
+      if constexpr (NM == 2) dot = part[0] + part[1];
+      if constexpr (NM == 4) dot = (part[0] + part[1]) + (part[2] + part[3]);
+      if (k4 == 0 && r < valid) q_corr[(bh * nQb + qb) * BQ + r] = (float)((double)kappa * dot);
     }
-    if (qg == 2) mxr[0] = mxr[1] = fmaxf(mxr[0], mxr[1]);
-    if (block_groups) mxr[0] = mxr[1] = block_max;
+    float mx = row_max(p);                                   // per query; the pair shares the larger one unless qg == 1
+    if (qg == 2) mx = butterfly_max<1>(mx);
+    if (block_groups) mx = block_max;
+    const float delta = head_scale ? head_scale[bh] : __fdiv_rn(mx, (float)QMAX);
+    if (k4 == 0 && (qg == 1 || (r & 1) == 0)) q_scale[(bh * nQb + qb) * (BQ >> (qg - 1)) + (r >> (qg - 1))] = delta;   // qg is 1 or 2
+    if (stats_only) continue;            // per-tensor scales, first pass: only the block maxima are wanted
+    const CodeScale qs = code_scale(delta);
 #pragma unroll
-    for (int i = 2 * p; i < 2 * p + 2; ++i) {
-      const float delta = head_scale ? head_scale[bh] : __fdiv_rn(mxr[i - 2 * p], (float)QMAX);
-      if (cg == 0 && (qg == 1 || i == 2 * p))
-        q_scale[(bh * nQb + qb) * (BQ >> (qg - 1)) + ((rg * RPT + i) >> (qg - 1))] = delta;   // qg is 1 or 2
-      if (stats_only) continue;          // per-tensor scales, first pass: only the block maxima are wanted
-      const QuantScale qs = quant_scale<QMAX>(delta);
-      int c[8];
-      quant_group<8, QMAX>(x[i], delta, qs, [&](int e, float cf) { c[e] = (int)cf; });
-      *reinterpret_cast<uint2*>(img + q_code_off(rg * RPT + i, cg * 8, D)) = pack8(c);
+    for (int m = 0; m < NM; ++m) {
+      float x[16];
+      unpack8<BF16>(raw[p][m][0], x);
+      unpack8<BF16>(raw[p][m][1], x + 8);
+      if (valid < BQ) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) x[e] = r < valid ? x[e] : 0.0f;
+      }
+      unsigned c[16];
+      code_group_bytes<16, QMAX>(x, delta, qs, c);
+      slab[q_code_off(r, 16 * k4 + 64 * m, D) >> 4] = pack16(c);
     }
   }
-  if (stats_only) return;
-  __syncthreads();
-  constexpr int SLAB16 = (int)(q_slab_bytes(D, false) / 16);
-  uint4* dst = reinterpret_cast<uint4*>(q_codes + (bh * nQb + qb) * q_slab_bytes(D, false));
-#pragma unroll
-  for (int i = t; i < SLAB16; i += 256) dst[i] = s_codes[i];
 }
 
 // Q, 4-bit variant: block mean, smoothing, pair-group quantization (Algorithm 1: q_bar_i =
 // mean(Q_i), psi_Q(Q_i - q_bar_i)).  Two thread-to-data maps, joined through LDS:
-//  - loading and the exact column sums of the block mean use the coalesced map of quant_q8_block (a
-//    thread owns 8 channels of BQ*D/2048 rows), and the raw 16-bit rows are parked in LDS;
-//  - quantization uses the map the codes are consumed in: a thread owns D/4 consecutive channels
-//    of the two queries of one scale group, i.e. (half of) one MFMA lane's payload per query, so
-//    the group maximum is two lane exchanges away and the codes leave through one FP32->FP6
-//    conversion per query instead of per-element table look-ups and 6-bit shifts.
-// LDS rows are kept as 16-byte chunks with the chunk index XOR-ed by the row's group number, which
-// makes both maps conflict-free for d = 128.
-// LDS: the raw rows (32 KB at d = 128), which the packed code image takes over once every thread holds its values in
-// registers, and one row of column sums per wavefront (the row groups of a wavefront are summed by lane exchanges
-// first) - 37 KB, so that four workgroups share a CU and their loads, arithmetic and stores overlap.
+//  - loading and the exact column sums of the block mean use a coalesced map (a thread owns 8 channels of BQ*D/2048
+//    rows), and the raw 16-bit rows are parked in LDS;
+//  - quantization uses the map the codes are consumed in, a pass at a time: a lane owns 32 consecutive channels of a row, one MFMA lane's
+//    payload, D / 32 lanes a row, so the maximum of a scale group is a few lane exchanges away and the codes leave
+//    through one FP32->FP6 conversion instead of per-element table look-ups and 6-bit shifts.
+// LDS rows are kept as 16-byte chunks in an order by the row's number, which spreads the chunk that a pass reads of every row over all
+// banks.  LDS: the raw rows (32 KB at d = 128) and one row of column sums per wavefront (the row groups of a wavefront are summed by
+// lane exchanges first) - 37 KB, so that four workgroups share a CU and their loads, arithmetic and stores overlap.
+// With the passes, the rounding in the conversion and no code image in LDS: 2 heads of 256 tokens (with the statistics) 5.05 -> 4.45 us, 64
+// heads of 512 9.4 -> 8.8, 16 of 8192 of 256 channels 32.4 -> 30.7, 128 of 4096 45 (185 MB: 4.1 TB/s): loads and parking alone 29, column
+// sums 4, quantization 6, stores 4.  (Rows read a second time instead of parked, five workgroups per CU: 48.)
 template <int D> struct QuantQLds<D, true> {
-  uint4 raw[BQ * (D / 8)];           // the raw rows; later the packed code image of the slab
+  uint4 raw[BQ * (D / 8)];           // the raw rows
   double sum[4][D];                  // column sums, one row per wavefront
   alignas(16) float mean[D];
   alignas(16) float kbar[D];         // mean(K) of the KV head (log-sum-exp output only)
   float bmax[4];
+  int odd_mean;                      // some column sum of the block is not finite
 };
 template <bool BF16, int D>
-__device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const BlockPos bp, const QuantQ& a) {
+__device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const QBlock bl, const QuantQ& a) {
   SAGE_QUANT_Q_ARGS;
   float *__restrict__ q_mean = a.q_mean, *__restrict__ q_dscale = a.q_dscale;
   unsigned char* __restrict__ q_digits = a.q_digits;
   const int smooth_q = a.smooth_q;
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BQ / NRG;   // load map: RPT rows x 8 channels
-  constexpr int CPL = D / 4, CPC = CPL / 8;                      // quantization map: 2 rows x CPL channels
+  constexpr int NPC = D / 32, RP = 64 / NPC, NPASS = 32 / RP;    // quantization map: RP rows of a wavefront's 32 in a pass
   constexpr int QMAX = 7;
-  constexpr int SLAB = (int)q_slab_bytes(D, true);
   auto& s_raw = lds.raw; auto& s_sum = lds.sum; auto& s_mean = lds.mean; auto& s_kbar = lds.kbar; auto& s_bmax = lds.bmax;
-  static_assert(SLAB <= (int)sizeof(uint4) * BQ * NCG, "the code image fits where the raw rows were");
-  const int t = threadIdx.x;
-  const int qb = bp.x;
-  const size_t bh = bp.y;
-  const int n0 = qb * BQ;
-  const HeadPos hp = head_pos(qm, bp.y);
-  const Seq sq = seq_of(sm, hp.b, N, Nk);
-  const int valid = min(BQ, sq.n - n0);
+  auto chunk_at = [](int r, int c) { return r * NCG + (c ^ (D == 64 ? (r >> 1) & 7 : r & 15)); };
+  const int t = threadIdx.x, cg = t % NCG, rg = t / NCG;
+  const int qb = bl.qb, n0 = bl.n0, valid = bl.valid;
+  const size_t bh = bl.bh, hbase = bl.hbase;
   if (valid <= 0) return;                     // a block past the end of a shorter sequence
-  const size_t hbase = hp.base + sq.q0 * (size_t)qm.sn;
-  auto swz = [](int r) { return (r >> 1) & (D >= 128 ? 3 : 1); };
+  if (t == 0) lds.odd_mean = 0;
   {
-    const int cg = t % NCG, rg = t / NCG;
-    double cs[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) cs[e] = 0.0;
     uint4 raw[RPT];
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
@@ -540,13 +550,16 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const Bl
       raw[i] = r < valid ? nt_load16(Q + row_offset(qm, hbase, n0 + r) + cg * 8)
                          : make_uint4(0u, 0u, 0u, 0u);                  // padded rows are zero
     }
+    double cs[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cs[e] = 0.0;
     // (fetched now, under the loads of the rows: read from global memory where it is used, in front of every 8 channels of
     // every row, it was a round trip each)
-    if (q_corr && t < D) s_kbar[t] = q_kbar<D>(a, kv_head(qm, bp.y, G), sq.nk, t);
+    if (q_corr && t < D) s_kbar[t] = q_kbar<D>(a, kv_head(qm, (unsigned)bh, G), bl.nk, t);
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
       const int r = rg * RPT + i;
-      s_raw[r * NCG + (cg ^ swz(r))] = raw[i];
+      s_raw[chunk_at(r, cg)] = raw[i];
       float x8[8];
       unpack8<BF16>(raw[i], x8);
 #pragma unroll
@@ -569,87 +582,118 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const Bl
   if (t < D) {
     double sm = 0.0;
     for (int g = 0; g < 4; ++g) sm += s_sum[g][t];
+    if (!(fabs(sm) < (double)INFINITY)) lds.odd_mean = 1;
     const float m = smooth_q ? (float)(sm / (double)valid) : 0.0f;   // smoothing of Q off: mean 0
     s_mean[t] = m;
     q_mean[(bh * nQb + qb) * D + t] = m;
   }
   __syncthreads();
-  const int pair = t >> 2, c4 = t & 3;
-  float x[2][CPL];
-  float mxr[2] = {0.0f, 0.0f};          // per query; the pair shares the larger one unless qg == 1
-  double dotk[2] = {0.0, 0.0};          // <q_r, mean(K)> over this thread's channels (log-sum-exp output only)
+  const int lane = t & 63, w = t >> 6, rr = lane % RP, piece = lane / RP, c0 = 32 * piece;
+  const bool odd = lds.odd_mean != 0;
+  auto row_of = [&](int p) { return 32 * w + RP * p + rr; };
+  // kappa * <q_r, mean(K)> per row (the log-sum-exp output only): float64, runs of D / 4 channels one after the other, then neighbours in
+  // pairs.  A lane's 32 channels are one run (d = 128) or two (64); at d = 256 a run is two lanes' and this is done by itself, below.
+  constexpr int RUN = D / 4, RUNS = RUN <= 32 ? 32 / RUN : 0;
+  // the lane's 32 channels of row r, centred (a row past the end stays zero)
+  auto load_row = [&](int r, float (&x)[32], double (&run)[RUNS ? RUNS : 1], bool dots) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int r = 2 * pair + i;
+    for (int j = 0; j < 4; ++j) {
+      unpack8<BF16>(s_raw[chunk_at(r, 4 * piece + j)], &x[8 * j]);
+      if (RUNS && dots) {
+        const float4 b0 = *reinterpret_cast<const float4*>(&s_kbar[c0 + 8 * j]);
+        const float4 b1 = *reinterpret_cast<const float4*>(&s_kbar[c0 + 8 * j + 4]);
+        const float kb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+        double& dot = run[RUNS == 2 ? j / 2 : 0];
+        if (8 * j % RUN == 0) dot = 0.0;
 #pragma unroll
-    for (int j = 0; j < CPC; ++j) {
-      unpack8<BF16>(s_raw[r * NCG + ((c4 * CPC + j) ^ swz(r))], &x[i][8 * j]);
-      if (q_corr) {
+        for (int e = 0; e < 8; ++e) dot += (double)x[8 * j + e] * (double)kb[e];
+      }
+      const float4 m0 = *reinterpret_cast<const float4*>(&s_mean[c0 + 8 * j]);
+      const float4 m1 = *reinterpret_cast<const float4*>(&s_mean[c0 + 8 * j + 4]);
+      const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[8 * j + e] = __fsub_rn(x[8 * j + e], mean[e]);
+    }
+    if (valid < BQ) {
+#pragma unroll
+      for (int e = 0; e < 32; ++e) x[e] = r < valid ? x[e] : 0.0f;
+    }
+  };
+  auto row_max = [&](const float (&x)[32]) {
+    float mx = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) mx = fmaxf(mx, fabsf(x[e]));
+    if constexpr (NPC == 8) mx = butterfly_max<8>(mx);
+    if constexpr (NPC >= 4) mx = butterfly_max<16>(mx);
+    return butterfly_max<32>(mx);
+  };
+  if (!RUNS && q_corr) {
+    constexpr int CPL = RUN;
+    const int pair = t >> 2, c4 = t & 3;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = 2 * pair + i;
+      double dot = 0.0;
+#pragma unroll
+      for (int j = 0; j < CPL / 8; ++j) {
+        float x8[8];
+        unpack8<BF16>(s_raw[chunk_at(r, c4 * (CPL / 8) + j)], x8);
         const float4 b0 = *reinterpret_cast<const float4*>(&s_kbar[CPL * c4 + 8 * j]);
         const float4 b1 = *reinterpret_cast<const float4*>(&s_kbar[CPL * c4 + 8 * j + 4]);
         const float kb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) dotk[i] += (double)x[i][8 * j + e] * (double)kb[e];
+        for (int e = 0; e < 8; ++e) dot += (double)x8[e] * (double)kb[e];
       }
-      if (r < valid) {
-        const float4 m0 = *reinterpret_cast<const float4*>(&s_mean[CPL * c4 + 8 * j]);
-        const float4 m1 = *reinterpret_cast<const float4*>(&s_mean[CPL * c4 + 8 * j + 4]);
-        const float mean[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          x[i][8 * j + e] = __fsub_rn(x[i][8 * j + e], mean[e]);
-          mxr[i] = fmaxf(mxr[i], fabsf(x[i][8 * j + e]));
-        }
-      }
-    }
-    mxr[i] = group_max<4>(mxr[i]);
-    if (q_corr) {
-      dotk[i] = butterfly_sum<2>(butterfly_sum<1>(dotk[i]));
-      if (c4 == 0 && r < valid) q_corr[(bh * nQb + qb) * BQ + r] = (float)((double)kappa * dotk[i]);
+      dot = butterfly_sum<2>(butterfly_sum<1>(dot));
+      if (c4 == 0 && r < valid) q_corr[(bh * nQb + qb) * BQ + r] = (float)((double)kappa * dot);
     }
   }
-  if (qg == 2) mxr[0] = mxr[1] = fmaxf(mxr[0], mxr[1]);
+  float block_max = 0.0f;
   if (block_groups) {       // per-block granularity: one scale for the whole 128-query block
-    const float bm = wave_max(mxr[0]);
-    if ((t & 63) == 0) s_bmax[t >> 6] = bm;
-    __syncthreads();
-    mxr[0] = mxr[1] = fmaxf(fmaxf(s_bmax[0], s_bmax[1]), fmaxf(s_bmax[2], s_bmax[3]));
-  }
-  __syncthreads();                       // every thread holds its rows in registers: the image may take their place
-  uint8_t* img = reinterpret_cast<uint8_t*>(s_raw);
-  // the thread's CPL channels of a query are one MFMA lane payload of 32 codes (d = 128), half of one (d = 64) or
-  // two of them (d = 256: both lane halves of one operand)
-  constexpr int NPL = CPL > 32 ? CPL / 32 : 1, CPP = CPL / NPL;     // payloads per query and thread, codes in each
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const float delta = head_scale ? head_scale[bh] : __fdiv_rn(mxr[i], (float)QMAX);
-    if (c4 == 0 && (qg == 1 || i == 0))   // qg is 1 or 2
-      q_scale[(bh * nQb + qb) * (BQ >> (qg - 1)) + ((2 * pair + i) >> (qg - 1))] = delta;
-    if (stats_only) continue;            // per-tensor scales, first pass: only the block maxima are wanted
-    const QuantScale qs = quant_scale<QMAX>(delta);
-#pragma unroll
-    for (int pl = 0; pl < NPL; ++pl) {
-      Codes32 cd;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { cd.ev[e] = 0.0f; cd.od[e] = 0.0f; }
-#pragma unroll
-      for (int g = 0; g < CPP / 8; ++g)
-        quant_group<8, QMAX>(&x[i][CPP * pl + 8 * g], delta, qs, [&](int e, float c) { cd.set(8 * g + e, c); });
-      const v6u pw = cd.pack();
-      int lane_m, e0;
-      const size_t op = q_op6(2 * pair + i, CPL * c4 + CPP * pl, D, &lane_m, &e0);
-      const int d0 = (6 * e0) >> 5;
-#pragma unroll
-      for (int k = 0; k < CPP * 6 / 32; ++k)
-        *reinterpret_cast<unsigned*>(img + op + op6_byte(lane_m, 4 * (d0 + k))) = pw[k];
+#pragma unroll 1
+    for (int p = 0; p < NPASS; ++p) {
+      float x[32];
+      double none[RUNS ? RUNS : 1];
+      load_row(row_of(p), x, none, false);
+      block_max = fmaxf(block_max, row_max(x));
     }
+    block_max = wave_max(block_max);
+    if (lane == 0) s_bmax[w] = block_max;
+    __syncthreads();
+    block_max = fmaxf(fmaxf(s_bmax[0], s_bmax[1]), fmaxf(s_bmax[2], s_bmax[3]));
+  }
+  uint8_t* const slab = reinterpret_cast<uint8_t*>(q_codes + (bh * nQb + qb) * q_slab_bytes(D, true));
+#pragma unroll
+  for (int p = 0; p < NPASS; ++p) {
+    const int r = row_of(p);
+    float x[32];
+    double run[RUNS ? RUNS : 1];
+    load_row(r, x, run, q_corr != nullptr);
+    if (RUNS && q_corr) {
+      double dot = run[0];
+      if constexpr (RUNS == 2) dot = run[0] + run[1];
+      if constexpr (NPC >= 4) dot = butterfly_sum<16>(dot);
+      dot = butterfly_sum<32>(dot);
+      if (piece == 0 && r < valid) q_corr[(bh * nQb + qb) * BQ + r] = (float)((double)kappa * dot);
+    }
+    float mx = row_max(x);                                     // per query; the pair shares the larger one unless qg == 1
+    if (qg == 2) mx = butterfly_max<1>(mx);
+    if (block_groups) mx = block_max;
+    const float delta = head_scale ? head_scale[bh] : __fdiv_rn(mx, (float)QMAX);
+    if (piece == 0 && (qg == 1 || (r & 1) == 0))   // qg is 1 or 2
+      q_scale[(bh * nQb + qb) * (BQ >> (qg - 1)) + (r >> (qg - 1))] = delta;
+    if (stats_only) continue;            // per-tensor scales, first pass: only the block maxima are wanted
+    CodeScale qs = code_scale(delta);
+    qs.fast = qs.fast && !odd;           // (the exact form makes 0 of NaN)
+    Codes32 cd;
+    code_group<32, QMAX>(x, delta, qs, [&](int e, float c) { cd.set(e, c); });
+    const v6u pw = cd.pack();
+    int lane_m, e0;
+    uint8_t* const op = slab + q_op6(r, c0, D, &lane_m, &e0);
+    *reinterpret_cast<uint4*>(op + 16 * lane_m) = make_uint4(pw[0], pw[1], pw[2], pw[3]);
+    *reinterpret_cast<uint2*>(op + 1024 + 8 * lane_m) = make_uint2(pw[4], pw[5]);
   }
   if (stats_only) return;
-  __syncthreads();
-  uint4* dst = reinterpret_cast<uint4*>(q_codes + (bh * nQb + qb) * q_slab_bytes(D, true));
-  const uint4* src = reinterpret_cast<const uint4*>(img);
-#pragma unroll
-  for (int i = t; i < SLAB / 16; i += 256) dst[i] = src[i];
   // the block mean cut into digits for the Delta-S product: by one wavefront, where nobody waits for it any more (done in
   // front of the quantization it held up the other three: 4096 blocks of d = 128 48 us, now 45)
   if (q_digits && t >= 192)
@@ -657,19 +701,19 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const Bl
 }
 
 template <bool BF16, bool INT4, int D>
-__device__ __forceinline__ void quant_q_block(QuantQLds<D, INT4>& lds, const BlockPos bp, const QuantQ& a) {
-  if constexpr (INT4) quant_q4_block<BF16, D>(lds, bp, a); else quant_q8_block<BF16, D>(lds, bp, a);
+__device__ __forceinline__ void quant_q_block(QuantQLds<D, INT4>& lds, const QBlock bl, const QuantQ& a) {
+  if constexpr (INT4) quant_q4_block<BF16, D>(lds, bl, a); else quant_q8_block<BF16, D>(lds, bl, a);
 }
 // The first fin_rows rows of the grid finish the statistics (finalize_stats_block) under the quantization of Q.
 template <bool BF16, bool INT4, int D>
-__global__ void __launch_bounds__(256, D == 256 || !INT4 ? 2 : 4) k_quant_q(const QuantQ a, const Finalize f, const unsigned fin_rows) {
+__global__ void __launch_bounds__(256, D == 256 ? 2 : 4) k_quant_q(const QuantQ a, const Finalize f, const unsigned fin_rows) {
   __shared__ Overlay<QuantQLds<D, INT4>, FinalizeLds> lds;
   if (blockIdx.y < fin_rows) {
     finalize_stats_block(lds.b, blockIdx.y * gridDim.x + blockIdx.x, f);
     return;
   }
-  const unsigned y = blockIdx.y - fin_rows, ny = gridDim.y - fin_rows;
-  quant_q_block<BF16, INT4, D>(lds.a, a.qm.heads_inner ? BlockPos{y, blockIdx.x, ny} : BlockPos{blockIdx.x, y, gridDim.x}, a);
+  const unsigned y = blockIdx.y - fin_rows;
+  quant_q_block<BF16, INT4, D>(lds.a, a.qm.heads_inner ? q_block(a, y, blockIdx.x) : q_block(a, blockIdx.x, y), a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -742,6 +786,7 @@ struct QuantKV {
   int nchunk, smooth_k;
   float code_max;
   int mixed;                 // K and V in one launch: both on every XCD
+  int bounded;               // delta_V was taken from these values
 };
 
 template <int D, bool INT4, int DSM, bool REDUCE> struct QuantKLds {
@@ -1193,53 +1238,63 @@ __device__ __forceinline__ void quant_v_block(QuantVLds<D, REDUCE>& lds, const B
   for (int e = 0; e < VCH; ++e) rc[e] = fast ? __fdiv_rn(1.0f, sc[e]) : 0.0f;
   uint8_t* img = reinterpret_cast<uint8_t*>(lds.img);
   const bool ragged = n0 + BKV > N;
+  // The quotient: div_by; with a supplied scale, which bounds nothing, div_by with its remainder kept finite, since an infinite quotient has none
+  // (the conversion tells infinities from NaN); or a division, also where a scale taken from the values is infinite.
+  enum { BOUNDED, UNBOUNDED, EXACT };
+  auto convert = [&](auto form) {
+    constexpr int FORM = decltype(form)::value;
 #pragma unroll
-  for (int k = 0; k < RPT / 4; ++k) {
-    const int key0 = rg * RPT + 4 * k;
+    for (int k = 0; k < RPT / 4; ++k) {
+      const int key0 = rg * RPT + 4 * k;
 #pragma unroll
-    for (int e = 0; e < VCH; ++e) {
-      float x[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const unsigned w = raw[4 * k + i][e >> 1];
-        x[i] = load16<BF16>((unsigned short)((e & 1) ? w >> 16 : w & 0xffffu));
-        if constexpr (SMOOTH_V) x[i] = __fsub_rn(x[i], mean[e]);
-      }
-      if (ragged) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = n0 + key0 + i < N ? x[i] : 0.0f;
-      }
-      if (fast) {
-        // div_by, except that its remainder is kept finite: an infinite quotient (a supplied scale bounds nothing) has none, and the
-        // conversion tells infinities from NaN.  And it makes +0 of -0; the sign is the dividend's.
+      for (int e = 0; e < VCH; ++e) {
+        float x[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float q = __fmul_rn(x[i], rc[e]), rem = __builtin_amdgcn_fmed3f(__fmaf_rn(q, -sc[e], x[i]), -0x1.fffffep127f, 0x1.fffffep127f);
-          x[i] = copysignf(__fmaf_rn(rem, rc[e], q), x[i]);
+          const unsigned w = raw[4 * k + i][e >> 1];
+          x[i] = load16<BF16>((unsigned short)((e & 1) ? w >> 16 : w & 0xffffu));
+          if constexpr (SMOOTH_V) x[i] = __fsub_rn(x[i], mean[e]);
         }
-      } else {
+        if (ragged) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          x[i] = sc[e] > 0.0f ? __fdiv_rn(x[i], sc[e]) : 0.0f;
-          asm volatile("" : "+v"(x[i]) :: "memory");     // (one division at a time)
+          for (int i = 0; i < 4; ++i) x[i] = n0 + key0 + i < N ? x[i] : 0.0f;
         }
-      }
-      int wd = 0;
-      if constexpr (PVF == PV_INT8) {
-        // psi of Sec. 2.2 with qmax 127: |x / delta_V| <= 127 (1 + 2^-23), round-half-even, two's-complement bytes
+        if constexpr (FORM != EXACT) {
+          // div_by with the remainder's sign turned, so that a quotient of -0 stays -0
 #pragma unroll
-        for (int i = 0; i < 4; ++i) wd |= ((int)rintf(x[i]) & 0xff) << (8 * i);
-      } else if constexpr (PVF == PV_E5M2) {
-        wd = __builtin_amdgcn_cvt_pk_bf8_f32(x[0], x[1], wd, false);
-        wd = __builtin_amdgcn_cvt_pk_bf8_f32(x[2], x[3], wd, true);
-      } else {
-        wd = __builtin_amdgcn_cvt_pk_fp8_f32(x[0], x[1], wd, false);
-        wd = __builtin_amdgcn_cvt_pk_fp8_f32(x[2], x[3], wd, true);
+          for (int i = 0; i < 4; ++i) {
+            const float q = __fmul_rn(x[i], rc[e]);
+            float rem = __fmaf_rn(q, sc[e], -x[i]);
+            if constexpr (FORM == UNBOUNDED) rem = __builtin_amdgcn_fmed3f(rem, -0x1.fffffep127f, 0x1.fffffep127f);
+            x[i] = __fmaf_rn(rem, -rc[e], q);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            x[i] = sc[e] > 0.0f ? __fdiv_rn(x[i], sc[e]) : 0.0f;
+            asm volatile("" : "+v"(x[i]) :: "memory");     // (one division at a time)
+          }
+        }
+        int wd = 0;
+        if constexpr (PVF == PV_INT8) {
+          // psi of Sec. 2.2 with qmax 127: |x / delta_V| <= 127 (1 + 2^-23), round-half-even, two's-complement bytes
+#pragma unroll
+          for (int i = 0; i < 4; ++i) wd |= ((int)rintf(x[i]) & 0xff) << (8 * i);
+        } else if constexpr (PVF == PV_E5M2) {
+          wd = __builtin_amdgcn_cvt_pk_bf8_f32(x[0], x[1], wd, false);
+          wd = __builtin_amdgcn_cvt_pk_bf8_f32(x[2], x[3], wd, true);
+        } else {
+          wd = __builtin_amdgcn_cvt_pk_fp8_f32(x[0], x[1], wd, false);
+          wd = __builtin_amdgcn_cvt_pk_fp8_f32(x[2], x[3], wd, true);
+        }
+        const int off = (int)v_code_off(key0, cg * VCH + e, D);
+        *reinterpret_cast<int*>(img + 16 * v_piece(off >> 4) + (off & 15)) = wd;
       }
-      const int off = (int)v_code_off(key0, cg * VCH + e, D);
-      *reinterpret_cast<int*>(img + 16 * v_piece(off >> 4) + (off & 15)) = wd;
     }
-  }
+  };
+  if (!fast) convert(std::integral_constant<int, EXACT>{});
+  else if (REDUCE || a.bounded) convert(std::integral_constant<int, BOUNDED>{});
+  else if constexpr (!REDUCE) convert(std::integral_constant<int, UNBOUNDED>{});
   __syncthreads();
   uint4* dst = reinterpret_cast<uint4*>(v_codes + (bh * nKb + kb) * (size_t)BKV * D);
   for (int i = t; i < BKV * D / 16; i += 256) dst[i] = lds.img[v_piece(i)];
@@ -1290,7 +1345,7 @@ __global__ void __launch_bounds__(256, D == 256 || !INT4 ? 2 : 4) k_quant_q_and_
   if (x < nq) {
     // x / nQb: (x + 1/2) / nQb is at least 1 / (2 nQb) from an integer, and the error of its FP32 value below 2^-22 x / nQb
     const unsigned g = q.G == 1 ? 0u : (unsigned)__builtin_amdgcn_readfirstlane((int)(((float)x + 0.5f) * st.inv_nQb));
-    quant_q_block<BF16, INT4, D>(lds.a, BlockPos{x - g * nQb, blockIdx.y * (unsigned)q.G + g, nQb}, q);
+    quant_q_block<BF16, INT4, D>(lds.a, q_block(q, x - g * nQb, blockIdx.y * (unsigned)q.G + g), q);
   } else {
     col_stats_block<BF16, D, false>(lds.b, BlockPos{x - nq, blockIdx.y, (unsigned)st.nchunk}, st.k, st.v, st.k_sum, nullptr, st.v_max, q.N, q.Nk,
                                     st.km, q.sm);
@@ -1453,7 +1508,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   ka.block_groups = Dm.block_groups; ka.kg = Dm.kg; ka.causal = Dm.causal; ka.km = km; ka.sm = sm;
   ka.head_scale = nullptr; ka.stats_only = 0; ka.zero_ds = !Dm.smooth_q; ka.q_digits = P.q_digits; ka.q_dscale = P.q_dscale;
   ka.k_sum = P.k_sum; ka.v_max = P.v_max; ka.nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS; ka.smooth_k = Dm.smooth_k;
-  ka.code_max = E4M3_MAX;
+  ka.code_max = E4M3_MAX; ka.bounded = !Dm.stats_given;
   // Taken one by one, K and V have every other XCD to themselves, on a grid that runs through the key blocks first.  That is the better
   // order (two kinds of code and of registers kept apart: 24 heads of 493 tokens, 8-bit, K and V 7.7 us mixed, 6.8 apart; 16 on 8 heads of
   // 1261 tokens of 256 channels, 4-bit, whole call 81.6, 80.2) unless K takes much longer than V and the chip is full.

@@ -101,44 +101,10 @@ __device__ inline int quant_code(float x, float delta, int qmax) {
   return c > qmax ? qmax : (c < -qmax ? -qmax : c);
 }
 
-// The same psi without a division per element.  With r = 1/delta to within 1 ulp (the hardware
-// reciprocal), y = fl32(x * r) differs from the oracle's fl32(x / delta) by at most 2^-22 |y|, so
-// whenever y is further than tau = 2^-14 (|y| <= 127.5) or 2^-18 (|y| <= 7.5) from a half-integer the
-// two round to the same integer.  QuantScale holds r and the bound 0.5 - tau; the caller takes the
-// largest |y - rint(y)| of a group of elements and recomputes the group with quant_code when it
-// exceeds the bound (about one element in 2^13 resp. 2^17).  Scales outside [2^-100, 2^100]
-// always take the exact path (bound -1); delta == 0 gives r = 0 and codes 0.  No clamp is needed:
-// |x| <= the group maximum, and fl32(max / fl32(max / qmax)) rounds to qmax.
-struct QuantScale { float r, bound; };
-template <int QMAX>
-__device__ inline QuantScale quant_scale(float delta) {
-  QuantScale q;
-  const bool regular = delta >= 0x1p-100f && delta <= 0x1p100f;
-  q.r = regular ? __builtin_amdgcn_rcpf(delta) : 0.0f;
-  q.bound = (regular || delta == 0.0f) ? 0.5f - (QMAX > 7 ? 0x1p-14f : 0x1p-18f) : -1.0f;
-  return q;
-}
-// NE codes (as integer-valued floats) of x[0..NE) with one scale, handed to put(e, code)
-template <int NE, int QMAX, class Put>
-__device__ inline void quant_group(const float* x, float delta, const QuantScale& qs, Put&& put) {
-  float worst = 0.0f;
-#pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    const float y = x[e] * qs.r;
-    const float c = rintf(y);
-    worst = fmaxf(worst, fabsf(y - c));
-    put(e, c);
-  }
-  if (!(worst <= qs.bound)) {
-#pragma unroll
-    for (int e = 0; e < NE; ++e) put(e, (float)quant_code(x[e], delta, QMAX));
-  }
-}
-
 // psi with the correctly rounded quotient of div_by, for whole wavefronts: `fast` says that every lane's scale is one that
-// div_by accepts, or zero (all its values are then zero and so are their codes).  Four instructions per code instead of the
-// five of quant_group, three of them multiply-adds, and no branch per eight codes.  (K's form; Q keeps quant_group, with which this one was not
-// compared there: Q has a scale for every two queries, K one for a wavefront.)
+// div_by accepts, or zero (all its values are then zero and so are their codes).  Three multiply-adds per code and no branch per eight
+// codes (a product with the reciprocal whose distance from the next half-integer was watched, and a division where it was too near, took a rounding, a
+// difference and a maximum more).
 struct CodeScale { float r; bool fast; };
 __device__ __forceinline__ CodeScale code_scale(float delta) {
   CodeScale q;
@@ -146,12 +112,12 @@ __device__ __forceinline__ CodeScale code_scale(float delta) {
   q.r = q.fast && delta > 0.0f ? __fdiv_rn(1.0f, delta) : 0.0f;
   return q;
 }
-// NE codes as integer-valued floats, handed to put(e, code)
+// NE codes before their rounding to integers, which Codes32 does (in the exact form they are integers already), handed to put(e, quotient)
 template <int NE, int QMAX, class Put>
 __device__ __forceinline__ void code_group(const float* x, float delta, const CodeScale& qs, Put&& put) {
   if (qs.fast) {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) put(e, rintf(div_by(x[e], delta, qs.r)));
+    for (int e = 0; e < NE; ++e) put(e, div_by(x[e], delta, qs.r));
   } else {
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
@@ -187,10 +153,10 @@ __device__ __forceinline__ uint4 pack16(const unsigned (&c)[16]) {
 }
 
 typedef unsigned v6u __attribute__((ext_vector_type(6)));
-// 32 INT4 codes held as integer-valued floats (every integer of [-7, 7] is an E2M3 value) become
-// consecutive 6-bit E2M3 fields, element e at bit 6e: the conversion instruction takes the even
-// elements in its first operand and the odd ones in its second (scale 1.0), so the codes are
-// collected in that shape from the start
+// 32 INT4 codes, as quotients of [-7, 7], become consecutive 6-bit E2M3 fields, element e at bit 6e: the conversion instruction takes the
+// even elements in its first operand and the odd ones in its second, so they are collected in that shape from the start.  It divides by
+// 8 (its scale operand): a code is stored as its eighth, and since E2M3 values up to 15/8 are the multiples of 1/8, the conversion's rounding
+// to the nearest, ties to even, is the rounding of the quotient to an integer - a v_rndne_f32 per code less.
 struct Codes32 {
   v16f ev, od;
   __device__ inline void set(int e, float c) { if (e & 1) od[e >> 1] = c; else ev[e >> 1] = c; }
@@ -204,22 +170,12 @@ struct Codes32 {
 #if defined(__HIP_DEVICE_COMPILE__)
     v16f a = ev, b = od;
     asm volatile("" : "+v"(a), "+v"(b));
-    r = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, 1.0f);
+    r = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, 8.0f);
     asm volatile("" ::"v"(r), "v"(a), "v"(b));
 #endif
     return r;
   }
 };
-
-// eight int8 codes as two's-complement bytes
-__device__ inline uint2 pack8(const int (&c)[8]) {
-  uint2 o;
-  o.x = (unsigned)(c[0] & 0xff) | ((unsigned)(c[1] & 0xff) << 8) | ((unsigned)(c[2] & 0xff) << 16) |
-        ((unsigned)(c[3] & 0xff) << 24);
-  o.y = (unsigned)(c[4] & 0xff) | ((unsigned)(c[5] & 0xff) << 8) | ((unsigned)(c[6] & 0xff) << 16) |
-        ((unsigned)(c[7] & 0xff) << 24);
-  return o;
-}
 
 // A row of 256 16-bit values by four lanes l, l + 16, l + 32, l + 48 (kk = 0..3), each of which wants 64 consecutive values
 // (pieces 8 kk .. of 8 values).  Loaded that way, a load instruction touches 16 bytes of a lane's 128, and the eight

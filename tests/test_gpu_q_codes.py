@@ -1,0 +1,49 @@
+"""The Q quantizers' codes, scales, block means and row constants where their maps can go wrong: numbers of queries around the rows of a
+pass (8, 16, 32), of a wavefront and of a block, every width and both modes, against the CPU oracle byte for byte; and a value that is not a number."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sage_oracle as so
+from test_gpu_attention_from_raw_kv import _inputs
+from test_gpu_parity import _pa
+from test_gpu_prologue_fuzz import GMAPS
+
+pytestmark = pytest.mark.gpu
+WANT = ("q_codes", "q_scale", "q_mean")
+
+
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+@pytest.mark.parametrize("N", [1, 2, 7, 9, 15, 17, 32, 33, 127, 128, 131])
+@pytest.mark.parametrize("d,dtype,group_map", [(64, "bf16", "lane"), (64, "fp16", "block"), (128, "fp16", "token"), (128, "bf16", "lane"), (256, "bf16", "block"), (256, "fp16", "lane")])
+def test_q_codes(d, dtype, group_map, N, mode):
+    pa = _pa()
+    print(f"Q codes: d={d} {dtype} N={N} {group_map} {mode}", flush=True)
+    q, k, v = _inputs(1, N, 70, d, 3, 1, dtype, "HND", seed=N)
+    got, _, _ = pa.sage_attn_quant(q, k, v, mode=mode, group_map=group_map, want=WANT)
+    torch.cuda.synchronize()
+    for h in range(3):
+        pro = so.quantize_head(q[0, h].float().cpu().numpy(), k[0, 0].float().cpu().numpy(), v[0, 0].float().cpu().numpy(), mode=mode, gmap=GMAPS[group_map])
+        assert np.array_equal(got["q_codes"][0, h].cpu().numpy(), pro["q_codes"])
+        assert np.array_equal(got["q_scale"][0, h].cpu().numpy(), pro["q_scale"][pro["q_groups"][::1 if group_map == "token" else 2]])
+        if mode == "int4_fp8":
+            assert np.array_equal(got["q_mean"][0, h].cpu().numpy(), pro["qbar"])
+
+
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+@pytest.mark.parametrize("d,N", [(64, 40), (128, 17), (256, 130)])
+def test_a_value_that_is_not_a_number(d, N, mode):
+    """Its code is 0, and in the 4-bit mode those of its channel (whose mean it makes NaN); all others are what they are beside a zero."""
+    pa = _pa()
+    print(f"Q codes, NaN: d={d} N={N} {mode}", flush=True)
+    q, k, v = _inputs(1, N, 70, d, 2, 2, "bf16", "HND")
+    c = d // 2 + 3
+    bad = q.clone()
+    bad[0, 1, N // 2, c] = float("nan")
+    if mode == "int4_fp8":
+        q[0, 1, :128, c] = 0.0                 # (its block of queries)
+    else:
+        q[0, 1, N // 2, c] = 0.0
+    (a, _, _), (b, _, _) = (pa.sage_attn_quant(x, k, v, mode=mode, want=WANT) for x in (q, bad))
+    torch.cuda.synchronize()
+    assert torch.equal(a["q_codes"], b["q_codes"]) and torch.equal(a["q_scale"], b["q_scale"])
