@@ -787,6 +787,7 @@ struct QuantKV {
   float code_max;
   int mixed;                 // K and V in one launch: both on every XCD
   int bounded;               // delta_V was taken from these values
+  int parts;                 // workgroups per key block of K (z of the grid)
 };
 
 template <int D, bool INT4, int DSM, bool REDUCE> struct QuantKLds {
@@ -805,7 +806,7 @@ template <int D, bool INT4, int DSM, bool REDUCE> struct QuantKLds {
   float bmax[4];
 };
 template <bool BF16, bool INT4, int D, int DSM = DS_DIGITS, bool REDUCE = false>
-__device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& lds, const BlockPos bp, const QuantKV& a) {
+__device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& lds, const BlockPos bp, const QuantKV& a, const int part = 0) {
   const unsigned short* __restrict__ K = a.k;
   float* __restrict__ k_scale = a.k_scale; int8_t* __restrict__ k_codes = a.k_codes;
   const float* __restrict__ q_mean = a.q_mean; float* __restrict__ delta_s = a.delta_s;
@@ -839,6 +840,11 @@ __device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& l
   const int nr = nQs - i0, nrow = INT4 ? G * nr : 0;
   const int bh0 = (int)bhkv * G;
   const float inv_nr = __builtin_amdgcn_rcpf((float)max(nr, 1));
+  // Of the steps this workgroup takes part `part` of a.parts (k_parts); the first one has the codes and scales too.
+  const int steps = (nrow + DS_ROWS - 1) / DS_ROWS;
+  const int row0 = DS_ROWS * (int)((unsigned)part * (unsigned)steps / (unsigned)a.parts);
+  const int row_end = min(nrow, DS_ROWS * (int)((unsigned)(part + 1) * (unsigned)steps / (unsigned)a.parts));
+  if (part > 0 && row0 >= row_end) return;
   // A step's rows: nr >= 16 leaves room for one change of head, `cut` rows of the current one and then the next one's;
   // shorter heads are told apart by a division per row.
   struct Step { int R, base, next, cut; };         // first row, its place in the [B H][nQb] arrays, that of the next head's first row, cut
@@ -919,7 +925,8 @@ __device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& l
   uint4 kraw[CPL / 8];
 #pragma unroll
   for (int p = 0; p < CPL / 8; ++p) kraw[p] = *reinterpret_cast<const uint4*>(krow + 8 * p);
-  Step step = step_at(0, 0, i0);
+  int g = part > 0 ? row0 / max(nr, 1) : 0, i = i0 + row0 - g * nr;       // head and query block of the step's first row
+  Step step = step_at(row0, g, i);
   if constexpr (INT4) load_q(step);
 
   // mean(K) of this head: reduced by the statistics pass, or here
@@ -927,7 +934,7 @@ __device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& l
     if (t < D) {
       const float m = a.smooth_k ? (float)(sum_partials(a.k_sum, (size_t)bhkv, a.nchunk, D, t) / (double)N) : 0.0f;
       s_kmean[t] = m;
-      if (kb == 0) a.k_mean[bhkv * D + t] = m;
+      if (kb == 0 && part == 0) a.k_mean[bhkv * D + t] = m;
     }
     __syncthreads();
   }
@@ -963,6 +970,7 @@ __device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& l
     __syncthreads();
     mx = fmaxf(fmaxf(s_bmax[0], s_bmax[1]), fmaxf(s_bmax[2], s_bmax[3]));
   }
+  if (part == 0) {
   const float delta = head_scale ? head_scale[bhkv] : __fdiv_rn(mx, (float)QMAX);
   const int ksh = kg == 16 ? 4 : (kg == 4 ? 2 : 0);
   if (k4 == 0 && (r16 & (kg - 1)) == 0) k_scale[(bhkv * nKb + kb) * (BKV >> ksh) + ((16 * w + r16) >> ksh)] = delta;
@@ -997,12 +1005,15 @@ __device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& l
       *reinterpret_cast<uint4*>(img + k_code_off(r, c0 + 16 * i, D)) = pack16(c);
     }
   }
+  }
   if constexpr (INT4) store_q(0);
   __syncthreads();
-  constexpr int BLK16 = (int)(k_block_bytes(D, INT4) / 16);
-  uint4* dst = reinterpret_cast<uint4*>(k_codes + (bhkv * nKb + kb) * k_block_bytes(D, INT4));
+  if (part == 0) {
+    constexpr int BLK16 = (int)(k_block_bytes(D, INT4) / 16);
+    uint4* dst = reinterpret_cast<uint4*>(k_codes + (bhkv * nKb + kb) * k_block_bytes(D, INT4));
 #pragma unroll
-  for (int i = t; i < BLK16; i += 256) dst[i] = s_codes[i];
+    for (int i = t; i < BLK16; i += 256) dst[i] = s_codes[i];
+  }
 
   if constexpr (INT4) {
     // the smoothed keys stay in FP32 registers and are widened per use (FP64 form): CPL more conversions per step instead
@@ -1038,13 +1049,12 @@ __device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& l
     }
     const unsigned rowstride = (unsigned)nKb * BKV;
     float* const out = delta_s + n0;
-    int g = 0, i = i0;
-    for (int half = 0; step.R < nrow; half ^= 1) {
+    for (int half = 0; step.R < row_end; half ^= 1) {
       // the next step's rows are on their way while this one is multiplied, and go to the other half of the buffer
       i += DS_ROWS;
       if (i >= nQs) { i -= nr; ++g; }
       const Step nxt = step_at(step.R + DS_ROWS, g, i);
-      if (nxt.R < nrow) load_q(nxt);
+      if (nxt.R < row_end) load_q(nxt);
       const int rows = min(nrow - step.R, DS_ROWS);
       const bool plain = plain_step(step);
       float* const out0 = out + (size_t)(unsigned)step.base * rowstride;      // (uniform: the lanes add 32-bit offsets)
@@ -1149,7 +1159,7 @@ __device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& l
         for (int v = 0; v < 4; ++v) val[v] = (float)(kap * acc[v]);
         put4(k4, 4, val);
       }
-      if (nxt.R >= nrow) break;
+      if (nxt.R >= row_end) break;
       store_q(half ^ 1);                           // (its last readers met the barrier that opened this step)
       __syncthreads();
       step = nxt;
@@ -1308,7 +1318,7 @@ template <int D, bool INT4, int DSM> constexpr int quant_k_occupancy() { return 
 template <bool BF16, bool INT4, int D, int DSM = DS_DIGITS>
 __global__ void __launch_bounds__(256, (quant_k_occupancy<D, INT4, DSM>())) k_quant_k(const QuantKV a) {
   __shared__ QuantKLds<D, INT4, DSM, false> lds;
-  quant_k_block<BF16, INT4, D, DSM>(lds, block_pos(a.km), a);
+  quant_k_block<BF16, INT4, D, DSM>(lds, block_pos(a.km), a, (int)blockIdx.z);
 }
 template <bool BF16, int D, bool SMOOTH_V, int PVF>
 __global__ void __launch_bounds__(256) k_quant_v(const QuantKV a) {
@@ -1358,8 +1368,8 @@ __global__ void __launch_bounds__(256, (quant_k_occupancy<D, INT4, DSM>())) k_qu
   BlockPos bp = block_pos(a.km);
   const bool is_v = a.mixed ? pair_second(blockIdx.y * gridDim.x + blockIdx.x) : (bp.x & 1) != 0;
   bp.x >>= 1; bp.nx >>= 1;
-  if (is_v) quant_v_block<BF16, D, SMOOTH_V, PV_E4M3, REDUCE>(lds.b, bp, a);
-  else quant_k_block<BF16, INT4, D, DSM, REDUCE>(lds.a, bp, a);
+  if (!is_v) quant_k_block<BF16, INT4, D, DSM, REDUCE>(lds.a, bp, a, (int)blockIdx.z);
+  else if (blockIdx.z == 0) quant_v_block<BF16, D, SMOOTH_V, PV_E4M3, REDUCE>(lds.b, bp, a);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1484,6 +1494,21 @@ static bool kv_pair(const Dims& Dm) {
   return blocks <= 800 || (rows <= 256 && blocks * rows <= 600000);
 }
 
+// Workgroups per key block of K, each with its share of the steps of the Delta-S product (and the loads and digits of the keys once more): where
+// the key blocks are few and the block means many - grouped KV heads, a long sequence - a workgroup per key block leaves much of the chip idle for
+// the length of its chain.  As many as make three rounds of the workgroups that fit, with four steps each, or six where the key
+// blocks alone make half a round.  Preprocessing, us, one / as many: 8 on 1 heads of 25318 tokens (396 key blocks, 99 steps) 157.8 /
+// 96.5, without a mask 167 / 130, 16 on 2 of 6000 56.3 / 36.9, 8 on 1 of 12000 of 64 channels 62.0 / 30.7, 48 on 6 of 4000 of 64 43.0 / 34.3, 4 on 2
+// of 32965 (1032, 33 steps) 95.5 / 86.3, 32 on 8 of 16384 (2048, 32) 169.4 / 165.2; but 2 of 20000 (626, 10 steps) two 39.5 for 38.8, 4 of 16384
+// (1024, 8 steps) 48.7 for 48.5, 4 x 4 of 29885 of 256 channels (7472, 15) 860 for 827.
+static int k_parts(const Dims& Dm) {
+  if (!Dm.int4 || Dm.ds_mode != DS_DIGITS || Dm.tensor_groups || !Dm.smooth_q) return 1;
+  const long long blocks = (long long)Dm.B * Dm.Hkv * Dm.nKb, steps = ((long long)(Dm.H / Dm.Hkv) * Dm.nQb + DS_ROWS - 1) / DS_ROWS;
+  const long long slots = Dm.d == 256 ? 512 : 1024;
+  const long long parts = min((3 * slots + blocks - 1) / blocks, steps / (2 * blocks < slots ? 4 : 6));
+  return (int)max(1LL, min(parts, 8LL));
+}
+
 template <bool BF16, bool INT4, int D>
 static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s) {
   const int BH = Dm.B * Dm.H, BHkv = Dm.B * Dm.Hkv;
@@ -1508,14 +1533,15 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   ka.block_groups = Dm.block_groups; ka.kg = Dm.kg; ka.causal = Dm.causal; ka.km = km; ka.sm = sm;
   ka.head_scale = nullptr; ka.stats_only = 0; ka.zero_ds = !Dm.smooth_q; ka.q_digits = P.q_digits; ka.q_dscale = P.q_dscale;
   ka.k_sum = P.k_sum; ka.v_max = P.v_max; ka.nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS; ka.smooth_k = Dm.smooth_k;
-  ka.code_max = E4M3_MAX; ka.bounded = !Dm.stats_given;
+  ka.code_max = E4M3_MAX; ka.bounded = !Dm.stats_given; ka.parts = k_parts(Dm);
   // Taken one by one, K and V have every other XCD to themselves, on a grid that runs through the key blocks first.  That is the better
   // order (two kinds of code and of registers kept apart: 24 heads of 493 tokens, 8-bit, K and V 7.7 us mixed, 6.8 apart; 16 on 8 heads of
   // 1261 tokens of 256 channels, 4-bit, whole call 81.6, 80.2) unless K takes much longer than V and the chip is full.
   ka.mixed = INT4 && D < 256 && !km.heads_inner && (!few_rows(Dm) || (long long)BHkv * Dm.nKb >= 256);
   // K and V in one launch; `reduced`: mean(K) and delta_V are in place
   auto quant_kv = [&](bool reduced) {
-    const dim3 grid = block_grid(km, 2 * Dm.nKb, BHkv);
+    dim3 grid = block_grid(km, 2 * Dm.nKb, BHkv);
+    grid.z = ka.parts;
 #define SAGE_QKV(DSM_)                                                                                                  \
   do {                                                                                                                  \
     if (Dm.smooth_v) k_quant_kv<BF16, INT4, D, DSM_, true, false><<<grid, 256, 0, s>>>(ka);                              \
@@ -1557,7 +1583,9 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   auto quant_k_pass = [&](const float* head_scale, int stats_only) {
     QuantKV x = ka;
     x.head_scale = head_scale; x.stats_only = stats_only;
-#define SAGE_QK(DSM_) k_quant_k<BF16, INT4, D, DSM_><<<block_grid(km, Dm.nKb, BHkv), 256, 0, s>>>(x)
+    dim3 grid = block_grid(km, Dm.nKb, BHkv);
+    grid.z = ka.parts;
+#define SAGE_QK(DSM_) k_quant_k<BF16, INT4, D, DSM_><<<grid, 256, 0, s>>>(x)
     // (the 8-bit build has no Delta-S: one instantiation, named by the default mode)
     if (INT4 && Dm.ds_mode == DS_FP32) SAGE_QK(INT4 ? DS_FP32 : DS_DIGITS);
     else if (INT4 && Dm.ds_mode == DS_FP64) SAGE_QK(INT4 ? DS_FP64 : DS_DIGITS);
