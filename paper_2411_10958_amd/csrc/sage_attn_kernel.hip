@@ -631,21 +631,13 @@ __global__ void __launch_bounds__(256) k_merge_splits(const AttnParams p) {
     const size_t bhkv = (size_t)b * p.Hkv + h / (p.H / p.Hkv);
     if (sq.nk == 0 || query >= sq.n) return;     // (rows ascend; a sequence without keys was written by the attention kernel)
     const size_t row0 = (size_t)tile * p.splits * BQ + r;       // this row in chunk 0; chunk s is s * BQ rows further
-    float e_max = -INFINITY;
-    for (int s0 = 0; s0 < p.splits; s0 += NB) {
-      float e[NB];
-#pragma unroll
-      for (int i = 0; i < NB; ++i) e[i] = p.part_el[(row0 + (size_t)min(s0 + i, p.splits - 1) * BQ) * 2];
-#pragma unroll
-      for (int i = 0; i < NB; ++i) e_max = fmaxf(e_max, e[i]);
-    }
-    float l = 0.0f;
-    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    // NB chunks at a time, all their loads issued before the first use (one round trip per batch, not one per chunk); the
+    // NB chunks at a time, all their loads issued before the first use (one round trip per batch, not one per chunk), those of
+    // the first batch and delta_V together with the first look at the offsets that weight them all: bound by these trips, not by
+    // bytes (512 queries on 16384 keys in three chunks 13.6 -> 12.8 us, a query of 128 heads in 16 chunks 7.0 -> 5.4).  The
     // chunks are summed in order
-    for (int s0 = 0; s0 < p.splits; s0 += NB) {
-      float e[NB], lc[NB];
-      v4f o4[NB];
+    float e[NB], lc[NB];
+    v4f o4[NB];
+    auto request = [&](int s0) {
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         const size_t row = row0 + (size_t)min(s0 + i, p.splits - 1) * BQ;
@@ -653,6 +645,22 @@ __global__ void __launch_bounds__(256) k_merge_splits(const AttnParams p) {
         lc[i] = p.part_el[row * 2 + 1];
         o4[i] = *reinterpret_cast<const v4f*>(p.part_o + row * D + c_lo);
       }
+    };
+    request(0);
+    const v4f vs = *reinterpret_cast<const v4f*>(p.v_scale + bhkv * D + c_lo);
+    float e_max = -INFINITY;
+    for (int s0 = NB; s0 < p.splits; s0 += NB) {
+      float x[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) x[i] = p.part_el[(row0 + (size_t)min(s0 + i, p.splits - 1) * BQ) * 2];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) e_max = fmaxf(e_max, x[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) e_max = fmaxf(e_max, e[i]);
+    float l = 0.0f;
+    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int s0 = 0;;) {
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         if (s0 + i >= p.splits || e[i] == -INFINITY) continue;     // (an empty chunk left its sums unwritten)
@@ -661,6 +669,9 @@ __global__ void __launch_bounds__(256) k_merge_splits(const AttnParams p) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[k] = __fmaf_rn(wgt, o4[i][k], acc[k]);
       }
+      s0 += NB;
+      if (s0 >= p.splits) break;
+      request(s0);
     }
     if (p.lse && c_lo == 0)
       p.lse[lse_index(p, sq, b, h, query)] =
@@ -668,16 +679,15 @@ __global__ void __launch_bounds__(256) k_merge_splits(const AttnParams p) {
     const float inv_l = __fdiv_rn(1.0f, l);
     unsigned short* orow = reinterpret_cast<unsigned short*>(p.out) +
                            row_offset(p.om, head_offset(p.om, (unsigned)bh), (int)sq.q0 + query) + c_lo;
-    const v4f vs = *reinterpret_cast<const v4f*>(p.v_scale + bhkv * D + c_lo);
-    float o4[4];
+    float y[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) o4[k] = __fmul_rn(__fmul_rn(acc[k], inv_l), vs[k]);
+    for (int k = 0; k < 4; ++k) y[k] = __fmul_rn(__fmul_rn(acc[k], inv_l), vs[k]);
     if (p.v_mean) {
       const v4f vm = *reinterpret_cast<const v4f*>(p.v_mean + bhkv * D + c_lo);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) o4[k] = __fadd_rn(o4[k], vm[k]);
+      for (int k = 0; k < 4; ++k) y[k] = __fadd_rn(y[k], vm[k]);
     }
-    *reinterpret_cast<uint2*>(orow) = make_uint2(pack16x2<BF16>(o4[0], o4[1]), pack16x2<BF16>(o4[2], o4[3]));
+    *reinterpret_cast<uint2*>(orow) = make_uint2(pack16x2<BF16>(y[0], y[1]), pack16x2<BF16>(y[2], y[3]));
   }
 }
 
