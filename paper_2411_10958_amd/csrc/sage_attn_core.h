@@ -17,7 +17,7 @@ struct AttnParams {
   void* out;
   int H, Hkv, N, Nk, nQb, nKb, total_tiles;   // N queries, Nk keys (of the longest sequence)
   TensorMap om;           // where the rows of `out` start
-  float kappa;
+  float qk_kappa;         // kappa, times 64 in the 4-bit mode (fp6_kappa); a product formed in the kernel instead cost short launches up to 2.7 us of 16
   SeqMap seq;             // variable-length batch: N, Nk, nQb, nKb describe the longest sequence
   float* lse;             // null, or where the row log-sum-exp goes
   const float* q_corr;    // kappa * <q_r, mean(K)> per query (read only with lse)
@@ -26,6 +26,7 @@ struct AttnParams {
   int splits;             // workgroups per tile (1: no split)
   float* part_o;          // [tile * splits + s][128 rows][d]: unnormalized O under the chunk's own exponent offset
   float* part_el;         // [tile * splits + s][128 rows][2]: that offset e and the sum l under it
+  float kappa;
 };
 
 inline AttnParams attn_params(const Dims& Dm, const Ptrs& P) {
@@ -40,6 +41,7 @@ inline AttnParams attn_params(const Dims& Dm, const Ptrs& P) {
   p.lse = P.lse; p.q_corr = P.q_corr; p.B = Dm.B;
   p.total_tiles = Dm.B * Dm.H * Dm.nQb;
   p.kappa = Dm.kappa;
+  p.qk_kappa = fp6_kappa(Dm.int4, Dm.kappa);
   p.splits = Dm.splits; p.part_o = P.part_o; p.part_el = P.part_el;
   return p;
 }

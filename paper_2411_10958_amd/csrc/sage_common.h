@@ -286,7 +286,7 @@ __host__ __device__ inline int e2m3_to_int4_code(unsigned b) {
   const int a = e == 0 ? m : (8 + m) << (e - 1);            // eight times the value
   return (b & 0x20) ? -a : a;
 }
-template <bool INT4> __device__ __forceinline__ float fp6_kappa(float kappa) { return INT4 ? 64.0f * kappa : kappa; }
+inline float fp6_kappa(bool int4, float kappa) { return int4 ? 64.0f * kappa : kappa; }
 // byte b (0..23) of lane_m's payload inside an op (16-byte plane, then 8-byte plane)
 __host__ __device__ inline int op6_byte(int lane_m, int b) {
   return b < 16 ? lane_m * 16 + b : 1024 + lane_m * 8 + (b - 16);
