@@ -17,7 +17,7 @@ struct AttnParams {
   void* out;
   int H, Hkv, N, Nk, nQb, nKb, total_tiles;   // N queries, Nk keys (of the longest sequence)
   TensorMap om;           // where the rows of `out` start
-  float qk_kappa;         // kappa, times 64 in the 4-bit mode (fp6_kappa); a product formed in the kernel instead cost short launches up to 2.7 us of 16
+  float kappa;
   SeqMap seq;             // variable-length batch: N, Nk, nQb, nKb describe the longest sequence
   float* lse;             // null, or where the row log-sum-exp goes
   const float* q_corr;    // kappa * <q_r, mean(K)> per query (read only with lse)
@@ -26,7 +26,6 @@ struct AttnParams {
   int splits;             // workgroups per tile (1: no split)
   float* part_o;          // [tile * splits + s][128 rows][d]: unnormalized O under the chunk's own exponent offset
   float* part_el;         // [tile * splits + s][128 rows][2]: that offset e and the sum l under it
-  float kappa;
 };
 
 inline AttnParams attn_params(const Dims& Dm, const Ptrs& P) {
@@ -41,7 +40,6 @@ inline AttnParams attn_params(const Dims& Dm, const Ptrs& P) {
   p.lse = P.lse; p.q_corr = P.q_corr; p.B = Dm.B;
   p.total_tiles = Dm.B * Dm.H * Dm.nQb;
   p.kappa = Dm.kappa;
-  p.qk_kappa = fp6_kappa(Dm.int4, Dm.kappa);
   p.splits = Dm.splits; p.part_o = P.part_o; p.part_el = P.part_el;
   return p;
 }
@@ -87,7 +85,7 @@ __host__ __device__ inline KeyChunk key_chunk(int s, int S, int nblk, int n_vis)
 // 32*kt + 16*(lane/32) + v of the block and to query lane%32 of the wavefront.
 // INT8 mode: v_mfma_i32_32x32x32_i8, int32 accumulators.  INT4 mode: the codes are 6-bit FP6 E2M3
 // values and feed v_mfma_f32_32x32x64_f8f6f4 in its FP6 operand format (twice the rate of the 8-bit
-// formats) as eighths; the FP32 accumulators hold the integers' sixty-fourths, exactly.  Either way the result is returned as
+// formats); the FP32 accumulators hold the exact integers.  Either way the result is returned as
 // raw 32-bit lanes.
 // The product is issued one MFMA ("step") at a time so that the steps can be spread between
 // pieces of vector work: step I works on key tile I % 2 and contraction piece I / 2 (64 channels

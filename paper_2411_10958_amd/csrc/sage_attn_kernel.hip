@@ -402,7 +402,7 @@ __global__ void __launch_bounds__(256, (attn_occupancy<D, GM, PVF>())) k_attn_fw
     read_scales(0);
     qk_tile<D, INT4>(ka, qreg, raw);    // the first block holds a visible key for every query
     Factors<GM> fn;
-    fn.set(dq, p.qk_kappa, ks);
+    fn.set(dq, p.kappa, ks);
     if (j_begin < n_plain) SAGE_DEQ_ALL(false, j_begin * BKV); else SAGE_DEQ_ALL(true, j_begin * BKV);
     alpha = update_max<D, INT4, GM, PVF>(st, sc, fn, m_sub);
     fj = fn;
@@ -455,7 +455,7 @@ __global__ void __launch_bounds__(256, (attn_occupancy<D, GM, PVF>())) k_attn_fw
     if constexpr (LATE_SCALES) read_scales(nx1);                                                     \
     st.l_run = __fmaf_rn(alpha, st.l_run, ls);                                                       \
     Factors<GM> fn;                                                                                  \
-    fn.set(dq, p.qk_kappa, ks);                                                                         \
+    fn.set(dq, p.kappa, ks);                                                                         \
     SAGE_Y(0, MASKED_NEXT_); SAGE_Y(1, MASKED_NEXT_); SAGE_Y(2, MASKED_NEXT_); SAGE_Y(3, MASKED_NEXT_); /* Y */ \
     SAGE_Y(4, MASKED_NEXT_); SAGE_Y(5, MASKED_NEXT_); SAGE_Y(6, MASKED_NEXT_); SAGE_Y(7, MASKED_NEXT_);         \
     alpha = update_max<D, INT4, GM, PVF>(st, sc, fn, m_sub);                                              \
@@ -480,7 +480,7 @@ __global__ void __launch_bounds__(256, (attn_occupancy<D, GM, PVF>())) k_attn_fw
     read_scales(cur);                                                                                \
     qk_tile<D, INT4>(ka, qreg, raw);                                                                 \
     Factors<GM> fn;                                                                                  \
-    fn.set(dq, p.qk_kappa, ks);                                                                         \
+    fn.set(dq, p.kappa, ks);                                                                         \
     SAGE_DEQ_ALL(MASKED_, j * BKV);                                                                  \
     alpha = update_max<D, INT4, GM, PVF>(st, sc, fn, m_sub);                                         \
     block_rescale<D>(st, alpha);                                                                     \
@@ -716,7 +716,7 @@ __global__ void __launch_bounds__(256) k_debug_qk(const int8_t* __restrict__ q_c
   for (int kt = 0; kt < 2; ++kt) {
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-      out[(w * WQ + n) * BKV + 32 * kt + 16 * half + v] = INT4 ? (int)(64.0f * __int_as_float(acc[kt][v])) : acc[kt][v];
+      out[(w * WQ + n) * BKV + 32 * kt + 16 * half + v] = INT4 ? (int)__int_as_float(acc[kt][v]) : acc[kt][v];
   }
 }
 

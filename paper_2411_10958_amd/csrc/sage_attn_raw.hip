@@ -524,7 +524,7 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
         KeyScales<0> ks;
         ks.s[0] = s_ks[cur][half];
         ks.s[1] = s_ks[cur][2 + half];
-        fac.set(dq, p.qk_kappa, ks);
+        fac.set(dq, p.kappa, ks);
         key_tile(std::integral_constant<int, 0>{});
         key_tile(std::integral_constant<int, 1>{});
       }

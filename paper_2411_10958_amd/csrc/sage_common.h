@@ -143,7 +143,7 @@ struct Dims {
 //            MFMA row rho = l%32 and channels 32*s + 16*(l/32) + 0..15, where row
 //            rho = 8g + 4h + r carries key 32*tile + 16h + 4g + r of the block, so that an
 //            accumulator lane (half h) ends up with 16 consecutive keys.
-//  INT4 mode (6-bit FP6 E2M3 codes of the integers' eighths, see the FP6 note below): one
+//  INT4 mode (6-bit FP6 E2M3 codes of the same integers, see the FP6 note below): one
 //  operand of v_mfma_f32_32x32x64_f8f6f4 ("op") covers 32 rows x 64 channels; lane l supplies row
 //  l%32 and channels 32*(l/32) + e, element e at bit 6e of a 24-byte payload.  An op is stored
 //  as 1536 bytes: a plane of 64 x 16 bytes (payload bytes 0..15 of lanes 0..63) followed by a
@@ -272,21 +272,22 @@ __host__ __device__ inline size_t v_code_off(int n, int c, int d) {
   return ((size_t)((blk * (d >> 5) + ct) * 2 + part) * 64 + ch + 32 * h) * 16 + byte;
 }
 
-// ---- INT4 codes travel as 6-bit FP6 E2M3 values: their eighths ----
-// gfx950 has no 4-bit integer MFMA, but c / 8 is an E2M3 value for every integer c of [-7, 7] (sign, 2 exponent
-// bits with bias 1, 3 mantissa bits: exponent 0 holds the multiples of 1/8 below 1), products
-// (<= 49/64) and their sums over d <= 256 channels are exact in the FP32 accumulator of
+// ---- INT4 codes travel as 6-bit FP6 E2M3 values ----
+// gfx950 has no 4-bit integer MFMA, but every integer in [-7, 7] is an E2M3 value (sign, 2 exponent
+// bits with bias 1, 3 mantissa bits: 1, 2, 3 = 1.5*2, 4, 5 = 1.25*4, 6 = 1.5*4, 7 = 1.75*4), products
+// (<= 49) and their sums over d <= 256 channels (<= 12544) are exact in the FP32 accumulator of
 // v_mfma_f32_32x32x64_f8f6f4, and the FP6 operand format runs at twice the rate of the 8-bit
 // formats: the gfx950 counterpart of "INT4 matmul is twice as fast as INT8".  The accumulators come
-// out as exact floats, sum of c_q c_k / 64 - no int->float conversion afterwards; the 64 goes into kappa (fp6_kappa).
+// out as exact integers in float - no int->float conversion afterwards.  (Stored as their eighths, which the conversion's own rounding
+// gives, the codes saved the quantizers a rounding instruction each, under 1 % of a call; but the 64 that the products then lack takes
+// a score's factor out of FP32 64 times earlier, and 0 times infinity is no score.)
 // (The quantizers produce the fields with the hardware FP32 -> FP6 conversion; the decoder below serves
 // the copy-out of sage_attn_quant.)
 __host__ __device__ inline int e2m3_to_int4_code(unsigned b) {
   const int e = (b >> 3) & 3, m = b & 7;
-  const int a = e == 0 ? m : (8 + m) << (e - 1);            // eight times the value
+  const int a = e == 0 ? 0 : ((8 + m) << (e - 1)) >> 3;     // (1 + m/8) * 2^(e-1)
   return (b & 0x20) ? -a : a;
 }
-inline float fp6_kappa(bool int4, float kappa) { return int4 ? 64.0f * kappa : kappa; }
 // byte b (0..23) of lane_m's payload inside an op (16-byte plane, then 8-byte plane)
 __host__ __device__ inline int op6_byte(int lane_m, int b) {
   return b < 16 ? lane_m * 16 + b : 1024 + lane_m * 8 + (b - 16);

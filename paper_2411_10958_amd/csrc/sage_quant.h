@@ -102,9 +102,9 @@ __device__ inline int quant_code(float x, float delta, int qmax) {
 }
 
 // psi with the correctly rounded quotient of div_by, for whole wavefronts: `fast` says that every lane's scale is one that
-// div_by accepts, or zero (all its values are then zero and so are their codes).  Three multiply-adds per code and no branch per eight
-// codes (a product with the reciprocal whose distance from the next half-integer was watched, and a division where it was too near, took a rounding, a
-// difference and a maximum more).
+// div_by accepts, or zero (all its values are then zero and so are their codes).  Three multiply-adds and a rounding per code and no
+// branch per eight codes (a product with the reciprocal whose distance from the next half-integer was watched, and a division where it was too
+// near, took a difference and a maximum more).
 struct CodeScale { float r; bool fast; };
 __device__ __forceinline__ CodeScale code_scale(float delta) {
   CodeScale q;
@@ -112,12 +112,12 @@ __device__ __forceinline__ CodeScale code_scale(float delta) {
   q.r = q.fast && delta > 0.0f ? __fdiv_rn(1.0f, delta) : 0.0f;
   return q;
 }
-// NE codes before their rounding to integers, which Codes32 does (in the exact form they are integers already), handed to put(e, quotient)
+// NE codes as integer-valued floats, handed to put(e, code)
 template <int NE, int QMAX, class Put>
 __device__ __forceinline__ void code_group(const float* x, float delta, const CodeScale& qs, Put&& put) {
   if (qs.fast) {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) put(e, div_by(x[e], delta, qs.r));
+    for (int e = 0; e < NE; ++e) put(e, rintf(div_by(x[e], delta, qs.r)));
   } else {
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
@@ -153,10 +153,10 @@ __device__ __forceinline__ uint4 pack16(const unsigned (&c)[16]) {
 }
 
 typedef unsigned v6u __attribute__((ext_vector_type(6)));
-// 32 INT4 codes, as quotients of [-7, 7], become consecutive 6-bit E2M3 fields, element e at bit 6e: the conversion instruction takes the
-// even elements in its first operand and the odd ones in its second, so they are collected in that shape from the start.  It divides by
-// 8 (its scale operand): a code is stored as its eighth, and since E2M3 values up to 15/8 are the multiples of 1/8, the conversion's rounding
-// to the nearest, ties to even, is the rounding of the quotient to an integer - a v_rndne_f32 per code less.
+// 32 INT4 codes held as integer-valued floats (every integer of [-7, 7] is an E2M3 value) become
+// consecutive 6-bit E2M3 fields, element e at bit 6e: the conversion instruction takes the even
+// elements in its first operand and the odd ones in its second (scale 1.0), so the codes are
+// collected in that shape from the start
 struct Codes32 {
   v16f ev, od;
   __device__ inline void set(int e, float c) { if (e & 1) od[e >> 1] = c; else ev[e >> 1] = c; }
@@ -170,7 +170,7 @@ struct Codes32 {
 #if defined(__HIP_DEVICE_COMPILE__)
     v16f a = ev, b = od;
     asm volatile("" : "+v"(a), "+v"(b));
-    r = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, 8.0f);
+    r = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, 1.0f);
     asm volatile("" ::"v"(r), "v"(a), "v"(b));
 #endif
     return r;
