@@ -957,8 +957,20 @@ __device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& l
 #pragma unroll
     for (int e = 0; e < CPL; ++e) x[e] = n0 + r < N ? x[e] : 0.0f;
   }
+  // A value that is not a number (a NaN key makes its channel's mean NaN, and so the channel of every key) leaves the scale alone and has
+  // code 0, which the exact form of the codes gives and the FP6 conversion, that has no NaN, does not.  The maximum that passes NaN on takes
+  // no instruction more than the one that does not.
+  bool odd = false;
+  if constexpr (INT4) {
 #pragma unroll
-  for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(x[e]));
+    for (int e = 0; e < CPL; ++e) mx = __builtin_elementwise_maximum(mx, fabsf(x[e]));
+    odd = __builtin_amdgcn_ballot_w64(mx != mx) != 0;
+    if (odd) mx = 0.0f;
+  }
+  if (!INT4 || odd) {
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(x[e]));
+  }
   // lanes l, l^16, l^32, l^48 hold one key: its maximum first, then (unless every key has its own
   // scale) the run of 4 keys, then (default) the wavefront's run of 16
   mx = butterfly_max<32>(butterfly_max<16>(mx));
@@ -976,7 +988,8 @@ __device__ __forceinline__ void quant_k_block(QuantKLds<D, INT4, DSM, REDUCE>& l
   if (k4 == 0 && (r16 & (kg - 1)) == 0) k_scale[(bhkv * nKb + kb) * (BKV >> ksh) + ((16 * w + r16) >> ksh)] = delta;
   if (stats_only) return;                // per-tensor scales, first pass: only the block maxima are wanted
   uint8_t* img = reinterpret_cast<uint8_t*>(s_codes);
-  const CodeScale qs = code_scale(delta);
+  CodeScale qs = code_scale(delta);
+  qs.fast = qs.fast && !odd;
   if constexpr (INT4) {
     // the lane's CPL codes are CPL*6/32 consecutive dwords of one MFMA lane's payload (all 6 of
     // them when d = 128; dwords 0..2 or 3..5 when d = 64), or two whole payloads (d = 256)

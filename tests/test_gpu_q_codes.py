@@ -1,5 +1,5 @@
 """The Q quantizers' codes, scales, block means and row constants where their maps can go wrong: numbers of queries around the rows of a
-pass (8, 16, 32), of a wavefront and of a block, every width and both modes, against the CPU oracle byte for byte; and a value that is not a number."""
+pass (8, 16, 32), of a wavefront and of a block, every width and both modes, against the CPU oracle byte for byte; and a value that is not a number, in Q and in K."""
 import numpy as np
 import pytest
 import torch
@@ -47,3 +47,40 @@ def test_a_value_that_is_not_a_number(d, N, mode):
     (a, _, _), (b, _, _) = (pa.sage_attn_quant(x, k, v, mode=mode, want=WANT) for x in (q, bad))
     torch.cuda.synchronize()
     assert torch.equal(a["q_codes"], b["q_codes"]) and torch.equal(a["q_scale"], b["q_scale"])
+
+
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+@pytest.mark.parametrize("kw", [dict(), dict(delta_s="digits"), dict(group_map="token"), dict(group_map="block"), dict(group_map="tensor"), dict(smooth_k=False), dict(smooth_v=True)])
+@pytest.mark.parametrize("d,Nk", [(64, 70), (128, 300), (256, 130)])
+def test_a_key_that_is_not_a_number(d, Nk, kw, mode):
+    """Its code is 0, and smoothed, those of its channel are; all other codes and scales are what they are beside a zero."""
+    pa = _pa()
+    print(f"K codes, NaN: d={d} N_kv={Nk} {kw} {mode}", flush=True)
+    q, k, v = _inputs(1, 40, Nk, d, 2, 2, "bf16", "HND")
+    c = d // 2 + 3
+    bad = k.clone()
+    bad[0, 1, Nk // 2, c] = float("nan")
+    if kw.get("smooth_k", True):
+        k[0, 1, :, c] = 0.0
+    else:
+        k[0, 1, Nk // 2, c] = 0.0
+    (a, _, _), (b, _, _) = (pa.sage_attn_quant(q, x, v, mode=mode, want=("k_codes", "k_scale"), **kw) for x in (k, bad))
+    torch.cuda.synchronize()
+    assert int(b["k_codes"].abs().max()) <= (7 if mode == "int4_fp8" else 127)
+    assert torch.equal(a["k_codes"], b["k_codes"]) and torch.equal(a["k_scale"], b["k_scale"])
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_a_key_that_is_not_a_number_beside_supplied_statistics(d):
+    """mean(K) is finite then, and only the value itself has code 0."""
+    pa = _pa()
+    print(f"K codes, NaN beside supplied statistics: d={d}", flush=True)
+    q, k, v = _inputs(1, 40, 200, d, 2, 2, "bf16", "HND")
+    stats = pa.sage_attn_kv_stats(k, v)
+    bad = k.clone()
+    bad[0, 1, 77, 5] = float("nan")
+    k[0, 1, 77, 5] = 0.0
+    stats[0][0, 1, 5] = 0.0                       # (a zero less this mean has code 0 too)
+    (a, _, _), (b, _, _) = (pa.sage_attn_quant(q, x, v, kv_stats=stats, want=("k_codes", "k_scale")) for x in (k, bad))
+    torch.cuda.synchronize()
+    assert torch.equal(a["k_codes"], b["k_codes"]) and torch.equal(a["k_scale"], b["k_scale"])
