@@ -130,7 +130,7 @@ typedef struct sage_attn_args {
   int group_map;          /* SAGE_GROUPS_*; 0 = the default */
   int N_kv;               /* keys / values per head (cross attention, chunked prefill); 0 = N */
   int layout;             /* SAGE_LAYOUT_*: memory order of q, k, v and out; 0 = [B, H, N, d] */
-  void* workspace;        /* device scratch of >= sage_attn_workspace_bytes(); 256-byte aligned */
+  void* workspace;        /* device scratch of >= sage_attn_workspace_bytes() (or less: see there); 256-byte aligned */
   size_t workspace_bytes;
   void* stream;           /* hipStream_t, NULL = default stream */
   const int* cu_seqlens_q; /* device, [B + 1] prefix sums of the query lengths, or NULL: fixed length N */
@@ -156,10 +156,11 @@ typedef struct sage_attn_args {
                               chunks by the rule that combines consecutive blocks in Eq. 1 (Sec. 2.1).  For calls with
                               few query tiles and many keys - a decode step, a short chunk of queries against a long
                               cache - where one workgroup per tile would leave most of the chip idle.  0: the library
-                              decides (it splits when there are fewer than 256 tiles, into whole rounds of workgroups, and
+                              decides (it splits when there are fewer than 256 tiles, so that the workgroups fill the chip
+                              or whole rounds of it, and
                               256 to 384 tiles - of 64 channels 511 - over keys long enough for chunks of 48 key
-                              blocks; sage_attn_kv_splits tells; sage_attn_fwd_static takes fewer chunks of the former and
-                              leaves the latter unsplit where only their partial results would not fit);
+                              blocks; in a workspace that is too small only for the partial results it takes fewer: below 256
+                              tiles as many as fit of at most ceil(512 / tiles), from there on one; sage_attn_kv_splits tells);
                               1: never; 2..64: this many (cut to one chunk per 8 key blocks at most).  Default groups
                               (SAGE_GROUPS_LANE, _BLOCK, _TENSOR) and SAGE_PV_E4M3 only, else 1.
                               With 2..8 query heads per KV head whose queries all fit one tile (N * H / H_kv <= 128,
@@ -175,11 +176,14 @@ typedef struct sage_attn_args {
 } sage_attn_args;
 
 /* Bytes of device scratch one call needs for these shapes (codes, scales, means, Delta-S, partial results of a
-   split key range).  Depends on the shapes, mode, options and kv_splits, not on pointers.  Returns 0 if those are invalid. */
+   split key range).  Depends on the shapes, mode, options and kv_splits, not on pointers.  Returns 0 if those are invalid.
+   With kv_splits = 0 a call also runs in what it needs unsplit, in fewer key chunks (see kv_splits): a workspace of
+   a larger call - more sequences, queries or keys - serves every smaller one, whichever number of chunks that takes. */
 size_t sage_attn_workspace_bytes(const sage_attn_args* args);
 
 /* The number of key chunks per query tile sage_attn_fwd_ex / sage_attn_core will use for these arguments (see
-   kv_splits); 0 if the arguments are invalid. */
+   kv_splits); 0 if the arguments are invalid.  workspace_bytes = 0 stands for sage_attn_workspace_bytes(); with
+   SAGE_STATIC_WORKSPACE_BYTES it is the number of sage_attn_fwd_static. */
 int sage_attn_kv_splits(const sage_attn_args* args);
 
 /* The whole forward pass of Algorithm 1: preprocessing (smoothing, Delta-S, quantization;
@@ -209,7 +213,8 @@ void sage_attn_release(void);
    the library's device image (every GPU the library is used on holds its own copy from the first call on it
    until the process ends): the call makes no hipMalloc / hipFree and no other allocating call, and ignores
    args->workspace / workspace_bytes.  q, k, v, out (and lse, cu_seqlens_*, k_mean_in, v_scale_in) are the
-   caller's, as everywhere.  Shapes whose sage_attn_workspace_bytes() exceeds SAGE_STATIC_WORKSPACE_BYTES are
+   caller's, as everywhere.  Shapes that do not fit SAGE_STATIC_WORKSPACE_BYTES - with kv_splits = 0, in one key chunk;
+   in fewer than their automatic ones they run, as sage_attn_fwd_ex does in a workspace of that size - are
    refused with SAGE_ERR_WORKSPACE before anything is launched; more than 64 devices: SAGE_ERR_UNSUPPORTED.
    All calls on one GPU share that GPU's array: calls that overlap there (two streams, two threads) race, and
    the caller must order them; nothing in it has to be cleared between calls. */

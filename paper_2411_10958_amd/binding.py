@@ -176,7 +176,7 @@ def sage_attn_workspace_bytes(args):
 
 
 def sage_attn_kv_splits(args):
-    """Key chunks per query tile the attention kernel will use for these arguments."""
+    """Key chunks per query tile the attention kernel will use for these arguments (in their workspace, where they have one)."""
     return int(load_library().sage_attn_kv_splits(ctypes.byref(args)))
 
 

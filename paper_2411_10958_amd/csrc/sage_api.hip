@@ -135,9 +135,23 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
   return SAGE_OK;
 }
 
-long long auto_tiles(const Dims& D) { return D.pack ? (long long)D.B * D.Hkv : (long long)D.B * D.H * D.nQb; }
-// A split that the library picked for a launch of 256 tiles or more (see validate).
-bool splits_by_choice(const Dims& D) { return !D.pack && D.splits > 1 && (long long)D.B * D.H * D.nQb >= 256; }
+// The workspace of a call that has `bytes` for it.  Where the library picked the chunks and only their partial results do not fit, there are fewer: as
+// many as fit of at most ceil(512 / tiles) below 256 tiles, one from there on; and where short queries share a tile, which takes partial results
+// in one chunk too, they don't where that alone does not fit (kv_splits = 1).  The partial results do not grow with the tiles (the chunks are whole
+// rounds of workgroups), everything else does: without this a workspace kept from a larger batch, or a longer chunk of queries, would not
+// serve the smaller one.
+Workspace fit_workspace(const sage_attn_args* a, Dims* D, size_t bytes) {
+  Workspace w = make_workspace(*D);
+  if (w.total <= bytes || a->kv_splits != 0) return w;
+  const long long tiles = D->pack ? (long long)D->B * D->Hkv : (long long)D->B * D->H * D->nQb;
+  D->splits = tiles >= 256 ? 1 : (int)std::min<long long>(D->splits, (512 + tiles - 1) / tiles);
+  while ((w = make_workspace(*D)).total > bytes && D->splits > 1) --D->splits;
+  if (w.total > bytes && D->pack) {
+    D->pack = 0;
+    w = make_workspace(*D);
+  }
+  return w;
+}
 
 int check_workspace(const sage_attn_args* a, const Workspace& w) {
   if (!a->workspace || a->workspace_bytes < w.total) return SAGE_ERR_WORKSPACE;
@@ -213,6 +227,7 @@ size_t sage_attn_workspace_bytes(const sage_attn_args* args) {
 int sage_attn_kv_splits(const sage_attn_args* args) {
   Dims D;
   if (validate(args, &D, false) != SAGE_OK) return 0;
+  if (args->workspace_bytes != 0) (void)fit_workspace(args, &D, args->workspace_bytes);
   return D.splits;
 }
 
@@ -220,7 +235,7 @@ int sage_attn_prologue(const sage_attn_args* args) {
   Dims D;
   int st = validate(args, &D, true);
   if (st != SAGE_OK) return st;
-  const Workspace w = make_workspace(D);
+  const Workspace w = fit_workspace(args, &D, args->workspace_bytes);
   if ((st = check_workspace(args, w)) != SAGE_OK) return st;
   const Ptrs P = ptrs_for(args, w);
   return hip_status(launch_prologue(D, P, (hipStream_t)args->stream));
@@ -230,7 +245,7 @@ int sage_attn_core(const sage_attn_args* args) {
   Dims D;
   int st = validate(args, &D, true);
   if (st != SAGE_OK) return st;
-  const Workspace w = make_workspace(D);
+  const Workspace w = fit_workspace(args, &D, args->workspace_bytes);
   if ((st = check_workspace(args, w)) != SAGE_OK) return st;
   Ptrs P = ptrs_for(args, w);
   P.lse = args->lse;
@@ -241,7 +256,7 @@ int sage_attn_fwd_ex(const sage_attn_args* args) {
   Dims D;
   int st = validate(args, &D, true);
   if (st != SAGE_OK) return st;
-  const Workspace w = make_workspace(D);
+  const Workspace w = fit_workspace(args, &D, args->workspace_bytes);
   if ((st = check_workspace(args, w)) != SAGE_OK) return st;
   return run_forward(D, args, w);
 }
@@ -278,13 +293,7 @@ int sage_attn_fwd_static(const sage_attn_args* args) {
   Dims D;
   int st = validate(args, &D, true);
   if (st != SAGE_OK) return st;
-  Workspace w = make_workspace(D);
-  if (w.total > (size_t)SAGE_STATIC_WORKSPACE_BYTES && args->kv_splits == 0 && D.splits > 1) {
-    // fits without the partial results of a split that is only there for speed, or with those of 512 workgroups
-    if (splits_by_choice(D)) D.splits = 1;
-    else D.splits = std::min(D.splits, (int)((512 + auto_tiles(D) - 1) / auto_tiles(D)));
-    w = make_workspace(D);
-  }
+  const Workspace w = fit_workspace(args, &D, (size_t)SAGE_STATIC_WORKSPACE_BYTES);
   if (w.total > (size_t)SAGE_STATIC_WORKSPACE_BYTES) return SAGE_ERR_WORKSPACE;   // beyond the built-in workspace
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return hip_status(hipErrorUnknown);
@@ -310,7 +319,7 @@ int sage_attn_kv_stats(const sage_attn_args* args, float* k_mean_out, float* v_s
   if (st != SAGE_OK) return st;
   if (!args->k || !args->v) return SAGE_ERR_INVALID_ARG;
   if (args->k_mean_in || (args->flags & (SAGE_FLAG_SMOOTH_V | SAGE_FLAG_NO_SMOOTH_K)) != 0) return SAGE_ERR_UNSUPPORTED;
-  const Workspace w = make_workspace(D);
+  const Workspace w = fit_workspace(args, &D, args->workspace_bytes);
   if ((st = check_workspace(args, w)) != SAGE_OK) return st;
   Ptrs P = make_ptrs(args->q, args->k, args->v, args->out, args->workspace, w);
   P.k_mean = k_mean_out;
@@ -330,7 +339,7 @@ int sage_attn_kv_stats_update(const sage_attn_args* args, double* k_sum_state, f
   if (args->cu_seqlens_q || args->k_mean_in || (args->flags & (SAGE_FLAG_SMOOTH_V | SAGE_FLAG_NO_SMOOTH_K)) != 0)
     return SAGE_ERR_UNSUPPORTED;
   if (n_before + (long long)D.Nk > MAX_TOKENS) return SAGE_ERR_UNSUPPORTED;
-  const Workspace w = make_workspace(D);
+  const Workspace w = fit_workspace(args, &D, args->workspace_bytes);
   if ((st = check_workspace(args, w)) != SAGE_OK) return st;
   Ptrs P = make_ptrs(args->q, args->k, args->v, args->out, args->workspace, w);
   P.k_mean = k_mean_out;
@@ -347,7 +356,7 @@ int sage_attn_quant(const sage_attn_args* args, const sage_quant_out* out) {
   if (!args->q || !args->k || !args->v) return SAGE_ERR_INVALID_ARG;
   if (args->cu_seqlens_q) return SAGE_ERR_UNSUPPORTED;   // the plain copy-out layouts are fixed-length
   if ((long long)D.B * D.H * D.nQb > 65535) return SAGE_ERR_UNSUPPORTED;  // grid limit of the copy-out kernels
-  const Workspace w = make_workspace(D);
+  const Workspace w = fit_workspace(args, &D, args->workspace_bytes);
   if ((st = check_workspace(args, w)) != SAGE_OK) return st;
   const Ptrs P = ptrs_for(args, w);
   D.causal = 0;      // (every value of Delta-S is handed out, also those no query under a causal mask would ask for)
@@ -364,7 +373,7 @@ int sage_attn_debug_qk(const sage_attn_args* args, int b, int h, int q_tile, int
   if (!out_acc || b < 0 || b >= D.B || h < 0 || h >= D.H || q_tile < 0 || q_tile >= D.nQb ||
       kv_block < 0 || kv_block >= D.nKb)
     return SAGE_ERR_INVALID_ARG;
-  const Workspace w = make_workspace(D);
+  const Workspace w = fit_workspace(args, &D, args->workspace_bytes);
   if ((st = check_workspace(args, w)) != SAGE_OK) return st;
   const Ptrs P = ptrs_for(args, w);
   return hip_status(launch_debug_qk(D, P, b, h, q_tile, kv_block, out_acc, (hipStream_t)args->stream));

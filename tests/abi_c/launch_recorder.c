@@ -61,7 +61,7 @@ static const struct { const char* name; size_t off; int pointer; } fields[] = {
     INT_FIELD(B), INT_FIELD(H), INT_FIELD(H_kv), INT_FIELD(N), INT_FIELD(d), INT_FIELD(causal), INT_FIELD(mode), INT_FIELD(dtype),
     INT_FIELD(flags), INT_FIELD(group_map), INT_FIELD(N_kv), INT_FIELD(layout), INT_FIELD(pv_format), INT_FIELD(kv_splits),
     PTR_FIELD(q), PTR_FIELD(k), PTR_FIELD(v), PTR_FIELD(out), PTR_FIELD(workspace), PTR_FIELD(cu_seqlens_q),
-    PTR_FIELD(cu_seqlens_k), PTR_FIELD(lse), PTR_FIELD(k_mean_in), PTR_FIELD(v_scale_in)};
+    PTR_FIELD(cu_seqlens_k), PTR_FIELD(lse), PTR_FIELD(k_mean_in), PTR_FIELD(v_scale_in), PTR_FIELD(workspace_bytes)};   /* (a size_t) */
 
 static int set_field(sage_attn_args* a, const char* name, long long value) {
   for (size_t i = 0; i < sizeof fields / sizeof fields[0]; ++i) {

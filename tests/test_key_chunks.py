@@ -1,4 +1,7 @@
 """Key chunks the library picks for launches of fewer than 256 tiles: whole rounds of workgroups (chunks_of_few_tiles in csrc/sage_api.hip)."""
+import math
+import random
+
 import pytest
 
 from launch_recorder import launches
@@ -45,15 +48,79 @@ def test_never_more_than_asked_for_or_than_the_keys_allow():
                     assert 1 <= S <= 64 and S <= max(1, blocks // 8), (d, N, tiles, blocks, S)
 
 
-# what fitted the built-in workspace with ceil(512 / tiles) chunks still does: in as many chunks as that, where it would not in more
-@pytest.mark.parametrize("kw", [dict(B=140, H=1, H_kv=1, N=1, N_kv=64 * 115, d=64), dict(B=1, H=65, H_kv=65, N=256, N_kv=64 * 90, d=64), dict(B=1, H=70, H_kv=70, N=256, N_kv=64 * 75, d=64),
-                                dict(B=1, H=56, H_kv=2, N=512, N_kv=64 * 76, d=64), dict(B=150, H=2, H_kv=1, N=1, N_kv=700, d=128)])
-def test_the_built_in_workspace_takes_what_it_took(kw):
+def _tiles(kw):
+    G = kw["H"] // kw["H_kv"]
+    return kw["B"] * (kw["H_kv"] if 2 <= G <= 8 and G * kw["N"] <= 128 else kw["H"] * -(-kw["N"] // 128))
+
+
+def _launched_chunks(entry, kw):
+    """(status, chunks per tile of the attention kernel that `entry` launches)"""
+    (status, seq), = launches([(entry, {**dict(d=128, dtype=1, mode=0), **kw})])
+    if status:
+        return status, None
+    if "k_merge_splits" not in [x.kernel for x in seq]:
+        return status, 1
+    grid, = [x.grid[0] for x in seq if x.kernel in ("k_attn_fwd", "k_attn_raw")]
+    return status, next(S for S in range(1, 65) if grid in (_tiles(kw) * S, 8 * -(-_tiles(kw) * S // 8)))
+
+
+# The built-in workspace: what does not fit it in the automatic chunks runs in ceil(512 / tiles) if those fit, in as many as do if not, from 256 tiles on in one
+@pytest.mark.parametrize("kw,auto,static", [(dict(B=1, H=65, H_kv=65, N=256, N_kv=64 * 90, d=64), 5, 4), (dict(B=1, H=130, H_kv=65, N=128, N_kv=64 * 85, d=64, mode=1), 5, 4),
+                                            (dict(B=40, H=1, H_kv=1, N=128, N_kv=64 * 77), 9, 7), (dict(B=1, H=32, H_kv=8, N=256, N_kv=64 * 72, d=256, mode=1), 8, 5),
+                                            (dict(B=2, H=32, H_kv=8, N=1, N_kv=64 * 105, d=256, mode=1), 13, 4), (dict(B=100, H=1, H_kv=1, N=1, N_kv=64 * 69, d=64), 5, 4),
+                                            (dict(B=100, H=2, H_kv=2, N=1, N_kv=64 * 33, d=64, mode=1), 4, 1), (dict(B=1, H=16, H_kv=8, N=2048, N_kv=11000, mode=1, causal=1), 3, 1)])
+def test_the_built_in_workspace(kw, auto, static):
     pa, _ = _lib()
-    a = _args(pa, **kw)
-    tiles = kw["B"] * (kw["H_kv"] if kw["N"] == 1 and kw["H"] > kw["H_kv"] else kw["H"] * ((kw["N"] + 127) // 128))
-    up = max(1, min(-(-512 // tiles), 64, -(-kw["N_kv"] // 64) // 8)) if tiles < 256 else 1
-    fitted = pa.sage_attn_workspace_bytes(_args(pa, kv_splits=up, **kw)) <= STATIC_BYTES
-    call = dict(dict(B=1, H=1, H_kv=1, d=128, dtype=1, mode=a.mode, layout=0, causal=0), **kw)
-    (status, _), = launches([("sage_attn_fwd_static", call)])
-    assert not fitted or status == 0, (kw, up)
+    need = lambda **x: pa.sage_attn_workspace_bytes(_args(pa, **{**kw, **x}))
+    assert need() > STATIC_BYTES >= need(kv_splits=static) and _chunks(**kw) == auto
+    assert static == (1 if _tiles(kw) >= 256 else -(-512 // _tiles(kw))) or need(kv_splits=static + 1) > STATIC_BYTES
+    assert _chunks(workspace_bytes=STATIC_BYTES, **kw) == static
+    assert _launched_chunks("sage_attn_fwd_static", kw) == (0, static)
+    assert _launched_chunks("sage_attn_fwd_ex", dict(kw, workspace_bytes=STATIC_BYTES)) == (0, static)
+    assert _launched_chunks("sage_attn_fwd_ex", kw) == (0, auto)
+    assert _launched_chunks("sage_attn_fwd_static", dict(kw, kv_splits=auto))[0] == -3            # (asked for: as many or none)
+
+
+def test_a_kept_workspace_serves_smaller_calls():
+    """... of fewer sequences, queries or keys: the partial results of their chunks, more per tile, may need more than the larger call's."""
+    pa, _ = _lib()
+    rng = random.Random(3)
+    calls, fewer = [], 0
+    for _ in range(4000):
+        Hkv = rng.choice([1, 2, 4, 8])
+        G = rng.choice([1, 1, 2, 4, 8, 16])
+        if Hkv * G * 2 > 128:
+            continue
+        draw = lambda hi: int(round(math.exp(rng.uniform(0, math.log(hi)))))
+        B, N, Nk = draw(256), draw(600), draw(20000)
+        Nk = max(N, Nk)
+        base = dict(H=Hkv * G, H_kv=Hkv, d=rng.choice([64, 128, 256]), mode=rng.choice([0, 1]), causal=rng.choice([0, 1]), flags=rng.choice([0, 0, 1]))
+        kept = pa.sage_attn_workspace_bytes(_args(pa, B=B, N=N, N_kv=Nk, **base))
+        n = rng.randint(1, N)
+        small = dict(base, B=rng.randint(max(1, B - 20), B), N=n, N_kv=rng.randint(max(n, Nk // 2), Nk))
+        calls.append(("sage_attn_fwd_ex", {**small, "dtype": 1, "workspace_bytes": kept}))
+        fewer += pa.sage_attn_workspace_bytes(_args(pa, **small)) > kept
+        if len(calls) % 3 == 0:
+            calls.append(("sage_attn_kv_stats", {**small, "flags": 0, "dtype": 1, "workspace_bytes": kept}))
+    assert fewer > 100
+    assert all(status == 0 for status, _ in launches(calls))
+
+
+@pytest.mark.parametrize("kw", [dict(B=27, H=32, H_kv=8, N=1, N_kv=8192), dict(B=3, H=16, H_kv=16, N=300, N_kv=9000, d=256), dict(B=40, H=16, H_kv=8, N=64, N_kv=300)])
+def test_too_small_a_workspace(kw):
+    """Chunk by chunk down to what one takes; a byte less is refused, and so is a chunk count that was asked for and does not fit."""
+    pa, _ = _lib()
+    need = lambda **x: pa.sage_attn_workspace_bytes(_args(pa, **{**kw, **x}))
+    one, auto = need(kv_splits=1), _chunks(**kw)
+    last = None
+    for S in range(-(-512 // _tiles(kw)) if auto > 1 else 1, 1, -1):
+        for extra, chunks in ((0, S), (-1, S - 1)):
+            size = need(kv_splits=S) + extra
+            if size >= need():
+                continue
+            assert _chunks(workspace_bytes=size, **kw) == chunks and _launched_chunks("sage_attn_fwd_ex", dict(kw, workspace_bytes=size)) == (0, chunks)
+            last = chunks
+    assert last in (1, None)
+    (status, _), (refused, none), (asked, _) = launches([("sage_attn_fwd_ex", {**dict(d=128, dtype=1, mode=0), **kw, **x}) for x in
+                                                        (dict(workspace_bytes=one), dict(workspace_bytes=one - 1), dict(workspace_bytes=need(kv_splits=2) - 1, kv_splits=2))])
+    assert status == 0 and refused == -3 and not none and (asked == -3 or need(kv_splits=2) == one)
