@@ -17,7 +17,9 @@ using namespace sage;
 // 58.2 / 46.8, 120 207 / 168, 150 253 / 220, 232 338 / 326; of 64 channels 96 of 12000 77.9 / 63.9; of 256 88 of 7000 154 / 118.
 // Where that leaves much of the chip idle, two or three full rounds that save an eighth of its time (a sixth where a chunk has 15 key
 // blocks or fewer): 140 tiles, three / seven chunks 217 / 197, 172, two / five 296 / 258, 210, two / seven 313 / 291, but 146 of 5000 keys, three /
-// seven 65.9 / 71.0, and 110, four / nine / thirteen, 165 / 160 / 171 and of 256 channels 147 / 155 / 173.
+// seven 65.9 / 71.0, and 110, four / nine / thirteen, 165 / 160 / 171 and of 256 channels 147 / 155 / 173.  Counted in half rounds, since the keys may allow
+// fewer chunks than fill two: 190 tiles of 32 blocks, two / four 43.1 / 39.1, but 200 - past three halves - 42.9 / 46.7, of 256 channels 97.6 / 106.  (Three
+// rounds cut short that way are none: 205 to 213 tiles of 48 to 55 blocks, two / six chunks 0.96 to 1.10.)
 // Attention alone: packed tiles of 80 columns, 24 of 20000 keys 44.5 / 38.2, of 256 channels 71.0 / 55.4, 90 of 8000 54.8 / 48.6; 256 channels, 144
 // of 9000 127 / 104, 45 of 30000 154 / 114, 200 of 6000 118 / 106, 180 of 3800 88.8 / 76.9, causal 61.4 / 63.3.
 // Other tiles of 128 (64) channels, of which three (four) workgroups fit a CU: floor where that is 480 workgroups and more (45 of 30000 91.0 /
@@ -28,11 +30,12 @@ using namespace sage;
 long long chunks_of_few_tiles(long long tiles, long long nKb, int d, bool short_queries, bool packed_batch) {
   const long long up = (512 + tiles - 1) / tiles, down = 512 / tiles;
   if (short_queries) {
-    long long S = down, rounds = 1;
+    long long S = down, halves = 2;
     for (long long r = 2; r <= 3 && 512 * r / tiles < 9; ++r) {
-      const long long s = 512 * r / tiles;
+      const long long s = std::min(512 * r / tiles, std::max(1LL, nKb / 8)), h = (s * tiles + 255) / 256;
+      if (r == 3 && s < 512 * r / tiles) break;
       const int part = nKb > 15 * s ? 8 : 6;
-      if (r * S * part <= rounds * s * (part - 1)) { S = s; rounds = r; }
+      if (h * S * part <= halves * s * (part - 1)) { S = s; halves = h; }
     }
     return S;
   }
