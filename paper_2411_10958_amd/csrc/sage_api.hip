@@ -21,13 +21,16 @@ using namespace sage;
 // fewer chunks than fill two: 190 tiles of 32 blocks, two / four 43.1 / 39.1, but 200 - past three halves - 42.9 / 46.7, of 256 channels 97.6 / 106.  (Three
 // rounds cut short that way are none: 205 to 213 tiles of 48 to 55 blocks, two / six chunks 0.96 to 1.10.)
 // Attention alone: packed tiles of 80 columns, 24 of 20000 keys 44.5 / 38.2, of 256 channels 71.0 / 55.4, 90 of 8000 54.8 / 48.6; 256 channels, 144
-// of 9000 127 / 104, 45 of 30000 154 / 114, 200 of 6000 118 / 106, 180 of 3800 88.8 / 76.9, causal 61.4 / 63.3.
+// of 9000 127 / 104, 45 of 30000 154 / 114, 200 of 6000 118 / 106.  Under a causal mask over as many keys as queries, most of 256-wide heads' chunks are
+// shorter than the longest and end where another can begin; with few blocks in each, three then beat two: 12 heads of 2000 tokens 46.2 / 52.1, 8 of 3000
+// 48.7 / 55.7, 5 of 4500 66.9 / 70.9, 12 of 2000 on 2500 keys 54.6 / 58.5, packed 3 x 3 of up to 2908 50.6 / 58.2; up to 210 tiles 0.87 to 1.03, mean 0.94,
+// with more 0.90 to 1.13, 1.03 (8 heads of 3800 61.1 / 68.9, but 10 of 3000 69.3 / 61.9); 4 of 6000 90.8 / 90.0, 2 of 12000 177 / 159, on twice the keys 0.99 to 1.16.
 // Other tiles of 128 (64) channels, of which three (four) workgroups fit a CU: floor where that is 480 workgroups and more (45 of 30000 91.0 /
 // 81.5, 30 of 10000 35.4 / 33.2, 100 of 4000 39.7 / 38.4), else as many as fit the chip while a chunk keeps more than 15 key blocks (144 of 9000, four
 // / five chunks 74.9 / 70.1, of 20000 142 / 126; 64 channels, four / seven 64.2 / 55.7 and 117 / 97; with fewer the partial results cost
 // the gain: 180 of 3800, three / four 41.3 / 42.7).  A packed batch, whose tiles are counted by its longest sequence, has fewer than that and keeps
 // ceil (3 of up to 4736 tokens, 222 tiles, three / four 60.0 / 60.3).
-long long chunks_of_few_tiles(long long tiles, long long nKb, int d, bool short_queries, bool packed_batch) {
+long long chunks_of_few_tiles(long long tiles, long long nKb, int d, bool short_queries, bool packed_batch, bool triangle) {
   const long long up = (512 + tiles - 1) / tiles, down = 512 / tiles;
   if (short_queries) {
     long long S = down, halves = 2;
@@ -39,7 +42,8 @@ long long chunks_of_few_tiles(long long tiles, long long nKb, int d, bool short_
     }
     return S;
   }
-  if (d == 256 || (down >= 3 && down * tiles >= 480)) return down;
+  if (d == 256) return triangle && down == 2 && nKb <= 72 && (packed_batch || tiles <= 210) ? up : down;
+  if (down >= 3 && down * tiles >= 480) return down;
   return packed_batch ? up : std::max(up, std::min((d == 64 ? 1024 : 768) / tiles, (nKb - 1) / 15));
 }
 
@@ -112,7 +116,8 @@ int validate(const sage_attn_args* a, Dims* D, bool need_io) {
     const int G = a->H / a->H_kv;
     D->pack = G >= 2 && G <= PACK_G && (long long)G * a->N <= BQ;     // (a->N: the longest sequence's queries)
     const long long tiles = D->pack ? (long long)a->B * a->H_kv : (long long)a->B * a->H * nQb;
-    long long S = a->kv_splits > 1 ? a->kv_splits : (tiles < 256 ? chunks_of_few_tiles(tiles, nKb, a->d, D->pack || (long long)G * a->N <= 32, a->cu_seqlens_q != nullptr) : 1);
+    long long S = a->kv_splits > 1 ? a->kv_splits : (tiles < 256 ? chunks_of_few_tiles(tiles, nKb, a->d, D->pack || (long long)G * a->N <= 32, a->cu_seqlens_q != nullptr,
+                                                                                                    a->causal && 5LL * a->N >= 4LL * Nk) : 1);
     if (a->kv_splits == 0 && !D->pack && tiles >= 256) {
       // One or two workgroups per CU, of the three that fit: a lone wavefront issues far fewer vector instructions than
       // two or three that share the SIMD.  Three chunks per tile while they make four workgroups per CU at most, two while they

@@ -41,6 +41,12 @@ def test_short_queries_on_few_keys(tiles, blocks, chunks):
         assert _chunks(B=tiles, H=4, H_kv=1, N=1, N_kv=64 * blocks, d=d) == chunks
 
 
+@pytest.mark.parametrize("H,N,Nk,causal,packed,chunks", [(12, 2000, 2000, 1, 0, 3), (12, 2000, 2000, 0, 0, 2), (12, 2000, 2500, 1, 0, 3), (12, 2000, 2501, 1, 0, 2), (5, 4608, 4608, 1, 0, 3),
+                                                         (5, 4609, 4609, 1, 0, 2), (6, 4480, 4480, 1, 0, 3), (8, 3800, 3800, 1, 0, 2), (8, 3800, 3800, 1, 1, 3), (8, 3800, 3800, 0, 1, 2), (9, 2000, 2000, 1, 0, 3)])
+def test_256_wide_heads_under_a_causal_mask(H, N, Nk, causal, packed, chunks):
+    assert _chunks(B=1, H=H, H_kv=H, N=N, N_kv=Nk, d=256, causal=causal, **(dict(layout=1, cu_seqlens_q=4096) if packed else {})) == chunks
+
+
 def test_a_packed_batch_is_counted_by_its_longest_sequence():
     for d, tiles, chunks in ((128, 144, 4), (64, 144, 4), (128, 45, 11), (256, 144, 3)):
         assert _chunks(B=1, H=tiles, H_kv=tiles, N=128, N_kv=64 * 300, d=d, layout=1, cu_seqlens_q=4096) == chunks
