@@ -26,9 +26,13 @@ using namespace sage;
 // 48.7 / 55.7, 5 of 4500 66.9 / 70.9, 12 of 2000 on 2500 keys 54.6 / 58.5, packed 3 x 3 of up to 2908 50.6 / 58.2; up to 210 tiles 0.87 to 1.03, mean 0.94,
 // with more 0.90 to 1.13, 1.03 (8 heads of 3800 61.1 / 68.9, but 10 of 3000 69.3 / 61.9); 4 of 6000 90.8 / 90.0, 2 of 12000 177 / 159, on twice the keys 0.99 to 1.16.
 // Other tiles of 128 (64) channels, of which three (four) workgroups fit a CU: floor where that is 480 workgroups and more (45 of 30000 91.0 /
-// 81.5, 30 of 10000 35.4 / 33.2, 100 of 4000 39.7 / 38.4), else as many as fit the chip while a chunk keeps more than 15 key blocks (144 of 9000, four
+// 81.5, 30 of 10000 35.4 / 33.2, 100 of 4000 39.7 / 38.4, 164 of 9000 79.7 / 77.6, of 25600 206 / 217 with calls alike; 170 of 2600 of 64 channels
+// 29.7 / 27.4), but for three chunks of many blocks of 64 channels (164 tiles, six / three, of 63 blocks 36.6 / 34.0, of 100 46.4 / 47.0, of 300 102 / 113,
+// which four had as 111); else as many as fit the chip while a chunk keeps more than 15 key blocks (144 of 9000, four
 // / five chunks 74.9 / 70.1, of 20000 142 / 126; 64 channels, four / seven 64.2 / 55.7 and 117 / 97; with fewer the partial results cost
-// the gain: 180 of 3800, three / four 41.3 / 42.7).  A packed batch, whose tiles are counted by its longest sequence, has fewer than that and keeps
+// the gain: 180 of 3800, three / four 41.3 / 42.7).  Of 64 channels, one chunk more than ceil that puts a fourth workgroup on some CUs is no gain (200 tiles
+// of 63 blocks, three / four 42.8 / 43.1, 154 of 82, four / five 41.7 / 44.1) unless it fills them and the keys are long (240, three / four, of 141 blocks
+// 75.9 / 77.4, of 200 102.6 / 101.2, of 600 314 / 289).  A packed batch, whose tiles are counted by its longest sequence, has fewer than that and keeps
 // ceil (3 of up to 4736 tokens, 222 tiles, three / four 60.0 / 60.3).
 long long chunks_of_few_tiles(long long tiles, long long nKb, int d, bool short_queries, bool packed_batch, bool triangle) {
   const long long up = (512 + tiles - 1) / tiles, down = 512 / tiles;
@@ -43,8 +47,12 @@ long long chunks_of_few_tiles(long long tiles, long long nKb, int d, bool short_
     return S;
   }
   if (d == 256) return triangle && down == 2 && nKb <= 72 && (packed_batch || tiles <= 210) ? up : down;
-  if (down >= 3 && down * tiles >= 480) return down;
-  return packed_batch ? up : std::max(up, std::min((d == 64 ? 1024 : 768) / tiles, (nKb - 1) / 15));
+  if (down * tiles >= 480 && (down > 3 || (down == 3 && (d == 128 || packed_batch || nKb <= 120)))) return down;
+  if (packed_batch) return up;
+  const long long full = (d == 64 ? 1024 : 768) / tiles;
+  long long fill = std::min(full, (nKb - 1) / 15);
+  if (d == 64 && fill == up + 1 && fill * tiles > 768 && (fill < full || nKb <= 160)) fill = up;
+  return std::max(up, fill);
 }
 
 int validate(const sage_attn_args* a, Dims* D, bool need_io) {

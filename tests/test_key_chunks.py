@@ -34,11 +34,18 @@ def test_longer_queries_fill_the_chip(d, tiles, blocks, chunks):
     assert _chunks(B=1, H=tiles, H_kv=tiles, N=128, N_kv=64 * blocks, d=d) == chunks
 
 
-# where the keys of short queries allow fewer chunks than fill two rounds
+# where the general rule is not the faster one: the keys of short queries allow fewer chunks than fill two rounds; 64-wide heads between three and four workgroups
+# per CU, and in three long chunks; 256-wide heads under a causal mask over about as many keys as queries
 @pytest.mark.parametrize("tiles,blocks,chunks", [(171, 40, 5), (171, 39, 4), (192, 32, 4), (193, 39, 2), (204, 39, 2), (204, 40, 5), (192, 31, 2), (172, 24, 2), (205, 55, 2), (213, 55, 2), (205, 106, 7)])
 def test_short_queries_on_few_keys(tiles, blocks, chunks):
     for d in (64, 128, 256):
         assert _chunks(B=tiles, H=4, H_kv=1, N=1, N_kv=64 * blocks, d=d) == chunks
+
+
+@pytest.mark.parametrize("tiles,blocks,chunks", [(154, 90, 4), (154, 91, 6), (160, 120, 3), (160, 121, 6), (170, 121, 6), (180, 61, 4), (192, 75, 4), (193, 75, 3), (204, 75, 3), (204, 76, 5), (205, 160, 3),
+                                                (205, 161, 4), (255, 160, 3), (255, 161, 4)])
+def test_64_wide_heads_fill_a_fourth_workgroup_per_CU_or_none(tiles, blocks, chunks):
+    assert _chunks(B=1, H=tiles, H_kv=tiles, N=128, N_kv=64 * blocks, d=64) == chunks
 
 
 @pytest.mark.parametrize("H,N,Nk,causal,packed,chunks", [(12, 2000, 2000, 1, 0, 3), (12, 2000, 2000, 0, 0, 2), (12, 2000, 2500, 1, 0, 3), (12, 2000, 2501, 1, 0, 2), (5, 4608, 4608, 1, 0, 3),
