@@ -28,6 +28,8 @@ _PV_FORMATS = {"e4m3": 0, "e5m2": 1, "int8": 2, 0: 0, 1: 1, 2: 2}
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+# The current stream's handle without a Stream object (2.0 -> 0.1 us a call).  The name is private to torch: a build without it makes the object.
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 class SageError(RuntimeError):
@@ -160,8 +162,8 @@ def make_args(q, k, v, out=None, causal=False, sm_scale=0.0, mode="int4_fp8", wo
         km_ptr, vs_ptr = km.data_ptr(), vs.data_ptr()
     if stream is not None:
         raw_stream = stream.cuda_stream
-    else:                          # (torch.cuda.current_stream(device).cuda_stream without the Stream object: 2.0 -> 0.1 us)
-        raw_stream = torch._C._cuda_getCurrentRawStream(q.get_device())
+    else:
+        raw_stream = _current_raw_stream(q.get_device())
     # the fields in their order: one call instead of an attribute at a time (the whole of this function 5.2 -> 2.0 us)
     return sage_attn_args(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr() if out is not None else 0,
                           B, H, Hkv, N, d, int(bool(causal)), float(sm_scale), _MODES[mode], _dtype_code(q), flags,

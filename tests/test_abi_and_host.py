@@ -168,3 +168,17 @@ def test_header_is_plain_c(tmp_path):
     res = subprocess.run(["gcc", "-std=c11", "-Wall", "-Werror", "-pedantic", "-fsyntax-only", "-I", os.path.join(ROOT, "include"),
                           str(src)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert res.returncode == 0, res.stdout
+
+
+def test_binding_without_torchs_private_stream_getter(monkeypatch):
+    import importlib.util
+    import types
+
+    import torch
+    from paper_2411_10958_amd import binding
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda index: types.SimpleNamespace(cuda_stream=4096 + index))
+    spec = importlib.util.spec_from_file_location("binding_of_another_torch", binding.__file__)
+    other = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(other)
+    assert other._current_raw_stream(3) == 4099
