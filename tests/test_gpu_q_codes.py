@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from oracle import sage_oracle as so
-from test_gpu_attention_from_raw_kv import _inputs
+from test_gpu_attention_from_raw_kv import _both, _inputs
 from test_gpu_parity import _pa
 from test_gpu_prologue_fuzz import GMAPS
 
@@ -28,6 +28,24 @@ def test_q_codes(d, dtype, group_map, N, mode):
         assert np.array_equal(got["q_scale"][0, h].cpu().numpy(), pro["q_scale"][pro["q_groups"][::1 if group_map == "token" else 2]])
         if mode == "int4_fp8":
             assert np.array_equal(got["q_mean"][0, h].cpu().numpy(), pro["qbar"])
+
+
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+@pytest.mark.parametrize("N", [1, 2, 7, 9, 15, 17, 32, 33, 127, 128, 131])
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "fp16"), (256, "bf16")])
+def test_row_constants(d, dtype, N, mode):
+    """Where all keys are alike, smoothing leaves zeros: every score is 0, and the log-sum-exp of a row is ln N_kv plus its row constant, sm_scale <q, k>.
+    The row constant is rounded to FP32 once, from float64 and an FP32 kappa, and then goes with a base-2 logarithm (20 at most, its offset included, of an
+    instruction good to 2^-22) and 448 N_kv, a sum in FP32 of 70 terms, through a sum and a product in FP32: errors of 2^-24 of kappa <q, k> / ln 2 and
+    20 each, together below 2^-20 of the two."""
+    pa = _pa()
+    print(f"row constants: d={d} {dtype} N={N} {mode}", flush=True)
+    q, k, v = _inputs(1, N, 70, d, 3, 1, dtype, "HND", seed=N)
+    k = k[:, :, :1].expand_as(k).contiguous()
+    (_, whole), (_, general) = _both(pa, q, k, v, pa.make_args(q, k, v, mode=mode))         # (the whole call of few queries quantizes Q elsewhere)
+    dot = (q[0].double() @ k[0, 0, 0].double()).flatten().cpu().numpy() / np.sqrt(d)
+    for lse in (whole, general):
+        assert (np.abs(lse.cpu().numpy() - (np.log(70.0) + dot)) <= 2.0**-20 * (np.abs(dot) + 20.0)).all()
 
 
 @pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
