@@ -510,13 +510,14 @@ __device__ __forceinline__ void quant_q8_block(QuantQLds<D, false>& lds, const Q
 //  - loading and the exact column sums of the block mean use a coalesced map (a thread owns 8 channels of BQ*D/2048
 //    rows), and the raw 16-bit rows are parked in LDS;
 //  - quantization uses the map the codes are consumed in, a pass at a time: a lane owns 32 consecutive channels of a row, one MFMA lane's
-//    payload, D / 32 lanes a row, so the maximum of a scale group is a few lane exchanges away and the codes leave
-//    through one FP32->FP6 conversion instead of per-element table look-ups and 6-bit shifts.
+//    payload, or 64 (d = 256), so the maximum of a scale group is two lane exchanges away and the codes leave
+//    through one FP32->FP6 conversion instead of per-element table look-ups and 6-bit shifts.  (32 channels a lane at d = 256 too, in four passes of 8 rows:
+//    codes in runs of 64 and 128 bytes, 16 heads of 13526 tokens, four sequences, token-major, 159 us, with 64 146, from an image in LDS 159.)
 // LDS rows are kept as 16-byte chunks in an order by the row's number, which spreads the chunk that a pass reads of every row over all
 // banks.  LDS: the raw rows (32 KB at d = 128) and one row of column sums per wavefront (the row groups of a wavefront are summed by
 // lane exchanges first) - 37 KB, so that four workgroups share a CU and their loads, arithmetic and stores overlap.
-// With the passes, the rounding in the conversion and no code image in LDS: 2 heads of 256 tokens (with the statistics) 5.05 -> 4.45 us, 64
-// heads of 512 9.4 -> 8.8, 16 of 8192 of 256 channels 32.4 -> 30.7, 128 of 4096 45 (185 MB: 4.1 TB/s): loads and parking alone 29, column
+// With the passes and no code image in LDS: 2 heads of 256 tokens (with the statistics) 5.05 -> 4.45 us, 64
+// heads of 512 9.4 -> 8.8, 16 of 8192 of 256 channels 29.2 -> 28.4, 128 of 4096 42 to 45 (185 MB: 4.1 to 4.4 TB/s): loads and parking alone 29, column
 // sums 4, quantization 6, stores 4.  (Rows read a second time instead of parked, five workgroups per CU: 48.)
 template <int D> struct QuantQLds<D, true> {
   uint4 raw[BQ * (D / 8)];           // the raw rows
@@ -533,7 +534,8 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const QB
   unsigned char* __restrict__ q_digits = a.q_digits;
   const int smooth_q = a.smooth_q;
   constexpr int NCG = D / 8, NRG = 256 / NCG, RPT = BQ / NRG;   // load map: RPT rows x 8 channels
-  constexpr int NPC = D / 32, RP = 64 / NPC, NPASS = 32 / RP;    // quantization map: RP rows of a wavefront's 32 in a pass
+  constexpr int CPL = D == 256 ? 64 : 32;                        // quantization map: channels per lane, lanes per row, and RP rows of a
+  constexpr int NPC = D / CPL, RP = 64 / NPC, NPASS = 32 / RP;   // wavefront's 32 in a pass
   constexpr int QMAX = 7;
   auto& s_raw = lds.raw; auto& s_sum = lds.sum; auto& s_mean = lds.mean; auto& s_kbar = lds.kbar; auto& s_bmax = lds.bmax;
   auto chunk_at = [](int r, int c) { return r * NCG + (c ^ (D == 64 ? (r >> 1) & 7 : r & 15)); };
@@ -588,18 +590,18 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const QB
     q_mean[(bh * nQb + qb) * D + t] = m;
   }
   __syncthreads();
-  const int lane = t & 63, w = t >> 6, rr = lane % RP, piece = lane / RP, c0 = 32 * piece;
+  const int lane = t & 63, w = t >> 6, rr = lane % RP, piece = lane / RP, c0 = CPL * piece;
   const bool odd = lds.odd_mean != 0;
   auto row_of = [&](int p) { return 32 * w + RP * p + rr; };
   // kappa * <q_r, mean(K)> per row (the log-sum-exp output only): float64, runs of D / 4 channels one after the other, then neighbours in
-  // pairs.  A lane's 32 channels are one run (d = 128) or two (64); at d = 256 a run is two lanes' and this is done by itself, below.
-  constexpr int RUN = D / 4, RUNS = RUN <= 32 ? 32 / RUN : 0;
-  // the lane's 32 channels of row r, centred (a row past the end stays zero)
-  auto load_row = [&](int r, float (&x)[32], double (&run)[RUNS ? RUNS : 1], bool dots) {
+  // pairs.  A lane's channels are one run, or two (d = 64).
+  constexpr int RUN = D / 4, RUNS = CPL / RUN;
+  // the lane's channels of row r, centred (a row past the end stays zero)
+  auto load_row = [&](int r, float (&x)[CPL], double (&run)[RUNS], bool dots) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      unpack8<BF16>(s_raw[chunk_at(r, 4 * piece + j)], &x[8 * j]);
-      if (RUNS && dots) {
+    for (int j = 0; j < CPL / 8; ++j) {
+      unpack8<BF16>(s_raw[chunk_at(r, CPL / 8 * piece + j)], &x[8 * j]);
+      if (dots) {
         const float4 b0 = *reinterpret_cast<const float4*>(&s_kbar[c0 + 8 * j]);
         const float4 b1 = *reinterpret_cast<const float4*>(&s_kbar[c0 + 8 * j + 4]);
         const float kb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
@@ -616,44 +618,22 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const QB
     }
     if (valid < BQ) {
 #pragma unroll
-      for (int e = 0; e < 32; ++e) x[e] = r < valid ? x[e] : 0.0f;
+      for (int e = 0; e < CPL; ++e) x[e] = r < valid ? x[e] : 0.0f;
     }
   };
-  auto row_max = [&](const float (&x)[32]) {
+  auto row_max = [&](const float (&x)[CPL]) {
     float mx = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 32; ++e) mx = fmaxf(mx, fabsf(x[e]));
-    if constexpr (NPC == 8) mx = butterfly_max<8>(mx);
-    if constexpr (NPC >= 4) mx = butterfly_max<16>(mx);
+    for (int e = 0; e < CPL; ++e) mx = fmaxf(mx, fabsf(x[e]));
+    if constexpr (NPC == 4) mx = butterfly_max<16>(mx);
     return butterfly_max<32>(mx);
   };
-  if (!RUNS && q_corr) {
-    constexpr int CPL = RUN;
-    const int pair = t >> 2, c4 = t & 3;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int r = 2 * pair + i;
-      double dot = 0.0;
-#pragma unroll
-      for (int j = 0; j < CPL / 8; ++j) {
-        float x8[8];
-        unpack8<BF16>(s_raw[chunk_at(r, c4 * (CPL / 8) + j)], x8);
-        const float4 b0 = *reinterpret_cast<const float4*>(&s_kbar[CPL * c4 + 8 * j]);
-        const float4 b1 = *reinterpret_cast<const float4*>(&s_kbar[CPL * c4 + 8 * j + 4]);
-        const float kb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dot += (double)x8[e] * (double)kb[e];
-      }
-      dot = butterfly_sum<2>(butterfly_sum<1>(dot));
-      if (c4 == 0 && r < valid) q_corr[(bh * nQb + qb) * BQ + r] = (float)((double)kappa * dot);
-    }
-  }
   float block_max = 0.0f;
   if (block_groups) {       // per-block granularity: one scale for the whole 128-query block
 #pragma unroll 1
     for (int p = 0; p < NPASS; ++p) {
-      float x[32];
-      double none[RUNS ? RUNS : 1];
+      float x[CPL];
+      double none[RUNS];
       load_row(row_of(p), x, none, false);
       block_max = fmaxf(block_max, row_max(x));
     }
@@ -666,13 +646,13 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const QB
 #pragma unroll
   for (int p = 0; p < NPASS; ++p) {
     const int r = row_of(p);
-    float x[32];
-    double run[RUNS ? RUNS : 1];
+    float x[CPL];
+    double run[RUNS];
     load_row(r, x, run, q_corr != nullptr);
-    if (RUNS && q_corr) {
+    if (q_corr) {
       double dot = run[0];
       if constexpr (RUNS == 2) dot = run[0] + run[1];
-      if constexpr (NPC >= 4) dot = butterfly_sum<16>(dot);
+      if constexpr (NPC == 4) dot = butterfly_sum<16>(dot);
       dot = butterfly_sum<32>(dot);
       if (piece == 0 && r < valid) q_corr[(bh * nQb + qb) * BQ + r] = (float)((double)kappa * dot);
     }
@@ -685,13 +665,16 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const QB
     if (stats_only) continue;            // per-tensor scales, first pass: only the block maxima are wanted
     CodeScale qs = code_scale(delta);
     qs.fast = qs.fast && !odd;           // (the exact form makes 0 of NaN)
-    Codes32 cd;
-    code_group<32, QMAX>(x, delta, qs, [&](int e, float c) { cd.set(e, c); });
-    const v6u pw = cd.pack();
-    int lane_m, e0;
-    uint8_t* const op = slab + q_op6(r, c0, D, &lane_m, &e0);
-    *reinterpret_cast<uint4*>(op + 16 * lane_m) = make_uint4(pw[0], pw[1], pw[2], pw[3]);
-    *reinterpret_cast<uint2*>(op + 1024 + 8 * lane_m) = make_uint2(pw[4], pw[5]);
+#pragma unroll
+    for (int pl = 0; pl < CPL / 32; ++pl) {                    // (one MFMA lane's payload, or the two lane halves of one operand)
+      Codes32 cd;
+      code_group<32, QMAX>(&x[32 * pl], delta, qs, [&](int e, float c) { cd.set(e, c); });
+      const v6u pw = cd.pack();
+      int lane_m, e0;
+      uint8_t* const op = slab + q_op6(r, c0 + 32 * pl, D, &lane_m, &e0);
+      *reinterpret_cast<uint4*>(op + 16 * lane_m) = make_uint4(pw[0], pw[1], pw[2], pw[3]);
+      *reinterpret_cast<uint2*>(op + 1024 + 8 * lane_m) = make_uint2(pw[4], pw[5]);
+    }
   }
   if (stats_only) return;
   // the block mean cut into digits for the Delta-S product: by one wavefront, where nobody waits for it any more (done in
