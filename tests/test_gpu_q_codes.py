@@ -31,6 +31,13 @@ def test_q_codes(d, dtype, group_map, N, mode):
 
 
 @pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
+@pytest.mark.parametrize("d,dtype,group_map", [(64, "bf16", "tensor"), (128, "fp16", "tensor"), (256, "bf16", "tensor"), (128, "bf16", "block"), (256, "fp16", "token"), (64, "fp16", "token")])
+@pytest.mark.parametrize("N", [1, 16, 129, 300])
+def test_q_codes_of_other_groups(d, dtype, group_map, N, mode):
+    test_q_codes(d, dtype, group_map, N, mode)
+
+
+@pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
 @pytest.mark.parametrize("N", [1, 2, 7, 9, 15, 17, 32, 33, 127, 128, 131])
 @pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "fp16"), (256, "bf16")])
 def test_row_constants(d, dtype, N, mode):
