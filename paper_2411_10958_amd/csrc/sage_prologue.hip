@@ -369,6 +369,7 @@ struct QuantQ {
   float* q_dscale;
   const double* k_sum;       // not null: mean(K) is not there yet, these are the partial sums of its chunks
   int nchunk, smooth_k;
+  int narrow;                // 8-bit, 64 channels: the NARROW map of quant_q8_block
 };
 // mean(K) of one channel, from k_mean or from the partial sums
 template <int D>
@@ -405,28 +406,33 @@ __device__ __forceinline__ QBlock q_block(const QuantQ& a, unsigned qb, unsigned
 // Against codes laid out in LDS, rows as 8 channels of 4 to 8 rows per thread and a byte extract per code: 32 heads of 8192 tokens 33 -> 25 us (100 MB:
 // 4.0 TB/s).  Bound: the loads in flight - a workgroup loads, computes and stores in turn, and a chip's worth of them starts together
 // (walking several blocks with the next one's rows requested ahead gained nothing: the 4-bit form 45 -> 51 us on 4096 blocks).
+// NARROW, for 64-wide heads of long token-major rows, whose 128 bytes lie apart: 8 channels a lane and 8 rows a pass in four, so that every load takes whole
+// runs (4 sequences of 64 heads of 2667 tokens 38.0 -> 31.7 us, of 17870 231 -> 215; the code image in LDS had 33.9 and 216).  Its four short chains cost
+// small calls more than that is worth (two sequences of 64 heads of 300 tokens, 384 blocks, 5.3 -> 6.0, of 900, 1024 blocks, 8.2 -> 7.3).
 template <int D, bool INT4> struct QuantQLds {               // (8-bit mode)
   alignas(16) float kbar[D];         // mean(K) of the KV head (log-sum-exp output only)
   float bmax[4];
 };
-template <bool BF16, int D>
+template <bool BF16, int D, bool NARROW>
 __device__ __forceinline__ void quant_q8_block(QuantQLds<D, false>& lds, const QBlock bl, const QuantQ& a) {
   SAGE_QUANT_Q_ARGS;
-  constexpr int NM = D / 64;                    // pieces of a row per lane
+  constexpr int NM = NARROW ? 1 : D / 64, NL = NARROW ? 1 : 2;           // pieces of a row per lane, loads of a piece
+  constexpr int NP = NARROW ? 4 : 2, RP = 32 / NP, PC = 8 * NL;          // passes, rows of a pass, channels of a piece
   constexpr int QMAX = 127;
-  const int t = threadIdx.x, w = t >> 6, r16 = t & 15, k4 = (t >> 4) & 3;
+  const int t = threadIdx.x, w = t >> 6, rr = NARROW ? (t >> 3) & 7 : t & 15, kc = NARROW ? t & 7 : (t >> 4) & 3;
+  static_assert(!NARROW || D == 64, "eight lanes a row");
   const int qb = bl.qb, n0 = bl.n0, valid = bl.valid;
   const size_t bh = bl.bh, hbase = bl.hbase;
   if (valid <= 0) return;                     // a block past the end of a shorter sequence
-  uint4 raw[2][NM][2];
+  uint4 raw[NP][NM][NL];
 #pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    const int r = 32 * w + 16 * p + r16;
-    const unsigned short* src = Q + row_offset(qm, hbase, n0 + min(r, valid - 1)) + 16 * k4;
+  for (int p = 0; p < NP; ++p) {
+    const int r = 32 * w + RP * p + rr;
+    const unsigned short* src = Q + row_offset(qm, hbase, n0 + min(r, valid - 1)) + PC * kc;
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) raw[p][m][i] = nt_load16(src + 64 * m + 8 * i);
+      for (int i = 0; i < NL; ++i) raw[p][m][i] = nt_load16(src + 64 * m + 8 * i);
     }
   }
   if (q_corr) {
@@ -439,68 +445,74 @@ __device__ __forceinline__ void quant_q8_block(QuantQLds<D, false>& lds, const Q
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < NL; ++i) {
         float x[8];
         unpack8<BF16>(raw[p][m][i], x);
 #pragma unroll
         for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(x[e]));
       }
     }
-    mx = butterfly_max<32>(butterfly_max<16>(mx));
-    return 32 * w + 16 * p + r16 < valid ? mx : 0.0f;      // (the rows past the end are copies of the last one: their codes are 0)
+    if constexpr (NARROW) mx = group_max<8>(mx);
+    else mx = butterfly_max<32>(butterfly_max<16>(mx));
+    return 32 * w + RP * p + rr < valid ? mx : 0.0f;      // (the rows past the end are copies of the last one: their codes are 0)
   };
   float block_max = 0.0f;
   if (block_groups) {       // per-block granularity: one scale for the whole 128-query block
-    block_max = group_max<16>(fmaxf(row_max(0), row_max(1)));
+#pragma unroll
+    for (int p = 0; p < NP; ++p) block_max = fmaxf(block_max, row_max(p));
+    block_max = wave_max(block_max);
     if ((t & 63) == 0) lds.bmax[w] = block_max;
     __syncthreads();
     block_max = fmaxf(fmaxf(lds.bmax[0], lds.bmax[1]), fmaxf(lds.bmax[2], lds.bmax[3]));
   }
-  uint4* const slab = reinterpret_cast<uint4*>(q_codes + (bh * nQb + qb) * q_slab_bytes(D, false));
+  int8_t* const slab = q_codes + (bh * nQb + qb) * q_slab_bytes(D, false);
 #pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    const int r = 32 * w + 16 * p + r16;
+  for (int p = 0; p < NP; ++p) {
+    const int r = 32 * w + RP * p + rr;
     if (q_corr) {
       // kappa * <q_r, mean(K)>, the row constant that smoothing K drops from the scores (Sec. 3.1; needed only for the log-sum-exp
       // output): float64 products and sums, one rounding; runs of 8 channels, then neighbours in pairs
       double part[NM];
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
-        double run[2];
+        double run[NL];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < NL; ++i) {
           float x[8];
           unpack8<BF16>(raw[p][m][i], x);
           run[i] = 0.0;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) run[i] += (double)x[e] * (double)lds.kbar[16 * k4 + 64 * m + 8 * i + e];
+          for (int e = 0; e < 8; ++e) run[i] += (double)x[e] * (double)lds.kbar[PC * kc + 64 * m + 8 * i + e];
         }
-        part[m] = butterfly_sum<32>(butterfly_sum<16>(run[0] + run[1]));
+        if constexpr (NARROW) part[m] = butterfly_sum<4>(butterfly_sum<2>(butterfly_sum<1>(run[0])));
+        else part[m] = butterfly_sum<32>(butterfly_sum<16>(run[0] + run[1]));
       }
       double dot = part[0];
       if constexpr (NM == 2) dot = part[0] + part[1];
       if constexpr (NM == 4) dot = (part[0] + part[1]) + (part[2] + part[3]);
-      if (k4 == 0 && r < valid) q_corr[(bh * nQb + qb) * BQ + r] = (float)((double)kappa * dot);
+      if (kc == 0 && r < valid) q_corr[(bh * nQb + qb) * BQ + r] = (float)((double)kappa * dot);
     }
     float mx = row_max(p);                                   // per query; the pair shares the larger one unless qg == 1
-    if (qg == 2) mx = butterfly_max<1>(mx);
+    if (qg == 2) mx = butterfly_max<NARROW ? 8 : 1>(mx);
     if (block_groups) mx = block_max;
     const float delta = head_scale ? head_scale[bh] : __fdiv_rn(mx, (float)QMAX);
-    if (k4 == 0 && (qg == 1 || (r & 1) == 0)) q_scale[(bh * nQb + qb) * (BQ >> (qg - 1)) + (r >> (qg - 1))] = delta;   // qg is 1 or 2
+    if (kc == 0 && (qg == 1 || (r & 1) == 0)) q_scale[(bh * nQb + qb) * (BQ >> (qg - 1)) + (r >> (qg - 1))] = delta;   // qg is 1 or 2
     if (stats_only) continue;            // per-tensor scales, first pass: only the block maxima are wanted
     const CodeScale qs = code_scale(delta);
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
-      float x[16];
-      unpack8<BF16>(raw[p][m][0], x);
-      unpack8<BF16>(raw[p][m][1], x + 8);
+      float x[PC];
+#pragma unroll
+      for (int i = 0; i < NL; ++i) unpack8<BF16>(raw[p][m][i], x + 8 * i);
       if (valid < BQ) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) x[e] = r < valid ? x[e] : 0.0f;
+        for (int e = 0; e < PC; ++e) x[e] = r < valid ? x[e] : 0.0f;
       }
-      unsigned c[16];
-      code_group_bytes<16, QMAX>(x, delta, qs, c);
-      slab[q_code_off(r, 16 * k4 + 64 * m, D) >> 4] = pack16(c);
+      unsigned c[PC];
+      code_group_bytes<PC, QMAX>(x, delta, qs, c);
+      int8_t* const to = slab + q_code_off(r, PC * kc + 64 * m, D);
+      if constexpr (NARROW) *reinterpret_cast<uint2*>(to) = make_uint2(pack4(c), pack4(c + 4));
+      else *reinterpret_cast<uint4*>(to) = pack16(c);
     }
   }
 }
@@ -697,7 +709,9 @@ __device__ __forceinline__ void quant_q4_block(QuantQLds<D, true>& lds, const QB
 
 template <bool BF16, bool INT4, int D>
 __device__ __forceinline__ void quant_q_block(QuantQLds<D, INT4>& lds, const QBlock bl, const QuantQ& a) {
-  if constexpr (INT4) quant_q4_block<BF16, D>(lds, bl, a); else quant_q8_block<BF16, D>(lds, bl, a);
+  if constexpr (INT4) quant_q4_block<BF16, D>(lds, bl, a);
+  else if constexpr (D == 64) { if (a.narrow) quant_q8_block<BF16, D, true>(lds, bl, a); else quant_q8_block<BF16, D, false>(lds, bl, a); }
+  else quant_q8_block<BF16, D, false>(lds, bl, a);
 }
 // The first fin_rows rows of the grid finish the statistics (finalize_stats_block) under the quantization of Q.
 template <bool BF16, bool INT4, int D>
@@ -1534,6 +1548,7 @@ static hipError_t launch_prologue_t(const Dims& Dm, const Ptrs& P, hipStream_t s
   qa.qm = qm; qa.sm = sm; qa.q_corr = nullptr; qa.k_mean = P.k_mean; qa.G = Dm.H / Dm.Hkv; qa.kappa = Dm.kappa;
   qa.head_scale = nullptr; qa.stats_only = 0; qa.smooth_q = Dm.smooth_q; qa.k_sum = nullptr; qa.nchunk = (Dm.Nk + STAT_ROWS - 1) / STAT_ROWS; qa.smooth_k = Dm.smooth_k;
   qa.q_digits = Dm.ds_mode == DS_DIGITS && Dm.smooth_q ? P.q_digits : nullptr; qa.q_dscale = P.q_dscale;
+  qa.narrow = qm.heads_inner && (long long)BH * Dm.nQb >= 512;
   QuantKV ka;
   ka.k = k; ka.v = v; ka.k_mean = P.k_mean; ka.v_scale = P.v_scale; ka.v_mean = v_mean;
   ka.k_scale = P.k_scale; ka.k_codes = P.k_codes; ka.v_codes = P.v_codes; ka.q_mean = P.q_mean; ka.delta_s = P.delta_s;

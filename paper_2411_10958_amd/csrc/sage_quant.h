@@ -142,15 +142,12 @@ __device__ __forceinline__ void code_group_bytes(const float* x, float delta, co
     }
   }
 }
-// the low bytes of sixteen words side by side
-__device__ __forceinline__ uint4 pack16(const unsigned (&c)[16]) {
-  unsigned wd[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    wd[q] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(c[4 * q + 3], c[4 * q + 2], 0x0c0c0400u),
-                                  __builtin_amdgcn_perm(c[4 * q + 1], c[4 * q], 0x0c0c0400u), 0x05040100u);
-  return make_uint4(wd[0], wd[1], wd[2], wd[3]);
+// the low bytes of four words side by side
+__device__ __forceinline__ unsigned pack4(const unsigned* c) {
+  return __builtin_amdgcn_perm(__builtin_amdgcn_perm(c[3], c[2], 0x0c0c0400u), __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0400u), 0x05040100u);
 }
+// ... of sixteen
+__device__ __forceinline__ uint4 pack16(const unsigned (&c)[16]) { return make_uint4(pack4(c), pack4(c + 4), pack4(c + 8), pack4(c + 12)); }
 
 typedef unsigned v6u __attribute__((ext_vector_type(6)));
 // 32 INT4 codes held as integer-valued floats (every integer of [-7, 7] is an E2M3 value) become

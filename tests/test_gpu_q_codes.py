@@ -37,6 +37,24 @@ def test_q_codes_of_other_groups(d, dtype, group_map, N, mode):
     test_q_codes(d, dtype, group_map, N, mode)
 
 
+# (token-major rows of 4096 values and 512 blocks: eight lanes a row in the 8-bit mode; a block less, and one that is all there is of a sequence)
+@pytest.mark.parametrize("mode", ["int8_fp8", "int4_fp8"])
+@pytest.mark.parametrize("group_map,lse", [("lane", True), ("token", False), ("block", True), ("tensor", False)])
+@pytest.mark.parametrize("B,N", [(8, 3), (8, 128), (7, 128), (4, 131), (3, 300)])
+def test_64_wide_heads_of_long_token_major_rows(B, N, group_map, lse, mode):
+    """The bits of the same heads one after the other in memory."""
+    pa = _pa()
+    print(f"Q, long rows: B={B} N={N} {group_map} {mode}", flush=True)
+    q, k, v = _inputs(B, N, 70, 64, 64, 4, "bf16", "HND")
+    kw = dict(mode=mode, group_map=group_map, return_lse=True) if lse else dict(mode=mode, group_map=group_map)
+    a = pa.sage_attn_fwd_ex(q, k, v, **kw)
+    b = pa.sage_attn_fwd_ex(*(x.transpose(1, 2).contiguous() for x in (q, k, v)), layout="NHD", **kw)
+    if lse:
+        assert torch.equal(a[1], b[1])
+        a, b = a[0], b[0]
+    assert torch.isfinite(a).all() and torch.equal(a, b.transpose(1, 2))
+
+
 @pytest.mark.parametrize("mode", ["int4_fp8", "int8_fp8"])
 @pytest.mark.parametrize("N", [1, 2, 7, 9, 15, 17, 32, 33, 127, 128, 131])
 @pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "fp16"), (256, "bf16")])
