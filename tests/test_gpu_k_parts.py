@@ -41,7 +41,7 @@ def test_every_head_has_the_bits_of_a_call_of_its_own(N, Nk, d, H, Hkv, dtype, c
 
 # B, then as above, and the groups of scales: more than one sequence, workgroups numbered heads first (token-major rows of 4096 values), a scale per key and per block
 MORE = [(3, 1100, 1100, 128, 16, 1, "bf16", True, "HND", "lane", 2), (2, 1500, 2100, 64, 32, 2, "fp16", False, "NHD", "token", 3), (2, 2049, 2049, 128, 16, 2, "bf16", True, "NHD", "block", 2),
-        (1, 1540, 300, 128, 512, 32, "bf16", False, "NHD", "lane", 3), (1, 1540, 1540, 256, 256, 16, "fp16", True, "NHD", "token", 2), (2, 4100, 4100, 256, 8, 1, "bf16", True, "HND", "token", 4)]
+        (1, 1540, 300, 128, 512, 32, "bf16", False, "NHD", "lane", 3), (1, 2100, 2100, 256, 256, 16, "fp16", True, "NHD", "token", 2), (2, 2000, 2000, 256, 16, 1, "bf16", True, "HND", "token", 4)]
 
 
 @pytest.mark.parametrize("B,N,Nk,d,H,Hkv,dtype,causal,layout,group_map,parts", MORE)
@@ -66,6 +66,17 @@ def test_every_sequence_and_head_has_the_bits_of_a_call_of_its_own(B, N, Nk, d, 
             g = h // (H // Hkv)
             o, l = pa.sage_attn_fwd_ex(*(x[b:b + 1].narrow(hd, i, 1).contiguous() for x, i in ((q, h), (k, g), (v, g))), **kw)
             assert torch.equal(o[0], out[b].narrow(hd - 1, h, 1)) and torch.equal(l[0], lse[b].narrow(0, h, 1)), (b, h)
+
+
+# 256 channels: without a mask only where they level out the workgroups per CU, under one fewer where the chip is full without; packed batches two
+@pytest.mark.parametrize("B,N,H,Hkv,causal,packed,parts", [(1, 4000, 64, 4, 0, 0, 1), (1, 8000, 32, 2, 0, 0, 1), (1, 16000, 4, 1, 0, 0, 1), (8, 1830, 16, 1, 0, 0, 1), (1, 8000, 8, 1, 0, 0, 2), (1, 4000, 24, 3, 0, 0, 2), (1, 8000, 48, 3, 0, 0, 4),
+                                                           (1, 8000, 64, 4, 0, 0, 1), (1, 16000, 32, 4, 0, 0, 2), (1, 16000, 8, 1, 1, 0, 2), (1, 8000, 8, 1, 1, 0, 3), (1, 16000, 16, 2, 1, 0, 4), (1, 30000, 2, 2, 1, 0, 1), (1, 17627, 2, 1, 1, 0, 2),
+                                                           (4, 4000, 16, 2, 0, 1, 2), (8, 3000, 32, 4, 0, 1, 2), (16, 4000, 64, 4, 1, 1, 1)])
+def test_parts_of_256_channels(B, N, H, Hkv, causal, packed, parts):
+    extra = dict(layout=1, cu_seqlens_q=4096, cu_seqlens_k=4096) if packed else {}
+    (status, seq), = launches([("sage_attn_fwd_ex", dict(B=B, H=H, H_kv=Hkv, N=N, N_kv=N, d=256, dtype=1, mode=0, causal=causal, kv_splits=1, **extra))])
+    assert status == 0
+    assert [x.grid[2] for x in seq if x.kernel in ("k_quant_kv", "k_quant_k")] == [parts]
 
 
 # packed batches: the parts are counted by the longest sequence, so a short one has fewer steps than parts, or no queries, or no keys
