@@ -1273,10 +1273,7 @@ __device__ __forceinline__ void quant_v_block(QuantVLds<D, REDUCE>& lds, const B
   const bool ragged = n0 + BKV > N;
   // The quotient: div_by; with a supplied scale, which bounds nothing, div_by with its remainder kept finite, since an infinite quotient has none
   // (the conversion tells infinities from NaN); or a division, also where a scale taken from the values is infinite.
-  // MIXED chooses at every four values, and keeps the sign by copying it: more instructions, but in the small calls of 256-wide heads, where each workgroup's
-  // loads, arithmetic and stores run one after the other, ordered so that those take less (128 KV heads of 310 keys, fp16, 4-bit 26.4 -> 24.4 us, 32 of 2000,
-  // 8-bit, 23.8 -> 22.5; k_quant_v on 16 heads of 8192 keys the other way round, 17.8 against 22.8).
-  enum { BOUNDED, UNBOUNDED, EXACT, MIXED };
+  enum { BOUNDED, UNBOUNDED, EXACT };
   auto convert = [&](auto form) {
     constexpr int FORM = decltype(form)::value;
 #pragma unroll
@@ -1295,13 +1292,7 @@ __device__ __forceinline__ void quant_v_block(QuantVLds<D, REDUCE>& lds, const B
 #pragma unroll
           for (int i = 0; i < 4; ++i) x[i] = n0 + key0 + i < N ? x[i] : 0.0f;
         }
-        if (FORM == MIXED && fast) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float q = __fmul_rn(x[i], rc[e]), rem = __builtin_amdgcn_fmed3f(__fmaf_rn(q, -sc[e], x[i]), -0x1.fffffep127f, 0x1.fffffep127f);
-            x[i] = copysignf(__fmaf_rn(rem, rc[e], q), x[i]);
-          }
-        } else if (FORM == BOUNDED || FORM == UNBOUNDED) {
+        if constexpr (FORM != EXACT) {
           // div_by with the remainder's sign turned, so that a quotient of -0 stays -0
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -1334,8 +1325,7 @@ __device__ __forceinline__ void quant_v_block(QuantVLds<D, REDUCE>& lds, const B
       }
     }
   };
-  if constexpr (REDUCE && D == 256) convert(std::integral_constant<int, MIXED>{});
-  else if (!fast) convert(std::integral_constant<int, EXACT>{});
+  if (!fast) convert(std::integral_constant<int, EXACT>{});
   else if (REDUCE || a.bounded) convert(std::integral_constant<int, BOUNDED>{});
   else if constexpr (!REDUCE) convert(std::integral_constant<int, UNBOUNDED>{});
   __syncthreads();
