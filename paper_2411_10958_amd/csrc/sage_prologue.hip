@@ -1525,26 +1525,26 @@ static bool kv_pair(const Dims& Dm) {
 // Preprocessing, us, one / as many: 8 on 1 heads of 25318 tokens (396 key blocks, 99 steps) 157.8 /
 // 96.5, without a mask 167 / 130, 16 on 2 of 6000 56.3 / 36.9, 8 on 1 of 12000 of 64 channels 62.0 / 30.7, 48 on 6 of 4000 of 64 43.0 / 34.3, 4 on 2
 // of 32965 (1032, 33 steps) 95.5 / 86.3, 32 on 8 of 16384 (2048, 32) 169.4 / 165.2, 96 on 12 of 12000 (2256, 47) 284.6 / 275.1, 56 on 7 of 25000 (2737, 98) 515 /
-// 489; but 2 of 20000 (626, 10 steps) two 39.5 for 38.8, 4 of 16384 (1024, 8 steps) 48.7 for 48.5.  Rounded up over rounded down, 160 shapes between: two parts
-// for one 0.91 to 1.02, three or four for one less 0.95 to 1.03.
+// 489; but 2 of 20000 (626, 10 steps) two 39.5 for 38.8, 4 of 16384 (1024, 8 steps) 48.7 for 48.5.  Rounded up over rounded down, 158 shapes between: two parts
+// for one 0.89 to 1.02 (mean 0.96), three or four for one less 0.95 to 1.03 (1.00).
 // 256 channels, where cutting the keys takes longer and one workgroup uses a CU nearly as well as the two that fit: without a mask all chains are equal, and
 // parts gain where they level the CUs out, not where 256, 512 or 1000 workgroups already do (one / as the other widths, 64 on 4 of 4000 tokens, 252 blocks
 // of 32 steps, the kernel 85 / 102; preprocessing of 4 on 1 of 16000 117 / 135, 16 on 2 of 8000 133 / 149, but 125 blocks of 32 steps two 74 for 93, 375 of 63 four
 // 224 for 254, 750 of 63 two 345 for 358).  Under a mask they level the chains: 250 blocks of 63 steps 165 / 136 with two, 150 with seven, 125 of 32 91.5 / 66
 // with three, 73 with eight; long sequences of one or two heads need the steps (938 blocks of 15 two 100 for 93).  136 shapes without a mask, as many over one: 0.59
-// to 1.02, mean 0.95, and 166 with one 0.48 to 1.04, 0.92; by the rule of the other widths 0.97, to 1.16, and 0.92, to 1.09.  A packed batch has
-// unequal chains too, and fewer blocks than its longest sequence lets one count: two parts (8 sequences of up to 3000, 32 on 4 heads, no mask, the kernel 74 / 65,
-// of 6000, 1000 and 5500, 64 on 4, 232 / 210; but 8000 and 700, 16 on 2, 95 / 101).
+// to 1.02, mean 0.95, and 166 with one 0.48 to 1.04, 0.92; by the rule of the other widths 0.97, to 1.16, and 0.92, to 1.09.  Packed batches, which have
+// fewer blocks than their longest sequence lets one count, by the rule of the other widths (60 under a mask 0.60 to 1.05, mean 0.90, 60 without 0.71 to 1.05,
+// 0.93; two parts for all of more than 128 blocks alike on average, with up to 16 % lost on two or three sequences).
 static int k_parts(const Dims& Dm) {
   if (!Dm.int4 || Dm.ds_mode != DS_DIGITS || Dm.tensor_groups || !Dm.smooth_q) return 1;
   const long long blocks = (long long)Dm.B * Dm.Hkv * Dm.nKb, steps = ((long long)(Dm.H / Dm.Hkv) * Dm.nQb + DS_ROWS - 1) / DS_ROWS;
-  const bool packed = Dm.seq.cu_q != nullptr, unequal = Dm.causal || packed;
+  const long long slots = Dm.d == 256 ? 512 : 1024;
   long long parts, each;                 // at most so many, with so many steps
-  if (Dm.d < 256) { parts = (3 * 1024 + blocks - 1) / blocks; each = blocks < 512 ? 4 : 6; }
-  else if (blocks <= 128) { parts = (unequal ? 384 : 256) / blocks; each = 4; }
-  else if (unequal) {
-    parts = packed ? (blocks < 2048 ? 2 : 1) : (blocks <= 256 ? 2 : (3 * 512 + blocks - 1) / blocks);
-    each = blocks <= 200 ? 4 : (packed || blocks <= 256 ? 6 : (blocks <= 768 ? 8 : 12));
+  if (Dm.d < 256 || Dm.seq.cu_q) { parts = (3 * slots + blocks - 1) / blocks; each = 2 * blocks < slots ? 4 : 6; }
+  else if (blocks <= 128) { parts = (Dm.causal ? 384 : 256) / blocks; each = 4; }
+  else if (Dm.causal) {
+    parts = blocks <= 256 ? 2 : (3 * slots + blocks - 1) / blocks;
+    each = blocks <= 200 ? 4 : (blocks <= 256 ? 6 : (blocks <= 768 ? 8 : 12));
   } else if (blocks <= 256) { parts = blocks <= 170 ? 3 : (blocks <= 200 ? 2 : 1); each = 4; }
   else if (blocks <= 640) { parts = (blocks - 1) % 256 >= 128 ? 1 : (steps >= 48 ? 4 : 2); each = 6; }
   else { parts = blocks < 1536 ? 2 : 1; each = 12; }
