@@ -627,8 +627,10 @@ __global__ void __launch_bounds__(RAW_THREADS, D == 256 ? 2 : 4) k_attn_raw(cons
 // to 1.21).  4 workgroups, one chunk each: of 12 blocks 1.00 (256 channels, 4-bit) to 1.30, of 20 0.86 (256, 4-bit), 1.00 (128) and
 // 1.11 (64), in the 8-bit mode 1.02, 1.16, 1.19; of 32 0.78, 0.87, 0.97 and 0.92, 1.06, 1.07.  With five to eight heads in a group,
 // 4-bit: one workgroup of 8 blocks of 256 channels 0.94, 4 of 12 of 128 channels 1.06, of 20 0.90.  16 workgroups: chunks of 20 blocks
-// of 256 channels 0.97 (4-bit) and 1.16, of 32 of 128 0.96 and 1.14, of 32 of 64 1.06 and 1.12.  Automatic chunks are of 8 to 15
-// blocks until there are 512 workgroups or 64 chunks.
+// of 256 channels 0.97 (4-bit) and 1.16, of 32 of 128 0.96 and 1.14, of 32 of 64 1.06 and 1.12.  Measured with
+// ceil(512 / tiles) chunks: of 8 to 15 blocks until there are 512 workgroups or 64 chunks.  The automatic ones are counted in whole rounds of workgroups
+// (chunks_of_few_tiles), so 147 tiles of 300 blocks have three of 100 in 441 workgroups; the two differ only where there are more workgroups than any line
+// below, and every call of 1 to 255 tiles and 1 to 1200 blocks goes the same way with either.
 // Where the general path has two (small_call) and the statistics are not supplied this kernel came after the statistics and their
 // reduction and saved none; these figures are of that form, 2 to 4 us a call before raw_reduces.  4-bit, up to 8 queries, 48 workgroups and more 0.99 to 2.05 at any length; 32 to 47, chunks of up
 // to 3 blocks 1.04 to 1.35, of more 0.90 to 1.21; fewer, of 4 blocks of 64 channels 0.99 to 1.08, of 2 of 128 1.01 to 1.15, of 3 of
