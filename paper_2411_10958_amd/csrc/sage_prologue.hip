@@ -403,8 +403,8 @@ __device__ __forceinline__ QBlock q_block(const QuantQ& a, unsigned qb, unsigned
 // paper's "two kernel implementations" leaves Q as it is).  One workgroup per 128 queries of one
 // (batch, head); a wavefront quantizes by itself.  Lane l of a pass holds row l % 16 and the 16-channel pieces l / 16 + 4 m, 32 bytes
 // each: four lanes read 128 consecutive bytes, and a piece is 16 bytes of codes.  Both passes' rows are requested together.
-// Against codes laid out in LDS, rows as 8 channels of 4 to 8 rows per thread and a byte extract per code: 32 heads of 8192 tokens 33 -> 25 us (100 MB:
-// 4.0 TB/s).  Bound: the loads in flight - a workgroup loads, computes and stores in turn, and a chip's worth of them starts together
+// Against codes laid out in LDS, rows as 8 channels of 4 to 8 rows per thread and a byte extract per code: 32 heads of 8192 tokens 36 -> 24 us (100 MB:
+// 4.2 TB/s).  Bound: the loads in flight - a workgroup loads, computes and stores in turn, and a chip's worth of them starts together
 // (walking several blocks with the next one's rows requested ahead gained nothing: the 4-bit form 45 -> 51 us on 4096 blocks).
 // NARROW, for 64-wide heads of long token-major rows, whose 128 bytes lie apart: 8 channels a lane and 8 rows a pass in four, so that every load takes whole
 // runs (4 sequences of 64 heads of 2667 tokens 38.0 -> 31.7 us, of 17870 231 -> 215; the code image in LDS had 33.9 and 216).  Its four short chains cost
@@ -529,7 +529,7 @@ __device__ __forceinline__ void quant_q8_block(QuantQLds<D, false>& lds, const Q
 // banks.  LDS: the raw rows (32 KB at d = 128) and one row of column sums per wavefront (the row groups of a wavefront are summed by
 // lane exchanges first) - 37 KB, so that four workgroups share a CU and their loads, arithmetic and stores overlap.
 // With the passes and no code image in LDS: 2 heads of 256 tokens (with the statistics) 5.05 -> 4.45 us, 64
-// heads of 512 9.4 -> 8.8, 16 of 8192 of 256 channels 29.2 -> 28.4, 128 of 4096 42 to 45 (185 MB: 4.1 to 4.4 TB/s): loads and parking alone 29, column
+// heads of 512 9.4 -> 8.8, 16 of 8192 of 256 channels 29.2 -> 28.1, 128 of 4096 42 to 45 (185 MB: 4.1 to 4.4 TB/s): loads and parking alone 29, column
 // sums 4, quantization 6, stores 4.  (Rows read a second time instead of parked, five workgroups per CU: 48.)
 template <int D> struct QuantQLds<D, true> {
   uint4 raw[BQ * (D / 8)];           // the raw rows
